@@ -75,6 +75,23 @@ def algorithmic_bytes(stats: dict, n_reads: int, n_bases: int, tile_len: int = 2
             "final_emit": 13.0 * n_bases,
         }
     cs = stats.get("chunk_suffixes", 0)
+    if stats.get("launches", {}).get("induce"):
+        # samples sorted, the rest induced: level 1 reads the text and writes
+        # the samples (12 B); a finished sample is 12 B read, its key read
+        # again and 9 B written; a row is written once (8 B and a code byte),
+        # read by the right-to-left steps, the L half also left to right
+        # (with the samples), and its BWT byte written
+        moved = stats.get("scattered_suffixes", 0) - cs
+        return {
+            "prep": 17.0 * n_reads + 0.1875 * n_bases,
+            "gen": 0.375 * n_bases,
+            "level_hist": 8.0 * (stats.get("level_suffixes", 0) - cs) + 12.0 * stats.get("regathered", 0),
+            "level_scan": 2.0 * 1024 * stats.get("level_suffixes", 0) / 4096,
+            "level_scatter": 0.375 * n_bases + 12.0 * cs + 24.0 * max(0, moved),
+            "local": 29.0 * cs + 16.0 * stats.get("window_fetches", 0),
+            "induce": (9.0 + 9.0 + 4.5 + 1.0) * n_bases + 9.0 * cs,
+            "final_emit": 16.0 * n_reads,
+        }
     fin = n_bases - cs
     scattered = stats.get("scattered_suffixes", 0)
     level1 = n_bases if stats.get("levels", 0) >= 1 and scattered >= n_bases else 0
@@ -91,17 +108,18 @@ def algorithmic_bytes(stats: dict, n_reads: int, n_bases: int, tile_len: int = 2
 
 KERNELS_OF_CLASS = {
     "prep": ["k_prep", "k_text_records", "k_rank_count", "k_rank_top", "k_rank_words"],
-    "gen": ["k_gen_hist", "k_gen"],
+    "gen": ["k_gen_hist", "k_gen", "k_sample_hist"],
     "level_hist": ["k_level_hist"],
     "level_scan": ["k_group_scan", "k_level_scan"],
-    "level_scatter": ["k_gen_scatter", "k_level_scatter"],
-    "local": ["k_local"],
-    "final_emit": ["k_emit_final", "k_term"],
+    "level_scatter": ["k_gen_scatter", "k_level_scatter", "k_sample_scatter"],
+    "local": ["k_local", "k_sample_chunk"],
+    "final_emit": ["k_emit_final", "k_sample_final", "k_term"],
+    "induce": ["k_ind_count", "k_ind_group", "k_ind_top", "k_ind_scatter", "k_ind_tail", "k_ind_emit"],
 }
 
 # the device code whose counter runs a traffic record holds (host code that
 # only sequences launches is not part of it)
-KERNEL_SOURCES = ("cxbwt_kernels.h", "device_common.h")
+KERNEL_SOURCES = ("cxbwt_kernels.h", "cxbwt_induce.h", "device_common.h")
 
 
 def kernel_sources_hash() -> str:

@@ -364,10 +364,14 @@ typedef struct cxbwt_stats {
   /* regathered + window_fetches is the number of (suffix, window r >= 1)
    * pairs for which another suffix of the same collection shares the
    * suffix's first 27 r bases: only tied suffixes load a later window
-   * (Section 3.2's stringword iterations, restricted to the ties).           */
+   * (Section 3.2's stringword iterations, restricted to the ties).
+   * A large build sorts the samples of its suffixes only (three tenths of
+   * them) and derives the order of the rest: chunks to window_fetches then
+   * count samples, whose windows hold 22 bases, later ones in a wave 25.     */
   /* With timing on (cxbwt_set_timing): summed kernel time in ms and launch
    * count per kernel class: 0 prep, 1 key generation, 2 level histogram,
-   * 3 level scan, 4 level scatter, 5 in-wave finish, 6 final emit.           */
+   * 3 level scan, 4 level scatter, 5 in-wave finish, 6 final emit, 7 the
+   * steps that derive the order of the suffixes that were not sorted.        */
   float ms[8];
   uint32_t launches[8];
   uint32_t level_batches;      /* batches the levels after the first ran in            */

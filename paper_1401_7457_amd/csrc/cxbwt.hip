@@ -53,6 +53,7 @@
 #include <vector>
 
 #include "cxbwt.h"
+#include "cxbwt_induce.h"
 #include "cxbwt_kernels.h"
 
 namespace {
@@ -250,7 +251,7 @@ int fill_u32(uint32_t *p, uint64_t n, uint32_t v, hipStream_t st) {
 }
 
 // Kernel classes timed by PhaseTimer (indices of cxbwt_stats.ms).
-enum Phase { PH_PREP = 0, PH_GEN, PH_HIST, PH_SCAN, PH_SCATTER, PH_LOCAL, PH_FINAL };
+enum Phase { PH_PREP = 0, PH_GEN, PH_HIST, PH_SCAN, PH_SCATTER, PH_LOCAL, PH_FINAL, PH_INDUCE };
 
 // Brackets kernel launches with HIP events on the build's stream when timing
 // is on; durations are summed at the host synchronisation points.
@@ -323,6 +324,10 @@ struct Buffers {
   CollMap *cmap;
   unsigned long long *seg_or, *seg_and, *stats;
   uint8_t *seg_split;
+  // a build by induced order: the sort buffers above hold its samples, in
+  // SampleKey's format, and finished ones go to smp
+  bool sample = false;
+  SampleOut smp{};
 };
 
 // End of the batch of segments starting at b0 that fits the per-segment and
@@ -381,16 +386,21 @@ constexpr unsigned PG_FILL = 256 * 2;
 // wave per segment.
 void launch_level_scan(const Buffers &B, uint32_t ns, uint32_t ngroups, const Lists &Ls, int force_split,
                        hipStream_t st, const uint32_t *dev_ns = nullptr, unsigned dev_grid = PG_SCAN) {
+#define CX_SCAN(F, COOP, GRID)                                                                                  \
+  k_level_scan<F, COOP, false><<<GRID, BLOCK, 0, st>>>(B.segs, B.group_prefix, ns, B.gsum, B.seg_or, B.seg_and, \
+                                                       B.seg_split, Ls, force_split, nullptr)
+  const unsigned waves_grid = (unsigned)ceil_div(ns, WAVES);
   if (dev_ns)
-    k_level_scan<false, true><<<dev_grid, BLOCK, 0, st>>>(B.segs, B.group_prefix, 0, B.gsum, B.seg_or, B.seg_and,
-                                                   B.seg_split, Ls, force_split, dev_ns);
-  else if (ngroups > 8u * ns)
-    k_level_scan<true, false><<<ns, BLOCK, 0, st>>>(B.segs, B.group_prefix, ns, B.gsum, B.seg_or, B.seg_and, B.seg_split,
-                                             Ls, force_split, nullptr);
-  else
-    k_level_scan<false, false><<<(unsigned)ceil_div(ns, WAVES), BLOCK, 0, st>>>(B.segs, B.group_prefix, ns, B.gsum,
-                                                                          B.seg_or, B.seg_and, B.seg_split, Ls,
-                                                                          force_split, nullptr);
+    k_level_scan<GeneralKey, false, true><<<dev_grid, BLOCK, 0, st>>>(B.segs, B.group_prefix, 0, B.gsum, B.seg_or,
+                                                                      B.seg_and, B.seg_split, Ls, force_split, dev_ns);
+  else if (ngroups > 8u * ns) {
+    if (B.sample) CX_SCAN(SampleKey, true, ns);
+    else CX_SCAN(GeneralKey, true, ns);
+  } else {
+    if (B.sample) CX_SCAN(SampleKey, false, waves_grid);
+    else CX_SCAN(GeneralKey, false, waves_grid);
+  }
+#undef CX_SCAN
 }
 
 // Tile prefixes (and group prefixes, and a copy of the list, when given) of
@@ -510,14 +520,20 @@ int launch_local(const Buffers &B, const Tuning &tu, uint64_t nb, uint32_t rmax,
 }
 
 // Finish the chunks and final groups a level produced.
-int finish_level(const Buffers &B, const Layout &Lo, const Tuning &tu, uint64_t nb, uint32_t rmax, uint8_t *bwt,
-                 uint32_t n_chunks, uint32_t n_finals, uint64_t final_tiles, uint64_t final_len, PhaseTimer &T,
+int finish_level(const Buffers &B, const Layout &Lo, const Tuning &tu, uint64_t nb, uint32_t rmax, uint32_t maxlen,
+                 uint8_t *bwt, uint32_t n_chunks, uint32_t n_finals, uint64_t final_tiles, uint64_t final_len, PhaseTimer &T,
                  hipStream_t st) {
   if (n_chunks > Lo.cap_chunks || n_finals > Lo.cap_finals) return fail_internal("work exceeds a workspace list or scratch area");
   int rc;
   if (n_chunks) {
     T.begin();
-    if ((rc = launch_local(B, tu, nb, rmax, bwt, n_chunks, nullptr, st))) return rc;
+    if (B.sample) {
+      k_sample_chunk<8, 4><<<n_chunks, LOCAL_WG, 0, st>>>(B.chunks, B.keys0, B.keys1, B.hdl0, B.hdl1, B.text, maxlen,
+                                                          B.smp, B.counters + C_STATUS, B.stats);
+      CX_LAUNCHED();
+    } else if ((rc = launch_local(B, tu, nb, rmax, bwt, n_chunks, nullptr, st))) {
+      return rc;
+    }
     T.end(PH_LOCAL);
     g_stats.chunks += n_chunks;
   }
@@ -525,9 +541,13 @@ int finish_level(const Buffers &B, const Layout &Lo, const Tuning &tu, uint64_t 
     if (final_tiles == 0 || final_tiles > 0xFFFFFFFFull) return fail_internal("work exceeds a workspace list or scratch area");
     if ((rc = prefix_list(B, B.finals, n_finals, tu.tile_len(), nullptr, B.tile_prefix, nullptr, st))) return rc;
     T.begin();
-    k_emit_final<false><<<(unsigned)final_tiles, BLOCK, 0, st>>>(B.finals, B.tile_prefix, n_finals, nullptr, tu.tile_len(),
-                                                          B.keys0, B.keys1, B.hdl0, B.hdl1, B.pos64, B.text, B.srank,
-                                                          B.cmap, bwt, B.start_row);
+    if (B.sample)
+      k_sample_final<<<(unsigned)final_tiles, BLOCK, 0, st>>>(B.finals, B.tile_prefix, n_finals, tu.tile_len(), B.keys0,
+                                                              B.keys1, B.hdl0, B.hdl1, B.text, B.smp);
+    else
+      k_emit_final<false><<<(unsigned)final_tiles, BLOCK, 0, st>>>(B.finals, B.tile_prefix, n_finals, nullptr,
+                                                                   tu.tile_len(), B.keys0, B.keys1, B.hdl0, B.hdl1,
+                                                                   B.pos64, B.text, B.srank, B.cmap, bwt, B.start_row);
     CX_LAUNCHED();
     T.end(PH_FINAL);
     g_stats.final_big += n_finals;
@@ -550,16 +570,18 @@ int launch_level_kernels(const Buffers &B, const Tuning &tu, const Lists &Ls, ui
                  g_scan = grid_from((sh.nsegs + WAVES - 1) / WAVES, PG_SCAN),
                  g_scatter = grid_from(sh.ntiles, tu.tile_items == 16 ? PG_SCATTER_WIDE : PG_SCATTER);
   T.begin();
-#define CX_HIST(P, SUBT)                                                                                         \
-  k_level_hist<P, SUBT><<<P ? g_hist : ntiles, BLOCK, 0, st>>>(B.segs, B.tile_prefix, nsg, dev_nsg, tu.tile_len(),  \
+#define CX_HIST(F, P, SUBT)                                                                                      \
+  k_level_hist<F, P, SUBT><<<P ? g_hist : ntiles, BLOCK, 0, st>>>(B.segs, B.tile_prefix, nsg, dev_nsg, tu.tile_len(), \
                                                                 B.keys0, B.keys1, B.hdl0, B.hdl1, B.text, nb,        \
                                                                 B.pos64, B.tile_hist, B.seg_or, B.seg_and)
-  if (tu.tile_items == 16) {
-    if (dev) CX_HIST(true, 2);
-    else CX_HIST(false, 2);
+  if (B.sample) {
+    CX_HIST(SampleKey, false, 2);  // always the wide tile
+  } else if (tu.tile_items == 16) {
+    if (dev) CX_HIST(GeneralKey, true, 2);
+    else CX_HIST(GeneralKey, false, 2);
   } else {
-    if (dev) CX_HIST(true, 1);
-    else CX_HIST(false, 1);
+    if (dev) CX_HIST(GeneralKey, true, 1);
+    else CX_HIST(GeneralKey, false, 1);
   }
 #undef CX_HIST
   CX_LAUNCHED();
@@ -574,19 +596,21 @@ int launch_level_kernels(const Buffers &B, const Tuning &tu, const Lists &Ls, ui
   CX_LAUNCHED();
   T.end(PH_SCAN);
   T.begin();
-#define CX_SCATTER(TI, NW, P)                                                                                   \
-  k_level_scatter<TI, NW, P><<<P ? g_scatter : ntiles, 64 * NW, 0, st>>>(                                       \
+#define CX_SCATTER(F, TI, NW, P)                                                                                \
+  k_level_scatter<F, TI, NW, P><<<P ? g_scatter : ntiles, 64 * NW, 0, st>>>(                                    \
       B.segs, B.tile_prefix, B.group_prefix, nsg, dev_nsg, B.seg_split, B.tile_hist, B.gsum, B.keys0, B.keys1,    \
       B.hdl0, B.hdl1)
-  if (tu.tile_items == 16) {
-    if (dev) CX_SCATTER(8, 8, true);
-    else CX_SCATTER(8, 8, false);
+  if (B.sample) {
+    CX_SCATTER(SampleKey, 8, 8, false);
+  } else if (tu.tile_items == 16) {
+    if (dev) CX_SCATTER(GeneralKey, 8, 8, true);
+    else CX_SCATTER(GeneralKey, 8, 8, false);
   } else if (tu.tile_items == 8) {
-    if (dev) CX_SCATTER(8, 4, true);
-    else CX_SCATTER(8, 4, false);
+    if (dev) CX_SCATTER(GeneralKey, 8, 4, true);
+    else CX_SCATTER(GeneralKey, 8, 4, false);
   } else {
-    if (dev) CX_SCATTER(6, 4, true);
-    else CX_SCATTER(6, 4, false);
+    if (dev) CX_SCATTER(GeneralKey, 6, 4, true);
+    else CX_SCATTER(GeneralKey, 6, 4, false);
   }
 #undef CX_SCATTER
   CX_LAUNCHED();
@@ -598,7 +622,7 @@ int launch_level_kernels(const Buffers &B, const Tuning &tu, const Lists &Ls, ui
 // prefixes in place.  Counts, splits, scatters, then finishes the chunks and
 // final groups the batch produced.
 int run_level_batch(const Buffers &B, const Layout &Lo, const Tuning &tu, const Lists &Ls, uint64_t nb,
-                    uint32_t rmax, uint8_t *bwt, uint32_t nsg, uint32_t ntiles, uint32_t ngroups, LevelOut &o,
+                    uint32_t rmax, uint32_t maxlen, uint8_t *bwt, uint32_t nsg, uint32_t ntiles, uint32_t ngroups, LevelOut &o,
                     PhaseTimer &T, hipStream_t st) {
   int rc;
   if ((rc = fill_u64((uint64_t *)B.seg_or, nsg, 0, st))) return rc;
@@ -608,7 +632,7 @@ int run_level_batch(const Buffers &B, const Layout &Lo, const Tuning &tu, const 
   if ((rc = launch_level_kernels(B, tu, Ls, nb, nsg, ntiles, ngroups, nullptr, T, st))) return rc;
   g_stats.level_batches++;
   if ((rc = read_level(B, o, T, st))) return rc;
-  return finish_level(B, Lo, tu, nb, rmax, bwt, o.n_chunks, o.n_finals, o.final_tiles, o.final_len, T, st);
+  return finish_level(B, Lo, tu, nb, rmax, maxlen, bwt, o.n_chunks, o.n_finals, o.final_tiles, o.final_len, T, st);
 }
 
 // Everything one build needs: its sizes, the caller's buffers, the workspace
@@ -839,7 +863,7 @@ int run_levels(const Build &b, LevelOut acc, uint32_t nbig, PhaseTimer &T, hipSt
     if ((rc = fill_u32(counters + C_NBIG, 1, 0, st))) return rc;
     if (nbig <= Lo.seg_slots && lt <= Lo.max_tiles && lg <= Lo.max_groups) {
       if ((rc = prefix_list(B, B.big_next, nbig, b.tile_len, B.segs, B.tile_prefix, B.group_prefix, st))) return rc;
-      if ((rc = run_level_batch(B, Lo, b.tu, b.Ls, b.nb, b.rmax, b.bwt, nbig, (uint32_t)lt, (uint32_t)lg, o, T,
+      if ((rc = run_level_batch(B, Lo, b.tu, b.Ls, b.nb, b.rmax, b.maxlen, b.bwt, nbig, (uint32_t)lt, (uint32_t)lg, o, T,
                                 st)))
         return rc;
       record_shape(g_stats.levels - 1, LevelShape{nbig, (uint32_t)lt, (uint32_t)lg, o.n_chunks, o.n_finals,
@@ -853,7 +877,7 @@ int run_levels(const Build &b, LevelOut acc, uint32_t nbig, PhaseTimer &T, hipSt
         const size_t b1 = batch_end(big, b0, Lo, b.tile_len);
         const std::vector<Seg> part(big.begin() + b0, big.begin() + b1);
         if ((rc = upload_segments(B, Lo, part, b.tile_len, tprefix, gprefix, ntiles, ngroups, st))) return rc;
-        if ((rc = run_level_batch(B, Lo, b.tu, b.Ls, b.nb, b.rmax, b.bwt, (uint32_t)part.size(), ntiles, ngroups, o,
+        if ((rc = run_level_batch(B, Lo, b.tu, b.Ls, b.nb, b.rmax, b.maxlen, b.bwt, (uint32_t)part.size(), ntiles, ngroups, o,
                                   T, st)))
           return rc;
         record_shape(g_stats.levels - 1, LevelShape{(uint32_t)part.size(), ntiles, ngroups, o.n_chunks, o.n_finals,
@@ -897,7 +921,7 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
     T.end(PH_GEN);
     CX_CHECK(hipMemcpyAsync(B.chunks, src.small.segs, sizeof(Seg) * src.small.ns, hipMemcpyHostToDevice, st));
     if (!src.big.ns) {
-      if ((rc = finish_level(B, Lo, b.tu, nb, b.rmax, b.bwt, src.small.ns, 0, 0, 0, T, st))) return rc;
+      if ((rc = finish_level(B, Lo, b.tu, nb, b.rmax, b.maxlen, b.bwt, src.small.ns, 0, 0, 0, T, st))) return rc;
     } else {
       // level 1 appends its chunks after these
       CX_CHECK(hipMemcpyAsync(counters + C_NCHUNK, src.nsmall, 4, hipMemcpyHostToDevice, st));
@@ -934,7 +958,7 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
       LevelOut o{};
       if ((rc = read_level(B, o, T, st))) return rc;
       record_shape(0, LevelShape{ns, ntiles, ngroups, o.n_chunks, o.n_finals, (uint32_t)o.final_tiles});
-      if ((rc = finish_level(B, Lo, b.tu, nb, b.rmax, b.bwt, o.n_chunks, o.n_finals, o.final_tiles, o.final_len, T,
+      if ((rc = finish_level(B, Lo, b.tu, nb, b.rmax, b.maxlen, b.bwt, o.n_chunks, o.n_finals, o.final_tiles, o.final_len, T,
                              st)))
         return rc;
       if ((rc = run_levels(b, o, o.n_big, T, st))) return rc;
@@ -1131,6 +1155,336 @@ int finish_device_levels(const Build &b, const uint32_t (&hc0)[C_COUNT], PhaseTi
   return CXBWT_OK;
 }
 
+// ---- the build by induced order ------------------------------------------
+// Taken from this many bases on: the steps are about thirty launches of their
+// own, so that 17 Mbases of 100-base reads at 20x take 1.67 ms here and 1.45
+// by the sort, 33 Mbases 2.15 and 2.84 ms (deeper reads gain from less on: at
+// 2000x, 20 Mbases take 5.8 ms here and 15.1 by the sort).
+#ifndef CXBWT_INDUCE_MIN_BASES
+#define CXBWT_INDUCE_MIN_BASES 20000000ull
+#endif
+// Not for reads this short: their suffixes end inside the first window, so
+// the sort has no windows to save (47 Mbases of 30-base reads: 4.0 ms by the
+// sort, 2.4 here), and their groups of identical suffixes are what final_big
+// reports.
+constexpr uint32_t INDUCE_MIN_READ = 33;
+
+// One collection's plan: the buckets' parts from the counted types.
+struct InduceColl {
+  uint32_t n[2][4][RUN_REGIONS + 1];  // [L, S][base][run]
+  uint32_t samples[4], maxrun[8];
+  uint64_t l0[4], s1[4];  // the L part's first row, the S part's end
+  uint64_t nl[4], ns[4], first_sample;
+};
+
+// Host image of everything the steps read: descriptors of every step, laid
+// out in one block for one copy.
+struct StepBlob {
+  std::vector<unsigned char> bytes;
+  size_t put(const void *p, size_t n) {
+    const size_t at = (bytes.size() + 15) & ~(size_t)15;
+    bytes.resize(at + n);
+    if (n) memcpy(bytes.data() + at, p, n);
+    return at;
+  }
+};
+struct StepPlan {
+  size_t segs = 0, tiles = 0, coll_tiles = 0, coll_groups = 0;
+  uint32_t nsegs = 0, ntiles = 0, ngroups = 0;
+};
+
+// src: the step's sources of every collection, in order.
+StepPlan plan_step(StepBlob &blob, const std::vector<std::vector<IndSeg>> &src) {
+  std::vector<IndSeg> segs;
+  std::vector<uint32_t> tiles{0}, ct{0}, cg{0};
+  for (const auto &list : src) {
+    for (const IndSeg &g : list) {
+      if (!g.len) continue;
+      segs.push_back(g);
+      tiles.push_back(tiles.back() + (uint32_t)ceil_div(g.len, IND_TILE));
+    }
+    cg.push_back(cg.back() + (uint32_t)ceil_div(tiles.back() - ct.back(), GROUP_TILES));
+    ct.push_back(tiles.back());
+  }
+  StepPlan p;
+  p.segs = blob.put(segs.data(), sizeof(IndSeg) * segs.size());
+  p.tiles = blob.put(tiles.data(), 4 * tiles.size());
+  p.coll_tiles = blob.put(ct.data(), 4 * ct.size());
+  p.coll_groups = blob.put(cg.data(), 4 * cg.size());
+  p.nsegs = (uint32_t)segs.size();
+  p.ntiles = tiles.back();
+  p.ngroups = cg.back();
+  return p;
+}
+
+// Plans and runs the build by induced order of b's collections above one
+// chunk (the others have been built).  *taken stays false, and nothing has
+// been written, where it does not apply.
+int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
+  *taken = false;
+  const Layout &Lo = b.Lo;
+  const uint64_t nb = b.nb;
+  const uint32_t nc = (uint32_t)b.big.size();
+  int rc;
+  // the text of every collection in tiles, counted
+  std::vector<uint32_t> tp, gp;
+  seg_prefixes(b.big, SMP_TILE, tp, gp);
+  const uint32_t ntiles = tp.back(), ngroups = gp.back();
+  const uint32_t replicas = std::max<uint32_t>(1, 64 / nc);
+  const uint64_t n_counts = (uint64_t)nc * replicas * TC_WORDS;
+  if (nc > Lo.seg_slots || nc > Lo.cap_finals || ntiles > Lo.max_tiles || ngroups > Lo.max_groups ||
+      4 * n_counts > 4 * 256 * Lo.max_groups)
+    return CXBWT_OK;
+  std::vector<Seg> text(b.big);
+  for (uint32_t c = 0; c < nc; ++c) text[c].coll = c;  // collections are numbered among those built here
+  Seg *d_text = b.B.finals;  // level 1 has no final groups
+  uint32_t *d_counts = b.B.gsum;
+  CX_CHECK(hipMemcpyAsync(d_text, text.data(), sizeof(Seg) * nc, hipMemcpyHostToDevice, st));
+  CX_CHECK(hipMemcpyAsync(b.B.tile_prefix, tp.data(), 4 * ((uint64_t)nc + 1), hipMemcpyHostToDevice, st));
+  CX_CHECK(hipMemcpyAsync(b.B.group_prefix, gp.data(), 4 * ((uint64_t)nc + 1), hipMemcpyHostToDevice, st));
+  if ((rc = fill_u32(d_counts, n_counts, 0, st))) return rc;
+  T.begin();
+  k_sample_hist<<<ntiles, BLOCK, 0, st>>>(d_text, b.B.tile_prefix, nc, b.B.text, b.B.tile_hist, d_counts, replicas);
+  CX_LAUNCHED();
+  T.end(PH_GEN);
+  std::vector<uint32_t> hc(n_counts);
+  CX_CHECK(hipMemcpyAsync(hc.data(), d_counts, 4 * n_counts, hipMemcpyDeviceToHost, st));
+  CX_CHECK(hipStreamSynchronize(st));
+  T.collect();
+
+  // the buckets' parts
+  std::vector<InduceColl> cs(nc);
+  uint64_t M = 0, tail = 0, tail_steps = 0;
+  for (uint32_t c = 0; c < nc; ++c) {
+    InduceColl &q = cs[c];
+    memset(&q, 0, sizeof(q));
+    for (uint32_t r = 0; r < replicas; ++r) {
+      const uint32_t *w = hc.data() + ((uint64_t)c * replicas + r) * TC_WORDS;
+      for (int i = 0; i < 128; ++i) (&q.n[0][0][0])[i] += w[i];
+      for (int i = 0; i < 8; ++i) q.maxrun[i] = std::max(q.maxrun[i], w[TC_MAXRUN + i]);
+      for (int i = 0; i < 4; ++i) q.samples[i] += w[TC_SAMPLES + i];
+    }
+    uint64_t at = text[c].start;
+    for (int d = 0; d < 4; ++d) {
+      for (int k = 0; k <= RUN_REGIONS; ++k) {
+        q.nl[d] += q.n[0][d][k];
+        q.ns[d] += q.n[1][d][k];
+      }
+      q.l0[d] = at;
+      at += q.nl[d] + q.ns[d];
+      q.s1[d] = at;
+      tail += (uint64_t)q.n[0][d][RUN_REGIONS] + q.n[1][d][RUN_REGIONS];
+    }
+    if (at != (uint64_t)text[c].start + text[c].len) return fail_internal("suffix types do not add up");
+    q.first_sample = M;
+    for (int d = 0; d < 4; ++d) M += q.samples[d];
+  }
+  for (int i = 0; i < 8; ++i) {
+    uint32_t longest = 0;
+    for (const InduceColl &q : cs) longest = std::max(longest, q.maxrun[i]);
+    tail_steps += longest > (uint32_t)RUN_REGIONS ? longest - RUN_REGIONS + 1 : 0;
+  }
+  // runs beyond the regions are followed a base at a time by one workgroup
+  // (about 5 us a base, 1 ns a suffix): left to the sort where they could
+  // cost half of what this saves (20 ns per 1000 bases) and more
+  if (tail_steps * 5000 + tail > nb / 100 + 50000) return CXBWT_OK;
+
+  // the samples' sort buffers, the sorted samples and the rows, in the space
+  // of the general sort buffers
+  Build s = b;
+  s.B.sample = true;
+  unsigned char *const arena = (unsigned char *)b.B.keys0;
+  const uint64_t room = (uint64_t)((unsigned char *)(b.B.hdl1 + nb) - arena);
+  uint64_t off = 0;
+  auto take = [&](uint64_t bytes) {
+    unsigned char *p = arena + off;
+    off = align_up(off + bytes);
+    return p;
+  };
+  s.B.keys0 = (uint64_t *)take(8 * M);
+  s.B.keys1 = (uint64_t *)take(8 * M);
+  s.B.hdl0 = (uint32_t *)take(4 * M);
+  s.B.hdl1 = (uint32_t *)take(4 * M);
+  s.B.smp.pl = (uint32_t *)take(4 * M);
+  s.B.smp.h = (uint32_t *)take(4 * M);
+  s.B.smp.code = (uint8_t *)take(M);
+  uint2 *rows = (uint2 *)take(8 * nb);
+  if (off > room) return CXBWT_OK;
+
+  // the steps: terminators; L of A, C, G; S of T, G, C; the rows of A
+  StepBlob blob;
+  std::vector<CollMap> cm(nc);
+  std::vector<uint32_t> cur((size_t)nc * 128, 0);
+  std::vector<IndTail> tails[2][4];
+  for (uint32_t c = 0; c < nc; ++c) {
+    cm[c] = b.cm[b.big[c].coll];
+    const InduceColl &q = cs[c];
+    for (int d = 0; d < 4; ++d) {
+      uint64_t l = q.l0[d], e = q.s1[d];
+      for (int k = 0; k < RUN_REGIONS; ++k) {
+        cur[(size_t)c * 128 + d * 16 + k] = (uint32_t)l;
+        cur[(size_t)c * 128 + 64 + d * 16 + k] = (uint32_t)e;
+        if (k == RUN_REGIONS - 1) {
+          tails[0][d].push_back(IndTail{(uint32_t)l, q.n[0][d][k], (uint32_t)(q.l0[d] + q.nl[d])});
+          tails[1][d].push_back(IndTail{(uint32_t)(e - q.n[1][d][k]), q.n[1][d][k], (uint32_t)(q.l0[d] + q.nl[d])});
+        }
+        l += q.n[0][d][k];
+        e -= q.n[1][d][k];
+      }
+    }
+  }
+  StepPlan seeds, left[3], right[4];
+  {
+    std::vector<std::vector<IndSeg>> src(nc);
+    for (uint32_t c = 0; c < nc; ++c) {
+      const uint64_t r0 = b.coll_reads[b.big[c].coll], r1 = b.coll_reads[b.big[c].coll + 1];
+      src[c] = {IndSeg{(uint32_t)r0, (uint32_t)(r1 - r0), c, SRC_READS}};
+    }
+    seeds = plan_step(blob, src);
+    for (int d = 0; d < 3; ++d) {
+      for (uint32_t c = 0; c < nc; ++c) {
+        uint64_t at = cs[c].first_sample;
+        for (int x = 0; x < d; ++x) at += cs[c].samples[x];
+        src[c] = {IndSeg{(uint32_t)cs[c].l0[d], (uint32_t)cs[c].nl[d], c, SRC_ROWS},
+                  IndSeg{(uint32_t)at, cs[c].samples[d], c, SRC_SAMPLES}};
+      }
+      left[d] = plan_step(blob, src);
+    }
+    for (int d = 0; d < 4; ++d) {
+      for (uint32_t c = 0; c < nc; ++c)
+        src[c] = {IndSeg{(uint32_t)cs[c].l0[d], (uint32_t)(cs[c].s1[d] - cs[c].l0[d]), c, SRC_ROWS}};
+      right[d] = plan_step(blob, src);
+    }
+  }
+  const size_t o_cm = blob.put(cm.data(), sizeof(CollMap) * nc);
+  const size_t o_cur = blob.put(cur.data(), 4 * cur.size());
+  size_t o_tail[2][4];
+  bool has_tail[2][4];
+  for (int t = 0; t < 2; ++t)
+    for (int d = 0; d < 4; ++d) {
+      o_tail[t][d] = blob.put(tails[t][d].data(), sizeof(IndTail) * nc);
+      has_tail[t][d] = false;
+      for (const InduceColl &q : cs) has_tail[t][d] |= q.n[t][d][RUN_REGIONS] != 0;
+    }
+  // (the descriptors take the place of the chunk list, which the sort is done with)
+  uint32_t most_tiles = seeds.ntiles, most_groups = seeds.ngroups;
+  for (const StepPlan &p : left) most_tiles = std::max(most_tiles, p.ntiles), most_groups = std::max(most_groups, p.ngroups);
+  for (const StepPlan &p : right) most_tiles = std::max(most_tiles, p.ntiles), most_groups = std::max(most_groups, p.ngroups);
+  if (blob.bytes.size() > sizeof(Seg) * Lo.cap_chunks || 256ull * most_tiles > Lo.tile_hist_bytes ||
+      256ull * most_groups > 4ull * 256 * Lo.max_groups)
+    return CXBWT_OK;
+  *taken = true;
+
+  // sort the samples: level 1 from the text, then levels and chunks
+  s.tu = Tuning{16, 8, CXBWT_SCHEDULE_MSD};
+  s.tile_len = s.tu.tile_len();
+  s.rmax = b.maxlen / SampleKey::FULL + 1;
+  s.Ls.rmax = s.rmax;
+  s.Ls.chunk = s.tu.chunk();
+  s.Ls.tile_len = s.tile_len;
+  std::vector<Seg> seg(nc);
+  g_stats.chunk_suffixes = M;
+  for (const Seg &g : b.small) g_stats.chunk_suffixes += g.len;
+  g_stats.levels = 1;
+  g_stats.big_segments += nc;
+  g_stats.level_suffixes += M;
+  for (uint32_t c = 0; c < nc; ++c) {
+    uint64_t len = 0;
+    for (int d = 0; d < 4; ++d) len += cs[c].samples[d];
+    seg[c] = Seg{(uint32_t)cs[c].first_sample, (uint32_t)len, 0, 0, 0, 0, 0, c};
+  }
+  if (M) {
+    CX_CHECK(hipMemcpyAsync(s.B.segs, seg.data(), sizeof(Seg) * nc, hipMemcpyHostToDevice, st));
+    if ((rc = fill_u32(s.B.counters + C_NFINAL, 3, 0, st))) return rc;
+    T.begin();
+    k_group_scan<false><<<ngroups, BLOCK, 0, st>>>(s.B.tile_prefix, s.B.group_prefix, nc, nullptr, s.B.tile_hist,
+                                                   s.B.gsum);
+    CX_LAUNCHED();
+    launch_level_scan(s.B, nc, ngroups, s.Ls, 1, st);
+    CX_LAUNCHED();
+    T.end(PH_SCAN);
+    T.begin();
+    k_sample_scatter<<<ntiles, 64 * SMP_NW, 0, st>>>(d_text, s.B.tile_prefix, s.B.group_prefix, nc, s.B.text,
+                                                     s.B.tile_hist, s.B.gsum, s.B.keys1, s.B.hdl1);
+    CX_LAUNCHED();
+    T.end(PH_SCATTER);
+    LevelOut o{};
+    if ((rc = read_level(s.B, o, T, st))) return rc;
+    if ((rc = finish_level(s.B, Lo, s.tu, nb, s.rmax, s.maxlen, s.bwt, o.n_chunks, o.n_finals, o.final_tiles,
+                           o.final_len, T, st)))
+      return rc;
+    if ((rc = run_levels(s, o, o.n_big, T, st))) return rc;
+  }
+
+  // the steps, with every size known
+  unsigned char *const dev = (unsigned char *)b.B.chunks;
+  CX_CHECK(hipMemcpyAsync(dev, blob.bytes.data(), blob.bytes.size(), hipMemcpyHostToDevice, st));
+  IndData D;
+  D.rows = rows;
+  D.bwt = b.bwt;
+  D.cmap = (const CollMap *)(dev + o_cm);
+  D.smp = s.B.smp;
+  D.text = b.B.text;
+  D.srank = b.B.srank;
+  D.offsets = b.offsets;
+  D.start_row = b.B.start_row;
+  D.hist = b.B.tile_hist;
+  D.gtot = b.B.gsum;
+  D.cursor = (uint32_t *)(dev + o_cur);
+  D.status = b.B.counters + C_STATUS;
+  D.nb = nb;
+  auto step = [&](const StepPlan &p, uint32_t base) {
+    return IndStep{(const IndSeg *)(dev + p.segs), (const uint32_t *)(dev + p.tiles),
+                   (const uint32_t *)(dev + p.coll_tiles), (const uint32_t *)(dev + p.coll_groups), p.nsegs, p.ntiles,
+                   nc, base};
+  };
+#define CX_STEP(LTR, PLAN, BASE)                                              \
+  do {                                                                        \
+    if ((PLAN).ntiles) {                                                      \
+      const IndStep P = step(PLAN, BASE);                                     \
+      const unsigned grid = (unsigned)ceil_div(P.ntiles, WAVES);              \
+      k_ind_count<LTR><<<grid, BLOCK, 0, st>>>(P, D);                         \
+      CX_LAUNCHED();                                                          \
+      k_ind_group<<<(PLAN).ngroups, BLOCK, 0, st>>>(P, D);                    \
+      CX_LAUNCHED();                                                          \
+      k_ind_top<LTR><<<nc, 64, 0, st>>>(P, D);                                \
+      CX_LAUNCHED();                                                          \
+      k_ind_scatter<LTR><<<grid, BLOCK, 0, st>>>(P, D);                       \
+      CX_LAUNCHED();                                                          \
+    }                                                                         \
+  } while (0)
+#define CX_TAIL(LTR, DIR, BASE)                                                                          \
+  do {                                                                                                   \
+    if (has_tail[DIR][BASE]) {                                                                           \
+      k_ind_tail<LTR><<<nc, TAIL_WG, 0, st>>>((const IndTail *)(dev + o_tail[DIR][BASE]), BASE, D);      \
+      CX_LAUNCHED();                                                                                     \
+    }                                                                                                    \
+  } while (0)
+  T.begin();
+  CX_STEP(true, seeds, 4u);
+  for (uint32_t d = 0; d < 4; ++d) {
+    CX_TAIL(true, 0, d);
+    if (d < 3) CX_STEP(true, left[d], d);
+  }
+  for (uint32_t d = 4; d-- > 0;) {
+    CX_TAIL(false, 1, d);
+    if (d) CX_STEP(false, right[d], d);
+  }
+  if (right[0].ntiles) {
+    const IndStep P = step(right[0], 0);
+    k_ind_emit<<<(unsigned)ceil_div(P.ntiles, WAVES), BLOCK, 0, st>>>(P, D);
+    CX_LAUNCHED();
+  }
+#undef CX_STEP
+#undef CX_TAIL
+  T.end(PH_INDUCE);
+  T.begin();
+  k_term<<<grid_for(b.n, 256), 256, 0, st>>>(b.offsets, b.n, b.nb, b.B.text, b.B.srank, b.B.start_row, b.term_pos);
+  CX_LAUNCHED();
+  T.end(PH_FINAL);
+  return CXBWT_OK;
+}
+
 // The whole build for ncoll collections laid end to end (a single build is
 // one collection).  coll_reads (host) holds ncoll + 1 read boundaries.
 int run_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n, uint64_t nb, uint32_t maxlen,
@@ -1148,10 +1502,22 @@ int run_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n, uint6
   if (ncoll == 1 && b.tu.schedule == CXBWT_SCHEDULE_STRINGWORD) {
     if ((rc = run_stringword(b, T, st))) return rc;
   } else {
+    bool done = false;
     Level1Vectors v;
     v.make(b);
-    level1_stats(b);
-    if ((rc = enqueue_body(b, v.src, 0, T, st))) return rc;
+    if (nb >= CXBWT_INDUCE_MIN_BASES && maxlen >= INDUCE_MIN_READ && !b.big.empty()) {
+      if (!b.small.empty()) {
+        // the collections of one chunk, by themselves (their samples' sort would come after anyway)
+        Level1Src small = v.src;
+        small.big = SegSrc{};
+        if ((rc = enqueue_body(b, small, 0, T, st))) return rc;
+      }
+      if ((rc = run_induced(b, &done, T, st))) return rc;
+    }
+    if (!done) {
+      level1_stats(b);
+      if ((rc = enqueue_body(b, v.src, 0, T, st))) return rc;
+    }
   }
   uint32_t hc[C_COUNT];
   if ((rc = read_totals(b, T, st, hc))) return rc;
@@ -1349,7 +1715,7 @@ int run_range_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n,
                  (uint8_t)(small ? 1 : 0), 0};
     if (small) {
       CX_CHECK(hipMemcpyAsync(b.B.chunks, &seg[i], sizeof(Seg), hipMemcpyHostToDevice, st));
-      if ((rc = finish_level(b.B, b.Lo, b.tu, nb, b.rmax, bwt, 1, 0, 0, 0, T, st))) return rc;
+      if ((rc = finish_level(b.B, b.Lo, b.tu, nb, b.rmax, b.maxlen, bwt, 1, 0, 0, 0, T, st))) return rc;
       continue;
     }
     CX_CHECK(hipMemcpyAsync(b.B.big_next, &seg[i], sizeof(Seg), hipMemcpyHostToDevice, st));

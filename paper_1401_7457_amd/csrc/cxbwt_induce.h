@@ -1,0 +1,1073 @@
+// cxbwt_induce.h -- the device side of the build by induced order: sort three
+// tenths of the suffixes, derive the order of the others from them.
+//
+// A suffix is of type S when it is below the suffix that follows it in its
+// read, else of type L (equal first bases: as its follower; the last suffix
+// of a read, one base before its terminator, is L).  The *samples* are the
+// S-type suffixes whose predecessor in the read is L-type: local minima, 29%
+// of the suffixes of random reads and at most half of any.  The samples are
+// sorted by the digit levels and chunks; then
+//
+//   left to right   the L-type suffixes of each first base, in order: walking
+//                   the terminators and then the buckets A, C, G (the L part
+//                   as far as it has grown, then the samples), an item whose
+//                   preceding base d is above the bucket's base c makes its
+//                   predecessor the next L-type suffix of bucket d;
+//   right to left   the S-type suffixes, from the buckets T, G, C down: a
+//                   preceding base d below c puts the predecessor before
+//                   the S-type suffixes of bucket d found so far.
+//
+// Each step is a stable partition of a bucket by the preceding base: streams
+// instead of 256-way scatters and random window loads, which is what a
+// suffix costs in the sort (two to four level passes of 24 B and 1.1 random
+// 16-byte loads for every suffix of 20x reads of 100 bases, at 51-57 G
+// loads/s on this device whatever the table).  An item is 8 bytes, its
+// position and the up to 15 bases before it, so a step reads no text.
+// Suffixes c^(k+1) x with the same base run on both sides of the bucket
+// border are all written by the step that finds the run's last member: the
+// run's k = 0..14 land in regions of their own (their sizes are counted
+// beforehand), so a bucket never feeds itself and the steps are few.
+#pragma once
+
+#include "cxbwt_kernels.h"
+
+namespace {
+
+// ---------------------------------------------------------------------------
+// windows of a text record, in 32-bit halves: a 64-bit shift by a register
+// costs two 32-bit ones, and on this device gives a wrong result now and then
+// when its amount sits in the last register the kernel is allocated
+// ---------------------------------------------------------------------------
+// {a, b} << n for n = 0, 2, .. 30, the high half
+__host__ __device__ __forceinline__ uint32_t funnel_left(uint32_t a, uint32_t b, uint32_t n) {
+  return n ? (a << n) | (b >> (32 - n)) : a;
+}
+struct Window {
+  uint32_t hi, lo;  // the bases from an offset of a record on, first highest (27 or more of the 32 are valid)
+};
+__host__ __device__ __forceinline__ Window window_at(const TextRec &t, uint32_t o) {
+  const uint32_t a = (uint32_t)(t.hi >> 32), b = (uint32_t)t.hi, c = (uint32_t)(t.lo >> 32);
+  return Window{funnel_left(a, b, 2 * o), funnel_left(b, c, 2 * o)};
+}
+// the first n (0..31) bases of a window
+__host__ __device__ __forceinline__ uint64_t first_bases(const Window &w, uint32_t n) {
+  const uint32_t hi = n >= 16 ? w.hi : w.hi & ~(~0u >> (2 * n));
+  const uint32_t lo = n > 16 ? w.lo & ~(~0u >> (2 * (n - 16))) : 0u;
+  return ((uint64_t)hi << 32) | lo;
+}
+// start bits of a record from offset o (0..16) on, 32 of them or up to its end
+__host__ __device__ __forceinline__ uint32_t starts_from(const TextRec &t, uint32_t o) {
+  const uint32_t lo = (uint32_t)t.lo, hi = (uint32_t)(t.lo >> 32) & 0x3FFu;
+  return o ? (lo >> o) | (hi << (32 - o)) : lo;
+}
+__host__ __device__ __forceinline__ uint32_t first_bit(uint32_t x) { return x ? (uint32_t)__builtin_ctz(x) : 64u; }
+// base at offset o (0..15) of a record, and the one before it
+__host__ __device__ __forceinline__ uint32_t base_in(const TextRec &t, uint32_t o) {
+  return ((uint32_t)(t.hi >> 32) >> (30 - 2 * o)) & 3u;
+}
+__host__ __device__ __forceinline__ uint32_t base_before(const TextRec &t, uint32_t o) {
+  return o ? ((uint32_t)(t.hi >> 32) >> (32 - 2 * o)) & 3u : (uint32_t)(t.lo >> 42) & 3u;
+}
+
+// ---------------------------------------------------------------------------
+// items: the bases before a position, and the key of a sample
+// ---------------------------------------------------------------------------
+// Preceding bases ("payload"): the nearest in bits 1..0, then the ones before
+// it, then a marker: 01 when more bases precede than are held, 10 when the
+// read begins there.  15 bases fit 32 bits.  A payload of 01 alone (nothing
+// held, something there) is never stored; 10 alone is a read's first base.
+constexpr uint32_t PL_UNKNOWN = 1u;
+constexpr uint32_t PL_START = 2u;
+constexpr uint32_t PL_BASES = 15;
+
+__host__ __device__ __forceinline__ uint32_t pl_top(uint32_t pl) { return 31u - (uint32_t)__builtin_clz(pl); }
+__host__ __device__ __forceinline__ uint32_t pl_len(uint32_t pl) { return pl_top(pl) >> 1; }
+__host__ __device__ __forceinline__ bool pl_more(uint32_t pl) { return !(pl_top(pl) & 1u); }
+
+// Payload of position p from the record before p's own (record p/16 - 1 holds
+// the 16 bases before p and their start bits; for p < 16 record 0).  `end`:
+// p is the end of a read of at least one base, whose own start bit belongs
+// to the next read.
+__host__ __device__ __forceinline__ uint32_t preceding_from(const TextRec &t, uint64_t p, bool end) {
+  const uint32_t o = (uint32_t)(p & 15);
+  const uint32_t at = p < 16 ? o : o + 16;  // p's offset in the record
+  const uint32_t top = (uint32_t)(t.hi >> 32);
+  const uint32_t x = p < 16 ? (o ? top >> (32 - 2 * o) : 0u) : funnel_left(top, (uint32_t)t.hi, 2 * o);
+  const uint32_t st = (uint32_t)t.lo & ((end ? 1u << at : 2u << at) - 1u);  // starts at or before p
+  const uint32_t dist = st ? at - (31u - (uint32_t)__builtin_clz(st)) : 32u;
+  const uint32_t len = dist < PL_BASES ? dist : PL_BASES;
+  return (x & ((1u << (2 * len)) - 1u)) | ((dist <= PL_BASES ? PL_START : PL_UNKNOWN) << (2 * len));
+}
+__host__ __device__ __forceinline__ uint32_t preceding(const TextRec *__restrict__ text, uint64_t p, bool end = false) {
+  return preceding_from(text[p < 16 ? 0 : (p >> 4) - 1], p, end);
+}
+
+// The nearest seven of them in 15 bits (a start that does not fit becomes
+// "more").
+constexpr int KEY_PL_BITS = 15;
+__host__ __device__ __forceinline__ uint32_t pl_trim(uint32_t pl) {
+  const uint32_t len = pl_len(pl);
+  if (len < 7 || (len == 7 && pl_more(pl))) return pl;
+  if (len == 7) return (pl & 0xFFFu) | (PL_UNKNOWN << 12);
+  return (pl & 0x3FFFu) | (PL_UNKNOWN << 14);
+}
+
+// Sample keys:  bits 63..20 22 bases, first highest, zero past the read's end
+//               bits 19..15 min(bases left, 22)
+//               bits 14..0  payload (not compared)
+// 22 bases leave room for seven preceding ones: 4% of the samples of random
+// reads are further than that from the sample before them and load their
+// preceding bases again, against 20% with five (24 bases).
+struct SampleKey {
+  static constexpr int LAST = 6;
+  static constexpr uint32_t FULL = 22;
+  static constexpr uint64_t REST = (1ull << KEY_PL_BITS) - 1;
+  static __host__ __device__ __forceinline__ uint32_t digit(uint64_t k, int j) {
+    return j < 5 ? (uint32_t)(k >> (56 - 8 * j)) & 0xFFu : j == 5 ? (uint32_t)(k >> 20) & 0xFu : clamp(k);
+  }
+  static __host__ __device__ __forceinline__ uint32_t clamp(uint64_t k) { return (uint32_t)(k >> KEY_PL_BITS) & 31u; }
+  static __host__ __device__ __forceinline__ int digit_of_bit(int top) {
+    return top >= 24 ? (63 - top) >> 3 : top >= 20 ? 5 : 6;
+  }
+  static __device__ __forceinline__ TextRec load(const TextRec *__restrict__ text, uint64_t nb, uint64_t p, uint32_t r) {
+    const uint64_t q = p + (uint64_t)FULL * r;
+    return text[(q <= nb ? q : nb) >> 4];
+  }
+  static __device__ __forceinline__ uint64_t combine(const TextRec &t, uint64_t nb, uint64_t p, uint32_t r, uint64_t old);
+};
+
+// Bases of the window at q (inside record t) up to the read's end and at most
+// `full` (<= 25) of them, first base highest; their number in `clamp`.
+__host__ __device__ __forceinline__ uint64_t later_window(const TextRec &t, uint64_t q, uint32_t full, uint32_t &clamp) {
+  const uint32_t o = (uint32_t)(q & 15);
+  const uint32_t left = first_bit(starts_from(t, o));
+  clamp = left < full ? left : full;
+  return first_bases(window_at(t, o), clamp);
+}
+
+__device__ __forceinline__ uint64_t SampleKey::combine(const TextRec &t, uint64_t nb, uint64_t p, uint32_t r,
+                                                       uint64_t old) {
+  const uint64_t q = p + (uint64_t)FULL * r;
+  if (q > nb) return old & REST;  // never taken for a live suffix
+  uint32_t cl;
+  const uint64_t x = later_window(t, q, FULL, cl);
+  return x | ((uint64_t)cl << KEY_PL_BITS) | (old & REST);
+}
+
+// Type of the suffix at p (t its record): its first base, the bases equal to
+// it that follow, and whether it is S.  left: bases to the read's end, as far
+// as the record shows (64: beyond it).
+struct SuffixType {
+  uint32_t base, run, left;
+  bool s;
+  Window bases;
+};
+__host__ __device__ __forceinline__ SuffixType suffix_type(const TextRec *__restrict__ text, TextRec t, uint64_t p) {
+  SuffixType r;
+  r.run = 0;
+  for (uint64_t q = p;;) {
+    const uint32_t o = (uint32_t)(q & 15);
+    const Window x = window_at(t, o);
+    const uint32_t next = first_bit(starts_from(t, o + 1));
+    const uint32_t left = next < 64 ? next + 1 : 64u;
+    if (q == p) {
+      r.base = x.hi >> 30;
+      r.left = left;
+      r.bases = x;
+    }
+    // a set pair: a base unlike the next
+    const uint32_t yh = x.hi ^ ((x.hi << 2) | (x.lo >> 30)), yl = x.lo ^ (x.lo << 2);
+    const uint32_t k = yh ? (uint32_t)__builtin_clz(yh) >> 1 : yl ? 16u + ((uint32_t)__builtin_clz(yl) >> 1) : 32u;
+    if (left <= 27 && k + 1 >= left) {  // the run reaches the terminator
+      r.run += left - 1;
+      r.s = false;
+      return r;
+    }
+    if (k < 26) {  // the base after the run is inside the 27 valid ones
+      r.run += k;
+      r.s = (((k < 15 ? x.hi : x.lo) >> (30 - 2 * ((k + 1) & 15))) & 3u) > r.base;
+      return r;
+    }
+    r.run += 26;
+    q += 26;  // the same base, in the same read
+    t = text[q >> 4];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// counting: what the regions of every bucket will hold, and the samples'
+// first digits per tile
+// ---------------------------------------------------------------------------
+// Per collection: [type (L, S)][base][run 0..14, 15 = longer] suffix counts,
+// the longest run per type and base, samples per first base.
+constexpr int TC_MAXRUN = 128, TC_SAMPLES = 136, TC_WORDS = 160;
+constexpr int RUN_REGIONS = 15;
+// A tile of text positions: slots of two neighbouring positions, at most one
+// of which is a sample.
+constexpr int SMP_NW = 8, SMP_TI = 8;
+constexpr uint32_t SMP_TILE = 64u * SMP_NW * SMP_TI * 2;
+
+__global__ __launch_bounds__(BLOCK) void k_sample_hist(const Seg *__restrict__ segs, const uint32_t *__restrict__ tile_prefix,
+                                                       uint32_t nsegs, const TextRec *__restrict__ text,
+                                                       uint32_t *__restrict__ tile_hist,
+                                                       uint32_t *__restrict__ counts, uint32_t replicas) {
+  constexpr uint32_t REP = 4;  // counter copies, against conflicts on the few hot classes
+  __shared__ uint32_t hist[256];
+  __shared__ uint32_t cls[REP][TC_WORDS];
+  const uint32_t tile = blockIdx.x;
+  const uint32_t s = find_upper(tile_prefix, nsegs, tile);
+  const Seg sg = segs[s];
+  const uint64_t t0 = sg.start + (uint64_t)(tile - tile_prefix[s]) * SMP_TILE;
+  const uint64_t t1 = min(t0 + (uint64_t)SMP_TILE, (uint64_t)sg.start + sg.len);
+  hist[threadIdx.x] = 0;
+  for (uint32_t i = threadIdx.x; i < REP * TC_WORDS; i += BLOCK) (&cls[0][0])[i] = 0;
+  __syncthreads();
+  uint32_t *const mine = cls[threadIdx.x % REP];
+  constexpr int PER = 8;  // record loads in flight per thread
+  for (uint64_t u0 = t0; u0 < t1; u0 += PER * BLOCK) {
+    TextRec tr[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const uint64_t p = u0 + (uint64_t)i * BLOCK + threadIdx.x;
+      tr[i] = text[(p < t1 ? p : t1 - 1) >> 4];
+    }
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const uint64_t p = u0 + (uint64_t)i * BLOCK + threadIdx.x;
+      if (p >= t1) continue;
+      const SuffixType ty = suffix_type(text, tr[i], p);
+      const uint32_t tb = (ty.s ? 4u : 0u) + ty.base;
+      atomicAdd(&mine[tb * 16 + min(ty.run, (uint32_t)RUN_REGIONS)], 1u);
+      if (ty.run >= RUN_REGIONS) atomicMax(&mine[TC_MAXRUN + tb], ty.run);
+      const uint32_t o = (uint32_t)(p & 15);
+      if (ty.s && !((tr[i].lo >> o) & 1u) && base_before(tr[i], o) > ty.base) {
+        atomicAdd(&hist[first_bases(ty.bases, min(ty.left, 4u)) >> 56], 1u);
+        atomicAdd(&mine[TC_SAMPLES + ty.base], 1u);
+      }
+    }
+  }
+  __syncthreads();
+  tile_hist[(uint64_t)tile * 256 + threadIdx.x] = hist[threadIdx.x];
+  uint32_t *const out = counts + ((uint64_t)sg.coll * replicas + tile % replicas) * TC_WORDS;
+  for (uint32_t i = threadIdx.x; i < TC_WORDS; i += BLOCK) {
+    uint32_t v = 0;
+    const bool most = i >= TC_MAXRUN && i < TC_SAMPLES;
+    for (uint32_t r = 0; r < REP; ++r) v = most ? max(v, cls[r][i]) : v + cls[r][i];
+    if (!v) continue;
+    if (most) atomicMax(&out[i], v);
+    else atomicAdd(&out[i], v);
+  }
+}
+
+// Level 1 of the samples: keys made from the text and scattered by their
+// first digit, a tile of SMP_TILE positions (at most half of them samples)
+// per workgroup.  segs: the collections' text; smp: where their samples go.
+__global__ __launch_bounds__(64 * SMP_NW) void k_sample_scatter(
+    const Seg *__restrict__ segs, const uint32_t *__restrict__ tile_prefix, const uint32_t *__restrict__ group_prefix,
+    uint32_t nsegs, const TextRec *__restrict__ text, const uint32_t *__restrict__ tile_hist,
+    const uint32_t *__restrict__ gsum, uint64_t *__restrict__ Ko, uint32_t *__restrict__ Ho) {
+  __shared__ ScatterSmem<SMP_TI, SMP_NW> S;
+  const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint32_t s = find_upper(tile_prefix, nsegs, tile);
+  const Seg sg = segs[s];
+  const uint32_t tl = tile - tile_prefix[s];
+  const uint64_t t0 = sg.start + (uint64_t)tl * SMP_TILE;
+  const uint64_t t1 = min(t0 + (uint64_t)SMP_TILE, (uint64_t)sg.start + sg.len);
+  uint64_t kr[SMP_TI];
+  uint32_t hr[SMP_TI], dig[SMP_TI];
+#pragma unroll
+  for (int i = 0; i < SMP_TI; ++i) {
+    kr[i] = 0;
+    hr[i] = 0;
+    dig[i] = NODIGIT;
+    const uint64_t p0 = t0 + 2ull * item_index<SMP_TI>(i);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const uint64_t p = p0 + j;
+      if (p >= t1) continue;
+      const uint64_t w = p >> 4;
+      const TextRec t = text[w], before = text[w ? w - 1 : 0];
+      const uint32_t o = (uint32_t)(p & 15);
+      const SuffixType ty = suffix_type(text, t, p);
+      if (ty.s && !((t.lo >> o) & 1u) && base_before(t, o) > ty.base) {
+        const uint32_t cl = ty.left < SampleKey::FULL ? ty.left : SampleKey::FULL;
+        const uint64_t x = first_bases(ty.bases, cl);
+        kr[i] = x | ((uint64_t)cl << KEY_PL_BITS) | pl_trim(preceding_from(before, p, false));
+        hr[i] = (uint32_t)p;
+        dig[i] = (uint32_t)(x >> 56);
+      }
+    }
+  }
+  const uint32_t g = group_prefix[s] + tl / GROUP_TILES;
+  if (threadIdx.x < 256)
+    S.goff[threadIdx.x] =
+        (uint64_t)gsum[(uint64_t)g * 256 + threadIdx.x] + tile_hist[(uint64_t)tile * 256 + threadIdx.x];
+  uint32_t pos[SMP_TI];
+  block_multisplit<SMP_TI, SMP_NW>(dig, pos, S.wcount, S.dstart, S.tmp);
+  __syncthreads();  // every wave has read its counters before the stage is written
+#pragma unroll
+  for (int i = 0; i < SMP_TI; ++i) {
+    if (dig[i] != NODIGIT) {
+      S.sk[pos[i]] = kr[i];
+      S.sh[pos[i]] = hr[i];
+    }
+  }
+  __syncthreads();
+  const uint32_t m = S.dstart[192];  // no sample begins with T
+  for (uint32_t q = threadIdx.x; q < m; q += 64 * SMP_NW) {
+    const uint64_t k = S.sk[q];
+    const uint32_t dd = (uint32_t)(k >> 56);
+    const uint64_t at = S.goff[dd] + (q - S.dstart[dd]);
+    Ko[at] = k;
+    Ho[at] = S.sh[q];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// rows: an item per suffix in its final place, and its code in its BWT byte
+// until the byte itself is written: bits 1..0 the preceding base, bit 2 set
+// for a read's first suffix, bits 6..3 the run of that base (1..15, 15 and
+// more alike) when it will be carried on, else 0.
+// ---------------------------------------------------------------------------
+constexpr uint32_t CODE_START = 4u;
+__host__ __device__ __forceinline__ uint32_t code_run(uint32_t code) { return code >> 3; }
+
+// Run of the nearest base of a payload with at least one, as far as it is held.
+__host__ __device__ __forceinline__ uint32_t pl_run(uint32_t pl) {
+  const uint32_t x = pl ^ ((pl & 3u) * 0x55555555u);
+  const uint32_t k = x ? (uint32_t)__builtin_ctz(x) >> 1 : 16u;
+  const uint32_t len = pl_len(pl);
+  return k < len ? k : len;
+}
+
+// Code of the item (p, pl) in bucket c.  A run that the payload does not show
+// the end of is looked up in the text when the step that reads the item
+// needs it (LTR: any other base; else only a lower one), so a stored item
+// that is carried on has its whole run, up to 15, in its payload.
+template <bool LTR>
+__device__ __forceinline__ uint32_t item_code(const TextRec *__restrict__ text, uint32_t c, uint64_t p, uint32_t &pl) {
+  if (pl == PL_UNKNOWN) pl = preceding(text, p);
+  if (pl == PL_START) return CODE_START;
+  const uint32_t e = pl & 3u;
+  if (LTR ? e == c : e >= c) return e;
+  uint32_t r = pl_run(pl);
+  if (r == pl_len(pl) && pl_more(pl) && r < PL_BASES) {
+    pl = preceding(text, p);
+    r = pl_run(pl);
+  }
+  return e | (r << 3);
+}
+
+// The sorted samples.
+struct SampleOut {
+  uint32_t *pl, *h;
+  uint8_t *code;
+};
+__device__ __forceinline__ void put_sample(const SampleOut &o, uint64_t at, uint64_t key, uint32_t first, uint32_t h,
+                                           const TextRec *__restrict__ text) {
+  uint32_t pl = (uint32_t)(key & SampleKey::REST);
+  const uint32_t code = item_code<true>(text, first, h, pl);
+  o.pl[at] = pl;
+  o.h[at] = h;
+  o.code[at] = (uint8_t)code;
+}
+
+// Groups of identical samples too large for one chunk, in place.
+__global__ __launch_bounds__(BLOCK) void k_sample_final(const Seg *__restrict__ segs, const uint32_t *__restrict__ tile_prefix,
+                                                        uint32_t nsegs, uint32_t tile_len, const uint64_t *__restrict__ keys0,
+                                                        const uint64_t *__restrict__ keys1, const uint32_t *__restrict__ hdl0,
+                                                        const uint32_t *__restrict__ hdl1, const TextRec *__restrict__ text,
+                                                        SampleOut out) {
+  const uint32_t tile = blockIdx.x;
+  const uint32_t s = find_upper(tile_prefix, nsegs, tile);
+  const Seg sg = segs[s];
+  const uint64_t t0 = sg.start + (uint64_t)(tile - tile_prefix[s]) * tile_len;
+  const uint64_t t1 = min(t0 + (uint64_t)tile_len, (uint64_t)sg.start + sg.len);
+  const uint64_t *K = sg.buf ? keys1 : keys0;
+  const uint32_t *H = sg.buf ? hdl1 : hdl0;
+  for (uint64_t j = t0 + threadIdx.x; j < t1; j += BLOCK) {
+    const uint32_t h = H[j];
+    // (the key may be a later window's: the first base comes from the text)
+    put_sample(out, j, K[j], base_in(text[h >> 4], h & 15u), h, text);
+  }
+}
+
+// ---------------------------------------------------------------------------
+// the chunk kernel of the samples: one wave sorts a chunk in LDS, as k_local
+// does, with keys of its own: bits 63..14 up to 25 bases, 13..9 the clamped
+// length, 8..0 the sample's place in the chunk as loaded.  The place is the
+// stable order among equal ordering bits, so keys are distinct and a rank is
+// one count of smaller keys; and it finds the sample's global key again, which
+// holds the payload, when the chunk is done.
+// ---------------------------------------------------------------------------
+constexpr uint64_t PLACE = 511ull;
+constexpr uint32_t CHUNK_WINDOW = 25;
+
+__device__ __forceinline__ uint32_t place_digit(uint64_t k, int j) {
+  return j < 5 ? (uint32_t)(k >> (56 - 8 * j)) & 0xFFu : j == 5 ? (uint32_t)(k >> 20) & 0xFu : (uint32_t)(k >> 9) & 31u;
+}
+__device__ __forceinline__ uint64_t place_mask(int j) {
+  return j < 5 ? 0xFFull << (56 - 8 * j) : j == 5 ? 0xFull << 20 : 31ull << 9;
+}
+
+struct PlaceDigit {
+  static __device__ __forceinline__ uint32_t digit(uint64_t k, int j) { return place_digit(k, j); }
+};
+
+// The bitonic network of bitonic_group on keys that are distinct.
+template <int LI>
+__device__ __forceinline__ void bitonic_places(LocalSmem<LI> &S, uint32_t a, uint32_t m, uint32_t lane) {
+  uint32_t P = 2;
+  while (P < m) P <<= 1;
+  for (uint32_t k = 2; k <= P; k <<= 1) {
+    for (uint32_t d = k >> 1; d > 0; d >>= 1) {
+      for (uint32_t q = lane; q < P / 2; q += LOCAL_WG) {
+        uint32_t i, l;
+        if (d == k >> 1) {  // mirrored pairs of a block of k
+          const uint32_t blk = q / d, off = q % d;
+          i = blk * k + off;
+          l = blk * k + (k - 1 - off);
+        } else {
+          i = (q / d) * 2 * d + (q % d);
+          l = i + d;
+        }
+        if (l < m) {
+          const uint64_t ki = S.K[a + i], kl = S.K[a + l];
+          if (ki > kl) {
+            const uint32_t hi = S.H[a + i], hl = S.H[a + l];
+            S.K[a + i] = kl;
+            S.K[a + l] = ki;
+            S.H[a + i] = hl;
+            S.H[a + l] = hi;
+          }
+        }
+      }
+      __syncthreads();
+    }
+  }
+}
+
+template <int LI>
+__device__ __forceinline__ void sort_big_places(LocalSmem<LI> &S, uint32_t ngroups, uint32_t lane) {
+  for (uint32_t g0 = 0; g0 < ngroups; g0 += LOCAL_WG) {
+    const uint32_t g = g0 + lane;
+    const bool big = g < ngroups && (uint32_t)S.hp[g + 1] - S.hp[g] > BIG_GROUP;
+    uint64_t todo = __ballot(big);
+    while (todo) {
+      const uint32_t b = g0 + (uint32_t)__builtin_ctzll(todo);
+      todo &= todo - 1;
+      const uint32_t x0 = S.hp[b];
+      bitonic_places(S, (uint32_t)S.live[x0], (uint32_t)S.hp[b + 1] - x0, lane);
+    }
+  }
+}
+
+// #{t in [a, e) : k_t < v} by the keys' low words (T = uint32_t) or whole, four
+// reads a step.  (The low words are read as parts of the 64-bit keys: read
+// through a pointer of another type, they need not follow the keys' writes.)
+template <typename T>
+__device__ __forceinline__ uint32_t count_smaller(const uint64_t *k, uint32_t a, uint32_t e, T v) {
+  uint32_t c = 0;
+  const uint64_t *p = k + a;
+  const uint64_t *const pe = k + e, *const pe3 = k + (e >= 3 ? e - 3 : 0);
+  for (; p < pe3; p += 4)
+    c += (uint32_t)((T)p[0] < v) + (uint32_t)((T)p[1] < v) + (uint32_t)((T)p[2] < v) + (uint32_t)((T)p[3] < v);
+  for (; p < pe; ++p) c += (uint32_t)((T)*p < v);
+  return c;
+}
+
+template <int LI, int OCC>
+__global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
+    const Seg *__restrict__ chunks, const uint64_t *__restrict__ keys0, const uint64_t *__restrict__ keys1,
+    const uint32_t *__restrict__ hdl0, const uint32_t *__restrict__ hdl1, const TextRec *__restrict__ text,
+    uint32_t maxlen, SampleOut out, uint32_t *status, unsigned long long *fetches) {
+  static_assert(LI * LOCAL_WG <= 512, "a place in a chunk is 9 bits");
+  __shared__ LocalSmem<LI> S;
+  const uint32_t lane = threadIdx.x;
+  const uint64_t le = lanemask_lt() | (1ull << lane);
+  uint32_t nfetch = 0;
+  const Seg ch = chunks[blockIdx.x];
+  const uint32_t m = ch.len;
+  const uint64_t *Kg = (ch.buf ? keys1 : keys0) + ch.start;
+  const uint32_t *Hg = (ch.buf ? hdl1 : hdl0) + ch.start;
+  {
+    uint64_t lk[LI];
+    uint32_t lh[LI];
+#pragma unroll
+    for (int i = 0; i < LI; ++i) {
+      const uint32_t j = i * LOCAL_WG + lane;
+      lk[i] = Kg[j < m ? j : m - 1];
+      lh[i] = Hg[j < m ? j : m - 1];
+    }
+#pragma unroll
+    for (int i = 0; i < LI; ++i) {
+      const uint32_t j = i * LOCAL_WG + lane;
+      if (j < m) {
+        S.K[j] = (lk[i] & (~0ull << 20)) | ((uint64_t)SampleKey::clamp(lk[i]) << 9) | j;
+        S.H[j] = lh[i];
+      }
+    }
+  }
+  __syncthreads();
+  // as k_local: ordered by digits d and d + 1 first (one bucket: d + 1 is
+  // enough), then groups of equal digits
+  const int d0 = ch.d;
+  const bool two = d0 < SampleKey::LAST;
+  if (two) {
+    const bool one_bucket = place_digit(S.K[0], d0) == place_digit(S.K[m - 1], d0);
+    wave_split<PlaceDigit>(S, m, d0 + 1, lane, le & ~(1ull << lane));
+    if (!one_bucket) wave_split<PlaceDigit>(S, m, d0, lane, le & ~(1ull << lane));
+  }
+  const uint64_t hmask = two ? (place_mask(d0) | place_mask(d0 + 1)) : place_mask(d0);
+  uint32_t n = 0, ngroups = 0;
+  {
+    uint32_t run = 0;
+#pragma unroll
+    for (int i = 0; i < LI; ++i) {
+      if (i * LOCAL_WG >= (int)m) break;
+      const uint32_t j = i * LOCAL_WG + lane;
+      bool keep = false, h = false;
+      if (j < m) {
+        const uint64_t kj = S.K[j];
+        h = j == 0 || ((kj ^ S.K[j - 1]) & hmask) != 0;
+        const bool hn = j + 1 >= m || ((S.K[j + 1] ^ kj) & hmask) != 0;
+        keep = !(h && hn);
+      }
+      const uint64_t hm = __ballot(h);
+      if (lane == 0) {
+        S.headw[2 * i] = (uint32_t)hm;
+        S.headw[2 * i + 1] = (uint32_t)(hm >> 32);
+      }
+      const uint64_t kb = __ballot(keep);
+      const uint64_t hb = __ballot(keep && h);
+      if (keep) {
+        const uint32_t xn = n + (uint32_t)__popcll(kb & (le >> 1));
+        const uint32_t g = run + (uint32_t)__popcll(hb & le) - 1u;
+        S.live[xn] = (uint16_t)j;
+        S.gr[xn] = (uint16_t)g;
+        if (h) S.hp[g] = (uint16_t)xn;
+      }
+      n += (uint32_t)__popcll(kb);
+      run += (uint32_t)__popcll(hb);
+    }
+    if (lane == 0) S.hp[run] = (uint16_t)n;
+    ngroups = run;
+  }
+  __syncthreads();
+  uint32_t depth = SampleKey::FULL * ((uint32_t)ch.r + 1);  // bases compared once the current window is sorted
+  uint32_t full = SampleKey::FULL;
+  bool fetch_round = false;
+  for (;;) {
+    if (!fetch_round) {
+      if (n == 0) break;
+    } else {
+      // drop single samples and runs of equal keys that end inside the
+      // window; see k_local
+      uint32_t kept = 0, run = 0;
+#pragma unroll
+      for (int i = 0; i < LI; ++i) {
+        if (i * LOCAL_WG >= (int)n) break;
+        const uint32_t x = i * LOCAL_WG + lane;
+        bool keep = false, hd = false, fresh = false;
+        uint16_t pos = 0;
+        if (x < n) {
+          pos = S.live[x];
+          const uint64_t kp = S.K[pos];
+          hd = head_at(S, pos);
+          if (!hd) fresh = hd = ((kp ^ S.K[pos - 1]) & ~PLACE) != 0;
+          bool next_hd = true;
+          if (x + 1 < n) {
+            const uint32_t p1 = S.live[x + 1];
+            next_hd = head_at(S, p1);
+            if (!next_hd) next_hd = ((S.K[p1] ^ kp) & ~PLACE) != 0;
+          }
+          keep = !(hd && next_hd) && ((uint32_t)(kp >> 9) & 31u) == full;
+        }
+        const uint64_t kb = __ballot(keep);
+        const uint64_t hb = __ballot(keep && hd);
+        if (keep) {
+          const uint32_t xn = kept + (uint32_t)__popcll(kb & (le >> 1));
+          const uint32_t g = run + (uint32_t)__popcll(hb & le) - 1u;
+          S.live[xn] = pos;
+          S.gr[xn] = (uint16_t)g;
+          if (hd) S.hp[g] = (uint16_t)xn;
+          if (fresh) atomicOr(&S.headw[pos >> 5], 1u << (pos & 31u));
+        }
+        kept += (uint32_t)__popcll(kb);
+        run += (uint32_t)__popcll(hb);
+      }
+      n = kept;
+      ngroups = run;
+      if (n == 0) break;
+      if (lane == 0) S.hp[run] = (uint16_t)n;
+      __syncthreads();
+      if (depth > maxlen) {  // a suffix this deep does not exist
+        if (lane == 0) atomicOr(status, ST_WINDOW_BOUND);
+        break;
+      }
+      // the next window of every live sample (all of them hold `depth`
+      // bases, so the window starts inside the read or at its end)
+      for (uint32_t x0 = 0; x0 < n; x0 += FETCH_BATCH * LOCAL_WG) {
+        TextRec tr[FETCH_BATCH];
+        uint32_t tp[FETCH_BATCH];
+        uint64_t q[FETCH_BATCH];
+#pragma unroll
+        for (int i = 0; i < FETCH_BATCH; ++i) {
+          const uint32_t x = x0 + i * LOCAL_WG + lane;
+          tp[i] = S.live[x < n ? x : 0];
+          q[i] = (uint64_t)S.H[tp[i]] + depth;
+        }
+#pragma unroll
+        for (int i = 0; i < FETCH_BATCH; ++i) tr[i] = text[q[i] >> 4];
+#pragma unroll
+        for (int i = 0; i < FETCH_BATCH; ++i) {
+          const uint32_t x = x0 + i * LOCAL_WG + lane;
+          if (x < n) {
+            uint32_t cl;
+            const uint64_t w = later_window(tr[i], q[i], CHUNK_WINDOW, cl);
+            S.K[tp[i]] = w | ((uint64_t)cl << 9) | (S.K[tp[i]] & PLACE);
+            ++nfetch;
+          }
+        }
+      }
+      depth += CHUNK_WINDOW;
+      full = CHUNK_WINDOW;
+      __syncthreads();
+    }
+    // rank inside each live group (a run of positions): every rank is taken
+    // before any entry moves.  After two splits from digit d >= 2 a group
+    // agrees in its keys' high words.
+    bool big_groups = false;
+    const bool low_words = !fetch_round && two && d0 >= 2;
+    for (uint32_t x = lane; x < n; x += LOCAL_WG) {
+      const uint32_t j = S.live[x];
+      const uint32_t g = S.gr[x];
+      const uint32_t x0 = S.hp[g];
+      const uint32_t a = S.live[x0];
+      const uint32_t e = a + ((uint32_t)S.hp[g + 1] - x0);
+      if (e - a > BIG_GROUP) {
+        S.gr[x] = (uint16_t)j;
+        big_groups = true;
+        continue;
+      }
+      const uint64_t kj = S.K[j];
+      const uint32_t c = low_words ? count_smaller<uint32_t>(S.K, a, e, (uint32_t)kj) : count_smaller<uint64_t>(S.K, a, e, kj);
+      S.gr[x] = (uint16_t)(a + c);
+    }
+    __syncthreads();
+    {
+      uint64_t sk[LI];
+      uint32_t sh[LI], sd[LI];
+#pragma unroll
+      for (int i = 0; i < LI; ++i) {
+        const uint32_t x = i * LOCAL_WG + lane;
+        if (x < n) {
+          const uint32_t j = S.live[x];
+          sk[i] = S.K[j];
+          sh[i] = S.H[j];
+          sd[i] = S.gr[x];
+        }
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < LI; ++i) {
+        const uint32_t x = i * LOCAL_WG + lane;
+        if (x < n) {
+          S.K[sd[i]] = sk[i];
+          S.H[sd[i]] = sh[i];
+        }
+      }
+    }
+    __syncthreads();
+    if (__ballot(big_groups)) sort_big_places(S, ngroups, lane);
+    fetch_round = true;
+  }
+  {
+    uint64_t g[LI];
+#pragma unroll
+    for (int i = 0; i < LI; ++i) {
+      const uint32_t j = i * LOCAL_WG + lane;
+      g[i] = Kg[j < m ? (uint32_t)(S.K[j] & PLACE) : 0u];
+    }
+#pragma unroll
+    for (int i = 0; i < LI; ++i) {
+      const uint32_t j = i * LOCAL_WG + lane;
+      if (j >= m) continue;
+      const uint32_t h = S.H[j];
+      // a key of a later window does not hold the first base
+      const uint32_t first = ch.r ? base_in(text[h >> 4], h & 15u) : (uint32_t)(g[i] >> 62);
+      put_sample(out, (uint64_t)ch.start + j, g[i], first, h, text);
+    }
+  }
+  nfetch = wave_incl_sum(nfetch);
+  if (lane == 63 && nfetch) atomicAdd(stat_slot(fetches), (unsigned long long)nfetch);
+}
+
+// ---------------------------------------------------------------------------
+// the steps: stable partitions of a bucket by the preceding base
+// ---------------------------------------------------------------------------
+// A step's sources, in order: runs of rows, of samples or (the first step) of
+// reads, a wave tile at a time; tiles in groups of GROUP_TILES within a
+// collection.  Classes: (base d, run index k) at d * 16 + k, one per lane.
+constexpr uint32_t IND_SLOTS = 32;
+constexpr uint32_t IND_TILE = 64 * IND_SLOTS;
+constexpr uint32_t IND_BATCH = 8;  // slots whose loads are in flight together
+enum { SRC_ROWS = 0, SRC_SAMPLES = 1, SRC_READS = 2 };
+struct IndSeg {
+  uint32_t start, len, coll, src;
+};
+struct IndStep {
+  const IndSeg *segs;
+  const uint32_t *tile_prefix;                 // nsegs + 1
+  const uint32_t *coll_tiles, *coll_groups;    // ncoll + 1 each
+  uint32_t nsegs, ntiles, ncoll, base;         // base: the bucket's (4: the terminators)
+};
+struct IndData {
+  uint2 *rows;  // {position, payload}
+  uint8_t *bwt;
+  const CollMap *cmap;
+  SampleOut smp;
+  const TextRec *text;
+  const uint32_t *srank;
+  const uint64_t *offsets;
+  uint64_t *start_row;
+  uint32_t *hist;    // per tile and class
+  uint32_t *gtot;    // per group and class
+  uint32_t *cursor;  // per collection, direction and class: where the next item goes (S: ends)
+  uint32_t *status;
+  uint64_t nb;
+};
+
+// Entry x of a segment: position, payload, code.
+__device__ __forceinline__ void ind_read_end(const IndData &D, uint64_t i, uint32_t &p, uint32_t &pl, uint32_t &code) {
+  const uint64_t a = D.offsets[i], e = D.offsets[i + 1];
+  p = 0;
+  pl = PL_START;
+  code = CODE_START;
+  if (e > a) {
+    pl = preceding(D.text, e, true);
+    p = (uint32_t)e;
+    code = (pl & 3u) | (pl_run(pl) << 3);
+  }
+}
+
+template <bool LTR>
+__device__ __forceinline__ bool ind_taken(uint32_t code, uint32_t c) {
+  return !(code & CODE_START) && (LTR ? c == 4 || (code & 3u) > c : (code & 3u) < c);
+}
+
+// Class counts of every wave tile.
+template <bool LTR>
+__global__ __launch_bounds__(BLOCK) void k_ind_count(IndStep P, IndData D) {
+  constexpr uint32_t REP = 16;  // counter copies per wave, against conflicts on the hot classes
+  __shared__ uint32_t cnt[WAVES][REP][65];
+  const uint32_t w = threadIdx.x >> 6, l = lane_id();
+  const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * WAVES + w));
+  for (uint32_t r = 0; r < REP; ++r) cnt[w][r][l] = 0;
+  __syncthreads();
+  if (tile < P.ntiles) {
+    const uint32_t s = find_upper(P.tile_prefix, P.nsegs, tile);
+    const IndSeg sg = P.segs[s];
+    const uint32_t t0 = (tile - P.tile_prefix[s]) * IND_TILE;
+    const uint32_t m = min(IND_TILE, sg.len - t0);
+    const uint64_t at0 = (uint64_t)sg.start + t0;
+    const uint8_t *codes = sg.src == SRC_SAMPLES ? D.smp.code + at0 : D.bwt + D.cmap[sg.coll].out_shift + at0;
+    for (uint32_t x0 = 0; x0 < m; x0 += IND_BATCH * 64) {
+      uint32_t code[IND_BATCH];
+#pragma unroll
+      for (uint32_t i = 0; i < IND_BATCH; ++i) {
+        const uint32_t x = x0 + i * 64 + l;
+        code[i] = CODE_START;
+        if (x < m) {
+          uint32_t p, pl;
+          if (LTR && sg.src == SRC_READS) ind_read_end(D, at0 + x, p, pl, code[i]);
+          else code[i] = codes[x];
+        }
+      }
+#pragma unroll
+      for (uint32_t i = 0; i < IND_BATCH; ++i)
+        if (ind_taken<LTR>(code[i], P.base))
+          atomicAdd(&cnt[w][l % REP][(code[i] & 3u) * 16 + code_run(code[i])], 1u);
+    }
+  }
+  __syncthreads();
+  if (tile < P.ntiles) {
+    uint32_t v = 0;
+    for (uint32_t r = 0; r < REP; ++r) v += cnt[w][r][l];
+    // runs longer than k: sum over the classes above, within the 16 of a base
+    uint32_t sum = v;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      const uint32_t t = __shfl_down(sum, o, 16);
+      if ((l & 15u) + o < 16) sum += t;
+    }
+    D.hist[(uint64_t)tile * 64 + l] = sum - v;
+  }
+}
+
+// Tile counts to exclusive prefixes inside a group, and the group's totals.
+__global__ __launch_bounds__(BLOCK) void k_ind_group(IndStep P, IndData D) {
+  constexpr uint32_t PER = GROUP_TILES / WAVES;
+  __shared__ uint32_t tot[WAVES][64];
+  const uint32_t g = blockIdx.x;
+  const uint32_t c = find_upper(P.coll_groups, P.ncoll, g);
+  const uint32_t tb = P.coll_tiles[c] + (g - P.coll_groups[c]) * GROUP_TILES;
+  const uint32_t te = min(tb + (uint32_t)GROUP_TILES, P.coll_tiles[c + 1]);
+  const uint32_t w = threadIdx.x >> 6, l = lane_id();
+  const uint32_t t0 = tb + w * PER;
+  uint32_t x[PER], sum = 0;
+#pragma unroll
+  for (uint32_t i = 0; i < PER; ++i) x[i] = t0 + i < te ? D.hist[(uint64_t)(t0 + i) * 64 + l] : 0u;
+#pragma unroll
+  for (uint32_t i = 0; i < PER; ++i) sum += x[i];
+  tot[w][l] = sum;
+  __syncthreads();
+  uint32_t run = 0;
+  for (uint32_t ww = 0; ww < w; ++ww) run += tot[ww][l];
+#pragma unroll
+  for (uint32_t i = 0; i < PER; ++i) {
+    if (t0 + i < te) D.hist[(uint64_t)(t0 + i) * 64 + l] = run;
+    run += x[i];
+  }
+  if (w == WAVES - 1) D.gtot[(uint64_t)g * 64 + l] = run;
+}
+
+// Group totals to first places, from the collection's cursors; one wave a
+// collection.  Right to left a step's items go in front of the earlier ones.
+template <bool LTR>
+__global__ __launch_bounds__(64) void k_ind_top(IndStep P, IndData D) {
+  constexpr uint32_t NB = 16;
+  const uint32_t c = blockIdx.x, l = threadIdx.x;
+  const uint32_t g0 = P.coll_groups[c], g1 = P.coll_groups[c + 1];
+  uint32_t *cur = D.cursor + ((uint64_t)c * 2 + (LTR ? 0 : 1)) * 64 + l;
+  uint32_t run = *cur;
+  if (!LTR) {
+    uint32_t g = g0;
+    for (; g + NB <= g1; g += NB) {
+      uint32_t x[NB];
+#pragma unroll
+      for (uint32_t i = 0; i < NB; ++i) x[i] = D.gtot[(uint64_t)(g + i) * 64 + l];
+#pragma unroll
+      for (uint32_t i = 0; i < NB; ++i) run -= x[i];
+    }
+    for (; g < g1; ++g) run -= D.gtot[(uint64_t)g * 64 + l];
+    *cur = run;
+  }
+  uint32_t g = g0;
+  for (; g + NB <= g1; g += NB) {
+    uint32_t x[NB];
+#pragma unroll
+    for (uint32_t i = 0; i < NB; ++i) x[i] = D.gtot[(uint64_t)(g + i) * 64 + l];
+#pragma unroll
+    for (uint32_t i = 0; i < NB; ++i) {
+      D.gtot[(uint64_t)(g + i) * 64 + l] = run;
+      run += x[i];
+    }
+  }
+  for (; g < g1; ++g) {
+    const uint32_t x = D.gtot[(uint64_t)g * 64 + l];
+    D.gtot[(uint64_t)g * 64 + l] = run;
+    run += x;
+  }
+  if (LTR) *cur = run;
+}
+
+// Copy k of the run that precedes item (p, pl): the suffix k + 1 bases
+// earlier, in bucket d at row g.
+template <bool LTR>
+__device__ __forceinline__ void ind_put(const IndData &D, const CollMap &cm, uint64_t g, uint32_t d, uint32_t k,
+                                        uint32_t r, uint32_t p, uint32_t pl) {
+  const uint32_t q = p - 1 - k;
+  uint32_t x = pl >> (2 * (k + 1));
+  const uint32_t code = k + 1 < r ? d : item_code<LTR>(D.text, d, q, x);
+  if (g >= D.nb) {
+    atomicOr(D.status, ST_LIST_OVERFLOW);
+    return;
+  }
+  D.rows[g] = make_uint2(q, x);
+  D.bwt[g + cm.out_shift] = (uint8_t)code;
+}
+
+// The BWT byte of a row whose step is the last to read its code.
+__device__ __forceinline__ void ind_emit(const IndData &D, const CollMap &cm, uint64_t j, uint32_t code, uint32_t p) {
+  const uint32_t lut = 'A' | ('C' << 8) | ('G' << 16) | ('T' << 24);
+  const bool first = (code & CODE_START) != 0;
+  D.bwt[j + cm.out_shift] = first ? (uint8_t)'$' : (uint8_t)(lut >> (8 * (code & 3u)));
+  if (first) D.start_row[start_rank(D.text, D.srank, p)] = (uint64_t)((int64_t)j + cm.row_shift);
+}
+
+// Class ranks of one slot: this lane's place, from the wave's class bases
+// (first class of d in nxt[d]); advances them.
+__device__ __forceinline__ uint32_t ind_place(bool ok, uint32_t d, uint32_t (&nxt)[4], uint32_t lo, uint32_t hi) {
+  uint32_t g = 0;
+#pragma unroll
+  for (uint32_t dd = 0; dd < 4; ++dd) {
+    if (dd < lo || dd >= hi) continue;
+    const bool is = ok && d == dd;
+    const uint64_t mk = __ballot(is);
+    if (is) g = nxt[dd] + bits_below_lane(mk);
+    nxt[dd] += (uint32_t)__popcll(mk);
+  }
+  return g;
+}
+
+// The partition itself, a wave a tile.  Copy 0 of every item first; the items
+// whose run is longer (a quarter of them) are listed and their further
+// copies written list by list, so that full waves write them.
+template <bool LTR>
+__global__ __launch_bounds__(BLOCK) void k_ind_scatter(IndStep P, IndData D) {
+  __shared__ uint16_t lists[WAVES][IND_TILE];
+  const uint32_t w = threadIdx.x >> 6, l = lane_id();
+  const uint32_t tile =
+      (uint32_t)__builtin_amdgcn_readfirstlane((int)(xcd_tile(blockIdx.x, gridDim.x) * WAVES + w));
+  if (tile >= P.ntiles) return;
+  uint16_t *const list = lists[w];
+  const uint32_t s = find_upper(P.tile_prefix, P.nsegs, tile);
+  const IndSeg sg = P.segs[s];
+  const CollMap cm = D.cmap[sg.coll];
+  const uint32_t t0 = (tile - P.tile_prefix[s]) * IND_TILE;
+  const uint32_t m = min(IND_TILE, sg.len - t0);
+  const uint64_t at0 = (uint64_t)sg.start + t0;
+  const uint32_t g = P.coll_groups[sg.coll] + (tile - P.coll_tiles[sg.coll]) / GROUP_TILES;
+  const uint32_t base = D.gtot[(uint64_t)g * 64 + l] + D.hist[(uint64_t)tile * 64 + l];
+  // bases the step's items can go to
+  const uint32_t lo = LTR ? (P.base == 4 ? 0u : P.base + 1) : 0u, hi = LTR ? 4u : P.base;
+  auto item = [&](uint32_t x, uint32_t &p, uint32_t &pl) {
+    if (!LTR || sg.src == SRC_ROWS) {
+      const uint2 v = D.rows[at0 + x];
+      p = v.x;
+      pl = v.y;
+    } else if (sg.src == SRC_SAMPLES) {
+      p = D.smp.h[at0 + x];
+      pl = D.smp.pl[at0 + x];
+    } else {
+      uint32_t code;
+      ind_read_end(D, at0 + x, p, pl, code);
+    }
+  };
+  uint32_t nxt[4];
+#pragma unroll
+  for (uint32_t dd = 0; dd < 4; ++dd) nxt[dd] = (uint32_t)__builtin_amdgcn_readlane((int)base, (int)(dd * 16));
+  uint32_t n1 = 0;
+  const uint8_t *codes = sg.src == SRC_SAMPLES ? D.smp.code + at0 : D.bwt + cm.out_shift + at0;
+  for (uint32_t x0 = 0; x0 < m; x0 += IND_BATCH * 64) {
+    uint32_t code[IND_BATCH], p[IND_BATCH], pl[IND_BATCH];
+#pragma unroll
+    for (uint32_t i = 0; i < IND_BATCH; ++i) {
+      const uint32_t x = x0 + i * 64 + l;
+      code[i] = CODE_START;
+      p[i] = 0;
+      pl[i] = PL_START;
+      if (x < m) {
+        if (LTR && sg.src == SRC_READS) {
+          ind_read_end(D, at0 + x, p[i], pl[i], code[i]);
+        } else {
+          code[i] = codes[x];
+          item(x, p[i], pl[i]);
+        }
+      }
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < IND_BATCH; ++i) {
+      const uint32_t x = x0 + i * 64 + l;
+      const bool ok = ind_taken<LTR>(code[i], P.base);
+      const uint32_t d = code[i] & 3u, r = code_run(code[i]);
+      const uint32_t to = ind_place(ok, d, nxt, lo, hi);
+      if (ok) ind_put<LTR>(D, cm, to, d, 0, r, p[i], pl[i]);
+      const uint64_t more = __ballot(ok && r > 1);
+      if (ok && r > 1) list[n1 + bits_below_lane(more)] = (uint16_t)(x | (r << 11));
+      n1 += (uint32_t)__popcll(more);
+      if (!LTR && x < m) ind_emit(D, cm, at0 + x, code[i], p[i]);
+    }
+  }
+  static_assert(IND_TILE <= 2048, "a list entry holds the place in 11 bits");
+  for (uint32_t k = 1; n1 && k < (uint32_t)RUN_REGIONS; ++k) {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the list is read by other lanes than wrote it
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (uint32_t dd = 0; dd < 4; ++dd) nxt[dd] = (uint32_t)__builtin_amdgcn_readlane((int)base, (int)(dd * 16 + k));
+    uint32_t n2 = 0;
+    for (uint32_t y0 = 0; y0 < n1; y0 += 64) {
+      const uint32_t y = y0 + l;
+      const bool in = y < n1;
+      const uint32_t e = in ? list[y] : 0u;
+      const uint32_t r = e >> 11;
+      uint32_t p = 0, pl = PL_START;
+      if (in) item(e & 2047u, p, pl);
+      const uint32_t d = pl & 3u;  // the preceding base is the payload's first
+      const uint32_t to = ind_place(in, d, nxt, lo, hi);
+      if (in) ind_put<LTR>(D, cm, to, d, k, r, p, pl);
+      const uint64_t more = __ballot(in && r > k + 1);
+      __builtin_amdgcn_wave_barrier();  // this slot's entries are read before any is overwritten
+      if (in && r > k + 1) list[n2 + bits_below_lane(more)] = (uint16_t)e;
+      n2 += (uint32_t)__popcll(more);
+    }
+    n1 = n2;
+  }
+}
+
+// Runs beyond the regions: the members of region 14 (and of every later one)
+// whose preceding base is still the bucket's, one base further, until there
+// is none.  One workgroup a collection; rare and short (runs of 16 and more).
+constexpr int TAIL_WG = 1024;
+struct IndTail {
+  uint32_t start, len, limit;  // region 14; the end (L) or start (S) of the bucket's part
+};
+template <bool LTR>
+__global__ __launch_bounds__(TAIL_WG) void k_ind_tail(const IndTail *__restrict__ tails, uint32_t c, IndData D) {
+  constexpr int NW = TAIL_WG / 64;
+  __shared__ uint32_t tmp[NW];
+  const IndTail t = tails[blockIdx.x];
+  const CollMap cm = D.cmap[blockIdx.x];
+  uint64_t s = t.start, e = s + t.len;
+  auto goes_on = [&](uint64_t j) {
+    return j < e && D.bwt[j + cm.out_shift] == (uint8_t)c;  // the bucket's base, no run
+  };
+  for (;;) {
+    uint32_t mine = 0, total = 0;
+    for (uint64_t j = s + threadIdx.x; j < e; j += TAIL_WG) mine += goes_on(j);
+    (void)block_excl_sum<NW>(mine, tmp, &total);
+    if (!total) return;
+    if (LTR ? e + total > t.limit : s < (uint64_t)t.limit + total) {
+      if (threadIdx.x == 0) atomicOr(D.status, ST_LIST_OVERFLOW);
+      return;
+    }
+    uint64_t to = LTR ? e : s - total;
+    const uint64_t first = to;
+    for (uint64_t j0 = s; j0 < e; j0 += TAIL_WG) {
+      const uint64_t j = j0 + threadIdx.x;
+      const bool on = goes_on(j);
+      uint32_t cnt = 0;
+      const uint32_t at = block_excl_sum<NW>(on ? 1u : 0u, tmp, &cnt);
+      if (on) {
+        const uint2 v = D.rows[j];
+        uint32_t x = v.y >> 2;
+        const uint32_t code = item_code<LTR>(D.text, c, v.x - 1, x);
+        D.rows[to + at] = make_uint2(v.x - 1, x);
+        D.bwt[to + at + cm.out_shift] = (uint8_t)code;
+      }
+      to += cnt;
+    }
+    __syncthreads();
+    s = first;
+    e = first + total;
+  }
+}
+
+// BWT bytes of the rows that no step reads (bucket A).
+__global__ __launch_bounds__(BLOCK) void k_ind_emit(IndStep P, IndData D) {
+  const uint32_t tile = blockIdx.x * WAVES + (threadIdx.x >> 6);
+  if (tile >= P.ntiles) return;
+  const uint32_t s = find_upper(P.tile_prefix, P.nsegs, tile);
+  const IndSeg sg = P.segs[s];
+  const CollMap cm = D.cmap[sg.coll];
+  const uint32_t t0 = (tile - P.tile_prefix[s]) * IND_TILE;
+  const uint32_t m = min(IND_TILE, sg.len - t0);
+  for (uint32_t x = lane_id(); x < m; x += 64) {
+    const uint64_t j = (uint64_t)sg.start + t0 + x;
+    const uint32_t code = D.bwt[j + cm.out_shift];
+    ind_emit(D, cm, j, code, code & CODE_START ? D.rows[j].x : 0u);
+  }
+}
+
+}  // namespace

@@ -115,6 +115,27 @@ struct Lists {
   uint32_t tile_len;  // suffixes per level tile
 };
 
+// Key formats of the level kernels: which bits order, how they fall into
+// digits, how many bases a full window holds, and how the key of a later
+// window is made.  GeneralKey is the key of device_common.h; SampleKey, of
+// the build by induced order, is in cxbwt_induce.h.
+struct GeneralKey {
+  static constexpr int LAST = 7;             // the digit that holds the clamped length
+  static constexpr uint32_t FULL = W;        // clamped length of a full window
+  static constexpr uint64_t REST = 7ull;     // bits that do not order
+  static __host__ __device__ __forceinline__ uint32_t digit(uint64_t k, int j) { return digit_of(k, j); }
+  static __host__ __device__ __forceinline__ uint32_t clamp(uint64_t k) { return clamp_of(k); }
+  // digit of the highest ordering bit that varies
+  static __host__ __device__ __forceinline__ int digit_of_bit(int top) { return top >= 8 ? (63 - top) >> 3 : 7; }
+  static __device__ __forceinline__ TextRec load(const TextRec *__restrict__ text, uint64_t nb, uint64_t p, uint32_t r) {
+    return window_load(text, nb, p, r);
+  }
+  static __device__ __forceinline__ uint64_t combine(const TextRec &t, uint64_t nb, uint64_t p, uint32_t r,
+                                                     uint64_t old) {
+    return window_combine(t, nb, p, r, (uint32_t)old & 7u);
+  }
+};
+
 // Number of read starts strictly before base p: for the first base of a
 // read, the index of that read among the non-empty reads.  srank[w] counts
 // the starts at positions below 16w.
@@ -462,7 +483,7 @@ struct ScatterSmem {
   uint32_t tmp[NW];
 };
 
-template <int TI, int NW>
+template <class F, int TI, int NW>
 __device__ __forceinline__ void tile_scatter(ScatterSmem<TI, NW> &S, const uint64_t (&kr)[TI],
                                              const uint32_t (&hr)[TI], const uint32_t (&dig)[TI], uint32_t m, int d,
                                              uint64_t *__restrict__ Ko, uint32_t *__restrict__ Ho) {
@@ -479,7 +500,7 @@ __device__ __forceinline__ void tile_scatter(ScatterSmem<TI, NW> &S, const uint6
   __syncthreads();
   for (uint32_t q = threadIdx.x; q < m; q += 64 * NW) {
     const uint64_t k = S.sk[q];
-    const uint32_t dd = digit_of(k, d);
+    const uint32_t dd = F::digit(k, d);
     const uint64_t g = S.goff[dd] + (q - S.dstart[dd]);
     Ko[g] = k;
     Ho[g] = S.sh[q];
@@ -529,7 +550,7 @@ __global__ __launch_bounds__(64 * NW) void k_gen_scatter(const Seg *__restrict__
   if (threadIdx.x < 256)
     S.goff[threadIdx.x] =
         (uint64_t)gsum[(uint64_t)g * 256 + threadIdx.x] + tile_hist[(uint64_t)tile * 256 + threadIdx.x];
-  tile_scatter(S, kr, hr, dig, m, 0, Ko, Ho);
+  tile_scatter<GeneralKey>(S, kr, hr, dig, m, 0, Ko, Ho);
 }
 
 // ---------------------------------------------------------------------------
@@ -543,7 +564,7 @@ __global__ __launch_bounds__(64 * NW) void k_gen_scatter(const Seg *__restrict__
 // given (a launch whose size was fixed before the count was known) and loop
 // over their work with the grid's stride; with the count passed by value
 // the grid covers the work and each workgroup takes one item.
-template <bool PERSIST, int SUBT>
+template <class F, bool PERSIST, int SUBT>
 __global__ __launch_bounds__(BLOCK) void k_level_hist(const Seg *__restrict__ segs, const uint32_t *__restrict__ tile_prefix,
                                                       uint32_t nsegs, const uint32_t *__restrict__ dev_nsegs,
                                                       uint32_t tile_len, uint64_t *keys0,
@@ -597,18 +618,18 @@ __global__ __launch_bounds__(BLOCK) void k_level_hist(const Seg *__restrict__ se
       }
 #pragma unroll
       for (int i = 0; i < MAX_TILE_ITEMS; ++i)
-        if (in[i]) tr[i] = window_load(text, nb, hh[i], sg.r);
+        if (in[i]) tr[i] = F::load(text, nb, hh[i], sg.r);
 #pragma unroll
       for (int i = 0; i < MAX_TILE_ITEMS; ++i)
         if (in[i]) {
-          kk[i] = window_combine(tr[i], nb, hh[i], sg.r, (uint32_t)kk[i] & 7u);
+          kk[i] = F::combine(tr[i], nb, hh[i], sg.r, kk[i]);
           K[u0 + (uint64_t)i * BLOCK + threadIdx.x] = kk[i];
         }
     }
 #pragma unroll
     for (int i = 0; i < MAX_TILE_ITEMS; ++i)
       if (in[i]) {
-        atomicAdd(&hist[digit_of(kk[i], sg.d)], 1u);
+        atomicAdd(&hist[F::digit(kk[i], sg.d)], 1u);
         o |= kk[i];
         a &= kk[i];
       }
@@ -616,8 +637,8 @@ __global__ __launch_bounds__(BLOCK) void k_level_hist(const Seg *__restrict__ se
   o = block_or(o, red);
   a = block_and(a, red);
   if (threadIdx.x == 0) {
-    atomicOr(&seg_or[s], (unsigned long long)order_bits(o));
-    atomicAnd(&seg_and[s], (unsigned long long)(a | 7ull));
+    atomicOr(&seg_or[s], (unsigned long long)(o & ~F::REST));
+    atomicAnd(&seg_and[s], (unsigned long long)(a | F::REST));
   }
   tile_hist[(uint64_t)tile * 256 + threadIdx.x] = hist[threadIdx.x];
   if (!PERSIST) break;
@@ -770,7 +791,7 @@ __device__ __forceinline__ uint32_t bits_below_lane(uint64_t m) {
 // wave: chunk boundaries come from a walk of one step per chunk over bucket
 // masks, and the list entries are written by all lanes at once from
 // positions reserved with one atomic per list per workgroup.
-template <bool COOP, bool PERSIST>
+template <class F, bool COOP, bool PERSIST>
 __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ segs,
                                                       const uint32_t *__restrict__ group_prefix, uint32_t nsegs,
                                                       uint32_t *__restrict__ gsum,
@@ -830,11 +851,11 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
     if (__ballot(one) && !force_split) {
       mode = 1;
       const unsigned long long o = seg_or[s], a = seg_and[s];
-      const uint64_t diff = (o ^ a) & ~7ull;
+      const uint64_t diff = (o ^ a) & ~F::REST;
       nx = sg;
       nx.regather = 0;
       if (diff == 0) {
-        if (clamp_of(a) < (uint32_t)W) {
+        if (F::clamp(a) < F::FULL) {
           nx = sg;
           nx_list = 2;
         } else if (sg.r + 1 > L.rmax) {
@@ -847,7 +868,7 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
         }
       } else {
         const int top = 63 - __builtin_clzll(diff);
-        nx.d = (uint8_t)(top >= 8 ? (63 - top) >> 3 : 7);
+        nx.d = (uint8_t)F::digit_of_bit(top);
         nx_list = 1;
       }
     } else {
@@ -956,9 +977,9 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
       ++nc;
       b = v >> 16;
     }
-    if (sg.d == 7) {
+    if (sg.d == F::LAST) {
       // bucket value b is the clamped length; all ordering bits agree
-      FIN[0] = BIG[0] & ((1ull << W) - 1);
+      FIN[0] = BIG[0] & ((1ull << F::FULL) - 1);
       NB[0] = BIG[0] & ~FIN[0];
       NB[1] = BIG[1];
       NB[2] = BIG[2];
@@ -992,8 +1013,8 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
     }
     blen = wave_total(blen);
     ls[K_NEXT_LEN - K_LEVEL_FIRST] = blen;
-    ls[K_NEXT_REGATHER - K_LEVEL_FIRST] = sg.d == 7 ? blen : 0u;
-    ls[K_NEXT_MAXR - K_LEVEL_FIRST] = nbg ? sg.r + (sg.d == 7 ? 1u : 0u) : 0u;
+    ls[K_NEXT_REGATHER - K_LEVEL_FIRST] = sg.d == F::LAST ? blen : 0u;
+    ls[K_NEXT_MAXR - K_LEVEL_FIRST] = nbg ? sg.r + (sg.d == F::LAST ? 1u : 0u) : 0u;
     ls[K_NEXT_TILES - K_LEVEL_FIRST] = wave_total(btiles);
     ls[K_NEXT_GROUPS - K_LEVEL_FIRST] = wave_total(bgroups);
     ls[K_FINAL_LEN - K_LEVEL_FIRST] = wave_total(flen);
@@ -1062,7 +1083,7 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
       if (at < L.cap_chunks) L.chunks[at] = Seg{sg.start + cstart[cw][j], clen[cw][j], sg.r, sg.d, nbuf, 0, 0, sg.coll};
       else overflow = true;
     }
-    const bool last = sg.d == 7;
+    const bool last = sg.d == F::LAST;
     uint32_t pb = 0, pf = 0;  // entries of the lower slots
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -1266,7 +1287,7 @@ __global__ __launch_bounds__(BLOCK) void k_seg_scan(const Seg *__restrict__ list
 }
 
 // Stable scatter of one tile by its segment's digit into the other buffer.
-template <int TI, int NW, bool PERSIST>
+template <class F, int TI, int NW, bool PERSIST>
 __global__ __launch_bounds__(64 * NW) void k_level_scatter(const Seg *__restrict__ segs,
                                                          const uint32_t *__restrict__ tile_prefix,
                                                          const uint32_t *__restrict__ group_prefix, uint32_t nsegs,
@@ -1314,7 +1335,7 @@ __global__ __launch_bounds__(64 * NW) void k_level_scatter(const Seg *__restrict
 #pragma unroll
   for (int i = 0; i < TI; ++i) {
     if (item_index<TI>(i) < m) {
-      dig[i] = digit_of(kr[i], d);
+      dig[i] = F::digit(kr[i], d);
     } else {
       kr[i] = 0;
       hr[i] = 0;
@@ -1325,7 +1346,7 @@ __global__ __launch_bounds__(64 * NW) void k_level_scatter(const Seg *__restrict
   if (threadIdx.x < 256)
     S.goff[threadIdx.x] =
         (uint64_t)gsum[(uint64_t)g * 256 + threadIdx.x] + tile_hist[(uint64_t)tile * 256 + threadIdx.x];
-  tile_scatter(S, kr, hr, dig, m, d, Ko, Ho);
+  tile_scatter<F>(S, kr, hr, dig, m, d, Ko, Ho);
   if (!PERSIST) break;
   }
 }
@@ -1400,7 +1421,7 @@ constexpr int FETCH_BATCH = 2;  // window loads in flight per lane
 
 // Stable split of the m suffixes of a chunk by 8-bit digit sel, in place
 // (every suffix is held in registers before any moves).
-template <int LI>
+template <class F, int LI>
 __device__ __forceinline__ void wave_split(LocalSmem<LI> &S, uint32_t m, int sel, uint32_t lane, uint64_t lt) {
   for (uint32_t x = lane; x < 256; x += LOCAL_WG) S.cnt[x] = 0;
   __syncthreads();
@@ -1414,7 +1435,7 @@ __device__ __forceinline__ void wave_split(LocalSmem<LI> &S, uint32_t m, int sel
     if (valid) {
       kr[i] = S.K[j];
       hr[i] = S.H[j];
-      dig[i] = digit_of(kr[i], sel);
+      dig[i] = F::digit(kr[i], sel);
     }
     if (i * LOCAL_WG >= (int)m) continue;
     // rank among the lanes of this slot with the same digit
@@ -1599,8 +1620,8 @@ __global__ __launch_bounds__(LOCAL_WG, OCC) void k_local(
     // a chunk of one bucket (its first and last suffixes share digit d) is
     // ordered by both digits after the first split
     const bool one_bucket = !ch.unsplit && digit_of(S.K[0], d0) == digit_of(S.K[m - 1], d0);
-    wave_split(S, m, d0 + 1, lane, le & ~(1ull << lane));
-    if (!one_bucket) wave_split(S, m, d0, lane, le & ~(1ull << lane));
+    wave_split<GeneralKey>(S, m, d0 + 1, lane, le & ~(1ull << lane));
+    if (!one_bucket) wave_split<GeneralKey>(S, m, d0, lane, le & ~(1ull << lane));
   }
   // The first groups: runs of equal digits d and d + 1 after two splits, of
   // equal digit d in a chunk of buckets, the whole chunk when unsplit; a
@@ -2197,7 +2218,7 @@ __global__ __launch_bounds__(64 * NW) void k_sched_scatter(const uint64_t *__res
   const uint32_t g = tile / GROUP_TILES;
   if (threadIdx.x < 256)
     S.goff[threadIdx.x] = (uint64_t)gsum[(uint64_t)g * 256 + threadIdx.x] + tile_hist[(uint64_t)tile * 256 + threadIdx.x];
-  tile_scatter(S, kr, hr, dig, m, d, Ko, Ho);
+  tile_scatter<GeneralKey>(S, kr, hr, dig, m, d, Ko, Ho);
 }
 
 // The sorted suffixes' BWT rows (window-0 keys carry the preceding symbol).

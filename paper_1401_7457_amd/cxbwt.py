@@ -39,7 +39,7 @@ TUNING_CHOICES = ((8, 6), (8, 8), (8, 3), (6, 6), (6, 8), (6, 3), (16, 6), (16, 
 SCHEDULE_MSD, SCHEDULE_STRINGWORD = 0, 1
 
 # kernel classes of cxbwt_stats.ms / launches
-KERNEL_CLASSES = ("prep", "gen", "level_hist", "level_scan", "level_scatter", "local", "final_emit", "unused")
+KERNEL_CLASSES = ("prep", "gen", "level_hist", "level_scan", "level_scatter", "local", "final_emit", "induce")
 
 _lock = threading.Lock()
 _lib = None
