@@ -1228,7 +1228,11 @@ int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
   int rc;
   // the text of every collection in tiles, counted
   std::vector<uint32_t> tp, gp;
-  seg_prefixes(b.big, SMP_TILE, tp, gp);
+  {
+    std::vector<Seg> whole(b.big);  // tiles begin at the record a collection begins in
+    for (Seg &g : whole) g.len = (uint32_t)std::min<uint64_t>((uint64_t)g.len + g.start % 16, 0xFFFFFFFFull);
+    seg_prefixes(whole, SMP_TILE, tp, gp);
+  }
   const uint32_t ntiles = tp.back(), ngroups = gp.back();
   const uint32_t replicas = std::max<uint32_t>(1, 64 / nc);
   const uint64_t n_counts = (uint64_t)nc * replicas * TC_WORDS;
@@ -1244,7 +1248,8 @@ int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
   CX_CHECK(hipMemcpyAsync(b.B.group_prefix, gp.data(), 4 * ((uint64_t)nc + 1), hipMemcpyHostToDevice, st));
   if ((rc = fill_u32(d_counts, n_counts, 0, st))) return rc;
   T.begin();
-  k_sample_hist<<<ntiles, BLOCK, 0, st>>>(d_text, b.B.tile_prefix, nc, b.B.text, b.B.tile_hist, d_counts, replicas);
+  k_sample_hist<<<(unsigned)ceil_div(ntiles, HIST_TILES), BLOCK, 0, st>>>(
+      d_text, b.B.tile_prefix, nc, ntiles, b.B.text, b.B.tile_hist, d_counts, replicas);
   CX_LAUNCHED();
   T.end(PH_GEN);
   std::vector<uint32_t> hc(n_counts);

@@ -202,77 +202,277 @@ __host__ __device__ __forceinline__ SuffixType suffix_type(const TextRec *__rest
 // the longest run per type and base, samples per first base.
 constexpr int TC_MAXRUN = 128, TC_SAMPLES = 136, TC_WORDS = 160;
 constexpr int RUN_REGIONS = 15;
-// A tile of text positions: slots of two neighbouring positions, at most one
-// of which is a sample.
+// Tiles of the text are runs of records, from the one a collection starts in.
 constexpr int SMP_NW = 8, SMP_TI = 8;
-constexpr uint32_t SMP_TILE = 64u * SMP_NW * SMP_TI * 2;
+constexpr uint32_t SMP_RECS = 64u * SMP_NW;
+constexpr uint32_t SMP_TILE = 16u * SMP_RECS;  // at most half of the positions are samples
+static_assert(SMP_TILE / 2 == 64 * SMP_NW * SMP_TI, "a tile's samples fit the scatter's slots");
 
-__global__ __launch_bounds__(BLOCK) void k_sample_hist(const Seg *__restrict__ segs, const uint32_t *__restrict__ tile_prefix,
-                                                       uint32_t nsegs, const TextRec *__restrict__ text,
-                                                       uint32_t *__restrict__ tile_hist,
-                                                       uint32_t *__restrict__ counts, uint32_t replicas) {
-  constexpr uint32_t REP = 4;  // counter copies, against conflicts on the few hot classes
-  __shared__ uint32_t hist[256];
-  __shared__ uint32_t cls[REP][TC_WORDS];
-  const uint32_t tile = blockIdx.x;
-  const uint32_t s = find_upper(tile_prefix, nsegs, tile);
-  const Seg sg = segs[s];
-  const uint64_t t0 = sg.start + (uint64_t)(tile - tile_prefix[s]) * SMP_TILE;
-  const uint64_t t1 = min(t0 + (uint64_t)SMP_TILE, (uint64_t)sg.start + sg.len);
-  hist[threadIdx.x] = 0;
-  for (uint32_t i = threadIdx.x; i < REP * TC_WORDS; i += BLOCK) (&cls[0][0])[i] = 0;
-  __syncthreads();
-  uint32_t *const mine = cls[threadIdx.x % REP];
-  constexpr int PER = 8;  // record loads in flight per thread
-  for (uint64_t u0 = t0; u0 < t1; u0 += PER * BLOCK) {
-    TextRec tr[PER];
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const uint64_t p = u0 + (uint64_t)i * BLOCK + threadIdx.x;
-      tr[i] = text[(p < t1 ? p : t1 - 1) >> 4];
-    }
-#pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const uint64_t p = u0 + (uint64_t)i * BLOCK + threadIdx.x;
-      if (p >= t1) continue;
-      const SuffixType ty = suffix_type(text, tr[i], p);
-      const uint32_t tb = (ty.s ? 4u : 0u) + ty.base;
-      atomicAdd(&mine[tb * 16 + min(ty.run, (uint32_t)RUN_REGIONS)], 1u);
-      if (ty.run >= RUN_REGIONS) atomicMax(&mine[TC_MAXRUN + tb], ty.run);
-      const uint32_t o = (uint32_t)(p & 15);
-      if (ty.s && !((tr[i].lo >> o) & 1u) && base_before(tr[i], o) > ty.base) {
-        atomicAdd(&hist[first_bases(ty.bases, min(ty.left, 4u)) >> 56], 1u);
-        atomicAdd(&mine[TC_SAMPLES + ty.base], 1u);
-      }
-    }
+// The 16 positions of a record at once.  A mask has a bit per position in the
+// position's pair of bits (the low one), first position highest.
+constexpr uint32_t LANES = 0x55555555u;
+__host__ __device__ __forceinline__ uint32_t reverse_bits(uint32_t x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_bitreverse32(x);
+#else
+  uint32_t r = 0;
+  for (int i = 0; i < 32; ++i) r |= ((x >> i) & 1u) << (31 - i);
+  return r;
+#endif
+}
+// bits 0..15 of x (first position lowest) as a mask
+__host__ __device__ __forceinline__ uint32_t to_lanes(uint32_t x) {
+  uint32_t y = reverse_bits(x) >> 16;
+  y = (y | (y << 8)) & 0x00FF00FFu;
+  y = (y | (y << 4)) & 0x0F0F0F0Fu;
+  y = (y | (y << 2)) & 0x33333333u;
+  return (y | (y << 1)) & LANES;
+}
+// pairs of a below those of b
+__host__ __device__ __forceinline__ uint32_t below(uint32_t a, uint32_t b) {
+  const uint32_t ah = a >> 1, bh = b >> 1;
+  return ((~ah & bh) | (~(ah ^ bh) & ~a & b)) & LANES;
+}
+struct RecordTypes {
+  uint32_t bases;    // the 16 bases
+  uint32_t s;        // S-type positions
+  uint32_t sample;
+  uint32_t eq, eq2;  // the next base is the same and in the same read; of the 16 positions after these
+  uint32_t cut;      // the read ends one or two positions on
+  bool slow;         // a run reaches past the 32 positions: the masks do not hold
+};
+__host__ __device__ __forceinline__ RecordTypes record_types(const TextRec &t) {
+  RecordTypes r;
+  const uint32_t a = (uint32_t)(t.hi >> 32), b = (uint32_t)t.hi, c = (uint32_t)(t.lo >> 32);
+  const uint32_t an = (a << 2) | (b >> 30), bn = (b << 2) | (c >> 30);
+  const uint32_t ends = starts_from(t, 1);  // bit i: the read of position i ends with it
+  const uint32_t ea = to_lanes(ends), eb = to_lanes(ends >> 16);
+  const uint32_t xa = a ^ an, xb = b ^ bn;
+  r.bases = a;
+  r.eq = ~(xa | (xa >> 1)) & LANES & ~ea;
+  r.eq2 = ~(xb | (xb >> 1)) & LANES & ~eb;
+  r.slow = r.eq2 == LANES;
+  r.cut = (ea << 2) | (eb >> 30) | (ea << 4) | (eb >> 28);
+  // S of position 16: of the last position of its run
+  const uint32_t last = ~r.eq2 & LANES;
+  const uint32_t s16 = last ? (below(b, bn) & ~eb) >> (31 - (uint32_t)__builtin_clz(last)) & 1u : 0u;
+  // S: below the next, or equal to it and the next one S (runs of up to 16
+  // here, by doubling)
+  uint32_t g = (below(a, an) & ~ea) | (r.eq & s16), p = r.eq;
+  g |= p & (g << 2);
+  p &= p << 2;
+  g |= p & (g << 4);
+  p &= p << 4;
+  g |= p & (g << 8);
+  p &= p << 8;
+  r.s = g | (p & (g << 16));
+  const uint32_t before = (a >> 2) | ((uint32_t)(t.lo >> 42) << 30);
+  r.sample = r.s & below(a, before) & ~to_lanes((uint32_t)t.lo);
+  return r;
+}
+// Positions of the record at 16 w that lie in [a, e); a lies before the
+// record's end.
+__host__ __device__ __forceinline__ uint32_t lanes_within(uint64_t w, uint64_t a, uint64_t e) {
+  const uint64_t p = 16 * w;
+  uint32_t m = p < e ? LANES : 0u;
+  if (p < a) m &= ~0u >> (2 * (uint32_t)(a - p));
+  if (p + 16 > e && p < e) m &= ~(~0u >> (2 * (uint32_t)(e - p)));
+  return m;
+}
+// the same, one position at a time
+__host__ __device__ __forceinline__ uint32_t slow_samples(const TextRec *__restrict__ text, const TextRec &t, uint64_t w,
+                                                          uint32_t valid) {
+  uint32_t m = 0;
+  for (uint32_t o = 0; o < 16; ++o) {
+    const uint32_t bit = 1u << (30 - 2 * o);
+    if (!(valid & bit)) continue;
+    const SuffixType ty = suffix_type(text, t, 16 * w + o);
+    if (ty.s && !((t.lo >> o) & 1u) && base_before(t, o) > ty.base) m |= bit;
   }
-  __syncthreads();
-  tile_hist[(uint64_t)tile * 256 + threadIdx.x] = hist[threadIdx.x];
-  uint32_t *const out = counts + ((uint64_t)sg.coll * replicas + tile % replicas) * TC_WORDS;
-  for (uint32_t i = threadIdx.x; i < TC_WORDS; i += BLOCK) {
-    uint32_t v = 0;
-    const bool most = i >= TC_MAXRUN && i < TC_SAMPLES;
-    for (uint32_t r = 0; r < REP; ++r) v = most ? max(v, cls[r][i]) : v + cls[r][i];
-    if (!v) continue;
-    if (most) atomicMax(&out[i], v);
-    else atomicAdd(&out[i], v);
-  }
+  return m;
 }
 
-// Level 1 of the samples: keys made from the text and scattered by their
-// first digit, a tile of SMP_TILE positions (at most half of them samples)
-// per workgroup.  segs: the collections' text; smp: where their samples go.
+// Counts of every collection and first-digit counts of every tile's samples.
+// A workgroup takes HIST_TILES neighbouring tiles and keeps the type counts in
+// registers (one and, one count-and-add per record, class and run length up
+// to 3; longer runs one by one).  The types of 16 positions cost about 80
+// operations this way: 0.86 -> 0.28 ms per 400 Mbases against a position a lane.
+constexpr uint32_t HIST_TILES = 8;
+__global__ __launch_bounds__(BLOCK) void k_sample_hist(const Seg *__restrict__ segs, const uint32_t *__restrict__ tile_prefix,
+                                                       uint32_t nsegs, uint32_t ntiles,
+                                                       const TextRec *__restrict__ text,
+                                                       uint32_t *__restrict__ tile_hist,
+                                                       uint32_t *__restrict__ counts, uint32_t replicas) {
+  constexpr int KR = 4;  // run lengths counted in registers
+  __shared__ uint32_t hist[256];
+  __shared__ uint32_t cls[TC_WORDS];
+  uint32_t acc[KR][8];  // suffixes of a type and base with runs of at least k
+  uint32_t smp[3];      // samples of a first base (none begins with T)
+  const uint32_t tile0 = blockIdx.x * HIST_TILES, tile1 = min(tile0 + HIST_TILES, ntiles);
+  uint32_t s = find_upper(tile_prefix, nsegs, tile0);
+  auto clear = [&]() {
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[k][j] = 0;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) smp[j] = 0;
+    for (uint32_t i = threadIdx.x; i < TC_WORDS; i += BLOCK) cls[i] = 0;
+  };
+  // adds the counts to those of segment s
+  auto flush = [&]() {
+#pragma unroll
+    for (int k = 0; k < KR; ++k)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const uint32_t v = wave_incl_sum(acc[k][j]);
+        if (lane_id() == 63 && v) {
+          atomicAdd(&cls[j * 16 + k], v);
+          if (k) atomicSub(&cls[j * 16 + k - 1], v);  // counted as at least k - 1 too
+        }
+      }
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const uint32_t v = wave_incl_sum(smp[j]);
+      if (lane_id() == 63 && v) atomicAdd(&cls[TC_SAMPLES + j], v);
+    }
+    __syncthreads();
+    uint32_t *const out = counts + ((uint64_t)segs[s].coll * replicas + blockIdx.x % replicas) * TC_WORDS;
+    for (uint32_t i = threadIdx.x; i < TC_WORDS; i += BLOCK) {
+      const uint32_t v = cls[i];
+      if (!v) continue;
+      if (i >= TC_MAXRUN && i < TC_SAMPLES) atomicMax(&out[i], v);
+      else atomicAdd(&out[i], v);
+    }
+    __syncthreads();
+  };
+  clear();
+  for (uint32_t tile = tile0; tile < tile1; ++tile) {
+    if (tile >= tile_prefix[s + 1]) {
+      __syncthreads();
+      flush();
+      while (tile >= tile_prefix[s + 1]) ++s;
+      clear();
+    }
+    const Seg sg = segs[s];
+    const uint64_t start = sg.start, end = start + sg.len;
+    const uint64_t w0 = start / 16 + (uint64_t)(tile - tile_prefix[s]) * SMP_RECS;
+    hist[threadIdx.x] = 0;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t h = 0; h < SMP_RECS / BLOCK; ++h) {
+      const uint64_t w = w0 + h * BLOCK + threadIdx.x;
+      const uint32_t valid = lanes_within(w, start, end);
+      if (!valid) continue;
+      const TextRec t = text[w];
+      const RecordTypes ty = record_types(t);
+      uint32_t sample = ty.sample & valid;
+      if (!ty.slow) {
+        const uint32_t bh = ty.bases >> 1, bl = ty.bases;
+        uint32_t m[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          m[j] = valid & ((j & 4) ? ty.s : ~ty.s) & ((j & 2) ? bh : ~bh) & ((j & 1) ? bl : ~bl);
+        uint32_t e = ty.eq, f = ty.eq2, e1 = ty.eq;  // positions with runs of at least k; the rest shifted along
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[0][j] += (uint32_t)__popc(m[j]);
+#pragma unroll
+        for (int k = 1; k < KR; ++k) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) acc[k][j] += (uint32_t)__popc(m[j] & e);
+          e1 = (e1 << 2) | (f >> 30);
+          f <<= 2;
+          e &= e1;
+        }
+        // runs of KR and more, one by one: moved from "at least k - 1" to k
+        for (uint32_t k = KR; e & valid; ++k) {
+          for (uint32_t left = e & valid; left;) {
+            const uint32_t bit = 31u - (uint32_t)__builtin_clz(left);
+            left &= ~(1u << bit);
+            const uint32_t j = (((ty.s >> bit) & 1u) << 2) | ((ty.bases >> bit) & 3u);
+            if (k <= RUN_REGIONS) {
+              atomicAdd(&cls[j * 16 + k], 1u);
+              atomicSub(&cls[j * 16 + k - 1], 1u);
+            }
+            if (k >= RUN_REGIONS) atomicMax(&cls[TC_MAXRUN + j], k);
+          }
+          e1 = (e1 << 2) | (f >> 30);
+          f <<= 2;
+          e &= e1;
+        }
+      } else {
+        sample = 0;
+        for (uint32_t o = 0; o < 16; ++o) {
+          const uint32_t bit = 1u << (30 - 2 * o);
+          if (!(valid & bit)) continue;
+          const SuffixType ty1 = suffix_type(text, t, 16 * w + o);
+          const uint32_t j = (ty1.s ? 4u : 0u) + ty1.base;
+          atomicAdd(&cls[j * 16 + min(ty1.run, (uint32_t)RUN_REGIONS)], 1u);
+          if (ty1.run >= RUN_REGIONS) atomicMax(&cls[TC_MAXRUN + j], ty1.run);
+          if (ty1.s && !((t.lo >> o) & 1u) && base_before(t, o) > ty1.base) sample |= bit;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 3; ++j)
+        smp[j] += (uint32_t)__popc(sample & ((j & 2) ? ty.bases >> 1 : ~(ty.bases >> 1)) &
+                                   ((j & 1) ? ty.bases : ~ty.bases));
+      // the digit: the four bases from the position on
+      const uint32_t a4 = ty.bases, b4 = (uint32_t)t.hi;
+#pragma unroll
+      for (int o = 0; o < 16; ++o)
+        if (sample & ~ty.cut & (1u << (30 - 2 * o)))
+          atomicAdd(&hist[(o <= 12 ? a4 >> (24 - 2 * o) : (a4 << (2 * o - 24)) | (b4 >> (56 - 2 * o))) & 0xFFu], 1u);
+      for (uint32_t left = sample & ty.cut; left;) {  // zero past the read's end
+        const uint32_t o = (uint32_t)__builtin_clz(left) >> 1;
+        left &= ~(1u << (30 - 2 * o));
+        const uint32_t n = first_bit(starts_from(t, o + 1)) + 1u;
+        atomicAdd(&hist[first_bases(window_at(t, o), min(n, 4u)) >> 56], 1u);
+      }
+    }
+    __syncthreads();
+    tile_hist[(uint64_t)tile * 256 + threadIdx.x] = hist[threadIdx.x];
+  }
+  __syncthreads();
+  flush();
+}
+
+// Level 1 of the samples: found 16 positions at a time by a lane each, their
+// places listed in text order, then a sample a lane: key, scatter by the
+// first digit.  (With a pair of positions a lane and no list, 7 of 10 lanes
+// made no key: 1.87 -> 0.79 ms per 400 Mbases.)
 __global__ __launch_bounds__(64 * SMP_NW) void k_sample_scatter(
     const Seg *__restrict__ segs, const uint32_t *__restrict__ tile_prefix, const uint32_t *__restrict__ group_prefix,
     uint32_t nsegs, const TextRec *__restrict__ text, const uint32_t *__restrict__ tile_hist,
     const uint32_t *__restrict__ gsum, uint64_t *__restrict__ Ko, uint32_t *__restrict__ Ho) {
   __shared__ ScatterSmem<SMP_TI, SMP_NW> S;
+  uint16_t *const list = reinterpret_cast<uint16_t *>(S.sh);  // read before the handles are staged
   const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
   const uint32_t s = find_upper(tile_prefix, nsegs, tile);
   const Seg sg = segs[s];
   const uint32_t tl = tile - tile_prefix[s];
-  const uint64_t t0 = sg.start + (uint64_t)tl * SMP_TILE;
-  const uint64_t t1 = min(t0 + (uint64_t)SMP_TILE, (uint64_t)sg.start + sg.len);
+  const uint64_t start = sg.start, end = start + sg.len;
+  const uint64_t w0 = start / 16 + (uint64_t)tl * SMP_RECS;
+  uint32_t m = 0;
+  {
+    const uint64_t w = w0 + threadIdx.x;
+    const uint32_t valid = lanes_within(w, start, end);
+    uint32_t sample = 0;
+    if (valid) {
+      const TextRec t = text[w];
+      const RecordTypes ty = record_types(t);
+      sample = ty.slow ? slow_samples(text, t, w, valid) : ty.sample & valid;
+    }
+    uint32_t at = block_excl_sum<SMP_NW>((uint32_t)__popc(sample), S.tmp, &m);
+    while (sample) {
+      const uint32_t o = (uint32_t)__builtin_clz(sample) >> 1;
+      sample &= ~(1u << (30 - 2 * o));
+      list[at++] = (uint16_t)(16 * threadIdx.x + o);
+    }
+  }
+  __syncthreads();
+  // each wave takes an equal run of the list, a multiple of 64
+  const uint32_t ni = (m + 64 * SMP_NW - 1) / (64 * SMP_NW);
+  const uint32_t first = (threadIdx.x >> 6) * 64 * ni + lane_id();
   uint64_t kr[SMP_TI];
   uint32_t hr[SMP_TI], dig[SMP_TI];
 #pragma unroll
@@ -280,23 +480,18 @@ __global__ __launch_bounds__(64 * SMP_NW) void k_sample_scatter(
     kr[i] = 0;
     hr[i] = 0;
     dig[i] = NODIGIT;
-    const uint64_t p0 = t0 + 2ull * item_index<SMP_TI>(i);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const uint64_t p = p0 + j;
-      if (p >= t1) continue;
-      const uint64_t w = p >> 4;
-      const TextRec t = text[w], before = text[w ? w - 1 : 0];
-      const uint32_t o = (uint32_t)(p & 15);
-      const SuffixType ty = suffix_type(text, t, p);
-      if (ty.s && !((t.lo >> o) & 1u) && base_before(t, o) > ty.base) {
-        const uint32_t cl = ty.left < SampleKey::FULL ? ty.left : SampleKey::FULL;
-        const uint64_t x = first_bases(ty.bases, cl);
-        kr[i] = x | ((uint64_t)cl << KEY_PL_BITS) | pl_trim(preceding_from(before, p, false));
-        hr[i] = (uint32_t)p;
-        dig[i] = (uint32_t)(x >> 56);
-      }
-    }
+    const uint32_t li = first + i * 64;
+    if ((uint32_t)i >= ni || li >= m) continue;
+    const uint32_t o16 = list[li];
+    const uint64_t w = w0 + (o16 >> 4);
+    const uint32_t o = o16 & 15u;
+    const TextRec t = text[w], before = text[w ? w - 1 : 0];
+    const uint32_t left = first_bit(starts_from(t, o + 1)) + 1u;
+    const uint32_t cl = left < SampleKey::FULL ? left : SampleKey::FULL;
+    const uint64_t x = first_bases(window_at(t, o), cl), p = 16 * w + o;
+    kr[i] = x | ((uint64_t)cl << KEY_PL_BITS) | pl_trim(preceding_from(before, p, false));
+    hr[i] = (uint32_t)p;
+    dig[i] = (uint32_t)(x >> 56);
   }
   const uint32_t g = group_prefix[s] + tl / GROUP_TILES;
   if (threadIdx.x < 256)
@@ -304,7 +499,7 @@ __global__ __launch_bounds__(64 * SMP_NW) void k_sample_scatter(
         (uint64_t)gsum[(uint64_t)g * 256 + threadIdx.x] + tile_hist[(uint64_t)tile * 256 + threadIdx.x];
   uint32_t pos[SMP_TI];
   block_multisplit<SMP_TI, SMP_NW>(dig, pos, S.wcount, S.dstart, S.tmp);
-  __syncthreads();  // every wave has read its counters before the stage is written
+  __syncthreads();  // every wave has read its counters and the list before the stage is written
 #pragma unroll
   for (int i = 0; i < SMP_TI; ++i) {
     if (dig[i] != NODIGIT) {
@@ -313,7 +508,6 @@ __global__ __launch_bounds__(64 * SMP_NW) void k_sample_scatter(
     }
   }
   __syncthreads();
-  const uint32_t m = S.dstart[192];  // no sample begins with T
   for (uint32_t q = threadIdx.x; q < m; q += 64 * SMP_NW) {
     const uint64_t k = S.sk[q];
     const uint32_t dd = (uint32_t)(k >> 56);
@@ -387,8 +581,9 @@ __global__ __launch_bounds__(BLOCK) void k_sample_final(const Seg *__restrict__ 
   const uint32_t *H = sg.buf ? hdl1 : hdl0;
   for (uint64_t j = t0 + threadIdx.x; j < t1; j += BLOCK) {
     const uint32_t h = H[j];
-    // (the key may be a later window's: the first base comes from the text)
-    put_sample(out, j, K[j], base_in(text[h >> 4], h & 15u), h, text);
+    const uint64_t k = K[j];
+    // a key of a later window does not hold the first base
+    put_sample(out, j, k, sg.r ? base_in(text[h >> 4], h & 15u) : (uint32_t)(k >> 62), h, text);
   }
 }
 
@@ -888,12 +1083,18 @@ __device__ __forceinline__ void ind_put(const IndData &D, const CollMap &cm, uin
   D.bwt[g + cm.out_shift] = (uint8_t)code;
 }
 
+__device__ __forceinline__ uint32_t bwt_symbol(uint32_t code) {
+  const uint32_t lut = 'A' | ('C' << 8) | ('G' << 16) | ('T' << 24);
+  return code & CODE_START ? (uint32_t)'$' : (lut >> (8 * (code & 3u))) & 0xFFu;
+}
+// Row j is the first suffix of the read starting at p.
+__device__ __forceinline__ void ind_first(const IndData &D, const CollMap &cm, uint64_t j, uint32_t p) {
+  D.start_row[start_rank(D.text, D.srank, p)] = (uint64_t)((int64_t)j + cm.row_shift);
+}
 // The BWT byte of a row whose step is the last to read its code.
 __device__ __forceinline__ void ind_emit(const IndData &D, const CollMap &cm, uint64_t j, uint32_t code, uint32_t p) {
-  const uint32_t lut = 'A' | ('C' << 8) | ('G' << 16) | ('T' << 24);
-  const bool first = (code & CODE_START) != 0;
-  D.bwt[j + cm.out_shift] = first ? (uint8_t)'$' : (uint8_t)(lut >> (8 * (code & 3u)));
-  if (first) D.start_row[start_rank(D.text, D.srank, p)] = (uint64_t)((int64_t)j + cm.row_shift);
+  D.bwt[j + cm.out_shift] = (uint8_t)bwt_symbol(code);
+  if (code & CODE_START) ind_first(D, cm, j, p);
 }
 
 // Class ranks of one slot: this lane's place, from the wave's class bases
@@ -1054,7 +1255,7 @@ __global__ __launch_bounds__(TAIL_WG) void k_ind_tail(const IndTail *__restrict_
   }
 }
 
-// BWT bytes of the rows that no step reads (bucket A).
+// BWT bytes of the rows that no step reads (bucket A), four a lane.
 __global__ __launch_bounds__(BLOCK) void k_ind_emit(IndStep P, IndData D) {
   const uint32_t tile = blockIdx.x * WAVES + (threadIdx.x >> 6);
   if (tile >= P.ntiles) return;
@@ -1062,11 +1263,29 @@ __global__ __launch_bounds__(BLOCK) void k_ind_emit(IndStep P, IndData D) {
   const IndSeg sg = P.segs[s];
   const CollMap cm = D.cmap[sg.coll];
   const uint32_t t0 = (tile - P.tile_prefix[s]) * IND_TILE;
-  const uint32_t m = min(IND_TILE, sg.len - t0);
-  for (uint32_t x = lane_id(); x < m; x += 64) {
-    const uint64_t j = (uint64_t)sg.start + t0 + x;
-    const uint32_t code = D.bwt[j + cm.out_shift];
-    ind_emit(D, cm, j, code, code & CODE_START ? D.rows[j].x : 0u);
+  const int64_t j0 = (int64_t)sg.start + t0, j1 = j0 + min(IND_TILE, sg.len - t0);
+  // whole words of the output, the rows at both ends of the tile by byte
+  const int64_t word0 = (int64_t)((uintptr_t)(D.bwt + cm.out_shift + j0) & 3u);
+  for (int64_t j = j0 - word0 + 4 * (int64_t)lane_id(); j < j1; j += 4 * 64) {
+    uint8_t *const at = D.bwt + cm.out_shift + j;
+    if (j >= j0 && j + 4 <= j1) {
+      const uint32_t c = *reinterpret_cast<const uint32_t *>(at);
+      uint32_t out = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out |= bwt_symbol((c >> (8 * i)) & 0xFFu) << (8 * i);
+      *reinterpret_cast<uint32_t *>(at) = out;
+      if (c & (CODE_START * 0x01010101u)) {
+        for (int i = 0; i < 4; ++i)
+          if ((c >> (8 * i)) & CODE_START) ind_first(D, cm, j + i, D.rows[j + i].x);
+      }
+    } else {
+      for (int i = 0; i < 4; ++i) {
+        if (j + i < j0 || j + i >= j1) continue;
+        const uint32_t c = at[i];
+        at[i] = (uint8_t)bwt_symbol(c);
+        if (c & CODE_START) ind_first(D, cm, j + i, D.rows[j + i].x);
+      }
+    }
   }
 }
 

@@ -234,7 +234,9 @@ __device__ __forceinline__ void block_multisplit(const uint32_t (&dig)[NI], uint
   for (int i = 0; i < NI; ++i) {
     const uint32_t d = dig[i];
     const bool valid = d != NODIGIT;
-    const uint64_t peers = wave_match8(d, __ballot(valid));
+    const uint64_t live = __ballot(valid);
+    if (!live) continue;
+    const uint64_t peers = wave_match8(d, live);
     if (valid) {
       const uint32_t before = wc[d];
       pos[i] = before + (uint32_t)__popcll(peers & lt);

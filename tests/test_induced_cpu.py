@@ -36,6 +36,9 @@ def it(tmp_path_factory):
     L.it_trim.restype = L.it_run.restype = u32
     L.it_window.argtypes = [vp, u64, u32, ctypes.POINTER(u32)]
     L.it_window.restype = u64
+    L.it_samples.argtypes = [vp, u64, u64, u64]
+    L.it_samples.restype = u32
+    L.it_masks.argtypes = [vp, u64, ctypes.POINTER(u32)]
     return L
 
 
@@ -93,6 +96,42 @@ def test_types_payloads_and_windows(it, alphabet):
                         for k in range(n):
                             want |= int(codes[p + depth + k]) << (62 - 2 * k)
                         assert (w, cl.value) == (want, n)
+
+
+@needs_hipcc
+@pytest.mark.parametrize("alphabet", ["ACGT", "AC", "A", "GT", "T"])
+def test_samples_of_whole_records(it, alphabet):
+    """Sixteen positions at once against one at a time, for every run of positions a tile may hold."""
+    rng = np.random.default_rng(7 + ord(alphabet[-1]) + len(alphabet))
+    lens = [int(x) for x in rng.choice([1, 2, 5, 15, 16, 17, 31, 32, 33, 40, 48, 70, 100], size=50)]
+    codes = rng.choice(["ACGT".index(c) for c in alphabet], size=sum(lens)).astype(np.uint8)
+    ends = np.cumsum(lens)
+    bounds = [(int(e) - n, int(e)) for e, n in zip(ends, lens)]
+    recs = _records(codes, bounds)
+    ptr = recs.ctypes.data_as(ctypes.c_void_p)
+    out = (ctypes.c_uint32 * 4)()
+    n = codes.size
+    s, sample, eq = np.zeros(n, bool), np.zeros(n, bool), np.zeros(n, bool)
+    for a, b in bounds:
+        for p in range(a, b):
+            it.it_type(ptr, p, out)
+            s[p], eq[p] = bool(out[2]), p + 1 < b and codes[p + 1] == codes[p]
+            sample[p] = s[p] and p > a and codes[p - 1] > codes[p]
+    slow = 0
+    for w in range((n + 15) // 16):
+        for a, e in ((0, n), (bounds[3][0], bounds[-4][1])):
+            if 16 * w + 16 <= a:
+                continue  # a tile begins at the record its collection begins in
+            got = it.it_samples(ptr, w, a, e)
+            want = sum(int(sample[p]) << (p - 16 * w) for p in range(16 * w, min(16 * w + 16, n)) if a <= p < e)
+            assert got & 0xFFFF == want, (w, a, e)
+        got = it.it_samples(ptr, w, 0, n)
+        slow += got >> 16
+        if not got >> 16:
+            it.it_masks(ptr, w, out)
+            for p in range(16 * w, min(16 * w + 16, n)):
+                assert (out[0] >> (p - 16 * w)) & 1 == s[p] and (out[1] >> (p - 16 * w)) & 1 == eq[p]
+    assert slow > 0 or len(alphabet) > 1  # long runs of one base take the slow way
 
 
 @needs_hipcc
