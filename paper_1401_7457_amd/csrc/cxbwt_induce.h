@@ -534,22 +534,29 @@ __host__ __device__ __forceinline__ uint32_t pl_run(uint32_t pl) {
   return k < len ? k : len;
 }
 
-// Code of the item (p, pl) in bucket c.  A run that the payload does not show
-// the end of is looked up in the text when the step that reads the item
-// needs it (LTR: any other base; else only a lower one), so a stored item
-// that is carried on has its whole run, up to 15, in its payload.
+// Code of an item with payload pl in bucket c.  CODE_LOOK when the payload
+// does not show enough: nothing held, or a run without its end in an item
+// that a step will carry on (left to right any other base, then only a lower
+// one); with the payload read from the text again it always does, so a stored
+// item that is carried on has its whole run, up to 15, in its payload.
+constexpr uint32_t CODE_LOOK = 0x80u;
 template <bool LTR>
-__device__ __forceinline__ uint32_t item_code(const TextRec *__restrict__ text, uint32_t c, uint64_t p, uint32_t &pl) {
-  if (pl == PL_UNKNOWN) pl = preceding(text, p);
+__host__ __device__ __forceinline__ uint32_t shown_code(uint32_t c, uint32_t pl) {
+  if (pl == PL_UNKNOWN) return CODE_LOOK;
   if (pl == PL_START) return CODE_START;
   const uint32_t e = pl & 3u;
   if (LTR ? e == c : e >= c) return e;
-  uint32_t r = pl_run(pl);
-  if (r == pl_len(pl) && pl_more(pl) && r < PL_BASES) {
+  const uint32_t r = pl_run(pl), len = pl_len(pl);
+  return r == len && r < PL_BASES && pl_more(pl) ? CODE_LOOK : e | (r << 3);
+}
+template <bool LTR>
+__device__ __forceinline__ uint32_t item_code(const TextRec *__restrict__ text, uint32_t c, uint64_t p, uint32_t &pl) {
+  uint32_t code = shown_code<LTR>(c, pl);
+  if (code == CODE_LOOK) {
     pl = preceding(text, p);
-    r = pl_run(pl);
+    code = shown_code<LTR>(c, pl);
   }
-  return e | (r << 3);
+  return code;
 }
 
 // The sorted samples.
@@ -1067,38 +1074,96 @@ __global__ __launch_bounds__(64) void k_ind_top(IndStep P, IndData D) {
   if (LTR) *cur = run;
 }
 
-// Copy k of the run that precedes item (p, pl): the suffix k + 1 bases
-// earlier, in bucket d at row g.
-template <bool LTR>
-__device__ __forceinline__ void ind_put(const IndData &D, const CollMap &cm, uint64_t g, uint32_t d, uint32_t k,
-                                        uint32_t r, uint32_t p, uint32_t pl) {
-  const uint32_t q = p - 1 - k;
-  uint32_t x = pl >> (2 * (k + 1));
-  const uint32_t code = k + 1 < r ? d : item_code<LTR>(D.text, d, q, x);
+// Work that waits for a load, put off until a wave's worth of it is there: a
+// lane in sixty needs one (a payload that has run out, a read's first
+// suffix), and one lane's load would hold up its wave for as long as sixty
+// four's.  Entries are (a, b, c) as the user of the list defines.
+struct WaveList {
+  uint32_t a[64], b[64];
+  uint8_t c[64];
+};
+// Appends the entries of the lanes with `on` (n: entries held, the same in
+// every lane); true when the list must be worked off first.
+__device__ __forceinline__ bool list_full(uint32_t n, uint64_t on) { return n + (uint32_t)__popcll(on) > 64; }
+__device__ __forceinline__ void list_append(WaveList &L, uint32_t &n, bool on, uint64_t mask, uint32_t a, uint32_t b,
+                                            uint32_t c) {
+  if (on) {
+    const uint32_t at = n + bits_below_lane(mask);
+    L.a[at] = a;
+    L.b[at] = b;
+    L.c[at] = (uint8_t)c;
+  }
+  n += (uint32_t)__popcll(mask);
+}
+__device__ __forceinline__ void wave_lds_fence() {  // LDS written by some lanes is read by others
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+__device__ __forceinline__ void put_row(const IndData &D, const CollMap &cm, uint64_t g, uint32_t q, uint32_t pl,
+                                        uint32_t code) {
   if (g >= D.nb) {
     atomicOr(D.status, ST_LIST_OVERFLOW);
     return;
   }
-  D.rows[g] = make_uint2(q, x);
+  D.rows[g] = make_uint2(q, pl);
   D.bwt[g + cm.out_shift] = (uint8_t)code;
+}
+
+// Rows (a: row, b: position, c: bucket) whose payload comes from the text.
+template <bool LTR>
+__device__ __forceinline__ void put_looked_up(const IndData &D, const CollMap &cm, WaveList &L, uint32_t &n) {
+  wave_lds_fence();
+  const uint32_t l = lane_id();
+  if (l < n) {
+    const uint32_t q = L.b[l];
+    const uint32_t pl = preceding(D.text, q);
+    put_row(D, cm, L.a[l], q, pl, shown_code<LTR>(L.c[l], pl));
+  }
+  n = 0;
+  wave_lds_fence();
+}
+
+// Copy k of the run that precedes item (p, pl), r long: the suffix k + 1 bases
+// earlier, in bucket d at row g, for the lanes with `on`.
+template <bool LTR>
+__device__ __forceinline__ void ind_put(const IndData &D, const CollMap &cm, WaveList &L, uint32_t &n, bool on,
+                                        uint32_t g, uint32_t d, uint32_t k, uint32_t r, uint32_t p, uint32_t pl) {
+  const uint32_t q = p - 1 - k;
+  const uint32_t x = pl >> (2 * (k + 1));
+  const uint32_t code = k + 1 < r ? d : shown_code<LTR>(d, x);
+  const bool look = on && code == CODE_LOOK;
+  if (on && !look) put_row(D, cm, g, q, x, code);
+  const uint64_t m = __ballot(look);
+  if (m) {
+    if (list_full(n, m)) put_looked_up<LTR>(D, cm, L, n);
+    list_append(L, n, look, m, g, q, d);
+  }
 }
 
 __device__ __forceinline__ uint32_t bwt_symbol(uint32_t code) {
   const uint32_t lut = 'A' | ('C' << 8) | ('G' << 16) | ('T' << 24);
   return code & CODE_START ? (uint32_t)'$' : (lut >> (8 * (code & 3u))) & 0xFFu;
 }
-// Row j is the first suffix of the read starting at p.
-__device__ __forceinline__ void ind_first(const IndData &D, const CollMap &cm, uint64_t j, uint32_t p) {
-  D.start_row[start_rank(D.text, D.srank, p)] = (uint64_t)((int64_t)j + cm.row_shift);
+// Rows of reads' first suffixes (a: row, b: position).
+__device__ __forceinline__ void put_first_rows(const IndData &D, const CollMap &cm, WaveList &L, uint32_t &n) {
+  wave_lds_fence();
+  const uint32_t l = lane_id();
+  if (l < n) D.start_row[start_rank(D.text, D.srank, L.b[l])] = (uint64_t)((int64_t)L.a[l] + cm.row_shift);
+  n = 0;
+  wave_lds_fence();
 }
-// The BWT byte of a row whose step is the last to read its code.
-__device__ __forceinline__ void ind_emit(const IndData &D, const CollMap &cm, uint64_t j, uint32_t code, uint32_t p) {
-  D.bwt[j + cm.out_shift] = (uint8_t)bwt_symbol(code);
-  if (code & CODE_START) ind_first(D, cm, j, p);
+__device__ __forceinline__ void note_first_rows(const IndData &D, const CollMap &cm, WaveList &L, uint32_t &n, bool on,
+                                                uint32_t j, uint32_t p) {
+  const uint64_t m = __ballot(on);
+  if (m) {
+    if (list_full(n, m)) put_first_rows(D, cm, L, n);
+    list_append(L, n, on, m, j, p, 0);
+  }
 }
 
-// Class ranks of one slot: this lane's place, from the wave's class bases
-// (first class of d in nxt[d]); advances them.
+// Class ranks of one slot: this lane's place, from the places the wave's
+// classes (base, k) have come to in nxt; advances them.
 __device__ __forceinline__ uint32_t ind_place(bool ok, uint32_t d, uint32_t (&nxt)[4], uint32_t lo, uint32_t hi) {
   uint32_t g = 0;
 #pragma unroll
@@ -1112,17 +1177,22 @@ __device__ __forceinline__ uint32_t ind_place(bool ok, uint32_t d, uint32_t (&nx
   return g;
 }
 
-// The partition itself, a wave a tile.  Copy 0 of every item first; the items
-// whose run is longer (a quarter of them) are listed and their further
-// copies written list by list, so that full waves write them.
+// The partition itself, a wave a tile, IND_BATCH slots at a time.  Copy 0 of
+// every item first; the items whose run is longer (a quarter of them) are
+// kept in LDS, and their further copies written k by k, so that full waves
+// write them.  (Listed per tile by place and loaded again they cost a second
+// read of the rows, 4.9 instead of 2.6 GB of the 300M rows of the
+// right-to-left steps of 400 Mbases.)
 template <bool LTR>
 __global__ __launch_bounds__(BLOCK) void k_ind_scatter(IndStep P, IndData D) {
-  __shared__ uint16_t lists[WAVES][IND_TILE];
+  __shared__ uint2 lists[WAVES][64 * IND_BATCH];
+  __shared__ WaveList looks[WAVES], firsts[LTR ? 1 : WAVES];
   const uint32_t w = threadIdx.x >> 6, l = lane_id();
+  uint32_t n_look = 0, n_first = 0;
   const uint32_t tile =
       (uint32_t)__builtin_amdgcn_readfirstlane((int)(xcd_tile(blockIdx.x, gridDim.x) * WAVES + w));
   if (tile >= P.ntiles) return;
-  uint16_t *const list = lists[w];
+  uint2 *const list = lists[w];
   const uint32_t s = find_upper(P.tile_prefix, P.nsegs, tile);
   const IndSeg sg = P.segs[s];
   const CollMap cm = D.cmap[sg.coll];
@@ -1130,26 +1200,20 @@ __global__ __launch_bounds__(BLOCK) void k_ind_scatter(IndStep P, IndData D) {
   const uint32_t m = min(IND_TILE, sg.len - t0);
   const uint64_t at0 = (uint64_t)sg.start + t0;
   const uint32_t g = P.coll_groups[sg.coll] + (tile - P.coll_tiles[sg.coll]) / GROUP_TILES;
-  const uint32_t base = D.gtot[(uint64_t)g * 64 + l] + D.hist[(uint64_t)tile * 64 + l];
+  // the place of class l's next item
+  uint32_t place = D.gtot[(uint64_t)g * 64 + l] + D.hist[(uint64_t)tile * 64 + l];
   // bases the step's items can go to
   const uint32_t lo = LTR ? (P.base == 4 ? 0u : P.base + 1) : 0u, hi = LTR ? 4u : P.base;
-  auto item = [&](uint32_t x, uint32_t &p, uint32_t &pl) {
-    if (!LTR || sg.src == SRC_ROWS) {
-      const uint2 v = D.rows[at0 + x];
-      p = v.x;
-      pl = v.y;
-    } else if (sg.src == SRC_SAMPLES) {
-      p = D.smp.h[at0 + x];
-      pl = D.smp.pl[at0 + x];
-    } else {
-      uint32_t code;
-      ind_read_end(D, at0 + x, p, pl, code);
-    }
-  };
   uint32_t nxt[4];
+  auto take_places = [&](uint32_t k) {
 #pragma unroll
-  for (uint32_t dd = 0; dd < 4; ++dd) nxt[dd] = (uint32_t)__builtin_amdgcn_readlane((int)base, (int)(dd * 16));
-  uint32_t n1 = 0;
+    for (uint32_t dd = 0; dd < 4; ++dd) nxt[dd] = (uint32_t)__builtin_amdgcn_readlane((int)place, (int)(dd * 16 + k));
+  };
+  auto keep_places = [&](uint32_t k) {
+#pragma unroll
+    for (uint32_t dd = 0; dd < 4; ++dd)
+      if (l == dd * 16 + k) place = nxt[dd];
+  };
   const uint8_t *codes = sg.src == SRC_SAMPLES ? D.smp.code + at0 : D.bwt + cm.out_shift + at0;
   for (uint32_t x0 = 0; x0 < m; x0 += IND_BATCH * 64) {
     uint32_t code[IND_BATCH], p[IND_BATCH], pl[IND_BATCH];
@@ -1162,49 +1226,60 @@ __global__ __launch_bounds__(BLOCK) void k_ind_scatter(IndStep P, IndData D) {
       if (x < m) {
         if (LTR && sg.src == SRC_READS) {
           ind_read_end(D, at0 + x, p[i], pl[i], code[i]);
+        } else if (LTR && sg.src == SRC_SAMPLES) {
+          code[i] = codes[x];
+          p[i] = D.smp.h[at0 + x];
+          pl[i] = D.smp.pl[at0 + x];
         } else {
           code[i] = codes[x];
-          item(x, p[i], pl[i]);
+          const uint2 v = D.rows[at0 + x];
+          p[i] = v.x;
+          pl[i] = v.y;
         }
       }
     }
+    uint32_t n1 = 0;
+    take_places(0);
 #pragma unroll
     for (uint32_t i = 0; i < IND_BATCH; ++i) {
       const uint32_t x = x0 + i * 64 + l;
       const bool ok = ind_taken<LTR>(code[i], P.base);
       const uint32_t d = code[i] & 3u, r = code_run(code[i]);
       const uint32_t to = ind_place(ok, d, nxt, lo, hi);
-      if (ok) ind_put<LTR>(D, cm, to, d, 0, r, p[i], pl[i]);
+      ind_put<LTR>(D, cm, looks[w], n_look, ok, to, d, 0, r, p[i], pl[i]);
       const uint64_t more = __ballot(ok && r > 1);
-      if (ok && r > 1) list[n1 + bits_below_lane(more)] = (uint16_t)(x | (r << 11));
+      if (ok && r > 1) list[n1 + bits_below_lane(more)] = make_uint2(p[i], pl[i]);
       n1 += (uint32_t)__popcll(more);
-      if (!LTR && x < m) ind_emit(D, cm, at0 + x, code[i], p[i]);
+      if (!LTR) {  // the last step to read this row's code
+        if (x < m) D.bwt[at0 + x + cm.out_shift] = (uint8_t)bwt_symbol(code[i]);
+        note_first_rows(D, cm, firsts[w], n_first, x < m && (code[i] & CODE_START), (uint32_t)(at0 + x), p[i]);
+      }
     }
-  }
-  static_assert(IND_TILE <= 2048, "a list entry holds the place in 11 bits");
-  for (uint32_t k = 1; n1 && k < (uint32_t)RUN_REGIONS; ++k) {
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the list is read by other lanes than wrote it
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (uint32_t dd = 0; dd < 4; ++dd) nxt[dd] = (uint32_t)__builtin_amdgcn_readlane((int)base, (int)(dd * 16 + k));
-    uint32_t n2 = 0;
-    for (uint32_t y0 = 0; y0 < n1; y0 += 64) {
-      const uint32_t y = y0 + l;
-      const bool in = y < n1;
-      const uint32_t e = in ? list[y] : 0u;
-      const uint32_t r = e >> 11;
-      uint32_t p = 0, pl = PL_START;
-      if (in) item(e & 2047u, p, pl);
-      const uint32_t d = pl & 3u;  // the preceding base is the payload's first
-      const uint32_t to = ind_place(in, d, nxt, lo, hi);
-      if (in) ind_put<LTR>(D, cm, to, d, k, r, p, pl);
-      const uint64_t more = __ballot(in && r > k + 1);
-      __builtin_amdgcn_wave_barrier();  // this slot's entries are read before any is overwritten
-      if (in && r > k + 1) list[n2 + bits_below_lane(more)] = (uint16_t)e;
-      n2 += (uint32_t)__popcll(more);
+    keep_places(0);
+    for (uint32_t k = 1; n1 && k < (uint32_t)RUN_REGIONS; ++k) {
+      wave_lds_fence();
+      take_places(k);
+      uint32_t n2 = 0;
+      for (uint32_t y0 = 0; y0 < n1; y0 += 64) {
+        const uint32_t y = y0 + l;
+        const bool in = y < n1;
+        const uint2 e = in ? list[y] : make_uint2(0, PL_START);
+        const uint32_t d = e.y & 3u;  // the preceding base is the payload's first
+        const uint32_t r = in ? pl_run(e.y) : 0u;
+        const uint32_t to = ind_place(in, d, nxt, lo, hi);
+        ind_put<LTR>(D, cm, looks[w], n_look, in, to, d, k, r, e.x, e.y);
+        const uint64_t more = __ballot(in && r > k + 1);
+        __builtin_amdgcn_wave_barrier();  // this slot's entries are read before any is overwritten
+        if (in && r > k + 1) list[n2 + bits_below_lane(more)] = e;
+        n2 += (uint32_t)__popcll(more);
+      }
+      keep_places(k);
+      n1 = n2;
     }
-    n1 = n2;
+    wave_lds_fence();
   }
+  if (n_look) put_looked_up<LTR>(D, cm, looks[w], n_look);
+  if (!LTR && n_first) put_first_rows(D, cm, firsts[w], n_first);
 }
 
 // Runs beyond the regions: the members of region 14 (and of every later one)
@@ -1257,36 +1332,46 @@ __global__ __launch_bounds__(TAIL_WG) void k_ind_tail(const IndTail *__restrict_
 
 // BWT bytes of the rows that no step reads (bucket A), four a lane.
 __global__ __launch_bounds__(BLOCK) void k_ind_emit(IndStep P, IndData D) {
-  const uint32_t tile = blockIdx.x * WAVES + (threadIdx.x >> 6);
+  __shared__ WaveList firsts[WAVES];
+  const uint32_t w = threadIdx.x >> 6;
+  const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * WAVES + w));
   if (tile >= P.ntiles) return;
   const uint32_t s = find_upper(P.tile_prefix, P.nsegs, tile);
   const IndSeg sg = P.segs[s];
   const CollMap cm = D.cmap[sg.coll];
   const uint32_t t0 = (tile - P.tile_prefix[s]) * IND_TILE;
   const int64_t j0 = (int64_t)sg.start + t0, j1 = j0 + min(IND_TILE, sg.len - t0);
+  uint32_t n_first = 0;
   // whole words of the output, the rows at both ends of the tile by byte
   const int64_t word0 = (int64_t)((uintptr_t)(D.bwt + cm.out_shift + j0) & 3u);
-  for (int64_t j = j0 - word0 + 4 * (int64_t)lane_id(); j < j1; j += 4 * 64) {
+  for (int64_t jj = j0 - word0; jj < j1; jj += 4 * 64) {
+    const int64_t j = jj + 4 * (int64_t)lane_id();
     uint8_t *const at = D.bwt + cm.out_shift + j;
-    if (j >= j0 && j + 4 <= j1) {
-      const uint32_t c = *reinterpret_cast<const uint32_t *>(at);
-      uint32_t out = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) out |= bwt_symbol((c >> (8 * i)) & 0xFFu) << (8 * i);
-      *reinterpret_cast<uint32_t *>(at) = out;
-      if (c & (CODE_START * 0x01010101u)) {
-        for (int i = 0; i < 4; ++i)
-          if ((c >> (8 * i)) & CODE_START) ind_first(D, cm, j + i, D.rows[j + i].x);
-      }
+    uint32_t c = 0;
+    const bool whole = j >= j0 && j + 4 <= j1;
+    if (whole) {
+      c = *reinterpret_cast<const uint32_t *>(at);
     } else {
-      for (int i = 0; i < 4; ++i) {
-        if (j + i < j0 || j + i >= j1) continue;
-        const uint32_t c = at[i];
-        at[i] = (uint8_t)bwt_symbol(c);
-        if (c & CODE_START) ind_first(D, cm, j + i, D.rows[j + i].x);
-      }
+      for (int i = 0; i < 4; ++i)
+        if (j + i >= j0 && j + i < j1) c |= (uint32_t)at[i] << (8 * i);
+    }
+    uint32_t out = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out |= bwt_symbol((c >> (8 * i)) & 0xFFu) << (8 * i);
+    if (whole) {
+      *reinterpret_cast<uint32_t *>(at) = out;
+    } else {
+      for (int i = 0; i < 4; ++i)
+        if (j + i >= j0 && j + i < j1) at[i] = (uint8_t)(out >> (8 * i));
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const bool first = ((c >> (8 * i)) & CODE_START) != 0;  // (only rows of the tile have a code)
+      const uint32_t p = first ? D.rows[j + i].x : 0u;
+      note_first_rows(D, cm, firsts[w], n_first, first, (uint32_t)(j + i), p);
     }
   }
+  if (n_first) put_first_rows(D, cm, firsts[w], n_first);
 }
 
 }  // namespace
