@@ -123,6 +123,7 @@ struct SampleKey {
   static constexpr uint32_t FULL = 22;
   static constexpr uint64_t REST = (1ull << KEY_PL_BITS) - 1;
   static __host__ __device__ __forceinline__ uint32_t digit(uint64_t k, int j) {
+    if (j >= ENDED) return GeneralKey::ended_digit(clamp(k), j);
     return j < 5 ? (uint32_t)(k >> (56 - 8 * j)) & 0xFFu : j == 5 ? (uint32_t)(k >> 20) & 0xFu : clamp(k);
   }
   static __host__ __device__ __forceinline__ uint32_t clamp(uint64_t k) { return (uint32_t)(k >> KEY_PL_BITS) & 31u; }
@@ -716,7 +717,7 @@ __global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
   const int d0 = ch.d;
   const bool two = d0 < SampleKey::LAST;
   if (two) {
-    const bool one_bucket = place_digit(S.K[0], d0) == place_digit(S.K[m - 1], d0);
+    const bool one_bucket = !ch.unsplit && place_digit(S.K[0], d0) == place_digit(S.K[m - 1], d0);
     wave_split<PlaceDigit>(S, m, d0 + 1, lane, le & ~(1ull << lane));
     if (!one_bucket) wave_split<PlaceDigit>(S, m, d0, lane, le & ~(1ull << lane));
   }
