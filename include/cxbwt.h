@@ -312,9 +312,11 @@ int cxbwt_job_done(const cxbwt_job *job);
  * cxbwt_graph_create -- capture a build.  Arguments as cxbwt_build_batch
  *   (coll_reads may be NULL with n_coll == 1 for a single collection), plus
  *   levels        sort levels scheduled inside the graph, level 1 included;
- *                 0 = enough for any input of max_read_len (8 per 27-base
- *                 window, plus 2).  Each scheduled level that finds no work
- *                 costs a few empty launches.
+ *                 0 = as many as the build at creation took and two more
+ *                 (small builds: three; at most 8 per 27-base window, plus
+ *                 2).  Each scheduled level that finds no work costs a few
+ *                 empty launches; levels that a replay needs beyond them run
+ *                 in cxbwt_graph_finish.
  *   stream        the caller's stream: creation first runs one eager build
  *                 on it (it writes bwt and term_pos) and waits; the counts
  *                 each of its levels saw size the captured launches (larger

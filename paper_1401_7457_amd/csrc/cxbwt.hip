@@ -483,9 +483,11 @@ unsigned grid_from(uint32_t seen, unsigned fixed) {
 // with dev_nchunks a launch of `grid` workgroups (0: a few waves per SIMD)
 // looping over a count on the device.
 int launch_local(const Buffers &B, const Tuning &tu, uint64_t nb, uint32_t rmax, uint8_t *bwt, uint32_t n_chunks,
-                 const uint32_t *dev_nchunks, hipStream_t st, unsigned grid = 0) {
+                 const uint32_t *dev_nchunks, hipStream_t st, unsigned grid = 0, unsigned most = ~0u) {
   // the looping form holds a few more registers: one wave per SIMD fewer
   // for the smallest chunk keeps it from spilling
+  // with a device count and no grid: the looping form, of at most `most`
+  // workgroups;
   // with a device count and a grid: the one-chunk form over the first
   // `grid` chunks, then the looping form over any beyond them
 #define CX_LOCAL(LI, OCC, OCCP)                                                                                  \
@@ -498,7 +500,7 @@ int launch_local(const Buffers &B, const Tuning &tu, uint64_t nb, uint32_t rmax,
                                                         B.srank, B.cmap, nb, rmax, bwt, B.start_row,             \
                                                         B.counters + C_STATUS, B.stats, 0, dev_nchunks, grid);   \
     } else if (dev_nchunks) {                                                                                    \
-      k_local<LI, OCCP, true><<<256u * 4u * OCCP, LOCAL_WG, 0, st>>>(                                            \
+      k_local<LI, OCCP, true><<<std::min(256u * 4u * OCCP, most), LOCAL_WG, 0, st>>>(                            \
           B.chunks, B.keys0, B.keys1, B.hdl0, B.hdl1, B.pos64, B.text, B.srank, B.cmap, nb, rmax, bwt, B.start_row,\
           B.counters + C_STATUS, B.stats, 0, dev_nchunks, 0);                                                    \
     } else {                                                                                                     \
@@ -710,9 +712,21 @@ void build_init(Build &b, const uint64_t *packed, const uint64_t *offsets, uint6
   b.coll_reads.assign(coll_reads, coll_reads + ncoll + 1);
 }
 
+// The level-1 plan of one collection, which its sizes give: one segment, or
+// one unsplit chunk.
+void plan_single(Build &b) {
+  b.cbase = {0, b.nb};
+  b.cm.assign(1, CollMap{b.n, (int64_t)b.n});
+  b.big.clear();
+  b.small.clear();
+  if (b.nb > (uint64_t)b.tu.chunk()) b.big.push_back(Seg{0, (uint32_t)b.nb, 0, 0, 0, 0, 0, 0});
+  else if (b.nb > 0) b.small.push_back(Seg{0, (uint32_t)b.nb, 0, 0, 0, 0, 1, 0});
+}
+
 // Clears the counters, statistics and read-start bitmap, validates the
-// offsets and marks the read starts.  With check_bases the collection bases
-// are compared with the planned ones (staged in the scan-group area).
+// offsets and marks the read starts.  For one collection the level-1 plan is
+// in place after it; for several, with bases_src, the collection bases are
+// compared with the planned ones (staged in the scan-group area).
 int enqueue_prep(const Build &b, const uint64_t *coll_reads_src, const uint64_t *bases_src, PhaseTimer &T,
                  hipStream_t st) {
   const Buffers &B = b.B;
@@ -720,15 +734,30 @@ int enqueue_prep(const Build &b, const uint64_t *coll_reads_src, const uint64_t 
   const uint64_t n_sbits = b.nb / 32 + 4;
   if (4 * n_sbits > b.Lo.tile_hist_bytes) return fail_internal("work exceeds a workspace list or scratch area");
   int rc;
-  if ((rc = fill_u32(B.counters, C_COUNT, 0, st))) return rc;
-  if ((rc = fill_u64((uint64_t *)B.stats, STAT_WORDS, 0, st))) return rc;
-  if ((rc = fill_u32(sbits, n_sbits, 0, st))) return rc;
-  CX_CHECK(hipMemcpyAsync(B.coll_reads, coll_reads_src, 8 * ((uint64_t)b.ncoll + 1), hipMemcpyHostToDevice, st));
+  if (b.ncoll == 1) {
+    OnePlan P{};
+    P.n = b.n;
+    P.nb = b.nb;
+    P.cm = CollMap{b.n, (int64_t)b.n};
+    P.seg = Seg{0, (uint32_t)b.nb, 0, 0, 0, 0, (uint8_t)(b.nb <= (uint64_t)b.tu.chunk()), 0};
+    P.ntiles = (uint32_t)ceil_div(b.nb, b.tile_len);
+    P.ngroups = (uint32_t)ceil_div(P.ntiles, GROUP_TILES);
+    k_begin<<<std::min(grid_for(std::max<uint64_t>(n_sbits, STAT_WORDS), 256), 4096u), 256, 0, st>>>(
+        P, B.counters, (uint64_t *)B.stats, STAT_WORDS, sbits, n_sbits, B.coll_reads, B.coll_bases, B.cmap, B.segs,
+        B.chunks, B.tile_prefix, B.group_prefix);
+    CX_LAUNCHED();
+  } else {
+    if ((rc = fill_u32(B.counters, C_COUNT, 0, st))) return rc;
+    if ((rc = fill_u64((uint64_t *)B.stats, STAT_WORDS, 0, st))) return rc;
+    if ((rc = fill_u32(sbits, n_sbits, 0, st))) return rc;
+    CX_CHECK(hipMemcpyAsync(B.coll_reads, coll_reads_src, 8 * ((uint64_t)b.ncoll + 1), hipMemcpyHostToDevice, st));
+  }
   T.begin();
   k_prep<<<grid_for(b.n, 256), 256, 0, st>>>(b.packed, b.offsets, b.n, b.nb, b.maxlen, B.coll_reads, b.ncoll, sbits,
                                             b.bwt, b.term_pos, B.counters + C_STATUS);
   CX_LAUNCHED();
   T.end(PH_PREP);
+  if (b.ncoll == 1) return CXBWT_OK;
   k_coll_bases<<<grid_for((uint64_t)b.ncoll + 1, 256), 256, 0, st>>>(b.offsets, B.coll_reads, b.ncoll,
                                                                      B.coll_bases);
   CX_LAUNCHED();
@@ -739,6 +768,14 @@ int enqueue_prep(const Build &b, const uint64_t *coll_reads_src, const uint64_t 
                                                                         B.counters + C_STATUS);
     CX_LAUNCHED();
   }
+  return CXBWT_OK;
+}
+
+// The last kernel of every build: term_pos, and the statistics' totals.
+int launch_term(const Build &b, hipStream_t st) {
+  k_term<<<grid_for(b.n, BLOCK), BLOCK, 0, st>>>(b.offsets, b.n, b.nb, b.B.text, b.B.srank, b.B.start_row, b.term_pos,
+                                                 b.B.stats, b.B.counters);
+  CX_LAUNCHED();
   return CXBWT_OK;
 }
 
@@ -755,10 +792,15 @@ int enqueue_records(const Build &b, PhaseTimer &T, hipStream_t st) {
   CX_LAUNCHED();
   k_rank_count<<<(unsigned)Lo.n_rank_blocks, BLOCK, 0, st>>>(sbits, Lo.n_rank_words, B.rank_blocks);
   CX_LAUNCHED();
-  k_rank_top<<<1, BLOCK, 0, st>>>(B.rank_blocks, (uint32_t)Lo.n_rank_blocks);
-  CX_LAUNCHED();
-  k_rank_words<<<(unsigned)Lo.n_rank_blocks, BLOCK, 0, st>>>(sbits, Lo.n_rank_words, B.rank_blocks, B.srank,
-                                                              Lo.n_rec);
+  if (Lo.n_rank_blocks <= RANK_SUM_BLOCKS) {
+    k_rank_words<true><<<(unsigned)Lo.n_rank_blocks, BLOCK, 0, st>>>(sbits, Lo.n_rank_words, B.rank_blocks, B.srank,
+                                                                     Lo.n_rec);
+  } else {
+    k_rank_top<<<1, BLOCK, 0, st>>>(B.rank_blocks, (uint32_t)Lo.n_rank_blocks);
+    CX_LAUNCHED();
+    k_rank_words<false><<<(unsigned)Lo.n_rank_blocks, BLOCK, 0, st>>>(sbits, Lo.n_rank_words, B.rank_blocks, B.srank,
+                                                                      Lo.n_rec);
+  }
   CX_LAUNCHED();
   T.end(PH_PREP);
   return CXBWT_OK;
@@ -895,6 +937,68 @@ int run_levels(const Build &b, LevelOut acc, uint32_t nbig, PhaseTimer &T, hipSt
   return CXBWT_OK;
 }
 
+// Whether the chunks and final groups of `levels` levels fit their lists
+// together.  A level makes at most 2 S / C chunks of the S suffixes that leave
+// it in chunks of up to C, plus one for every segment it splits and every
+// large bucket (each of more than C suffixes) it makes: over three levels at
+// most 7 nb / C, which for C = 384 is less than the 4 nb / 192 that the list
+// holds for one level of the smallest chunks.  Final groups are disjoint.
+bool lists_hold_all(const Build &b, uint32_t levels) {
+  return b.tu.chunk_items >= 6 && levels <= 3 && b.Lo.seg_slots <= NEXT_SEGS;
+}
+
+// Levels scheduled at once for a build that the host will only look at when
+// they are through (it finishes the build if that is not all): one level of
+// 256 buckets, two of 65536, and the split of their ended suffixes.
+uint32_t levels_ahead(const Build &b) {
+  return b.nb <= 16ull * b.tu.chunk() ? 1u : b.nb <= 256ull * b.tu.chunk() ? 2u : 3u;
+}
+
+// After level 1's scan and scatter: the rest of `levels` levels sized on the
+// device, then all their chunks and final groups.  Five launches a level.
+// Grids cover the counts seen (or the most that level 2 can have; later
+// levels of a small build hold little); every kernel loops.
+int enqueue_listed_levels(const Build &b, uint32_t levels, PhaseTimer &T, hipStream_t st,
+                          const std::vector<LevelShape> *shapes) {
+  const Buffers &B = b.B;
+  const Layout &Lo = b.Lo;
+  const uint64_t nb = b.nb, chunk = b.tu.chunk();
+  int rc;
+  uint32_t seen_chunks = 0;
+  for (uint32_t lv = 0;; ++lv) {
+    if (shapes && lv < shapes->size()) seen_chunks += (*shapes)[lv].nchunks;
+    const int last = lv + 1 == levels;
+    k_next_level<<<1, NEXT_WG, 0, st>>>(B.counters, B.stats, B.big_next, B.segs, B.tile_prefix, B.group_prefix, B.seg_or,
+                                        B.seg_and, b.tile_len, Lo.seg_slots, Lo.max_tiles, Lo.max_groups, last);
+    CX_LAUNCHED();
+    if (last) break;
+    LevelShape sh;
+    if (shapes && lv + 1 < shapes->size()) {
+      sh = (*shapes)[lv + 1];
+    } else {
+      const uint64_t segs = std::min<uint64_t>(256ull * b.big.size(), nb / (chunk + 1) + 1);
+      sh.nsegs = (uint32_t)(lv == 0 ? segs : segs / 8 + 1);
+      sh.ntiles = (uint32_t)((lv == 0 ? nb : nb / 8) / b.tile_len + sh.nsegs);
+      sh.ngroups = (uint32_t)(sh.ntiles / GROUP_TILES + sh.nsegs);
+    }
+    if ((rc = launch_level_kernels(B, b.tu, b.Ls, nb, 0, 0, 0, B.counters + C_NCUR, T, st, &sh))) return rc;
+  }
+  T.begin();
+  // chunks hold two thirds of a chunk's suffixes and more on average; a small
+  // build takes the looping kernel alone
+  const uint64_t expect = std::max<uint64_t>(seen_chunks, 3 * nb / (2 * chunk) + 1);
+  if ((rc = launch_local(B, b.tu, nb, b.rmax, b.bwt, (uint32_t)Lo.cap_chunks, B.counters + C_NCHUNK, st,
+                         nb <= 1u << 20 ? 0u : grid_from((uint32_t)expect, 0), (unsigned)expect)))
+    return rc;
+  T.end(PH_LOCAL);
+  T.begin();
+  k_emit_groups<<<(unsigned)std::min<uint64_t>(PG_EMIT, nb / (2 * chunk) + 16), BLOCK, 0, st>>>(
+      B.finals, B.counters + C_NFINAL, B.keys0, B.keys1, B.hdl0, B.hdl1, B.text, B.srank, B.cmap, b.bwt, B.start_row);
+  CX_LAUNCHED();
+  T.end(PH_FINAL);
+  return CXBWT_OK;
+}
+
 // Text records, read-end ranks, the collections that fit one chunk, and
 // level 1.  Then either (device_levels = 0) the host schedules levels 2..
 // with a counter readback per level, or the next device_levels levels are
@@ -908,18 +1012,20 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
   uint32_t *counters = B.counters;
   const uint64_t nb = b.nb;
   int rc;
-  if (b.ncoll) CX_CHECK(hipMemcpyAsync(B.cmap, src.cm, sizeof(CollMap) * b.ncoll, hipMemcpyHostToDevice, st));
+  const bool planned = b.ncoll == 1;  // enqueue_prep has put the plan in place
+  if (!planned) CX_CHECK(hipMemcpyAsync(B.cmap, src.cm, sizeof(CollMap) * b.ncoll, hipMemcpyHostToDevice, st));
   if (nb == 0) return CXBWT_OK;
 
   // collections that fit one chunk: keys in read order, one unsplit chunk each
   if (src.small.ns) {
-    if ((rc = upload_src(B, Lo, src.small, st))) return rc;
+    if (!planned && (rc = upload_src(B, Lo, src.small, st))) return rc;
     T.begin();
     k_gen<<<src.small.ntiles, BLOCK, 0, st>>>(B.segs, B.tile_prefix, src.small.ns, b.tile_len, B.text, nb, B.keys0,
                                               B.hdl0);
     CX_LAUNCHED();
     T.end(PH_GEN);
-    CX_CHECK(hipMemcpyAsync(B.chunks, src.small.segs, sizeof(Seg) * src.small.ns, hipMemcpyHostToDevice, st));
+    if (!planned)
+      CX_CHECK(hipMemcpyAsync(B.chunks, src.small.segs, sizeof(Seg) * src.small.ns, hipMemcpyHostToDevice, st));
     if (!src.big.ns) {
       if ((rc = finish_level(B, Lo, b.tu, nb, b.rmax, b.maxlen, b.bwt, src.small.ns, 0, 0, 0, T, st))) return rc;
     } else {
@@ -930,7 +1036,7 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
   if (src.big.ns) {
     // level 1: keys computed from the 2-bit reads, counted, recomputed, scattered
     const uint32_t ns = src.big.ns, ntiles = src.big.ntiles, ngroups = src.big.ngroups;
-    if ((rc = upload_src(B, Lo, src.big, st))) return rc;
+    if (!planned && (rc = upload_src(B, Lo, src.big, st))) return rc;
     T.begin();
     if (b.tu.tile_items == 16)
       k_gen_hist<2><<<ntiles, BLOCK, 0, st>>>(B.segs, B.tile_prefix, ns, b.tile_len, B.text, nb, B.tile_hist);
@@ -962,6 +1068,8 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
                              st)))
         return rc;
       if ((rc = run_levels(b, o, o.n_big, T, st))) return rc;
+    } else if (lists_hold_all(b, device_levels)) {
+      if ((rc = enqueue_listed_levels(b, device_levels, T, st, shapes))) return rc;
     } else {
       const uint32_t *ncur = counters + C_NCUR;
       const LevelShape none;
@@ -995,23 +1103,21 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
     }
   }
   T.begin();
-  k_term<<<grid_for(b.n, 256), 256, 0, st>>>(b.offsets, b.n, b.nb, B.text, B.srank, B.start_row, b.term_pos);
-  CX_LAUNCHED();
+  if ((rc = launch_term(b, st))) return rc;
   T.end(PH_FINAL);
   return CXBWT_OK;
 }
 
-// Statistics counters of the build, and the device status.
+// The counters of a build whose last kernel (launch_term) is enqueued: the
+// device status, and the statistics' totals.
 int read_totals(const Build &b, PhaseTimer &T, hipStream_t st, uint32_t (&hc)[C_COUNT]) {
-  std::vector<uint64_t> hs(STAT_WORDS);
   CX_CHECK(hipMemcpyAsync(hc, b.B.counters, sizeof(hc), hipMemcpyDeviceToHost, st));
-  CX_CHECK(hipMemcpyAsync(hs.data(), b.B.stats, 8 * STAT_WORDS, hipMemcpyDeviceToHost, st));
   CX_CHECK(hipStreamSynchronize(st));
   T.collect();
-  for (int i = 0; i < STAT_SPREAD; ++i) {
-    g_stats.window_fetches += hs[K_FETCHES * STAT_KIND + i * STAT_STRIDE];
-    g_stats.scattered_suffixes += hs[K_SCATTERED * STAT_KIND + i * STAT_STRIDE];
-  }
+  uint64_t t[2];
+  memcpy(t, hc + C_TOTALS, sizeof(t));
+  g_stats.window_fetches += t[0];
+  g_stats.scattered_suffixes += t[1];
   return CXBWT_OK;
 }
 
@@ -1050,6 +1156,7 @@ int run_stringword(const Build &b, PhaseTimer &T, hipStream_t st) {
   const Buffers &B = b.B;
   const Layout &Lo = b.Lo;
   const uint64_t nb = b.nb;
+  int rc;
   g_stats.schedule = CXBWT_SCHEDULE_STRINGWORD;
   if (b.ncoll) CX_CHECK(hipMemcpyAsync(B.cmap, b.cm.data(), sizeof(CollMap), hipMemcpyHostToDevice, st));
   if (nb) {
@@ -1062,7 +1169,7 @@ int run_stringword(const Build &b, PhaseTimer &T, hipStream_t st) {
     uint32_t *H[2] = {B.hdl0, B.hdl1};
     unsigned long long *orand = B.seg_or;  // OR and AND of a window's ordering bits
     const unsigned grid = (unsigned)std::min<uint64_t>(ceil_div(nb, BLOCK), 65536);
-    int cur = 0, rc;
+    int cur = 0;
     for (int w = (int)b.rmax - 1; w >= 0; --w) {
       if ((rc = fill_u64((uint64_t *)orand, 1, 0, st))) return rc;
       if ((rc = fill_u64((uint64_t *)orand + 1, 1, ~0ull, st))) return rc;
@@ -1108,8 +1215,7 @@ int run_stringword(const Build &b, PhaseTimer &T, hipStream_t st) {
     T.end(PH_FINAL);
   }
   T.begin();
-  k_term<<<grid_for(b.n, 256), 256, 0, st>>>(b.offsets, b.n, b.nb, B.text, B.srank, B.start_row, b.term_pos);
-  CX_LAUNCHED();
+  if ((rc = launch_term(b, st))) return rc;
   T.end(PH_FINAL);
   return CXBWT_OK;
 }
@@ -1144,9 +1250,7 @@ int finish_device_levels(const Build &b, const uint32_t (&hc0)[C_COUNT], PhaseTi
   acc.next_tiles = f[K_NEXT_TILES - K_LEVEL_FIRST];
   acc.next_groups = f[K_NEXT_GROUPS - K_LEVEL_FIRST];
   if ((rc = run_levels(b, acc, hc[C_NBIG], T, st))) return rc;
-  k_term<<<grid_for(b.n, 256), 256, 0, st>>>(b.offsets, b.n, b.nb, b.B.text, b.B.srank, b.B.start_row,
-                                              b.term_pos);
-  CX_LAUNCHED();
+  if ((rc = launch_term(b, st))) return rc;
   // the statistics block still holds the device levels' counts: take the rest only
   g_stats.window_fetches = 0;
   g_stats.scattered_suffixes = 0;
@@ -1484,8 +1588,7 @@ int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
 #undef CX_TAIL
   T.end(PH_INDUCE);
   T.begin();
-  k_term<<<grid_for(b.n, 256), 256, 0, st>>>(b.offsets, b.n, b.nb, b.B.text, b.B.srank, b.B.start_row, b.term_pos);
-  CX_LAUNCHED();
+  if ((rc = launch_term(b, st))) return rc;
   T.end(PH_FINAL);
   return CXBWT_OK;
 }
@@ -1500,19 +1603,27 @@ int run_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n, uint6
   PhaseTimer T{st, allow_timing && g_timing != 0, {}};
   Build b;
   build_init(b, packed, offsets, n, nb, maxlen, coll_reads, ncoll, bwt, term_pos, ws);
+  const bool msd = !(ncoll == 1 && b.tu.schedule == CXBWT_SCHEDULE_STRINGWORD);
+  const bool induce = msd && nb >= CXBWT_INDUCE_MIN_BASES && maxlen >= INDUCE_MIN_READ;
+  // small builds run their levels without a look from the host in between;
+  // for one collection it need not look at the offsets' verdict either
+  // (kernels stay in bounds on invalid offsets, as in a replayed graph)
+  const bool ahead = msd && !induce && lists_hold_all(b, levels_ahead(b));
   int rc;
   if ((rc = enqueue_prep(b, b.coll_reads.data(), nullptr, T, st))) return rc;
   if ((rc = enqueue_records(b, T, st))) return rc;
-  if ((rc = plan_level1(b, T, st))) return rc;
-  if (ncoll == 1 && b.tu.schedule == CXBWT_SCHEDULE_STRINGWORD) {
+  if (ahead && ncoll == 1) plan_single(b);
+  else if ((rc = plan_level1(b, T, st))) return rc;
+  uint32_t hc[C_COUNT];
+  if (!msd) {
     if ((rc = run_stringword(b, T, st))) return rc;
   } else {
     bool done = false;
     Level1Vectors v;
     v.make(b);
-    if (nb >= CXBWT_INDUCE_MIN_BASES && maxlen >= INDUCE_MIN_READ && !b.big.empty()) {
+    if (induce && !b.big.empty()) {
       if (!b.small.empty()) {
-        // the collections of one chunk, by themselves (their samples' sort would come after anyway)
+        // the collections of one chunk, by themselves
         Level1Src small = v.src;
         small.big = SegSrc{};
         if ((rc = enqueue_body(b, small, 0, T, st))) return rc;
@@ -1521,10 +1632,14 @@ int run_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n, uint6
     }
     if (!done) {
       level1_stats(b);
-      if ((rc = enqueue_body(b, v.src, 0, T, st))) return rc;
+      const bool listed = ahead && !b.big.empty();
+      if ((rc = enqueue_body(b, v.src, listed ? levels_ahead(b) : 0, T, st))) return rc;
+      if (listed) {
+        if ((rc = read_totals(b, T, st, hc))) return rc;
+        return finish_device_levels(b, hc, T, st);
+      }
     }
   }
-  uint32_t hc[C_COUNT];
   if ((rc = read_totals(b, T, st, hc))) return rc;
   if (hc[C_STATUS]) return fail_status(hc[C_STATUS]);
   return CXBWT_OK;
@@ -1731,8 +1846,7 @@ int run_range_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n,
     if ((rc = run_levels(b, acc, 1, T, st))) return rc;
   }
   T.begin();
-  k_term<<<grid_for(n, 256), 256, 0, st>>>(offsets, n, nb, b.B.text, b.B.srank, b.B.start_row, term_pos);
-  CX_LAUNCHED();
+  if ((rc = launch_term(b, st))) return rc;
   T.end(PH_FINAL);
   uint32_t hc[C_COUNT];
   if ((rc = read_totals(b, T, st, hc))) return rc;
@@ -1811,6 +1925,13 @@ int graph_capture(GraphPlan &P, hipStream_t st) {
   src.small = SegSrc{(const Seg *)(h + o_ss), (const uint32_t *)(h + o_stp), (const uint32_t *)(h + o_sgp),
                      (uint32_t)nsm, v.stp.back(), v.sgp.back()};
   src.nsmall = (const uint32_t *)(h + o_ns);
+  // levels by default: as many as this build took and two more (a replay that
+  // needs more is completed by graph_finish); three when all can be listed,
+  // which is then their cheapest form
+  if (!P.levels) {
+    const uint32_t took = (uint32_t)P.shapes.size();
+    P.levels = took <= 3 && lists_hold_all(b, 3) ? 3 : std::min(took + 2, 8 * b.rmax + 2);
+  }
   // capture: every size below is fixed now or read on the device
   CX_CHECK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
   rc = enqueue_prep(b, (const uint64_t *)(h + o_cr), (const uint64_t *)(h + o_cb), T, st);
@@ -1980,11 +2101,16 @@ int cxbwt_pack(const uint8_t *ascii, uint64_t n_bases, uint64_t *packed, uint32_
   if (n_bases > CXBWT_MAX_RANGE_BASES) return CXBWT_ERANGE;
   if (!packed || (n_bases && !ascii)) return CXBWT_EINVAL;
   hipStream_t st = (hipStream_t)stream;
+  const uint64_t nw = cxbwt_packed_words(n_bases);
+  if (nw <= PACK_SMALL_WORDS) {
+    k_pack_small<<<1, PACK_WG, 0, st>>>(ascii, n_bases, packed, nw, d_status);
+    CX_LAUNCHED();
+    return CXBWT_OK;
+  }
   if (d_status) {
     int rc = fill_u32(d_status, 1, 0, st);
     if (rc) return rc;
   }
-  const uint64_t nw = cxbwt_packed_words(n_bases);
   k_pack<<<grid_for(nw, 256), 256, 0, st>>>(ascii, n_bases, packed, nw, d_status);
   CX_LAUNCHED();
   return CXBWT_OK;
@@ -2143,7 +2269,7 @@ int cxbwt_graph_create(const uint64_t *packed, const uint64_t *offsets, uint64_t
   if (!g) return CXBWT_ENOMEM;
   build_init(g->p.b, packed, offsets, n_reads, n_bases, max_read_len, coll_reads, n_coll, bwt, term_pos,
              (unsigned char *)workspace);
-  g->p.levels = levels ? levels : 8 * g->p.b.rmax + 2;
+  g->p.levels = levels;
   // the eager pass runs on the caller's stream; the capture on a stream of
   // its own (a capture needs a non-default stream)
   hipStream_t cs = nullptr;

@@ -41,7 +41,7 @@ constexpr uint32_t ST_PLAN_MISMATCH = 32u;  // inputs no longer match a captured
 // levels are scheduled on the device keeps its running totals (G_*) from
 // C_CUM on.
 enum { C_STATUS = 0, C_NFINAL = 1, C_NCHUNK = 2, C_NBIG = 3, C_NCUR = 4, C_FLAGS = 5, C_FOLD = 16, C_CUM = 32,
-       C_COUNT = 64 };
+       C_TOTALS = 52, C_COUNT = 64 };  // C_TOTALS: window fetches, scattered suffixes (k_term)
 enum { G_LEVELS, G_BIGSEG, G_LEVSUF, G_REGATH, G_MAXWIN, G_CHUNKS, G_FINALS, G_FINLEN, G_BATCHES, G_COUNT };
 constexpr uint32_t FL_STALLED = 1u;     // a level did not fit the scratch: the host finishes the build
 constexpr uint32_t FL_INCOMPLETE = 2u;  // segments remain after the last scheduled level
@@ -225,6 +225,37 @@ __global__ void k_fill_u32(uint32_t *p, uint64_t n, uint32_t v) {
   for (; i < n; i += (uint64_t)gridDim.x * blockDim.x) p[i] = v;
 }
 
+// What a build of one collection starts from, in one launch: cleared counters,
+// statistics and read-start bitmap, and the level-1 plan, which needs no look
+// at the offsets (k_prep checks that they begin at 0 and end at nb).
+struct OnePlan {
+  uint64_t n, nb;
+  Seg seg;             // the collection: a level-1 segment, or a chunk
+  CollMap cm;
+  uint32_t ntiles, ngroups;
+};
+__global__ __launch_bounds__(256) void k_begin(OnePlan P, uint32_t *counters, uint64_t *stats, uint64_t n_stats,
+                                               uint32_t *sbits, uint64_t n_sbits, uint64_t *coll_reads,
+                                               uint64_t *coll_bases, CollMap *cmap, Seg *segs, Seg *chunks,
+                                               uint32_t *tile_prefix, uint32_t *group_prefix) {
+  const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
+  for (uint64_t i = i0; i < C_COUNT; i += step) counters[i] = 0;
+  for (uint64_t i = i0; i < n_stats; i += step) stats[i] = 0;
+  for (uint64_t i = i0; i < n_sbits; i += step) sbits[i] = 0;
+  if (i0 == 0) {
+    coll_reads[0] = 0;
+    coll_reads[1] = P.n;
+    coll_bases[0] = 0;
+    coll_bases[1] = P.nb;
+    cmap[0] = P.cm;
+    segs[0] = P.seg;
+    if (P.seg.unsplit) chunks[0] = P.seg;
+    tile_prefix[0] = group_prefix[0] = 0;
+    tile_prefix[1] = P.ntiles;
+    group_prefix[1] = P.ngroups;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // a0: read packing (ASCII -> 2-bit, first base in the top bits)
 // ---------------------------------------------------------------------------
@@ -234,16 +265,12 @@ __device__ __forceinline__ uint32_t base_code(uint32_t c, bool &bad) {
   return ((c >> 2) ^ (c >> 1)) & 3u;
 }
 
-// One thread per 32-base word.  Full words with a 16-byte aligned source
-// are read as two 16-byte loads (a wave covers 2 KB contiguously); the tail
-// word and unaligned sources go byte by byte.
-__global__ void k_pack(const uint8_t *__restrict__ ascii, uint64_t nb, uint64_t *__restrict__ packed, uint64_t nwords,
-                       uint32_t *status) {
-  const uint64_t w = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (w >= nwords) return;
+// Word w.  Full words with a 16-byte aligned source are read as two 16-byte
+// loads (a wave covers 2 KB contiguously); the tail word and unaligned
+// sources go byte by byte.
+__device__ __forceinline__ uint64_t pack_word(const uint8_t *__restrict__ ascii, uint64_t nb, uint64_t w, bool &bad) {
   const uint64_t t0 = w * 32;
   uint64_t x = 0;
-  bool bad = false;
   if (t0 + 32 <= nb && ((uintptr_t)ascii & 15) == 0) {
     const uint4 *src = reinterpret_cast<const uint4 *>(ascii + t0);
     const uint4 a = src[0], b = src[1];
@@ -263,8 +290,30 @@ __global__ void k_pack(const uint8_t *__restrict__ ascii, uint64_t nb, uint64_t 
       x |= (uint64_t)base_code(ascii[t], bad) << (62 - 2 * j);
     }
   }
-  packed[w] = x;
+  return x;
+}
+
+// One thread per 32-base word.
+__global__ void k_pack(const uint8_t *__restrict__ ascii, uint64_t nb, uint64_t *__restrict__ packed, uint64_t nwords,
+                       uint32_t *status) {
+  const uint64_t w = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (w >= nwords) return;
+  bool bad = false;
+  packed[w] = pack_word(ascii, nb, w, bad);
   if (bad && status) atomicOr(status, ST_BAD_CHAR);
+}
+
+// The same for few words, in one workgroup that clears the status first (a
+// launch less).
+constexpr int PACK_WG = 1024;
+constexpr uint64_t PACK_SMALL_WORDS = PACK_WG;
+__global__ __launch_bounds__(PACK_WG) void k_pack_small(const uint8_t *__restrict__ ascii, uint64_t nb,
+                                                        uint64_t *__restrict__ packed, uint64_t nwords,
+                                                        uint32_t *status) {
+  bool bad = false;
+  for (uint64_t w = threadIdx.x; w < nwords; w += PACK_WG) packed[w] = pack_word(ascii, nb, w, bad);
+  const int any = __syncthreads_or(bad);
+  if (status && threadIdx.x == 0) *status = any ? ST_BAD_CHAR : 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -360,17 +409,23 @@ __global__ void k_coll_bases(const uint64_t *__restrict__ offsets, const uint64_
 // owns the start bits of its first 16 positions)
 // ---------------------------------------------------------------------------
 constexpr int RANK_WPT = 16;                      // words per thread
+constexpr uint32_t RANK_SUM_BLOCKS = 512;         // most blocks that add up the counts before them themselves
 constexpr int RANK_BLOCK_WORDS = BLOCK * RANK_WPT;
 
-// Counted on the read-start bitmap (32 positions a word, two records).
+// Counted on the read-start bitmap (32 positions a word, two records); a wave
+// owns RANK_WPT * 64 neighbouring words, a word a lane at a time (a lane with
+// neighbouring words of its own read and wrote 64-byte strides: 126 against
+// 45 us for the ranks of 400 Mbases).
+__device__ __forceinline__ uint64_t rank_word(int i) {
+  return (uint64_t)blockIdx.x * RANK_BLOCK_WORDS + item_index<RANK_WPT>(i);
+}
 __global__ __launch_bounds__(BLOCK) void k_rank_count(const uint32_t *__restrict__ sbits, uint64_t nw,
                                                       uint32_t *__restrict__ blocksum) {
   __shared__ uint32_t tmp[WAVES];
-  const uint64_t w0 = (uint64_t)blockIdx.x * RANK_BLOCK_WORDS + (uint64_t)threadIdx.x * RANK_WPT;
   uint32_t c = 0;
 #pragma unroll
   for (int i = 0; i < RANK_WPT; ++i)
-    if (w0 + i < nw) c += (uint32_t)__popc(sbits[w0 + i]);
+    if (rank_word(i) < nw) c += (uint32_t)__popc(sbits[rank_word(i)]);
   uint32_t total;
   block_excl_sum(c, tmp, &total);
   if (threadIdx.x == 0) blocksum[blockIdx.x] = total;
@@ -389,26 +444,42 @@ __global__ __launch_bounds__(BLOCK) void k_rank_top(uint32_t *__restrict__ block
   }
 }
 
-// srank of records 2k and 2k+1 from bitmap word k.
+// srank of records 2k and 2k+1 from bitmap word k.  SUM: blocksum holds the
+// blocks' counts, and every block adds up those before it (for few blocks, a
+// launch less); else k_rank_top has scanned them.
+template <bool SUM>
 __global__ __launch_bounds__(BLOCK) void k_rank_words(const uint32_t *__restrict__ sbits, uint64_t nw,
                                                       const uint32_t *__restrict__ blocksum,
                                                       uint32_t *__restrict__ srank, uint64_t nrec) {
   __shared__ uint32_t tmp[WAVES];
-  const uint64_t w0 = (uint64_t)blockIdx.x * RANK_BLOCK_WORDS + (uint64_t)threadIdx.x * RANK_WPT;
-  uint32_t word[RANK_WPT];
-  uint32_t c = 0;
-#pragma unroll
-  for (int i = 0; i < RANK_WPT; ++i) {
-    word[i] = w0 + i < nw ? sbits[w0 + i] : 0u;
-    c += (uint32_t)__popc(word[i]);
+  uint32_t first;
+  if (SUM) {
+    uint32_t v = 0;
+    for (uint32_t b = threadIdx.x; b < blockIdx.x; b += BLOCK) v += blocksum[b];
+    block_excl_sum(v, tmp, &first);
+  } else {
+    first = blocksum[blockIdx.x];
   }
-  uint32_t run = blocksum[blockIdx.x] + block_excl_sum(c, tmp, nullptr);
+  uint32_t word[RANK_WPT], ex[RANK_WPT];
+#pragma unroll
+  for (int i = 0; i < RANK_WPT; ++i) word[i] = rank_word(i) < nw ? sbits[rank_word(i)] : 0u;
+  uint32_t carry = 0;
 #pragma unroll
   for (int i = 0; i < RANK_WPT; ++i) {
-    const uint64_t r0 = 2 * (w0 + i);
-    if (r0 < nrec) srank[r0] = run;
-    if (r0 + 1 < nrec) srank[r0 + 1] = run + (uint32_t)__popc(word[i] & 0xFFFFu);
-    run += (uint32_t)__popc(word[i]);
+    const uint32_t c = (uint32_t)__popc(word[i]), inc = wave_incl_sum(c);
+    ex[i] = carry + inc - c;
+    carry += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+  }
+  if (lane_id() == 0) tmp[threadIdx.x >> 6] = carry;
+  __syncthreads();
+  for (uint32_t w = 0; w < (threadIdx.x >> 6); ++w) first += tmp[w];
+#pragma unroll
+  for (int i = 0; i < RANK_WPT; ++i) {
+    const uint64_t r0 = 2 * rank_word(i);
+    const uint32_t run = first + ex[i];
+    const uint32_t next = run + (uint32_t)__popc(word[i] & 0xFFFFu);
+    if (r0 + 1 < nrec) *reinterpret_cast<uint2 *>(srank + r0) = make_uint2(run, next);
+    else if (r0 < nrec) srank[r0] = run;
   }
 }
 
@@ -416,9 +487,20 @@ __global__ __launch_bounds__(BLOCK) void k_rank_words(const uint32_t *__restrict
 // (A replayed graph runs this even when k_prep found the offsets invalid:
 // reads that leave the text are skipped, and the result is then reported
 // as an error.)
-__global__ void k_term(const uint64_t *__restrict__ offsets, uint64_t n, uint64_t nb,
-                       const TextRec *__restrict__ text, const uint32_t *__restrict__ srank,
-                       const uint64_t *__restrict__ start_row, uint64_t *__restrict__ term_pos) {
+// Being the last kernel of a build, it also folds the statistics that are
+// summed over all its kernels, so that the host reads the counters only.
+__global__ __launch_bounds__(BLOCK) void k_term(const uint64_t *__restrict__ offsets, uint64_t n, uint64_t nb,
+                                                const TextRec *__restrict__ text, const uint32_t *__restrict__ srank,
+                                                const uint64_t *__restrict__ start_row, uint64_t *__restrict__ term_pos,
+                                                const unsigned long long *__restrict__ stats,
+                                                uint32_t *__restrict__ counters) {
+  if (blockIdx.x == 0 && threadIdx.x < 2 * 64) {
+    static_assert(STAT_SPREAD == 64 && K_FETCHES == 0 && K_SCATTERED == 1, "a wave per kind");
+    unsigned long long v = stats[(threadIdx.x >> 6) * STAT_KIND + (uint64_t)lane_id() * STAT_STRIDE];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (lane_id() == 0) reinterpret_cast<unsigned long long *>(counters + C_TOTALS)[threadIdx.x >> 6] = v;
+  }
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   const uint64_t a = offsets[i], b = offsets[i + 1];
@@ -1210,6 +1292,93 @@ __global__ void k_level_step(uint32_t *__restrict__ c, uint64_t seg_slots, uint6
   g[G_BATCHES] += 1;
 }
 
+// The same step, with k_level_fold's work before it and k_seg_count's,
+// k_seg_scan's and k_fill_seg's after it, in one workgroup: for builds whose
+// per-segment scratch holds few segments, where a launch costs more than the
+// list.  The chunks and final groups of all levels stay in their lists, for
+// one launch each after the last level (`totals`: C_NCHUNK and C_NFINAL are
+// the build's).
+constexpr int NEXT_WG = 1024;
+constexpr uint64_t NEXT_SEGS = 8192;  // most segments it takes: about 1 us per thousand
+__global__ __launch_bounds__(NEXT_WG) void k_next_level(uint32_t *__restrict__ c, unsigned long long *__restrict__ stats,
+                                                        const Seg *__restrict__ list, Seg *__restrict__ segs,
+                                                        uint32_t *__restrict__ tile_prefix,
+                                                        uint32_t *__restrict__ group_prefix,
+                                                        unsigned long long *__restrict__ seg_or,
+                                                        unsigned long long *__restrict__ seg_and, uint32_t tile_len,
+                                                        uint64_t seg_slots, uint64_t max_tiles, uint64_t max_groups,
+                                                        int last) {
+  constexpr int NW = NEXT_WG / 64;
+  __shared__ unsigned long long f[K_LEVEL_KINDS];
+  __shared__ uint32_t tmp[NW];
+  __shared__ uint32_t cur;
+  const uint32_t w = threadIdx.x >> 6, l = lane_id();
+  if (c[C_FLAGS] & (FL_STALLED | FL_INCOMPLETE)) return;  // keep what the host resumes from
+  if (w < (uint32_t)K_LEVEL_KINDS) {
+    unsigned long long *slot = stats + (K_LEVEL_FIRST + w) * STAT_KIND + (uint64_t)l * STAT_STRIDE;
+    unsigned long long v = *slot;
+    *slot = 0;
+    const bool most = w + K_LEVEL_FIRST == K_NEXT_MAXR;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const unsigned long long t = __shfl_xor(v, o, 64);
+      v = most ? max(v, t) : v + t;
+    }
+    if (l == 0) f[w] = v;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    unsigned long long *const out = reinterpret_cast<unsigned long long *>(c + C_FOLD);
+    for (int k = 0; k < K_LEVEL_KINDS; ++k) out[k] = f[k];
+    unsigned long long *g = reinterpret_cast<unsigned long long *>(c + C_CUM);
+    g[G_CHUNKS] = c[C_NCHUNK];
+    g[G_FINALS] = c[C_NFINAL];
+    g[G_FINLEN] += f[K_FINAL_LEN - K_LEVEL_FIRST];
+    const uint32_t nbig = c[C_NBIG];
+    cur = 0;
+    if (nbig && last) {
+      c[C_FLAGS] |= FL_INCOMPLETE;
+    } else if (nbig && (nbig > seg_slots || f[K_NEXT_TILES - K_LEVEL_FIRST] > max_tiles ||
+                        f[K_NEXT_GROUPS - K_LEVEL_FIRST] > max_groups)) {
+      c[C_FLAGS] |= FL_STALLED;
+    } else if (nbig) {
+      cur = nbig;
+      c[C_NBIG] = 0;
+      g[G_LEVELS] += 1;
+      g[G_BIGSEG] += nbig;
+      g[G_LEVSUF] += f[K_NEXT_LEN - K_LEVEL_FIRST];
+      g[G_REGATH] += f[K_NEXT_REGATHER - K_LEVEL_FIRST];
+      g[G_MAXWIN] = max(g[G_MAXWIN], f[K_NEXT_MAXR - K_LEVEL_FIRST]);
+      g[G_BATCHES] += 1;
+    }
+    c[C_NCUR] = cur;
+  }
+  __syncthreads();
+  const uint32_t n = cur;
+  uint32_t tiles = 0, groups = 0;
+  for (uint32_t i0 = 0; i0 < n; i0 += NEXT_WG) {
+    const uint32_t i = i0 + threadIdx.x;
+    Seg sg{};
+    if (i < n) sg = list[i];
+    const uint32_t t = (sg.len + tile_len - 1) / tile_len, g = (t + GROUP_TILES - 1) / GROUP_TILES;
+    uint32_t tt, tg;
+    const uint32_t et = block_excl_sum<NW>(t, tmp, &tt), eg = block_excl_sum<NW>(g, tmp, &tg);
+    if (i < n) {
+      segs[i] = sg;
+      tile_prefix[i] = tiles + et;
+      group_prefix[i] = groups + eg;
+      seg_or[i] = 0;
+      seg_and[i] = ~0ull;
+    }
+    tiles += tt;
+    groups += tg;
+  }
+  if (n && threadIdx.x == 0) {
+    tile_prefix[n] = tiles;
+    group_prefix[n] = groups;
+  }
+}
+
 // A replayed build checks that the collection bases are those it was
 // captured for.
 __global__ void k_check_bases(const uint64_t *__restrict__ got, const uint64_t *__restrict__ want, uint32_t count,
@@ -1407,6 +1576,25 @@ __global__ __launch_bounds__(BLOCK) void k_emit_final(const Seg *__restrict__ se
     for (uint64_t j = t0 + threadIdx.x; j < t1; j += BLOCK)
       emit_row(j, cm, K[j], H[j], pos64, text, srank, bwt, start_row);
     if (!PERSIST) break;
+  }
+}
+
+// The same with a workgroup per group at a time, no tile prefixes: for small
+// builds, whose groups are short.
+__global__ __launch_bounds__(BLOCK) void k_emit_groups(const Seg *__restrict__ segs, const uint32_t *__restrict__ dev_nsegs,
+                                                       const uint64_t *__restrict__ keys0, const uint64_t *__restrict__ keys1,
+                                                       const uint32_t *__restrict__ hdl0, const uint32_t *__restrict__ hdl1,
+                                                       const TextRec *__restrict__ text, const uint32_t *__restrict__ srank,
+                                                       const CollMap *__restrict__ cmap, uint8_t *__restrict__ bwt,
+                                                       uint64_t *__restrict__ start_row) {
+  const uint32_t n = *dev_nsegs;
+  for (uint32_t s = blockIdx.x; s < n; s += gridDim.x) {
+    const Seg sg = segs[s];
+    const uint64_t *K = (sg.buf ? keys1 : keys0) + sg.start;
+    const uint32_t *H = (sg.buf ? hdl1 : hdl0) + sg.start;
+    const CollMap cm = cmap[sg.coll];
+    for (uint32_t j = threadIdx.x; j < sg.len; j += BLOCK)
+      emit_row((uint64_t)sg.start + j, cm, K[j], H[j], nullptr, text, srank, bwt, start_row);
   }
 }
 
