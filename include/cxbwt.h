@@ -392,7 +392,8 @@ typedef struct cxbwt_stats {
  *   chunk_items  suffixes per lane of the one-wave chunk kernel (3, 6 or 8):
  *                the largest run of small buckets finished in LDS is 64 x this
  * The output is the same for every choice; only speed differs.  Default
- * (8, 6).  CXBWT_EINVAL for other values.  cxbwt_get_tuning reads the
+ * (8, 6); a build on a thread that chose nothing takes (16, 8) where that
+ * is the faster.  CXBWT_EINVAL for other values.  cxbwt_get_tuning reads the
  * current choice (CXBWT_EINVAL on NULL).  The workspace size does not depend
  * on the choice.  The autotuner in the Python package times the choices on a
  * sample of a workload and sets the fastest.

@@ -71,10 +71,17 @@ struct Tuning {
   uint32_t tile_items;   // 6, 8 or 16 suffixes per 256 threads' thread in a level tile (16: 8 waves x 8)
   uint32_t chunk_items;  // 3, 6 or 8 suffixes per lane in a chunk
   uint32_t schedule = CXBWT_SCHEDULE_MSD;  // sort schedule of single-collection builds
+  bool chosen = false;   // by the caller (cxbwt_set_tuning, cxbwt_opts)
   uint32_t tile_len() const { return BLOCK * tile_items; }
   uint32_t chunk() const { return LOCAL_WG * chunk_items; }
 };
 thread_local Tuning g_tuning{8, 6};
+
+// Suffixes sorted at once from which a build whose instantiation nobody chose
+// takes 16 x 8 instead of 8 x 6 (8 x 6 and 16 x 8: 8 Mbases of 100-base reads
+// 0.576 and 0.550 ms, 8.75 of 100 to 250 bases 0.622 and 0.644, 16 Mbases 1.18
+// and 0.93, 200 Mbases in four ranges 13.9 and 13.0).
+constexpr uint64_t LARGE_SORT = 12000000;
 
 // tile_items 16 is the wide tile: 8 waves x 8 items (4096 suffixes); the
 // histogram kernels take it as two sub-tiles of BLOCK * MAX_TILE_ITEMS
@@ -157,7 +164,9 @@ Layout make_layout(uint64_t n_reads, uint64_t nb_text, uint32_t n_coll, uint64_t
   L.rank_blocks = take(4 * L.n_rank_blocks);
   L.start_row = take(8 * n_reads);
   // the read-start bitmap (one bit per base) lives here before level 1
+  // and a range's level 1 counts here per RANGE_TILE positions
   L.tile_hist_bytes = std::max<uint64_t>(4 * 256 * L.max_tiles, 4 * (nb_text / 32 + 4));
+  if (nb_text > nb) L.tile_hist_bytes = std::max<uint64_t>(L.tile_hist_bytes, 4 * 256 * ceil_div(nb_text, RANGE_TILE));
   L.tile_hist = take(L.tile_hist_bytes);
   L.gsum = take(4 * 256 * L.max_groups);
   L.segs = take(sizeof(Seg) * seg_slots);
@@ -703,6 +712,11 @@ void build_init(Build &b, const uint64_t *packed, const uint64_t *offsets, uint6
   b.Lo = make_layout(n, nb, ncoll, m_sort, wide);
   b.B = buffers_of(ws, b.Lo);
   b.tu = g_tuning;
+  // nobody chose: large sorts take the wide tile and the long chunk
+  if (!b.tu.chosen && b.Lo.sort_cap >= LARGE_SORT) {
+    b.tu.tile_items = 16;
+    b.tu.chunk_items = 8;
+  }
   b.rmax = maxlen / W + 1;
   b.tile_len = b.tu.tile_len();
   uint32_t *c = b.B.counters;
@@ -1661,6 +1675,7 @@ struct Range {
   uint64_t lo, hi, count, before;
   uint32_t common;
   uint64_t skip = 0;  // a piece of one class of identical suffixes: its first member in read order
+  bool piece = false;
 };
 
 // Ordering bits of the smallest and largest key with this prefix.
@@ -1740,6 +1755,7 @@ int plan_ranges(const Build &b, uint64_t m, std::vector<Range> &ranges, hipStrea
       for (uint64_t k = 0; k < c.count; k += m) {
         Range r{c.prefix, c.prefix, std::min<uint64_t>(m, c.count - k), before, 0};
         r.skip = k;
+        r.piece = true;
         ranges.push_back(r);
         before += r.count;
       }
@@ -1787,6 +1803,53 @@ int list_range(const Build &b, const Range &r, PhaseTimer &T, hipStream_t st) {
   return CXBWT_OK;
 }
 
+// Level 1 of range `r` as seg (of digit seg.d), and what it hands on; *fits
+// false, and nothing done, where the scratch is too small for the counts.
+int range_level1(const Build &b, const Range &r, const Seg &seg, bool *fits, LevelOut &o, PhaseTimer &T,
+                 hipStream_t st) {
+  const Buffers &B = b.B;
+  const Layout &Lo = b.Lo;
+  const uint64_t ntiles = ceil_div(b.nb, RANGE_TILE), ngroups = ceil_div(ntiles, GROUP_TILES);
+  *fits = 4 * 256 * ntiles <= Lo.tile_hist_bytes && ngroups <= Lo.max_groups && ntiles <= 0x7FFFFFFFull;
+  if (!*fits) return CXBWT_OK;
+  int rc;
+  const uint32_t tp[2] = {0, (uint32_t)ntiles}, gp[2] = {0, (uint32_t)ngroups};
+  CX_CHECK(hipMemcpyAsync(B.segs, &seg, sizeof(Seg), hipMemcpyHostToDevice, st));
+  CX_CHECK(hipMemcpyAsync(B.tile_prefix, tp, sizeof(tp), hipMemcpyHostToDevice, st));
+  CX_CHECK(hipMemcpyAsync(B.group_prefix, gp, sizeof(gp), hipMemcpyHostToDevice, st));
+  if ((rc = fill_u32(B.counters + C_NFINAL, 3, 0, st))) return rc;  // final, chunk and segment counts
+  const bool fast = (uint32_t)r.lo == 0 && (uint32_t)r.hi == ~7u && seg.d <= 3;
+  T.begin();
+  if (fast) k_range_hist<true><<<(unsigned)ntiles, BLOCK, 0, st>>>(B.text, b.nb, r.lo, r.hi, seg.d, B.tile_hist);
+  else k_range_hist<false><<<(unsigned)ntiles, BLOCK, 0, st>>>(B.text, b.nb, r.lo, r.hi, seg.d, B.tile_hist);
+  CX_LAUNCHED();
+  T.end(PH_GEN);
+  T.begin();
+  k_group_scan<false><<<(unsigned)ngroups, BLOCK, 0, st>>>(B.tile_prefix, B.group_prefix, 1, nullptr, B.tile_hist,
+                                                           B.gsum);
+  CX_LAUNCHED();
+  launch_level_scan(B, 1, (uint32_t)ngroups, b.Ls, 1, st);
+  CX_LAUNCHED();
+  T.end(PH_SCAN);
+  T.begin();
+#define CX_RANGE_SCATTER(FAST)                                                                                     \
+  k_range_scatter<FAST><<<(unsigned)ntiles, 64 * RANGE_NW, 0, st>>>(B.text, b.nb, r.lo, r.hi, seg.d, B.tile_hist, B.gsum, \
+                                                                    B.keys1, B.hdl1, B.pos64)
+  if (fast) CX_RANGE_SCATTER(true);
+  else CX_RANGE_SCATTER(false);
+#undef CX_RANGE_SCATTER
+  CX_LAUNCHED();
+  T.end(PH_SCATTER);
+  g_stats.levels++;
+  g_stats.host_levels++;
+  g_stats.big_segments++;
+  g_stats.level_suffixes += r.count;
+  g_stats.level_batches++;
+  if ((rc = read_level(B, o, T, st))) return rc;
+  return finish_level(B, Lo, b.tu, b.nb, b.rmax, b.maxlen, b.bwt, o.n_chunks, o.n_finals, o.final_tiles, o.final_len, T,
+                      st);
+}
+
 // One collection built in ranges of at most m suffixes: the bare
 // terminators and text records as for a whole build, the ranges planned
 // from prefix counts, then each range listed, sorted (levels and chunks) and
@@ -1827,12 +1890,21 @@ int run_range_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n,
     // the row map of this range, in the one collection slot (stream order:
     // after the previous range's kernels have read theirs)
     CX_CHECK(hipMemcpyAsync(b.B.cmap, &cm[i], sizeof(CollMap), hipMemcpyHostToDevice, st));
-    if ((rc = list_range(b, r, T, st))) return rc;
     const bool small = r.count <= (uint64_t)b.tu.chunk();
     // a range that fits a chunk: one unsplit chunk; else one segment whose
     // keys agree on their first `common` digits
     seg[i] = Seg{0, (uint32_t)r.count, 0, (uint8_t)std::min<uint32_t>(r.common, small ? 6 : 7), 0, 0,
                  (uint8_t)(small ? 1 : 0), 0};
+    if (!small && !r.piece) {
+      bool fits = false;
+      LevelOut o{};
+      if ((rc = range_level1(b, r, seg[i], &fits, o, T, st))) return rc;
+      if (fits) {
+        if ((rc = run_levels(b, o, o.n_big, T, st))) return rc;
+        continue;
+      }
+    }
+    if ((rc = list_range(b, r, T, st))) return rc;
     if (small) {
       CX_CHECK(hipMemcpyAsync(b.B.chunks, &seg[i], sizeof(Seg), hipMemcpyHostToDevice, st));
       if ((rc = finish_level(b.B, b.Lo, b.tu, nb, b.rmax, b.maxlen, bwt, 1, 0, 0, 0, T, st))) return rc;
@@ -2027,6 +2099,7 @@ bool job_choices(const cxbwt_opts *opts, Tuning &tu, int &timing) {
   tu.tile_items = opts->tile_items;
   tu.chunk_items = opts->chunk_items;
   tu.schedule = opts->schedule;
+  tu.chosen = true;
   timing = opts->timing ? 1 : 0;
   return true;
 }
@@ -2308,6 +2381,7 @@ int cxbwt_set_tuning(uint32_t tile_items, uint32_t chunk_items) {
   if (!tuning_ok(tile_items, chunk_items)) return CXBWT_EINVAL;
   g_tuning.tile_items = tile_items;
   g_tuning.chunk_items = chunk_items;
+  g_tuning.chosen = true;
   return CXBWT_OK;
 }
 

@@ -34,42 +34,6 @@
 namespace {
 
 // ---------------------------------------------------------------------------
-// windows of a text record, in 32-bit halves: a 64-bit shift by a register
-// costs two 32-bit ones, and on this device gives a wrong result now and then
-// when its amount sits in the last register the kernel is allocated
-// ---------------------------------------------------------------------------
-// {a, b} << n for n = 0, 2, .. 30, the high half
-__host__ __device__ __forceinline__ uint32_t funnel_left(uint32_t a, uint32_t b, uint32_t n) {
-  return n ? (a << n) | (b >> (32 - n)) : a;
-}
-struct Window {
-  uint32_t hi, lo;  // the bases from an offset of a record on, first highest (27 or more of the 32 are valid)
-};
-__host__ __device__ __forceinline__ Window window_at(const TextRec &t, uint32_t o) {
-  const uint32_t a = (uint32_t)(t.hi >> 32), b = (uint32_t)t.hi, c = (uint32_t)(t.lo >> 32);
-  return Window{funnel_left(a, b, 2 * o), funnel_left(b, c, 2 * o)};
-}
-// the first n (0..31) bases of a window
-__host__ __device__ __forceinline__ uint64_t first_bases(const Window &w, uint32_t n) {
-  const uint32_t hi = n >= 16 ? w.hi : w.hi & ~(~0u >> (2 * n));
-  const uint32_t lo = n > 16 ? w.lo & ~(~0u >> (2 * (n - 16))) : 0u;
-  return ((uint64_t)hi << 32) | lo;
-}
-// start bits of a record from offset o (0..16) on, 32 of them or up to its end
-__host__ __device__ __forceinline__ uint32_t starts_from(const TextRec &t, uint32_t o) {
-  const uint32_t lo = (uint32_t)t.lo, hi = (uint32_t)(t.lo >> 32) & 0x3FFu;
-  return o ? (lo >> o) | (hi << (32 - o)) : lo;
-}
-__host__ __device__ __forceinline__ uint32_t first_bit(uint32_t x) { return x ? (uint32_t)__builtin_ctz(x) : 64u; }
-// base at offset o (0..15) of a record, and the one before it
-__host__ __device__ __forceinline__ uint32_t base_in(const TextRec &t, uint32_t o) {
-  return ((uint32_t)(t.hi >> 32) >> (30 - 2 * o)) & 3u;
-}
-__host__ __device__ __forceinline__ uint32_t base_before(const TextRec &t, uint32_t o) {
-  return o ? ((uint32_t)(t.hi >> 32) >> (32 - 2 * o)) & 3u : (uint32_t)(t.lo >> 42) & 3u;
-}
-
-// ---------------------------------------------------------------------------
 // items: the bases before a position, and the key of a sample
 // ---------------------------------------------------------------------------
 // Preceding bases ("payload"): the nearest in bits 1..0, then the ones before

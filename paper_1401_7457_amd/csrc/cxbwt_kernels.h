@@ -737,8 +737,12 @@ __global__ __launch_bounds__(BLOCK) void k_level_hist(const Seg *__restrict__ se
   o = block_or(o, red);
   a = block_and(a, red);
   if (threadIdx.x == 0) {
-    atomicOr(&seg_or[s], (unsigned long long)(o & ~F::REST));
-    atomicAnd(&seg_and[s], (unsigned long long)(a | F::REST));
+    // (a segment of many tiles: few of them change its words, and a stale read
+    // costs no more than an atomic)
+    o &= ~F::REST;
+    a |= F::REST;
+    if ((seg_or[s] | o) != seg_or[s]) atomicOr(&seg_or[s], (unsigned long long)o);
+    if ((seg_and[s] & a) != seg_and[s]) atomicAnd(&seg_and[s], (unsigned long long)a);
   }
   tile_hist[(uint64_t)tile * 256 + threadIdx.x] = hist[threadIdx.x];
   if (!PERSIST) break;
@@ -2164,11 +2168,13 @@ __global__ __launch_bounds__(BLOCK) void k_prefix_hist(const TextRec *__restrict
   for (uint64_t w = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; w < nrec; w += (uint64_t)gridDim.x * BLOCK) {
     const TextRec t = text[w];
     const uint64_t p0 = 16 * w;
-    for (uint32_t o = 0; o < 16 && p0 + o < nb; ++o) {
-      const uint64_t p = p0 + o;
-      uint32_t prev3 = 4;
-      if (!((t.lo >> o) & 1u)) prev3 = o ? rec_base_at(t, o - 1) : (uint32_t)(t.lo >> 42) & 3u;
-      const uint64_t k = window_combine(t, nb, p, 0, prev3);
+    const uint32_t ends = starts_from(t, 1);
+#pragma unroll
+    for (uint32_t o = 0; o < 16; ++o) {
+      if (p0 + o >= nb) continue;
+      uint64_t k;
+      if (depth <= 3) k = (uint64_t)first_word(t, ends, o) << 32;  // the digits looked at are in the first 16 bases
+      else k = window_combine(t, nb, p0 + o, 0, 0);
       const uint64_t top = prefix_of(k, depth);
       uint32_t lo = 0, hi = np;  // first prefix >= top
       while (lo < hi) {
@@ -2215,6 +2221,132 @@ __global__ __launch_bounds__(BLOCK) void k_range_count(const TextRec *__restrict
   uint32_t total;
   block_excl_sum(c, tmp, &total);
   if (threadIdx.x == 0) tile_count[blockIdx.x] = total;
+}
+
+// Members of the range in record w, bit o for position 16 w + o.  FAST: the
+// range is one of the keys' first 16 bases (lo's low half zero, hi's ones).
+template <bool FAST>
+__device__ __forceinline__ uint32_t members_of(const TextRec *__restrict__ text, uint64_t nb, uint64_t w, uint64_t lo,
+                                               uint64_t hi) {
+  if (16 * w >= nb) return 0;
+  uint32_t in = 0;
+  if (FAST) {
+    const TextRec t = text[w];
+    const uint32_t ends = starts_from(t, 1), lo32 = (uint32_t)(lo >> 32), hi32 = (uint32_t)(hi >> 32);
+#pragma unroll
+    for (uint32_t o = 0; o < 16; ++o) {
+      const uint32_t x = first_word(t, ends, o);
+      in |= (x >= lo32 && x <= hi32 ? 1u : 0u) << o;
+    }
+    if (16 * w + 16 > nb) in &= (1u << (uint32_t)(nb - 16 * w)) - 1u;
+  } else {
+    uint64_t k[LIST_ITEMS];
+    in = record_keys_in_range(text, nb, w, lo, hi, k);
+  }
+  return in;
+}
+
+// Level 1 of a range (its members' digit d) straight from the text, as for a
+// whole build: counted per tile of RANGE_TILE positions, then listed per
+// tile, their keys made on full waves and scattered.  (Listed in position
+// order first, then split like any segment: 1.26 ms for 60M of 200 Mbases,
+// 0.15 + 0.38 so.)
+constexpr int RANGE_NW = 8, RANGE_TI = 8;
+constexpr uint32_t RANGE_RECS = 64u * RANGE_NW;
+constexpr uint32_t RANGE_TILE = 16u * RANGE_RECS;
+template <bool FAST>
+__global__ __launch_bounds__(BLOCK) void k_range_hist(const TextRec *__restrict__ text, uint64_t nb, uint64_t lo,
+                                                      uint64_t hi, int d, uint32_t *__restrict__ tile_hist) {
+  __shared__ uint32_t hist[256];
+  hist[threadIdx.x] = 0;
+  __syncthreads();
+  for (uint32_t h = 0; h < RANGE_RECS / BLOCK; ++h) {
+    const uint64_t w = (uint64_t)blockIdx.x * RANGE_RECS + h * BLOCK + threadIdx.x;
+    uint32_t in = members_of<FAST>(text, nb, w, lo, hi);
+    if (!in) continue;
+    const TextRec t = text[w];
+    if (FAST) {
+      const uint32_t ends = starts_from(t, 1);
+#pragma unroll
+      for (uint32_t o = 0; o < 16; ++o)
+        if ((in >> o) & 1u) atomicAdd(&hist[(first_word(t, ends, o) >> (24 - 8 * d)) & 0xFFu], 1u);
+    } else {
+      for (; in; in &= in - 1u)
+        atomicAdd(&hist[digit_of(window_combine(t, nb, 16 * w + (uint32_t)__builtin_ctz(in), 0, 0), d)], 1u);
+    }
+  }
+  __syncthreads();
+  tile_hist[(uint64_t)blockIdx.x * 256 + threadIdx.x] = hist[threadIdx.x];
+}
+
+template <bool FAST>
+__global__ __launch_bounds__(64 * RANGE_NW) void k_range_scatter(const TextRec *__restrict__ text, uint64_t nb,
+                                                                 uint64_t lo, uint64_t hi, int d,
+                                                                 const uint32_t *__restrict__ tile_hist,
+                                                                 const uint32_t *__restrict__ gsum,
+                                                                 uint64_t *__restrict__ Ko, uint32_t *__restrict__ Ho,
+                                                                 uint64_t *__restrict__ pos64) {
+  constexpr uint32_t CAP = 64 * RANGE_NW * RANGE_TI;  // members scattered at once
+  __shared__ ScatterSmem<RANGE_TI, RANGE_NW> S;
+  uint16_t *const list = reinterpret_cast<uint16_t *>(S.sh);  // read before the handles are staged
+  const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
+  const uint64_t w0 = (uint64_t)tile * RANGE_RECS;
+  uint32_t m = 0;
+  const uint32_t mine = members_of<FAST>(text, nb, w0 + threadIdx.x, lo, hi);
+  const uint32_t at0 = block_excl_sum<RANGE_NW>((uint32_t)__popc(mine), S.tmp, &m);
+  if (threadIdx.x < 256)
+    S.goff[threadIdx.x] = (uint64_t)gsum[(uint64_t)(tile / GROUP_TILES) * 256 + threadIdx.x] +
+                          tile_hist[(uint64_t)tile * 256 + threadIdx.x];
+  for (uint32_t q0 = 0; q0 < m; q0 += CAP) {
+    const uint32_t mm = min(m - q0, CAP);
+    uint32_t at = at0;
+    for (uint32_t in = mine; in; in &= in - 1u, ++at)
+      if (at - q0 < CAP) list[at - q0] = (uint16_t)(16 * threadIdx.x + (uint32_t)__builtin_ctz(in));
+    __syncthreads();
+    const uint32_t ni = (mm + 64 * RANGE_NW - 1) / (64 * RANGE_NW);  // slots a wave takes
+    const uint32_t first = (threadIdx.x >> 6) * 64 * ni + lane_id();
+    uint64_t kr[RANGE_TI];
+    uint32_t hr[RANGE_TI], dig[RANGE_TI], pos[RANGE_TI];
+#pragma unroll
+    for (int i = 0; i < RANGE_TI; ++i) {
+      kr[i] = 0;
+      hr[i] = 0;
+      dig[i] = NODIGIT;
+      const uint32_t li = first + i * 64;
+      if ((uint32_t)i >= ni || li >= mm) continue;
+      const uint32_t o16 = list[li];
+      const uint64_t p = 16 * w0 + o16;
+      kr[i] = first_key_from(text[p >> 4], nb, p);
+      hr[i] = pos64 ? o16 : (uint32_t)p;
+      dig[i] = digit_of(kr[i], d);
+    }
+    block_multisplit<RANGE_TI, RANGE_NW>(dig, pos, S.wcount, S.dstart, S.tmp);
+    __syncthreads();  // every wave has read its counters before the stage is written
+#pragma unroll
+    for (int i = 0; i < RANGE_TI; ++i) {
+      if (dig[i] != NODIGIT) {
+        S.sk[pos[i]] = kr[i];
+        S.sh[pos[i]] = hr[i];
+      }
+    }
+    __syncthreads();
+    for (uint32_t q = threadIdx.x; q < mm; q += 64 * RANGE_NW) {
+      const uint64_t k = S.sk[q];
+      const uint32_t dd = digit_of(k, d);
+      const uint64_t g = S.goff[dd] + (q - S.dstart[dd]);
+      Ko[g] = k;
+      // wide positions: the handle is the member's place, which is in position
+      // order among equal keys
+      if (pos64) pos64[g] = 16 * w0 + S.sh[q];
+      Ho[g] = pos64 ? (uint32_t)g : S.sh[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 256) {
+      const uint32_t next = threadIdx.x < 255 ? S.dstart[threadIdx.x + 1] : mm;
+      S.goff[threadIdx.x] += next - S.dstart[threadIdx.x];
+    }
+    __syncthreads();
+  }
 }
 
 // In place: exclusive prefix sums of n counts, per block of BLOCK *
