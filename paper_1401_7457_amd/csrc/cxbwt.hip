@@ -662,6 +662,7 @@ struct Build {
   std::vector<uint64_t> coll_reads, cbase;
   std::vector<CollMap> cm;
   std::vector<Seg> big, small;  // level-1 segments; collections that fit one chunk
+  bool planned = false;         // k_begin's plan of one collection is in place on the device
 };
 
 Buffers buffers_of(unsigned char *ws, const Layout &Lo) {
@@ -724,6 +725,7 @@ void build_init(Build &b, const uint64_t *packed, const uint64_t *offsets, uint6
                (uint32_t)b.Lo.cap_chunks, b.B.finals, c + C_NFINAL, (uint32_t)b.Lo.cap_finals, c + C_STATUS, b.rmax,
                b.B.stats, b.tu.chunk(), b.tile_len};
   b.coll_reads.assign(coll_reads, coll_reads + ncoll + 1);
+  b.planned = ncoll == 1;
 }
 
 // The level-1 plan of one collection, which its sizes give: one segment, or
@@ -1026,7 +1028,7 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
   uint32_t *counters = B.counters;
   const uint64_t nb = b.nb;
   int rc;
-  const bool planned = b.ncoll == 1;  // enqueue_prep has put the plan in place
+  const bool planned = b.planned;
   if (!planned) CX_CHECK(hipMemcpyAsync(B.cmap, src.cm, sizeof(CollMap) * b.ncoll, hipMemcpyHostToDevice, st));
   if (nb == 0) return CXBWT_OK;
 
@@ -1643,6 +1645,7 @@ int run_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n, uint6
         if ((rc = enqueue_body(b, small, 0, T, st))) return rc;
       }
       if ((rc = run_induced(b, &done, T, st))) return rc;
+      b.planned = false;  // its tiles have taken the plan's place
     }
     if (!done) {
       level1_stats(b);

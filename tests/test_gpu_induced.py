@@ -90,3 +90,20 @@ def test_induced_batch_of_uneven_collections():
     assert sum(c.n_bases for c in cols) >= SIZE * 0.9
     for i, (c, (b, t)) in enumerate(zip(cols, cxbwt.build_batch_host(cols))):
         assert oracle.check_bwt(b, t, c.text, c.offsets) == 0, f"collection {i}"
+
+
+@pytest.mark.parametrize("tuning", [(8, 3), (6, 6)])
+def test_sorted_whole_under_a_chosen_tuning(tuning):
+    # the sort that follows a declined induction has its own tiles
+    col = _long_runs(np.random.default_rng(5))
+    before = cxbwt.get_tuning()
+    try:
+        cxbwt.set_tuning(*tuning)
+        _say(f"long runs, tuning {tuning}: reads={col.n_reads} bases={col.n_bases}")
+        b, t = cxbwt.build_host(col.text, col.offsets)
+        st = cxbwt.last_stats()
+    finally:
+        cxbwt.set_tuning(*before)
+    assert st["chunk_suffixes"] > col.n_bases // 2  # sorted whole
+    rc = oracle.check_bwt(b, t, col.text, col.offsets)
+    assert rc == 0, f"invariant {rc} fails"
