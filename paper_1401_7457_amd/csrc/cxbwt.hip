@@ -539,8 +539,17 @@ int finish_level(const Buffers &B, const Layout &Lo, const Tuning &tu, uint64_t 
   if (n_chunks) {
     T.begin();
     if (B.sample) {
-      k_sample_chunk<8, 4><<<n_chunks, LOCAL_WG, 0, st>>>(B.chunks, B.keys0, B.keys1, B.hdl0, B.hdl1, B.text, maxlen,
-                                                          B.smp, B.counters + C_STATUS, B.stats);
+#define CX_CHUNK(LI, OCC, PAIR, ABOVE)                                                                             \
+  k_sample_chunk<LI, OCC, PAIR><<<n_chunks, LOCAL_WG, 0, st>>>(B.chunks, B.keys0, B.keys1, B.hdl0, B.hdl1, B.text, \
+                                                               maxlen, ABOVE, B.smp, B.counters + C_STATUS, B.stats)
+      if (maxlen >= PAIR_MIN_READ) {
+        CX_CHUNK(4, 6, true, 0);
+        CX_LAUNCHED();
+        CX_CHUNK(8, 4, true, PAIR_PACK);
+      } else {
+        CX_CHUNK(8, 4, false, 0);
+      }
+#undef CX_CHUNK
       CX_LAUNCHED();
     } else if ((rc = launch_local(B, tu, nb, rmax, bwt, n_chunks, nullptr, st))) {
       return rc;
@@ -723,7 +732,7 @@ void build_init(Build &b, const uint64_t *packed, const uint64_t *offsets, uint6
   uint32_t *c = b.B.counters;
   b.Ls = Lists{b.B.big_next, c + C_NBIG, (uint32_t)b.Lo.cap_big, b.B.chunks, (unsigned long long *)(c + C_NCHUNK),
                (uint32_t)b.Lo.cap_chunks, b.B.finals, c + C_NFINAL, (uint32_t)b.Lo.cap_finals, c + C_STATUS, b.rmax,
-               b.B.stats, b.tu.chunk(), b.tile_len};
+               b.B.stats, b.tu.chunk(), b.tu.chunk(), b.tile_len};
   b.coll_reads.assign(coll_reads, coll_reads + ncoll + 1);
   b.planned = ncoll == 1;
 }
@@ -1505,7 +1514,8 @@ int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
   s.tile_len = s.tu.tile_len();
   s.rmax = b.maxlen / SampleKey::FULL + 1;
   s.Ls.rmax = s.rmax;
-  s.Ls.chunk = s.tu.chunk();
+  s.Ls.chunk = SAMPLE_CHUNK;
+  s.Ls.pack = b.maxlen >= PAIR_MIN_READ ? PAIR_PACK : SAMPLE_CHUNK;
   s.Ls.tile_len = s.tile_len;
   std::vector<Seg> seg(nc);
   g_stats.chunk_suffixes = M;

@@ -564,11 +564,29 @@ __global__ __launch_bounds__(BLOCK) void k_sample_final(const Seg *__restrict__ 
 // does, with keys of its own: bits 63..14 up to 25 bases, 13..9 the clamped
 // length, 8..0 the sample's place in the chunk as loaded.  The place is the
 // stable order among equal ordering bits, so keys are distinct and a rank is
-// one count of smaller keys; and it finds the sample's global key again, which
-// holds the payload, when the chunk is done.
+// one count of smaller keys; only keys move, the handle and what else is
+// known of a sample stay at its place.  A tied sample loads a record for a
+// window of 25 bases.  PAIR: it loads the record after it too, which is in the
+// same request three times of four, for a window of 18 more that waits at its
+// place, while the handles, read once in two windows now, are not held.
+//
+// What bounds it is latency and requests: half of the issue slots are empty,
+// and the waves of a CU are as many as its LDS holds (17 or 21 bytes a
+// sample).  With PAIR, buckets are packed into chunks of at most 256, 28
+// waves a CU, and only one above that takes a chunk of up to 512 (15 waves)
+// before it is worth a level.
+//
+// PAIR is for reads above 160 bases, whose ties pass more windows: 200 Mbases
+// of 400 bases 8.8 -> 8.1 ms a build, 1.2 Gbases of 250 bases 41.8 -> 37.3.
+// Reads of 75 to 150 bases lose 1%; of 100 bases, 400 Mbases gain 1.6% and 2
+// Gbases with repeats lose 3%.  (Text lines of 64 bytes, three windows each:
+// equal at 200 Mbases, 3% slower at 2 G.  Chunks of 256 alone, without those
+// of 512: 2 Gbases 54 -> 66 ms.)
 // ---------------------------------------------------------------------------
+constexpr uint32_t SAMPLE_CHUNK = 512, PAIR_PACK = 256;
+constexpr uint32_t PAIR_MIN_READ = 161;
 constexpr uint64_t PLACE = 511ull;
-constexpr uint32_t CHUNK_WINDOW = 25;
+constexpr uint32_t WINDOW_0 = 25, WINDOW_1 = 18;  // of a pair of records: 59 bases and 58 starts, less an offset
 
 __device__ __forceinline__ uint32_t place_digit(uint64_t k, int j) {
   return j < 5 ? (uint32_t)(k >> (56 - 8 * j)) & 0xFFu : j == 5 ? (uint32_t)(k >> 20) & 0xFu : (uint32_t)(k >> 9) & 31u;
@@ -577,13 +595,85 @@ __device__ __forceinline__ uint64_t place_mask(int j) {
   return j < 5 ? 0xFFull << (56 - 8 * j) : j == 5 ? 0xFull << 20 : 31ull << 9;
 }
 
-struct PlaceDigit {
-  static __device__ __forceinline__ uint32_t digit(uint64_t k, int j) { return place_digit(k, j); }
+// The windows of q (offset o in its record t; u the record after it): bases
+// and clamped length as in a chunk key, place zero.
+__device__ __forceinline__ void pair_windows(const TextRec &t, const TextRec &u, uint32_t o, uint64_t &w0, uint64_t &w1) {
+  const uint32_t near = first_bit(starts_from(t, o)), far = 16u + first_bit(starts_from(u, o));
+  const uint32_t left = near < 16 ? near : far;  // to the read's end
+  const uint32_t n0 = min(left, WINDOW_0), n1 = min(left - n0, WINDOW_1);
+  w0 = first_bases(window_at(t, o), n0) | ((uint64_t)n0 << 9);
+  const uint32_t r = o + WINDOW_0 - 16;  // in u
+  const uint32_t a = (uint32_t)(u.hi >> 32), b = (uint32_t)u.hi, c = (uint32_t)(u.lo >> 32);
+  const uint32_t x = r < 16 ? a : b, y = r < 16 ? b : c, z = r < 16 ? c : 0u;
+  w1 = first_bases(Window{funnel_left(x, y, 2 * (r & 15u)), funnel_left(y, z, 2 * (r & 15u))}, n1) | ((uint64_t)n1 << 9);
+}
+
+template <int LI, bool PAIR>
+struct SampleSmem {
+  static constexpr int CHUNK = LOCAL_WG * LI;
+  uint64_t K[CHUNK];     // key of each position
+  uint64_t W[PAIR ? CHUNK : 1];  // by place: the window after the current one
+  uint32_t H[PAIR ? 1 : CHUNK];  // by place: handle
+  union {
+    struct {  // as in LocalSmem
+      uint16_t live[CHUNK];
+      uint16_t gr[CHUNK];
+      uint16_t hp[CHUNK / 2 + 1];
+    };
+    struct {
+      uint16_t cnt[256];
+      uint16_t dstart[256];
+    };
+  };
+  uint32_t headw[CHUNK / 32];
 };
+template <int LI, bool PAIR>
+__device__ __forceinline__ bool sample_head(const SampleSmem<LI, PAIR> &S, uint32_t j) {
+  return (S.headw[j >> 5] >> (j & 31u)) & 1u;
+}
+
+// wave_split on keys alone.
+template <int LI, bool PAIR>
+__device__ __forceinline__ void split_places(SampleSmem<LI, PAIR> &S, uint32_t m, int sel, uint32_t lane, uint64_t lt) {
+  for (uint32_t x = lane; x < 256; x += LOCAL_WG) S.cnt[x] = 0;
+  __syncthreads();
+  uint64_t kr[LI];
+  uint32_t dig[LI], pos[LI];
+#pragma unroll
+  for (int i = 0; i < LI; ++i) {
+    const uint32_t j = i * LOCAL_WG + lane;
+    const bool valid = j < m;
+    dig[i] = NODIGIT;
+    if (valid) {
+      kr[i] = S.K[j];
+      dig[i] = place_digit(kr[i], sel);
+    }
+    if (i * LOCAL_WG >= (int)m) continue;
+    const uint64_t peers = wave_match8(dig[i], __ballot(valid));
+    if (valid) {
+      const uint32_t before = S.cnt[dig[i]];
+      pos[i] = before + (uint32_t)__popcll(peers & lt);
+      if ((peers & lt) == 0) S.cnt[dig[i]] = before + (uint32_t)__popcll(peers);
+    }
+    __syncthreads();
+  }
+  const uint32_t c0 = S.cnt[4 * lane], c1 = S.cnt[4 * lane + 1], c2 = S.cnt[4 * lane + 2], c3 = S.cnt[4 * lane + 3];
+  const uint32_t tot = c0 + c1 + c2 + c3;
+  const uint32_t ex = wave_incl_sum(tot) - tot;
+  S.dstart[4 * lane] = ex;
+  S.dstart[4 * lane + 1] = ex + c0;
+  S.dstart[4 * lane + 2] = ex + c0 + c1;
+  S.dstart[4 * lane + 3] = ex + c0 + c1 + c2;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < LI; ++i)
+    if (dig[i] != NODIGIT) S.K[S.dstart[dig[i]] + pos[i]] = kr[i];
+  __syncthreads();
+}
 
 // The bitonic network of bitonic_group on keys that are distinct.
-template <int LI>
-__device__ __forceinline__ void bitonic_places(LocalSmem<LI> &S, uint32_t a, uint32_t m, uint32_t lane) {
+template <int LI, bool PAIR>
+__device__ __forceinline__ void bitonic_places(SampleSmem<LI, PAIR> &S, uint32_t a, uint32_t m, uint32_t lane) {
   uint32_t P = 2;
   while (P < m) P <<= 1;
   for (uint32_t k = 2; k <= P; k <<= 1) {
@@ -601,11 +691,8 @@ __device__ __forceinline__ void bitonic_places(LocalSmem<LI> &S, uint32_t a, uin
         if (l < m) {
           const uint64_t ki = S.K[a + i], kl = S.K[a + l];
           if (ki > kl) {
-            const uint32_t hi = S.H[a + i], hl = S.H[a + l];
             S.K[a + i] = kl;
             S.K[a + l] = ki;
-            S.H[a + i] = hl;
-            S.H[a + l] = hi;
           }
         }
       }
@@ -614,8 +701,8 @@ __device__ __forceinline__ void bitonic_places(LocalSmem<LI> &S, uint32_t a, uin
   }
 }
 
-template <int LI>
-__device__ __forceinline__ void sort_big_places(LocalSmem<LI> &S, uint32_t ngroups, uint32_t lane) {
+template <int LI, bool PAIR>
+__device__ __forceinline__ void sort_big_places(SampleSmem<LI, PAIR> &S, uint32_t ngroups, uint32_t lane) {
   for (uint32_t g0 = 0; g0 < ngroups; g0 += LOCAL_WG) {
     const uint32_t g = g0 + lane;
     const bool big = g < ngroups && (uint32_t)S.hp[g + 1] - S.hp[g] > BIG_GROUP;
@@ -630,8 +717,7 @@ __device__ __forceinline__ void sort_big_places(LocalSmem<LI> &S, uint32_t ngrou
 }
 
 // #{t in [a, e) : k_t < v} by the keys' low words (T = uint32_t) or whole, four
-// reads a step.  (The low words are read as parts of the 64-bit keys: read
-// through a pointer of another type, they need not follow the keys' writes.)
+// reads a step.
 template <typename T>
 __device__ __forceinline__ uint32_t count_smaller(const uint64_t *k, uint32_t a, uint32_t e, T v) {
   uint32_t c = 0;
@@ -643,20 +729,22 @@ __device__ __forceinline__ uint32_t count_smaller(const uint64_t *k, uint32_t a,
   return c;
 }
 
-template <int LI, int OCC>
+template <int LI, int OCC, bool PAIR>
 __global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
     const Seg *__restrict__ chunks, const uint64_t *__restrict__ keys0, const uint64_t *__restrict__ keys1,
     const uint32_t *__restrict__ hdl0, const uint32_t *__restrict__ hdl1, const TextRec *__restrict__ text,
-    uint32_t maxlen, SampleOut out, uint32_t *status, unsigned long long *fetches) {
+    uint32_t maxlen, uint32_t above, SampleOut out, uint32_t *status, unsigned long long *fetches) {
   static_assert(LI * LOCAL_WG <= 512, "a place in a chunk is 9 bits");
-  __shared__ LocalSmem<LI> S;
+  __shared__ SampleSmem<LI, PAIR> S;
   const uint32_t lane = threadIdx.x;
   const uint64_t le = lanemask_lt() | (1ull << lane);
   uint32_t nfetch = 0;
   const Seg ch = chunks[blockIdx.x];
   const uint32_t m = ch.len;
+  if (m <= above || m > LI * LOCAL_WG) return;  // the other kernel's
   const uint64_t *Kg = (ch.buf ? keys1 : keys0) + ch.start;
   const uint32_t *Hg = (ch.buf ? hdl1 : hdl0) + ch.start;
+  auto handle = [&](uint32_t place) { return PAIR ? Hg[place] : S.H[PAIR ? 0 : place]; };
   {
     uint64_t lk[LI];
     uint32_t lh[LI];
@@ -664,14 +752,14 @@ __global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
     for (int i = 0; i < LI; ++i) {
       const uint32_t j = i * LOCAL_WG + lane;
       lk[i] = Kg[j < m ? j : m - 1];
-      lh[i] = Hg[j < m ? j : m - 1];
+      if (!PAIR) lh[i] = Hg[j < m ? j : m - 1];
     }
 #pragma unroll
     for (int i = 0; i < LI; ++i) {
       const uint32_t j = i * LOCAL_WG + lane;
       if (j < m) {
         S.K[j] = (lk[i] & (~0ull << 20)) | ((uint64_t)SampleKey::clamp(lk[i]) << 9) | j;
-        S.H[j] = lh[i];
+        if (!PAIR) S.H[PAIR ? 0 : j] = lh[i];
       }
     }
   }
@@ -682,8 +770,8 @@ __global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
   const bool two = d0 < SampleKey::LAST;
   if (two) {
     const bool one_bucket = !ch.unsplit && place_digit(S.K[0], d0) == place_digit(S.K[m - 1], d0);
-    wave_split<PlaceDigit>(S, m, d0 + 1, lane, le & ~(1ull << lane));
-    if (!one_bucket) wave_split<PlaceDigit>(S, m, d0, lane, le & ~(1ull << lane));
+    split_places(S, m, d0 + 1, lane, le & ~(1ull << lane));
+    if (!one_bucket) split_places(S, m, d0, lane, le & ~(1ull << lane));
   }
   const uint64_t hmask = two ? (place_mask(d0) | place_mask(d0 + 1)) : place_mask(d0);
   uint32_t n = 0, ngroups = 0;
@@ -723,6 +811,7 @@ __global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
   __syncthreads();
   uint32_t depth = SampleKey::FULL * ((uint32_t)ch.r + 1);  // bases compared once the current window is sorted
   uint32_t full = SampleKey::FULL;
+  bool held = false;  // the next window has come with the current one
   bool fetch_round = false;
   for (;;) {
     if (!fetch_round) {
@@ -740,12 +829,12 @@ __global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
         if (x < n) {
           pos = S.live[x];
           const uint64_t kp = S.K[pos];
-          hd = head_at(S, pos);
+          hd = sample_head(S, pos);
           if (!hd) fresh = hd = ((kp ^ S.K[pos - 1]) & ~PLACE) != 0;
           bool next_hd = true;
           if (x + 1 < n) {
             const uint32_t p1 = S.live[x + 1];
-            next_hd = head_at(S, p1);
+            next_hd = sample_head(S, p1);
             if (!next_hd) next_hd = ((S.K[p1] ^ kp) & ~PLACE) != 0;
           }
           keep = !(hd && next_hd) && ((uint32_t)(kp >> 9) & 31u) == full;
@@ -772,33 +861,51 @@ __global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
         if (lane == 0) atomicOr(status, ST_WINDOW_BOUND);
         break;
       }
-      // the next window of every live sample (all of them hold `depth`
-      // bases, so the window starts inside the read or at its end)
-      for (uint32_t x0 = 0; x0 < n; x0 += FETCH_BATCH * LOCAL_WG) {
-        TextRec tr[FETCH_BATCH];
-        uint32_t tp[FETCH_BATCH];
-        uint64_t q[FETCH_BATCH];
+      // the next window of every live sample: all of them hold `depth` bases,
+      // so it starts inside the read or at its end, and all have loaded the
+      // same windows
+      if (!PAIR || !held) {
+        for (uint32_t x0 = 0; x0 < n; x0 += FETCH_BATCH * LOCAL_WG) {
+          TextRec t[FETCH_BATCH], u[FETCH_BATCH];
+          uint32_t tp[FETCH_BATCH], at[FETCH_BATCH], o[FETCH_BATCH];
 #pragma unroll
-        for (int i = 0; i < FETCH_BATCH; ++i) {
-          const uint32_t x = x0 + i * LOCAL_WG + lane;
-          tp[i] = S.live[x < n ? x : 0];
-          q[i] = (uint64_t)S.H[tp[i]] + depth;
-        }
+          for (int i = 0; i < FETCH_BATCH; ++i) {
+            const uint32_t x = x0 + i * LOCAL_WG + lane;
+            tp[i] = S.live[x < n ? x : 0];
+            at[i] = (uint32_t)(S.K[tp[i]] & PLACE);
+            const uint64_t q = (uint64_t)handle(at[i]) + depth;
+            o[i] = (uint32_t)(q & 15);
+            t[i] = text[q >> 4];
+            if (PAIR) u[i] = text[(q >> 4) + 1];
+          }
 #pragma unroll
-        for (int i = 0; i < FETCH_BATCH; ++i) tr[i] = text[q[i] >> 4];
-#pragma unroll
-        for (int i = 0; i < FETCH_BATCH; ++i) {
-          const uint32_t x = x0 + i * LOCAL_WG + lane;
-          if (x < n) {
-            uint32_t cl;
-            const uint64_t w = later_window(tr[i], q[i], CHUNK_WINDOW, cl);
-            S.K[tp[i]] = w | ((uint64_t)cl << 9) | (S.K[tp[i]] & PLACE);
-            ++nfetch;
+          for (int i = 0; i < FETCH_BATCH; ++i) {
+            const uint32_t x = x0 + i * LOCAL_WG + lane;
+            if (x < n) {
+              if constexpr (PAIR) {
+                uint64_t w0, w1;
+                pair_windows(t[i], u[i], o[i], w0, w1);
+                S.K[tp[i]] = w0 | at[i];
+                S.W[at[i]] = w1;
+              } else {
+                const uint32_t n0 = min(first_bit(starts_from(t[i], o[i])), WINDOW_0);
+                S.K[tp[i]] = first_bases(window_at(t[i], o[i]), n0) | ((uint64_t)n0 << 9) | at[i];
+              }
+            }
           }
         }
+        if (lane == 0) nfetch += n;
+        full = WINDOW_0;
+      } else {
+        for (uint32_t x = lane; x < n; x += LOCAL_WG) {
+          const uint32_t j = S.live[x];
+          const uint32_t at = (uint32_t)(S.K[j] & PLACE);
+          S.K[j] = S.W[PAIR ? at : 0] | at;
+        }
+        full = WINDOW_1;
       }
-      depth += CHUNK_WINDOW;
-      full = CHUNK_WINDOW;
+      held = !held;
+      depth += full;
       __syncthreads();
     }
     // rank inside each live group (a run of positions): every rank is taken
@@ -824,14 +931,12 @@ __global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
     __syncthreads();
     {
       uint64_t sk[LI];
-      uint32_t sh[LI], sd[LI];
+      uint32_t sd[LI];
 #pragma unroll
       for (int i = 0; i < LI; ++i) {
         const uint32_t x = i * LOCAL_WG + lane;
         if (x < n) {
-          const uint32_t j = S.live[x];
-          sk[i] = S.K[j];
-          sh[i] = S.H[j];
+          sk[i] = S.K[S.live[x]];
           sd[i] = S.gr[x];
         }
       }
@@ -839,10 +944,7 @@ __global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
 #pragma unroll
       for (int i = 0; i < LI; ++i) {
         const uint32_t x = i * LOCAL_WG + lane;
-        if (x < n) {
-          S.K[sd[i]] = sk[i];
-          S.H[sd[i]] = sh[i];
-        }
+        if (x < n) S.K[sd[i]] = sk[i];
       }
     }
     __syncthreads();
@@ -851,23 +953,25 @@ __global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
   }
   {
     uint64_t g[LI];
+    uint32_t hh[LI];
 #pragma unroll
     for (int i = 0; i < LI; ++i) {
       const uint32_t j = i * LOCAL_WG + lane;
-      g[i] = Kg[j < m ? (uint32_t)(S.K[j] & PLACE) : 0u];
+      const uint32_t at = j < m ? (uint32_t)(S.K[j] & PLACE) : 0u;
+      g[i] = Kg[at];
+      hh[i] = handle(at);
     }
 #pragma unroll
     for (int i = 0; i < LI; ++i) {
       const uint32_t j = i * LOCAL_WG + lane;
       if (j >= m) continue;
-      const uint32_t h = S.H[j];
+      const uint32_t h = hh[i];
       // a key of a later window does not hold the first base
       const uint32_t first = ch.r ? base_in(text[h >> 4], h & 15u) : (uint32_t)(g[i] >> 62);
       put_sample(out, (uint64_t)ch.start + j, g[i], first, h, text);
     }
   }
-  nfetch = wave_incl_sum(nfetch);
-  if (lane == 63 && nfetch) atomicAdd(stat_slot(fetches), (unsigned long long)nfetch);
+  if (lane == 0 && nfetch) atomicAdd(stat_slot(fetches), (unsigned long long)nfetch);
 }
 
 // ---------------------------------------------------------------------------

@@ -112,6 +112,7 @@ struct Lists {
   uint32_t rmax;
   unsigned long long *stats;  // the statistics block (K_* kinds)
   uint32_t chunk;  // largest run finished by one wave (the selected chunk size)
+  uint32_t pack;   // several buckets make one chunk up to this size
   uint32_t tile_len;  // suffixes per level tile
 };
 
@@ -1021,10 +1022,10 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
       BIG[i] = __ballot(cv[i] > C);
     }
     // chunks: a chunk starts at a non-empty small bucket and takes the
-    // following buckets while its size stays within C and no big bucket
+    // following buckets while its size stays within L.pack and no big bucket
     // intervenes.  Every lane first finds, for its four buckets b, where a
     // chunk starting at b would end (e: the first big bucket after b, or the
-    // first bucket that would take the size above C, by binary search on the
+    // first bucket that would take it above L.pack, by binary search on the
     // bucket starts) and where the next chunk would start (the first
     // non-empty small bucket at or after e); the walk over the chunk starts
     // is then one LDS read per chunk.
@@ -1048,12 +1049,12 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
       const uint32_t b = (uint32_t)i * 64 + l;
       const uint32_t sb = bv[i];
       // largest x >= b whose prefix bv[x] + cv[x] = wbv[x + 1] stays within
-      // sb + C (monotone in x); differences, so sb + C cannot wrap
+      // sb + L.pack (monotone in x); differences, so the sum cannot wrap
       uint32_t x = b;
 #pragma unroll
       for (uint32_t step = 128; step > 0; step >>= 1) {
         const uint32_t y = x + step;
-        if (y < 256 && wbv[cw][y + 1] - sb <= C) x = y;
+        if (y < 256 && wbv[cw][y + 1] - sb <= L.pack) x = y;
       }
       const uint64_t mb = BIG[i] & above;
       const uint32_t nbig = mb ? (uint32_t)i * 64 + (uint32_t)__builtin_ctzll(mb) : big_after[i];

@@ -107,3 +107,16 @@ def test_sorted_whole_under_a_chosen_tuning(tuning):
     assert st["chunk_suffixes"] > col.n_bases // 2  # sorted whole
     rc = oracle.check_bwt(b, t, col.text, col.offsets)
     assert rc == 0, f"invariant {rc} fails"
+
+
+@pytest.mark.parametrize("lens", [[160], [161], [22, 47, 64, 65, 66, 108, 161, 151], [300]])
+def test_windows_of_long_reads(lens):
+    # ties that last to the reads' ends, which fall on and beside the ends of
+    # the windows (22, then 25 and 18 in turn) of the reads that take two at once
+    rng = np.random.default_rng(lens[0] + len(lens))
+    n = int(SIZE // np.mean(lens))
+    col = datagen.sample_reads(rng, datagen.random_genome(rng, 40_000), n, rng.choice(lens, size=n), 0.001)
+    _say(f"lengths {lens}: reads={col.n_reads} bases={col.n_bases}")
+    b, t = cxbwt.build_host(col.text, col.offsets)
+    rc = oracle.check_bwt(b, t, col.text, col.offsets)
+    assert rc == 0, f"invariant {rc} fails"
