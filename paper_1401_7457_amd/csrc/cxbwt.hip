@@ -417,12 +417,15 @@ void launch_level_scan(const Buffers &B, uint32_t ns, uint32_t ngroups, const Li
 // scan-group totals area as scratch.  With dev_n the count is on the device
 // and n is only its bound.
 int prefix_list(const Buffers &B, const Seg *list, uint32_t n, uint32_t tile_len, Seg *copy, uint32_t *tprefix,
-                uint32_t *gprefix, hipStream_t st, const uint32_t *dev_n = nullptr) {
+                uint32_t *gprefix, hipStream_t st, const uint32_t *dev_n = nullptr, bool begin = false) {
   if (!n) return CXBWT_OK;
   const unsigned nwg = (unsigned)ceil_div(n, SEGP_WG);
-  k_seg_count<<<nwg, BLOCK, 0, st>>>(list, n, dev_n, tile_len, B.gsum);
-  CX_LAUNCHED();
-  k_seg_scan<<<nwg, BLOCK, 0, st>>>(list, n, dev_n, tile_len, B.gsum, copy, tprefix, gprefix);
+  if (nwg > 1) {
+    k_seg_count<<<nwg, BLOCK, 0, st>>>(list, n, dev_n, tile_len, B.gsum);
+    CX_LAUNCHED();
+  }
+  k_seg_scan<<<nwg, BLOCK, 0, st>>>(list, n, dev_n, tile_len, B.gsum, copy, tprefix, gprefix,
+                                    begin ? B.counters : nullptr, B.seg_or, B.seg_and);
   CX_LAUNCHED();
   return CXBWT_OK;
 }
@@ -434,15 +437,8 @@ struct LevelOut {
   uint64_t next_len, next_regather, next_maxr, next_tiles, next_groups, final_len, final_tiles;
 };
 
-// Fold the level statistics, read the counters back (the one wait of a
-// level batch).
-int read_level(const Buffers &B, LevelOut &o, PhaseTimer &T, hipStream_t st) {
-  uint32_t hc[C_COUNT];
-  k_level_fold<<<1, 64, 0, st>>>(B.stats, (unsigned long long *)(B.counters + C_FOLD), nullptr);
-  CX_LAUNCHED();
-  CX_CHECK(hipMemcpyAsync(hc, B.counters, sizeof(hc), hipMemcpyDeviceToHost, st));
-  CX_CHECK(hipStreamSynchronize(st));
-  T.collect();
+LevelOut level_out(const uint32_t *hc) {
+  LevelOut o{};
   uint64_t f[K_LEVEL_KINDS];
   memcpy(f, hc + C_FOLD, sizeof(f));
   o.status = hc[C_STATUS];
@@ -456,8 +452,88 @@ int read_level(const Buffers &B, LevelOut &o, PhaseTimer &T, hipStream_t st) {
   o.next_groups = f[K_NEXT_GROUPS - K_LEVEL_FIRST];
   o.final_len = f[K_FINAL_LEN - K_LEVEL_FIRST];
   o.final_tiles = f[K_FINAL_TILES - K_LEVEL_FIRST];
+  return o;
+}
+
+// Fold the level statistics, read the counters back and wait for everything.
+int read_level(const Buffers &B, LevelOut &o, PhaseTimer &T, hipStream_t st) {
+  uint32_t hc[C_COUNT];
+  k_level_fold<<<1, 64, 0, st>>>(B.stats, B.counters, nullptr, nullptr);
+  CX_LAUNCHED();
+  CX_CHECK(hipMemcpyAsync(hc, B.counters, sizeof(hc), hipMemcpyDeviceToHost, st));
+  CX_CHECK(hipStreamSynchronize(st));
+  T.collect();
+  o = level_out(hc);
   return o.status ? CXBWT_EDEVICE : CXBWT_OK;
 }
+
+// Counters blocks in host memory that the device writes: one a build while
+// its levels run, kept for the builds that follow (at most 16 of them).
+struct HostBlocks {
+  std::mutex m;
+  std::vector<uint32_t *> idle;
+  uint32_t *take() {
+    {
+      std::lock_guard<std::mutex> g(m);
+      if (!idle.empty()) {
+        uint32_t *p = idle.back();
+        idle.pop_back();
+        return p;
+      }
+    }
+    uint32_t *p = nullptr;
+    if (hipHostMalloc((void **)&p, 4 * C_COUNT, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    return p;
+  }
+  void give(uint32_t *p) {
+    {
+      std::lock_guard<std::mutex> g(m);
+      if (idle.size() < 16) {
+        idle.push_back(p);
+        return;
+      }
+    }
+    (void)hipHostFree(p);
+  }
+};
+HostBlocks g_host_blocks;
+
+// A level's counters without a wait for what was enqueued after it: post()
+// behind the level's kernels, wait() when they are needed.
+struct LevelWait {
+  uint32_t *block = nullptr;
+  hipEvent_t ev = nullptr;
+  bool posted = false;
+  bool open() {
+    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      ev = nullptr;
+      return false;
+    }
+    return (block = g_host_blocks.take()) != nullptr;
+  }
+  int post(const Buffers &B, hipStream_t st) {
+    k_level_fold<<<1, 64, 0, st>>>(B.stats, B.counters, nullptr, block);
+    CX_LAUNCHED();
+    posted = true;
+    CX_CHECK(hipEventRecord(ev, st));
+    return CXBWT_OK;
+  }
+  int wait(LevelOut &o) {
+    CX_CHECK(hipEventSynchronize(ev));
+    posted = false;
+    o = level_out(block);
+    return o.status ? CXBWT_EDEVICE : CXBWT_OK;
+  }
+  ~LevelWait() {
+    // (after an error the device may still write the block: it stays out)
+    if (block && !posted) g_host_blocks.give(block);
+    if (ev) (void)hipEventDestroy(ev);
+  }
+};
 
 // Work counts of one level as an eager build saw them (level 1 at index 0).
 // A captured build sizes its launches from them, so that each workgroup
@@ -648,7 +724,6 @@ int run_level_batch(const Buffers &B, const Layout &Lo, const Tuning &tu, const 
   if ((rc = fill_u64((uint64_t *)B.seg_or, nsg, 0, st))) return rc;
   if ((rc = fill_u64((uint64_t *)B.seg_and, nsg, ~0ull, st))) return rc;
   if ((rc = fill_u32(B.counters + C_NFINAL, 2, 0, st))) return rc;  // final and chunk counts
-  T.begin();
   if ((rc = launch_level_kernels(B, tu, Ls, nb, nsg, ntiles, ngroups, nullptr, T, st))) return rc;
   g_stats.level_batches++;
   if ((rc = read_level(B, o, T, st))) return rc;
@@ -903,20 +978,62 @@ int finish_finals_dev(const Build &b, hipStream_t st, unsigned emit_grid = PG_EM
   return CXBWT_OK;
 }
 
-// Levels 2.. on the host's schedule: every segment of a level is split by
-// one digit.  A level that fits the per-segment and per-tile scratch runs
+// What a level left in the lists for chunks and final groups, still to be
+// finished.
+struct LevelRest {
+  LevelOut o{};
+  int half = 0;  // of the lists; the other is free
+  bool open = false;
+};
+int finish_rest(const Build &b, LevelRest &rest, PhaseTimer &T, hipStream_t st) {
+  if (!rest.open) return CXBWT_OK;
+  rest.open = false;
+  Buffers B = b.B;
+  if (rest.half) {
+    B.chunks += b.Lo.cap_chunks / 2;
+    B.finals += b.Lo.cap_finals / 2;
+  }
+  const LevelOut &o = rest.o;
+  return finish_level(B, b.Lo, b.tu, b.nb, b.rmax, b.maxlen, b.bwt, o.n_chunks, o.n_finals, o.final_tiles, o.final_len, T,
+                      st);
+}
+
+// Levels 2.. on the host's schedule, after a level 1 (or a range's list, or
+// what the device left) that handed on acc: every segment of a level is split
+// by one digit.  A level that fits the per-segment and per-tile scratch runs
 // as one batch whose segment list is prepared on the device; a larger one
-// is cut into batches on the host.  acc is what the previous level handed
-// on, nbig its segment count.
-int run_levels(const Build &b, LevelOut acc, uint32_t nbig, PhaseTimer &T, hipStream_t st) {
+// is cut into batches on the host.
+//
+// The chunks and final groups of a level (of level 1 too: `first`) are
+// launched behind the next level's kernels, so that the host reads that
+// level's counts and plans the one after while they run, and the device does
+// not wait for it (with the segment list's kernels, six of which became one or
+// two: 20 Mbases at 2000x, 17 levels, 5.65 -> 5.07 ms; 200 Mbases in four
+// ranges 13.0 -> 12.6; 400 Mbases, 5 levels, 11.6 -> 11.4).  Two levels then share the lists: with chunks of 512 a
+// level makes at most nb / 128 chunks and nb / 513 groups (four lists' worth of
+// S / C as in lists_hold_all, and the samples, packed by 256, are at most half
+// of nb), and half of the lists holds nb / 96 and nb / 386.  Smaller chunks are
+// finished at once.
+int run_levels(const Build &b, LevelOut acc, bool first, PhaseTimer &T, hipStream_t st) {
   const Buffers &B = b.B;
   const Layout &Lo = b.Lo;
-  uint32_t *counters = B.counters;
   std::vector<Seg> big;
   std::vector<uint32_t> tprefix, gprefix;
   uint32_t ntiles = 0, ngroups = 0;
-  LevelOut o{};
+  uint32_t nbig = acc.n_big;
   int rc;
+  LevelWait behind;
+  const uint32_t half_chunks = (uint32_t)(Lo.cap_chunks / 2), half_finals = (uint32_t)(Lo.cap_finals / 2);
+  const bool halves = b.Ls.chunk >= 512 && nbig && behind.open();
+  LevelRest rest;
+  if (first) {
+    rest.o = acc;
+    rest.open = true;
+    if (!halves || acc.n_chunks > half_chunks || acc.n_finals > half_finals) {
+      if ((rc = finish_rest(b, rest, T, st))) return rc;
+    }
+  }
+  LevelOut o{};
   while (nbig) {
     if (nbig > Lo.cap_big) return fail_internal("work exceeds a workspace list or scratch area");
     g_stats.levels++;
@@ -927,16 +1044,37 @@ int run_levels(const Build &b, LevelOut acc, uint32_t nbig, PhaseTimer &T, hipSt
     g_stats.max_window = std::max<uint32_t>(g_stats.max_window, (uint32_t)acc.next_maxr);
     const uint64_t lt = acc.next_tiles, lg = acc.next_groups;
     acc = LevelOut{};
-    if ((rc = fill_u32(counters + C_NBIG, 1, 0, st))) return rc;
     if (nbig <= Lo.seg_slots && lt <= Lo.max_tiles && lg <= Lo.max_groups) {
-      if ((rc = prefix_list(B, B.big_next, nbig, b.tile_len, B.segs, B.tile_prefix, B.group_prefix, st))) return rc;
-      if ((rc = run_level_batch(B, Lo, b.tu, b.Ls, b.nb, b.rmax, b.maxlen, b.bwt, nbig, (uint32_t)lt, (uint32_t)lg, o, T,
-                                st)))
+      Lists Ls = b.Ls;
+      LevelRest made;
+      if (halves) {
+        made.half = rest.open ? !rest.half : 0;
+        Ls.chunks += made.half * half_chunks;
+        Ls.finals += made.half * half_finals;
+        Ls.cap_chunks = half_chunks;
+        Ls.cap_finals = half_finals;
+      }
+      if ((rc = prefix_list(B, B.big_next, nbig, b.tile_len, B.segs, B.tile_prefix, B.group_prefix, st, nullptr, true)))
         return rc;
+      if ((rc = launch_level_kernels(B, b.tu, Ls, b.nb, nbig, (uint32_t)lt, (uint32_t)lg, nullptr, T, st))) return rc;
+      g_stats.level_batches++;
+      if (halves) {
+        if ((rc = behind.post(B, st))) return rc;
+        if ((rc = finish_rest(b, rest, T, st))) return rc;
+        if ((rc = behind.wait(o))) return rc;
+      } else if ((rc = read_level(B, o, T, st))) {
+        return rc;
+      }
       record_shape(g_stats.levels - 1, LevelShape{nbig, (uint32_t)lt, (uint32_t)lg, o.n_chunks, o.n_finals,
                                                   (uint32_t)o.final_tiles});
+      made.o = o;
+      made.open = true;
+      rest = made;
+      if (!halves && (rc = finish_rest(b, rest, T, st))) return rc;
       acc = o;
     } else {
+      if ((rc = finish_rest(b, rest, T, st))) return rc;
+      if ((rc = fill_u32(B.counters + C_NBIG, 1, 0, st))) return rc;
       big.resize(nbig);
       CX_CHECK(hipMemcpyAsync(big.data(), B.big_next, sizeof(Seg) * nbig, hipMemcpyDeviceToHost, st));
       CX_CHECK(hipStreamSynchronize(st));
@@ -959,7 +1097,7 @@ int run_levels(const Build &b, LevelOut acc, uint32_t nbig, PhaseTimer &T, hipSt
     }
     nbig = o.n_big;
   }
-  return CXBWT_OK;
+  return finish_rest(b, rest, T, st);
 }
 
 // Whether the chunks and final groups of `levels` levels fit their lists
@@ -1089,10 +1227,7 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
       LevelOut o{};
       if ((rc = read_level(B, o, T, st))) return rc;
       record_shape(0, LevelShape{ns, ntiles, ngroups, o.n_chunks, o.n_finals, (uint32_t)o.final_tiles});
-      if ((rc = finish_level(B, Lo, b.tu, nb, b.rmax, b.maxlen, b.bwt, o.n_chunks, o.n_finals, o.final_tiles, o.final_len, T,
-                             st)))
-        return rc;
-      if ((rc = run_levels(b, o, o.n_big, T, st))) return rc;
+      if ((rc = run_levels(b, o, true, T, st))) return rc;
     } else if (lists_hold_all(b, device_levels)) {
       if ((rc = enqueue_listed_levels(b, device_levels, T, st, shapes))) return rc;
     } else {
@@ -1103,7 +1238,7 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
       };
       for (uint32_t lv = 0;; ++lv) {
         // the level just scanned: fold, finish its chunks and final groups
-        k_level_fold<<<1, 64, 0, st>>>(B.stats, (unsigned long long *)(counters + C_FOLD), counters + C_FLAGS);
+        k_level_fold<<<1, 64, 0, st>>>(B.stats, counters, counters + C_FLAGS, nullptr);
         CX_LAUNCHED();
         T.begin();
         if ((rc = launch_local(B, b.tu, nb, b.rmax, b.bwt, (uint32_t)Lo.cap_chunks, counters + C_NCHUNK, st,
@@ -1274,7 +1409,8 @@ int finish_device_levels(const Build &b, const uint32_t (&hc0)[C_COUNT], PhaseTi
   acc.next_maxr = f[K_NEXT_MAXR - K_LEVEL_FIRST];
   acc.next_tiles = f[K_NEXT_TILES - K_LEVEL_FIRST];
   acc.next_groups = f[K_NEXT_GROUPS - K_LEVEL_FIRST];
-  if ((rc = run_levels(b, acc, hc[C_NBIG], T, st))) return rc;
+  acc.n_big = hc[C_NBIG];
+  if ((rc = run_levels(b, acc, false, T, st))) return rc;
   if ((rc = launch_term(b, st))) return rc;
   // the statistics block still holds the device levels' counts: take the rest only
   g_stats.window_fetches = 0;
@@ -1545,10 +1681,7 @@ int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
     T.end(PH_SCATTER);
     LevelOut o{};
     if ((rc = read_level(s.B, o, T, st))) return rc;
-    if ((rc = finish_level(s.B, Lo, s.tu, nb, s.rmax, s.maxlen, s.bwt, o.n_chunks, o.n_finals, o.final_tiles,
-                           o.final_len, T, st)))
-      return rc;
-    if ((rc = run_levels(s, o, o.n_big, T, st))) return rc;
+    if ((rc = run_levels(s, o, true, T, st))) return rc;
   }
 
   // the steps, with every size known
@@ -1816,7 +1949,7 @@ int list_range(const Build &b, const Range &r, PhaseTimer &T, hipStream_t st) {
   return CXBWT_OK;
 }
 
-// Level 1 of range `r` as seg (of digit seg.d), and what it hands on; *fits
+// Level 1 of range `r` as seg (of digit seg.d), and what it makes; *fits
 // false, and nothing done, where the scratch is too small for the counts.
 int range_level1(const Build &b, const Range &r, const Seg &seg, bool *fits, LevelOut &o, PhaseTimer &T,
                  hipStream_t st) {
@@ -1858,9 +1991,7 @@ int range_level1(const Build &b, const Range &r, const Seg &seg, bool *fits, Lev
   g_stats.big_segments++;
   g_stats.level_suffixes += r.count;
   g_stats.level_batches++;
-  if ((rc = read_level(B, o, T, st))) return rc;
-  return finish_level(B, Lo, b.tu, b.nb, b.rmax, b.maxlen, b.bwt, o.n_chunks, o.n_finals, o.final_tiles, o.final_len, T,
-                      st);
+  return read_level(B, o, T, st);
 }
 
 // One collection built in ranges of at most m suffixes: the bare
@@ -1913,7 +2044,7 @@ int run_range_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n,
       LevelOut o{};
       if ((rc = range_level1(b, r, seg[i], &fits, o, T, st))) return rc;
       if (fits) {
-        if ((rc = run_levels(b, o, o.n_big, T, st))) return rc;
+        if ((rc = run_levels(b, o, true, T, st))) return rc;
         continue;
       }
     }
@@ -1928,7 +2059,8 @@ int run_range_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n,
     acc.next_len = r.count;
     acc.next_tiles = ceil_div(r.count, b.tile_len);
     acc.next_groups = ceil_div(acc.next_tiles, GROUP_TILES);
-    if ((rc = run_levels(b, acc, 1, T, st))) return rc;
+    acc.n_big = 1;
+    if ((rc = run_levels(b, acc, false, T, st))) return rc;
   }
   T.begin();
   if ((rc = launch_term(b, st))) return rc;

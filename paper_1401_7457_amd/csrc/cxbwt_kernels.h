@@ -1227,12 +1227,14 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
   }
 }
 
-// Folds the level kinds of the statistics block into out[0..K_LEVEL_KINDS)
-// (sums, a maximum for the window) and clears them for the next scan.  One
-// wave.
+// Folds the level kinds of the statistics block into the words from C_FOLD on
+// (sums, a maximum for the window) and clears them for the next scan.  With
+// host, the counters block goes to host memory too (a copy would be a launch
+// of its own, and wait for the stream).  One wave.
 __global__ __launch_bounds__(64) void k_level_fold(unsigned long long *__restrict__ stats,
-                                                   unsigned long long *__restrict__ out,
-                                                   const uint32_t *__restrict__ flags) {
+                                                   uint32_t *__restrict__ counters,
+                                                   const uint32_t *__restrict__ flags, uint32_t *__restrict__ host) {
+  unsigned long long *const out = reinterpret_cast<unsigned long long *>(counters + C_FOLD);
   const uint32_t l = lane_id();
   if (flags && (*flags & (FL_STALLED | FL_INCOMPLETE))) return;  // keep what the host resumes from
   for (int k = K_LEVEL_FIRST; k < K_KINDS; ++k) {
@@ -1245,6 +1247,11 @@ __global__ __launch_bounds__(64) void k_level_fold(unsigned long long *__restric
       v = k == K_NEXT_MAXR ? max(v, t) : v + t;
     }
     if (l == 0) out[k - K_LEVEL_FIRST] = v;
+  }
+  if (host) {
+    static_assert(C_COUNT == 64, "a word a lane");
+    __syncthreads();
+    host[l] = counters[l];
   }
 }
 
@@ -1396,7 +1403,9 @@ __global__ void k_check_bases(const uint64_t *__restrict__ got, const uint64_t *
 // item_index<SEGP_ITEMS> in each workgroup of BLOCK threads; k_seg_count
 // writes per-workgroup totals (tiles, groups), k_seg_scan adds the totals
 // of the workgroups before it, writes tile_prefix[i] and group_prefix[i]
-// (and entry n: the totals) and, when copy is given, the list itself.
+// (and entry n: the totals) and, when copy is given, the list itself.  With
+// counters it also clears what the level that follows counts and collects.  A
+// list of one workgroup needs no totals.
 constexpr int SEGP_ITEMS = 16;
 constexpr uint32_t SEGP_WG = BLOCK * SEGP_ITEMS;
 
@@ -1438,11 +1447,15 @@ __global__ __launch_bounds__(BLOCK) void k_seg_scan(const Seg *__restrict__ list
                                                     const uint32_t *__restrict__ dev_n, uint32_t tile_len,
                                                     const uint32_t *__restrict__ wg_tot, Seg *__restrict__ copy,
                                                     uint32_t *__restrict__ tile_prefix,
-                                                    uint32_t *__restrict__ group_prefix) {
+                                                    uint32_t *__restrict__ group_prefix,
+                                                    uint32_t *__restrict__ counters,
+                                                    unsigned long long *__restrict__ seg_or,
+                                                    unsigned long long *__restrict__ seg_and) {
   __shared__ uint32_t tmp[WAVES];
   __shared__ uint32_t wt[WAVES][2];
   if (dev_n) n = *dev_n;
   if ((uint64_t)blockIdx.x * SEGP_WG >= n) return;
+  if (counters && blockIdx.x == 0 && threadIdx.x == 0) counters[C_NFINAL] = counters[C_NCHUNK] = counters[C_NBIG] = 0;
   // base of this workgroup: the totals of the workgroups before it
   uint32_t bt = 0, bg = 0;
   for (uint32_t k = threadIdx.x; k < blockIdx.x; k += BLOCK) {
@@ -1483,6 +1496,10 @@ __global__ __launch_bounds__(BLOCK) void k_seg_scan(const Seg *__restrict__ list
       tile_prefix[at] = wbt + pt[i];
       if (group_prefix) group_prefix[at] = wbg + pg[i];
       if (copy) copy[at] = list[at];
+      if (counters) {
+        seg_or[at] = 0;
+        seg_and[at] = ~0ull;
+      }
       if (at == n - 1) {
         tile_prefix[n] = wbt + pt[i] + t[i];
         if (group_prefix) group_prefix[n] = wbg + pg[i] + g[i];
