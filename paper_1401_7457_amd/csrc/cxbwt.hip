@@ -1422,9 +1422,10 @@ int finish_device_levels(const Build &b, const uint32_t (&hc0)[C_COUNT], PhaseTi
 
 // ---- the build by induced order ------------------------------------------
 // Taken from this many bases on: the steps are about thirty launches of their
-// own, so that 17 Mbases of 100-base reads at 20x take 1.67 ms here and 1.45
-// by the sort, 33 Mbases 2.15 and 2.84 ms (deeper reads gain from less on: at
-// 2000x, 20 Mbases take 5.8 ms here and 15.1 by the sort).
+// own, so that 18 Mbases of 100-base reads at 20x take 1.24 ms here and 1.14
+// by the sort, 20 Mbases 1.28 and 1.32, 30 Mbases 1.59 and 1.85 (deeper reads
+// gain from less on: at 2000x, 10 Mbases take 3.8 ms here and 10.0 by the
+// sort, but the depth is not known before).
 #ifndef CXBWT_INDUCE_MIN_BASES
 #define CXBWT_INDUCE_MIN_BASES 20000000ull
 #endif

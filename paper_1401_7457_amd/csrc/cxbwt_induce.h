@@ -1170,12 +1170,12 @@ __device__ __forceinline__ void wave_lds_fence() {  // LDS written by some lanes
 }
 
 __device__ __forceinline__ void put_row(const IndData &D, const CollMap &cm, uint64_t g, uint32_t q, uint32_t pl,
-                                        uint32_t code) {
+                                        uint32_t code, bool read = true) {
   if (g >= D.nb) {
     atomicOr(D.status, ST_LIST_OVERFLOW);
     return;
   }
-  D.rows[g] = make_uint2(q, pl);
+  if (read) D.rows[g] = make_uint2(q, pl);
   D.bwt[g + cm.out_shift] = (uint8_t)code;
 }
 
@@ -1202,7 +1202,12 @@ __device__ __forceinline__ void ind_put(const IndData &D, const CollMap &cm, Wav
   const uint32_t x = pl >> (2 * (k + 1));
   const uint32_t code = k + 1 < r ? d : shown_code<LTR>(d, x);
   const bool look = on && code == CODE_LOOK;
-  if (on && !look) put_row(D, cm, g, q, x, code);
+  // Right to left nothing reads a row of A but for a read's first suffix and
+  // the runs beyond the regions: half of the rows written, whole lines (400
+  // Mbases 1.76 -> 1.61 ms).  Left out one by one, the other rows that nothing
+  // reads save nothing.
+  const bool read = LTR || d != 0 || (code & CODE_START) || k + 1 >= (uint32_t)RUN_REGIONS;
+  if (on && !look) put_row(D, cm, g, q, x, code, read);
   const uint64_t m = __ballot(look);
   if (m) {
     if (list_full(n, m)) put_looked_up<LTR>(D, cm, L, n);
