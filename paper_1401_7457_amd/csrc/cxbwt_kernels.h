@@ -689,10 +689,12 @@ __global__ __launch_bounds__(BLOCK) void k_level_hist(const Seg *__restrict__ se
   const uint32_t *H = sg.buf ? hdl1 : hdl0;
   hist[threadIdx.x] = 0;
   __syncthreads();
-  // all loads of a sub-tile (keys, and for a re-keyed segment handles and
-  // then records) are issued before any result is used; the sub-tiles one
-  // after the other (holding both sets of keys at once costs more in
-  // occupancy than the second wait)
+  // all keys of a sub-tile are loaded before any is used; the sub-tiles one
+  // after the other.  What bounds this is the waves that wait for their keys:
+  // both sub-tiles' keys at once cost more of them than the second wait does,
+  // and so did the records of eight re-keyed suffixes at once, which few
+  // segments need (four: 61 registers instead of 85, eight waves a SIMD; 20
+  // Mbases at 2000x 4.98 -> 4.90 ms a build, 400 Mbases 11.33 -> 11.27)
   uint64_t o = 0, a = ~0ull;
   // SUBT sub-tiles of BLOCK * MAX_TILE_ITEMS (two for the wide tile)
 #pragma unroll
@@ -707,25 +709,30 @@ __global__ __launch_bounds__(BLOCK) void k_level_hist(const Seg *__restrict__ se
       if (in[i]) kk[i] = K[j];
     }
     if (sg.regather) {
-      uint64_t hh[MAX_TILE_ITEMS];
-      TextRec tr[MAX_TILE_ITEMS];
+      constexpr int NB = PERSIST ? MAX_TILE_ITEMS : 4;  // (small builds have waves to spare)
+      static_assert(MAX_TILE_ITEMS % NB == 0, "whole batches");
 #pragma unroll
-      for (int i = 0; i < MAX_TILE_ITEMS; ++i)
-        if (in[i]) hh[i] = H[u0 + (uint64_t)i * BLOCK + threadIdx.x];
-      if (pos64) {
+      for (int i0 = 0; i0 < MAX_TILE_ITEMS; i0 += NB) {
+        uint64_t hh[NB];
+        TextRec tr[NB];
 #pragma unroll
-        for (int i = 0; i < MAX_TILE_ITEMS; ++i)
-          if (in[i]) hh[i] = pos64[hh[i]];
-      }
+        for (int i = 0; i < NB; ++i)
+          if (in[i0 + i]) hh[i] = H[u0 + (uint64_t)(i0 + i) * BLOCK + threadIdx.x];
+        if (pos64) {
 #pragma unroll
-      for (int i = 0; i < MAX_TILE_ITEMS; ++i)
-        if (in[i]) tr[i] = F::load(text, nb, hh[i], sg.r);
-#pragma unroll
-      for (int i = 0; i < MAX_TILE_ITEMS; ++i)
-        if (in[i]) {
-          kk[i] = F::combine(tr[i], nb, hh[i], sg.r, kk[i]);
-          K[u0 + (uint64_t)i * BLOCK + threadIdx.x] = kk[i];
+          for (int i = 0; i < NB; ++i)
+            if (in[i0 + i]) hh[i] = pos64[hh[i]];
         }
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+          if (in[i0 + i]) tr[i] = F::load(text, nb, hh[i], sg.r);
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+          if (in[i0 + i]) {
+            kk[i0 + i] = F::combine(tr[i], nb, hh[i], sg.r, kk[i0 + i]);
+            K[u0 + (uint64_t)(i0 + i) * BLOCK + threadIdx.x] = kk[i0 + i];
+          }
+      }
     }
 #pragma unroll
     for (int i = 0; i < MAX_TILE_ITEMS; ++i)
