@@ -78,9 +78,10 @@ def algorithmic_bytes(stats: dict, n_reads: int, n_bases: int, tile_len: int = 2
     if stats.get("launches", {}).get("induce"):
         # samples sorted, the rest induced: level 1 reads the text and writes
         # the samples (12 B); a finished sample is 12 B read, its key read
-        # again and 9 B written; a row is written once (8 B and a code byte),
-        # read by the right-to-left steps, the L half also left to right
-        # (with the samples), and its BWT byte written
+        # again and 9 B written; a row is written once (8 B and a code byte,
+        # of A the code alone), read by the right-to-left steps (of A the code
+        # alone), the L half also left to right (with the samples), and its
+        # BWT byte written
         moved = stats.get("scattered_suffixes", 0) - cs
         return {
             "prep": 17.0 * n_reads + 0.1875 * n_bases,
@@ -89,7 +90,7 @@ def algorithmic_bytes(stats: dict, n_reads: int, n_bases: int, tile_len: int = 2
             "level_scan": 2.0 * 1024 * stats.get("level_suffixes", 0) / 4096,
             "level_scatter": 0.375 * n_bases + 12.0 * cs + 24.0 * max(0, moved),
             "local": 29.0 * cs + 16.0 * stats.get("window_fetches", 0),
-            "induce": (9.0 + 9.0 + 4.5 + 1.0) * n_bases + 9.0 * cs,
+            "induce": (7.0 + 6.75 + 4.5 + 1.25) * n_bases + 9.0 * cs,
             "final_emit": 16.0 * n_reads,
         }
     fin = n_bases - cs
@@ -108,12 +109,12 @@ def algorithmic_bytes(stats: dict, n_reads: int, n_bases: int, tile_len: int = 2
 
 KERNELS_OF_CLASS = {
     "prep": ["k_prep", "k_text_records", "k_rank_count", "k_rank_top", "k_rank_words"],
-    "gen": ["k_gen_hist", "k_gen", "k_sample_hist"],
+    "gen": ["k_gen_hist", "k_gen", "k_sample_hist", "k_range_hist"],
     "level_hist": ["k_level_hist"],
     "level_scan": ["k_group_scan", "k_level_scan"],
-    "level_scatter": ["k_gen_scatter", "k_level_scatter", "k_sample_scatter"],
+    "level_scatter": ["k_gen_scatter", "k_level_scatter", "k_sample_scatter", "k_range_scatter"],
     "local": ["k_local", "k_sample_chunk"],
-    "final_emit": ["k_emit_final", "k_sample_final", "k_term"],
+    "final_emit": ["k_emit_final", "k_emit_groups", "k_sample_final", "k_term"],
     "induce": ["k_ind_count", "k_ind_group", "k_ind_top", "k_ind_scatter", "k_ind_tail", "k_ind_emit"],
 }
 

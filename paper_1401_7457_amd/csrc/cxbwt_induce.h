@@ -261,7 +261,7 @@ __host__ __device__ __forceinline__ uint32_t slow_samples(const TextRec *__restr
 // A workgroup takes HIST_TILES neighbouring tiles and keeps the type counts in
 // registers (one and, one count-and-add per record, class and run length up
 // to 3; longer runs one by one).  The types of 16 positions cost about 80
-// operations this way: 0.86 -> 0.28 ms per 400 Mbases against a position a lane.
+// operations this way: 0.86 -> 0.30 ms per 400 Mbases against a position a lane.
 constexpr uint32_t HIST_TILES = 8;
 __global__ __launch_bounds__(BLOCK) void k_sample_hist(const Seg *__restrict__ segs, const uint32_t *__restrict__ tile_prefix,
                                                        uint32_t nsegs, uint32_t ntiles,
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(BLOCK) void k_sample_hist(const Seg *__restrict__ s
 // Level 1 of the samples: found 16 positions at a time by a lane each, their
 // places listed in text order, then a sample a lane: key, scatter by the
 // first digit.  (With a pair of positions a lane and no list, 7 of 10 lanes
-// made no key: 1.87 -> 0.79 ms per 400 Mbases.)
+// made no key: 1.87 -> 0.85 ms per 400 Mbases.)
 __global__ __launch_bounds__(64 * SMP_NW) void k_sample_scatter(
     const Seg *__restrict__ segs, const uint32_t *__restrict__ tile_prefix, const uint32_t *__restrict__ group_prefix,
     uint32_t nsegs, const TextRec *__restrict__ text, const uint32_t *__restrict__ tile_hist,
@@ -1255,8 +1255,10 @@ __device__ __forceinline__ uint32_t ind_place(bool ok, uint32_t d, uint32_t (&nx
 // every item first; the items whose run is longer (a quarter of them) are
 // kept in LDS, and their further copies written k by k, so that full waves
 // write them.  (Listed per tile by place and loaded again they cost a second
-// read of the rows, 4.9 instead of 2.6 GB of the 300M rows of the
-// right-to-left steps of 400 Mbases.)
+// read of a quarter of the rows: 2.46 instead of 1.90 GB counted in the
+// right-to-left steps of 400 Mbases.)  Bound by the scattered writes: 4.0 GB
+// read and written right to left in 1.61 ms, 4.2 GB left to right in 1.28,
+// half to two thirds of the rate of a copy.
 template <bool LTR>
 __global__ __launch_bounds__(BLOCK) void k_ind_scatter(IndStep P, IndData D) {
   __shared__ uint2 lists[WAVES][64 * IND_BATCH];
