@@ -481,11 +481,15 @@ struct HostBlocks {
         return p;
       }
     }
+    // (a capture on another thread is not disturbed: nothing here is part of it)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
     uint32_t *p = nullptr;
     if (hipHostMalloc((void **)&p, 4 * C_COUNT, hipHostMallocPortable) != hipSuccess) {
       (void)hipGetLastError();
-      return nullptr;
+      p = nullptr;
     }
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     return p;
   }
   void give(uint32_t *p) {
@@ -506,7 +510,7 @@ HostBlocks g_host_blocks;
 struct LevelWait {
   uint32_t *block = nullptr;
   hipEvent_t ev = nullptr;
-  bool posted = false;
+  bool posted = false, recorded = false;
   bool open() {
     if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
       (void)hipGetLastError();
@@ -519,11 +523,13 @@ struct LevelWait {
     k_level_fold<<<1, 64, 0, st>>>(B.stats, B.counters, nullptr, block);
     CX_LAUNCHED();
     posted = true;
-    CX_CHECK(hipEventRecord(ev, st));
+    recorded = hipEventRecord(ev, st) == hipSuccess;
+    if (!recorded) (void)hipGetLastError();  // (an event of another device than the stream's)
     return CXBWT_OK;
   }
-  int wait(LevelOut &o) {
-    CX_CHECK(hipEventSynchronize(ev));
+  int wait(LevelOut &o, hipStream_t st) {
+    if (recorded) CX_CHECK(hipEventSynchronize(ev));
+    else CX_CHECK(hipStreamSynchronize(st));
     posted = false;
     o = level_out(block);
     return o.status ? CXBWT_EDEVICE : CXBWT_OK;
@@ -1061,7 +1067,7 @@ int run_levels(const Build &b, LevelOut acc, bool first, PhaseTimer &T, hipStrea
       if (halves) {
         if ((rc = behind.post(B, st))) return rc;
         if ((rc = finish_rest(b, rest, T, st))) return rc;
-        if ((rc = behind.wait(o))) return rc;
+        if ((rc = behind.wait(o, st))) return rc;
       } else if ((rc = read_level(B, o, T, st))) {
         return rc;
       }
@@ -1787,6 +1793,7 @@ int run_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n, uint6
         Level1Src small = v.src;
         small.big = SegSrc{};
         if ((rc = enqueue_body(b, small, 0, T, st))) return rc;
+        v.src.small = SegSrc{};
       }
       if ((rc = run_induced(b, &done, T, st))) return rc;
       b.planned = false;  // its tiles have taken the plan's place

@@ -120,3 +120,20 @@ def test_windows_of_long_reads(lens):
     b, t = cxbwt.build_host(col.text, col.offsets)
     rc = oracle.check_bwt(b, t, col.text, col.offsets)
     assert rc == 0, f"invariant {rc} fails"
+
+
+def test_batch_sorted_whole_among_small_collections():
+    # long runs in one collection: the sort takes all above one chunk, and the
+    # small ones are finished once
+    rng = np.random.default_rng(8)
+    cols = [datagen.random_collection(rng, 3, [40]), _long_runs(rng), datagen.random_collection(rng, 4, [50]),
+            datagen.sample_reads(rng, datagen.random_genome(rng, 20_000), 2000, 75, 0.01)]
+    _say(f"batch: {[c.n_bases for c in cols]}")
+    outs = cxbwt.build_batch_host(cols)
+    st = cxbwt.last_stats()
+    assert st["chunk_suffixes"] > cols[1].n_bases // 2  # sorted whole
+    for i, (c, (b, t)) in enumerate(zip(cols, outs)):
+        assert oracle.check_bwt(b, t, c.text, c.offsets) == 0, f"collection {i}"
+    # the chunks are those of the collections above one chunk, and one each of the small
+    cxbwt.build_batch_host([cols[1], cols[3]])
+    assert st["chunks"] == cxbwt.last_stats()["chunks"] + 2
