@@ -1428,12 +1428,13 @@ int finish_device_levels(const Build &b, const uint32_t (&hc0)[C_COUNT], PhaseTi
 
 // ---- the build by induced order ------------------------------------------
 // Taken from this many bases on: the steps are about thirty launches of their
-// own, so that 18 Mbases of 100-base reads at 20x take 1.24 ms here and 1.14
-// by the sort, 20 Mbases 1.28 and 1.32, 30 Mbases 1.59 and 1.85 (deeper reads
-// gain from less on: at 2000x, 10 Mbases take 3.8 ms here and 10.0 by the
-// sort, but the depth is not known before).
+// own, and up to 16.7 Mbases the sort lists its levels: 16 Mbases of 100-base
+// reads at 20x take 0.97 ms here and 0.95 by the sort, 17 Mbases 0.99 and 1.08,
+// 18 of 250 bases 1.21 and 1.41 (deeper reads gain from less on: at 2000x, 10
+// Mbases take 3.8 ms here and 9.7 by the sort, but the depth is not known
+// before).
 #ifndef CXBWT_INDUCE_MIN_BASES
-#define CXBWT_INDUCE_MIN_BASES 20000000ull
+#define CXBWT_INDUCE_MIN_BASES 16500000ull
 #endif
 // Not for reads this short: their suffixes end inside the first window, so
 // the sort has no windows to save (47 Mbases of 30-base reads: 4.0 ms by the
@@ -1722,7 +1723,7 @@ int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
       CX_LAUNCHED();                                                          \
       k_ind_group<<<(PLAN).ngroups, BLOCK, 0, st>>>(P, D);                    \
       CX_LAUNCHED();                                                          \
-      k_ind_top<LTR><<<nc, 64, 0, st>>>(P, D);                                \
+      k_ind_top<LTR><<<nc, 64 * TOP_WAVES, 0, st>>>(P, D);                    \
       CX_LAUNCHED();                                                          \
       k_ind_scatter<LTR><<<grid, BLOCK, 0, st>>>(P, D);                       \
       CX_LAUNCHED();                                                          \

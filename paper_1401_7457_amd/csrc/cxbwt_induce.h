@@ -980,7 +980,12 @@ __global__ __launch_bounds__(LOCAL_WG, OCC) void k_sample_chunk(
 // A step's sources, in order: runs of rows, of samples or (the first step) of
 // reads, a wave tile at a time; tiles in groups of GROUP_TILES within a
 // collection.  Classes: (base d, run index k) at d * 16 + k, one per lane.
-constexpr uint32_t IND_SLOTS = 32;
+// A tile is what a wave loads at once: a build of 20 Mbases fills the device
+// only so, and larger ones have fewer waves at work on their last tiles (512
+// rows instead of 2048, with the scan of the groups' totals shared by a
+// workgroup: 20 Mbases 1.25 -> 1.06 ms, 20 at 2000x 5.0 -> 4.6, 400 11.3 -> 10.9,
+// 2 Gbases 53.8 -> 51.3).
+constexpr uint32_t IND_SLOTS = 8;
 constexpr uint32_t IND_TILE = 64 * IND_SLOTS;
 constexpr uint32_t IND_BATCH = 8;  // slots whose loads are in flight together
 enum { SRC_ROWS = 0, SRC_SAMPLES = 1, SRC_READS = 2 };
@@ -1030,7 +1035,7 @@ __device__ __forceinline__ bool ind_taken(uint32_t code, uint32_t c) {
 // Class counts of every wave tile.
 template <bool LTR>
 __global__ __launch_bounds__(BLOCK) void k_ind_count(IndStep P, IndData D) {
-  constexpr uint32_t REP = 16;  // counter copies per wave, against conflicts on the hot classes
+  constexpr uint32_t REP = 8;  // counter copies per wave, against conflicts on the hot classes
   __shared__ uint32_t cnt[WAVES][REP][65];
   const uint32_t w = threadIdx.x >> 6, l = lane_id();
   const uint32_t tile = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * WAVES + w));
@@ -1103,44 +1108,48 @@ __global__ __launch_bounds__(BLOCK) void k_ind_group(IndStep P, IndData D) {
   if (w == WAVES - 1) D.gtot[(uint64_t)g * 64 + l] = run;
 }
 
-// Group totals to first places, from the collection's cursors; one wave a
-// collection.  Right to left a step's items go in front of the earlier ones.
+// Group totals to first places, from the collection's cursors; one workgroup
+// a collection, its waves a run of groups each (one wave alone took 0.83 ms of
+// the 52 of 2 Gbases).  Right to left a step's items go in front of the
+// earlier ones.
+constexpr int TOP_WAVES = 16;
 template <bool LTR>
-__global__ __launch_bounds__(64) void k_ind_top(IndStep P, IndData D) {
-  constexpr uint32_t NB = 16;
-  const uint32_t c = blockIdx.x, l = threadIdx.x;
+__global__ __launch_bounds__(64 * TOP_WAVES) void k_ind_top(IndStep P, IndData D) {
+  constexpr uint32_t NB = 8;
+  __shared__ uint32_t tot[TOP_WAVES][64];
+  const uint32_t c = blockIdx.x, w = threadIdx.x >> 6, l = lane_id();
   const uint32_t g0 = P.coll_groups[c], g1 = P.coll_groups[c + 1];
+  const uint32_t per = (g1 - g0 + TOP_WAVES - 1) / TOP_WAVES;
+  const uint32_t b = min(g0 + w * per, g1), e = min(b + per, g1);
   uint32_t *cur = D.cursor + ((uint64_t)c * 2 + (LTR ? 0 : 1)) * 64 + l;
-  uint32_t run = *cur;
-  if (!LTR) {
-    uint32_t g = g0;
-    for (; g + NB <= g1; g += NB) {
-      uint32_t x[NB];
-#pragma unroll
-      for (uint32_t i = 0; i < NB; ++i) x[i] = D.gtot[(uint64_t)(g + i) * 64 + l];
-#pragma unroll
-      for (uint32_t i = 0; i < NB; ++i) run -= x[i];
-    }
-    for (; g < g1; ++g) run -= D.gtot[(uint64_t)g * 64 + l];
-    *cur = run;
-  }
-  uint32_t g = g0;
-  for (; g + NB <= g1; g += NB) {
+  const uint32_t from = *cur;
+  uint32_t sum = 0;
+  for (uint32_t g = b; g < e; g += NB) {
     uint32_t x[NB];
 #pragma unroll
-    for (uint32_t i = 0; i < NB; ++i) x[i] = D.gtot[(uint64_t)(g + i) * 64 + l];
+    for (uint32_t i = 0; i < NB; ++i) x[i] = g + i < e ? D.gtot[(uint64_t)(g + i) * 64 + l] : 0u;
+#pragma unroll
+    for (uint32_t i = 0; i < NB; ++i) sum += x[i];
+  }
+  tot[w][l] = sum;
+  __syncthreads();  // (and every wave has read the cursors)
+  uint32_t before = 0, total = 0;
+  for (uint32_t ww = 0; ww < (uint32_t)TOP_WAVES; ++ww) {
+    before += ww < w ? tot[ww][l] : 0u;
+    total += tot[ww][l];
+  }
+  uint32_t run = (LTR ? from : from - total) + before;
+  if (w == 0) *cur = LTR ? from + total : from - total;
+  for (uint32_t g = b; g < e; g += NB) {
+    uint32_t x[NB];
+#pragma unroll
+    for (uint32_t i = 0; i < NB; ++i) x[i] = g + i < e ? D.gtot[(uint64_t)(g + i) * 64 + l] : 0u;
 #pragma unroll
     for (uint32_t i = 0; i < NB; ++i) {
-      D.gtot[(uint64_t)(g + i) * 64 + l] = run;
+      if (g + i < e) D.gtot[(uint64_t)(g + i) * 64 + l] = run;
       run += x[i];
     }
   }
-  for (; g < g1; ++g) {
-    const uint32_t x = D.gtot[(uint64_t)g * 64 + l];
-    D.gtot[(uint64_t)g * 64 + l] = run;
-    run += x;
-  }
-  if (LTR) *cur = run;
 }
 
 // Work that waits for a load, put off until a wave's worth of it is there: a
