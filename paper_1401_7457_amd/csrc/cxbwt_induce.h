@@ -1213,7 +1213,7 @@ __device__ __forceinline__ void ind_put(const IndData &D, const CollMap &cm, Wav
   const bool look = on && code == CODE_LOOK;
   // Right to left nothing reads a row of A but for a read's first suffix and
   // the runs beyond the regions: half of the rows written, whole lines (400
-  // Mbases 1.76 -> 1.61 ms).  Left out one by one, the other rows that nothing
+  // Mbases 1.76 -> 1.61 ms with tiles of 2048).  Left out one by one, the other rows that nothing
   // reads save nothing.
   const bool read = LTR || d != 0 || (code & CODE_START) || k + 1 >= (uint32_t)RUN_REGIONS;
   if (on && !look) put_row(D, cm, g, q, x, code, read);
@@ -1266,7 +1266,8 @@ __device__ __forceinline__ uint32_t ind_place(bool ok, uint32_t d, uint32_t (&nx
 // write them.  (Listed per tile by place and loaded again they cost a second
 // read of a quarter of the rows: 2.46 instead of 1.90 GB counted in the
 // right-to-left steps of 400 Mbases.)  Bound by its traffic: 10.3 GB read and
-// written in both directions in 2.9 ms, 3.5 TB/s where a copy reaches 4.5.
+// written in both directions in 2.41 ms (1.35 right to left), 4.3 TB/s where a
+// copy reaches 4.5.
 template <bool LTR>
 __global__ __launch_bounds__(BLOCK) void k_ind_scatter(IndStep P, IndData D) {
   __shared__ uint2 lists[WAVES][64 * IND_BATCH];
