@@ -114,7 +114,7 @@ KERNELS_OF_CLASS = {
     "level_scan": ["k_group_scan", "k_level_scan"],
     "level_scatter": ["k_gen_scatter", "k_level_scatter", "k_sample_scatter", "k_range_scatter"],
     "local": ["k_local", "k_sample_chunk"],
-    "final_emit": ["k_emit_final", "k_emit_groups", "k_sample_final", "k_term"],
+    "final_emit": ["k_emit_final", "k_sample_final", "k_term"],
     "induce": ["k_ind_count", "k_ind_group", "k_ind_top", "k_ind_scatter", "k_ind_tail", "k_ind_emit"],
 }
 

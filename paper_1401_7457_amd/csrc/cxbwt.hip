@@ -1113,7 +1113,8 @@ int run_levels(const Build &b, LevelOut acc, bool first, PhaseTimer &T, hipStrea
 // most 7 nb / C, which for C = 384 is less than the 4 nb / 192 that the list
 // holds for one level of the smallest chunks.  Final groups are disjoint.
 bool lists_hold_all(const Build &b, uint32_t levels) {
-  return b.tu.chunk_items >= 6 && levels <= 3 && b.Lo.seg_slots <= NEXT_SEGS;
+  return b.tu.chunk_items >= 6 && levels <= 3 && b.Lo.seg_slots <= NEXT_SEGS &&
+         b.Lo.cap_finals + 1 <= 256 * b.Lo.max_groups;  // their tile prefixes
 }
 
 // Levels scheduled at once for a build that the host will only look at when
@@ -1138,7 +1139,8 @@ int enqueue_listed_levels(const Build &b, uint32_t levels, PhaseTimer &T, hipStr
     if (shapes && lv < shapes->size()) seen_chunks += (*shapes)[lv].nchunks;
     const int last = lv + 1 == levels;
     k_next_level<<<1, NEXT_WG, 0, st>>>(B.counters, B.stats, B.big_next, B.segs, B.tile_prefix, B.group_prefix, B.seg_or,
-                                        B.seg_and, b.tile_len, Lo.seg_slots, Lo.max_tiles, Lo.max_groups, last);
+                                        B.seg_and, b.tile_len, Lo.seg_slots, Lo.max_tiles, Lo.max_groups, B.finals,
+                                        (uint32_t)Lo.cap_finals, B.gsum, last);
     CX_LAUNCHED();
     if (last) break;
     LevelShape sh;
@@ -1161,8 +1163,9 @@ int enqueue_listed_levels(const Build &b, uint32_t levels, PhaseTimer &T, hipStr
     return rc;
   T.end(PH_LOCAL);
   T.begin();
-  k_emit_groups<<<(unsigned)std::min<uint64_t>(PG_EMIT, nb / (2 * chunk) + 16), BLOCK, 0, st>>>(
-      B.finals, B.counters + C_NFINAL, B.keys0, B.keys1, B.hdl0, B.hdl1, B.text, B.srank, B.cmap, b.bwt, B.start_row);
+  k_emit_final<true><<<(unsigned)std::min<uint64_t>(PG_EMIT, nb / (2 * chunk) + 16), BLOCK, 0, st>>>(
+      B.finals, B.gsum, 0, B.counters + C_NFINAL, b.tile_len, B.keys0, B.keys1, B.hdl0, B.hdl1, B.pos64, B.text, B.srank,
+      B.cmap, b.bwt, B.start_row);
   CX_LAUNCHED();
   T.end(PH_FINAL);
   return CXBWT_OK;

@@ -1315,8 +1315,12 @@ __global__ void k_level_step(uint32_t *__restrict__ c, uint64_t seg_slots, uint6
 // k_seg_scan's and k_fill_seg's after it, in one workgroup: for builds whose
 // per-segment scratch holds few segments, where a launch costs more than the
 // list.  The chunks and final groups of all levels stay in their lists, for
-// one launch each after the last level (`totals`: C_NCHUNK and C_NFINAL are
-// the build's).
+// one launch each after the last level, before which it writes the groups'
+// tile prefixes to `fprefix`, the scan groups' totals area, which is free
+// then.  (The groups' rows are given out by the tile.  With a workgroup a
+// group, a build of 15 M reads of one base, four groups, took 16.2 ms, and 1.44
+// so; 640000 copies of a read of 25 bases 3.14 and 0.47; 1 Mbase of 100-base
+// reads the same.)
 constexpr int NEXT_WG = 1024;
 constexpr uint64_t NEXT_SEGS = 8192;  // most segments it takes: about 1 us per thousand
 __global__ __launch_bounds__(NEXT_WG) void k_next_level(uint32_t *__restrict__ c, unsigned long long *__restrict__ stats,
@@ -1326,12 +1330,25 @@ __global__ __launch_bounds__(NEXT_WG) void k_next_level(uint32_t *__restrict__ c
                                                         unsigned long long *__restrict__ seg_or,
                                                         unsigned long long *__restrict__ seg_and, uint32_t tile_len,
                                                         uint64_t seg_slots, uint64_t max_tiles, uint64_t max_groups,
-                                                        int last) {
+                                                        const Seg *__restrict__ finals, uint32_t cap_finals,
+                                                        uint32_t *__restrict__ fprefix, int last) {
   constexpr int NW = NEXT_WG / 64;
   __shared__ unsigned long long f[K_LEVEL_KINDS];
   __shared__ uint32_t tmp[NW];
   __shared__ uint32_t cur;
   const uint32_t w = threadIdx.x >> 6, l = lane_id();
+  if (last) {
+    const uint32_t n = min(c[C_NFINAL], cap_finals);
+    uint32_t tiles = 0;
+    for (uint32_t i0 = 0; i0 < n; i0 += NEXT_WG) {
+      const uint32_t i = i0 + threadIdx.x;
+      uint32_t total;
+      const uint32_t e = block_excl_sum<NW>(i < n ? (finals[i].len + tile_len - 1) / tile_len : 0u, tmp, &total);
+      if (i < n) fprefix[i] = tiles + e;
+      tiles += total;
+    }
+    if (threadIdx.x == 0) fprefix[n] = tiles;
+  }
   if (c[C_FLAGS] & (FL_STALLED | FL_INCOMPLETE)) return;  // keep what the host resumes from
   if (w < (uint32_t)K_LEVEL_KINDS) {
     unsigned long long *slot = stats + (K_LEVEL_FIRST + w) * STAT_KIND + (uint64_t)l * STAT_STRIDE;
@@ -1605,25 +1622,6 @@ __global__ __launch_bounds__(BLOCK) void k_emit_final(const Seg *__restrict__ se
     for (uint64_t j = t0 + threadIdx.x; j < t1; j += BLOCK)
       emit_row(j, cm, K[j], H[j], pos64, text, srank, bwt, start_row);
     if (!PERSIST) break;
-  }
-}
-
-// The same with a workgroup per group at a time, no tile prefixes: for small
-// builds, whose groups are short.
-__global__ __launch_bounds__(BLOCK) void k_emit_groups(const Seg *__restrict__ segs, const uint32_t *__restrict__ dev_nsegs,
-                                                       const uint64_t *__restrict__ keys0, const uint64_t *__restrict__ keys1,
-                                                       const uint32_t *__restrict__ hdl0, const uint32_t *__restrict__ hdl1,
-                                                       const TextRec *__restrict__ text, const uint32_t *__restrict__ srank,
-                                                       const CollMap *__restrict__ cmap, uint8_t *__restrict__ bwt,
-                                                       uint64_t *__restrict__ start_row) {
-  const uint32_t n = *dev_nsegs;
-  for (uint32_t s = blockIdx.x; s < n; s += gridDim.x) {
-    const Seg sg = segs[s];
-    const uint64_t *K = (sg.buf ? keys1 : keys0) + sg.start;
-    const uint32_t *H = (sg.buf ? hdl1 : hdl0) + sg.start;
-    const CollMap cm = cmap[sg.coll];
-    for (uint32_t j = threadIdx.x; j < sg.len; j += BLOCK)
-      emit_row((uint64_t)sg.start + j, cm, K[j], H[j], nullptr, text, srank, bwt, start_row);
   }
 }
 
