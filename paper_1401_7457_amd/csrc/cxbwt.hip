@@ -825,8 +825,8 @@ void plan_single(Build &b) {
   b.cm.assign(1, CollMap{b.n, (int64_t)b.n});
   b.big.clear();
   b.small.clear();
-  if (b.nb > (uint64_t)b.tu.chunk()) b.big.push_back(Seg{0, (uint32_t)b.nb, 0, 0, 0, 0, 0, 0});
-  else if (b.nb > 0) b.small.push_back(Seg{0, (uint32_t)b.nb, 0, 0, 0, 0, 1, 0});
+  if (b.nb > (uint64_t)b.tu.chunk()) b.big.push_back(Seg{0, (uint32_t)b.nb, 0, 0, 0, 0, 0, 0, 0});
+  else if (b.nb > 0) b.small.push_back(Seg{0, (uint32_t)b.nb, 0, 0, 0, 0, 1, 0, 0});
 }
 
 // Clears the counters, statistics and read-start bitmap, validates the
@@ -845,7 +845,7 @@ int enqueue_prep(const Build &b, const uint64_t *coll_reads_src, const uint64_t 
     P.n = b.n;
     P.nb = b.nb;
     P.cm = CollMap{b.n, (int64_t)b.n};
-    P.seg = Seg{0, (uint32_t)b.nb, 0, 0, 0, 0, (uint8_t)(b.nb <= (uint64_t)b.tu.chunk()), 0};
+    P.seg = Seg{0, (uint32_t)b.nb, 0, 0, 0, 0, (uint8_t)(b.nb <= (uint64_t)b.tu.chunk()), 0, 0};
     P.ntiles = (uint32_t)ceil_div(b.nb, b.tile_len);
     P.ngroups = (uint32_t)ceil_div(P.ntiles, GROUP_TILES);
     k_begin<<<std::min(grid_for(std::max<uint64_t>(n_sbits, STAT_WORDS), 256), 4096u), 256, 0, st>>>(
@@ -931,8 +931,8 @@ int plan_level1(Build &b, PhaseTimer &T, hipStream_t st) {
     const uint64_t bc = b.cbase[c + 1] - b.cbase[c];
     b.cm[c].out_shift = b.coll_reads[c + 1];
     b.cm[c].row_shift = (int64_t)nc - (int64_t)b.cbase[c];
-    if (bc > (uint64_t)b.tu.chunk()) b.big.push_back(Seg{(uint32_t)b.cbase[c], (uint32_t)bc, 0, 0, 0, 0, 0, c});
-    else if (bc > 0) b.small.push_back(Seg{(uint32_t)b.cbase[c], (uint32_t)bc, 0, 0, 0, 0, 1, c});
+    if (bc > (uint64_t)b.tu.chunk()) b.big.push_back(Seg{(uint32_t)b.cbase[c], (uint32_t)bc, 0, 0, 0, 0, 0, 0, c});
+    else if (bc > 0) b.small.push_back(Seg{(uint32_t)b.cbase[c], (uint32_t)bc, 0, 0, 0, 0, 1, 0, c});
   }
   return CXBWT_OK;
 }
@@ -1673,7 +1673,7 @@ int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
   for (uint32_t c = 0; c < nc; ++c) {
     uint64_t len = 0;
     for (int d = 0; d < 4; ++d) len += cs[c].samples[d];
-    seg[c] = Seg{(uint32_t)cs[c].first_sample, (uint32_t)len, 0, 0, 0, 0, 0, c};
+    seg[c] = Seg{(uint32_t)cs[c].first_sample, (uint32_t)len, 0, 0, 0, 0, 0, 0, c};
   }
   if (M) {
     CX_CHECK(hipMemcpyAsync(s.B.segs, seg.data(), sizeof(Seg) * nc, hipMemcpyHostToDevice, st));
@@ -2050,7 +2050,7 @@ int run_range_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n,
     // a range that fits a chunk: one unsplit chunk; else one segment whose
     // keys agree on their first `common` digits
     seg[i] = Seg{0, (uint32_t)r.count, 0, (uint8_t)std::min<uint32_t>(r.common, small ? 6 : 7), 0, 0,
-                 (uint8_t)(small ? 1 : 0), 0};
+                 (uint8_t)(small ? 1 : 0), 0, 0};
     if (!small && !r.piece) {
       bool fits = false;
       LevelOut o{};

@@ -57,6 +57,7 @@ struct Seg {
   uint8_t buf : 1;
   uint8_t regather : 1;  // keys must be re-fetched for window r before use
   uint8_t unsplit : 1;   // chunk only: suffixes are not yet in the order of digit d
+  uint8_t plain : 1;     // levels only: few suffixes end here, ended ones are not split off first
   uint32_t coll;         // collection the suffixes belong to
 };
 static_assert(sizeof(Seg) == 16, "segment records are 16 bytes");
@@ -129,7 +130,11 @@ struct Lists {
 // reads, are then final at once instead of passing every later level (levels
 // of a 1 Mbase build 5 -> 3, 690 -> 500 us; of 400 Mbases 7 -> 4, 12.5 -> 11.6
 // ms; where nothing ends there the pass is wasted: 20 Mbases at 2000x, 5.85 ->
-// 6.05 ms).
+// 6.05 ms).  Where fewer than one in eight end (runs of A inside the reads,
+// whose every digit is zero), what is left and all that comes of it is Seg::plain
+// and split by its own digits only: in random reads about half of bucket 0 end
+// there; with runs of 90 A in a tenth of the reads of 20 Mbases a pass before
+// every digit made 28 levels 49, and 4.9 ms 7.2.
 constexpr int ENDED = 16;
 constexpr uint32_t ENDED_NOT = 31;
 struct GeneralKey {
@@ -980,6 +985,7 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
         }
       } else {
         const int top = 63 - __builtin_clzll(diff);
+        if (sg.d >= ENDED) nx.plain = 1;
         nx.d = (uint8_t)F::digit_of_bit(top);
         nx_list = 1;
       }
@@ -1199,7 +1205,7 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
     for (uint32_t j = l; j < nc; j += 64) {
       const uint32_t at = base_c + j;
       if (at < L.cap_chunks)
-        L.chunks[at] = Seg{sg.start + cstart[cw][j], clen[cw][j], sg.r, sd, nbuf, 0, (uint8_t)ended, sg.coll};
+        L.chunks[at] = Seg{sg.start + cstart[cw][j], clen[cw][j], sg.r, sd, nbuf, 0, (uint8_t)ended, 0, sg.coll};
       else overflow = true;
     }
     const bool last = sg.d == F::LAST;
@@ -1207,7 +1213,7 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
     // split off; before digit d + 1 of bucket 0 they are split off first
     const auto next_digit = [&](uint32_t bucket) {
       if (ended) return sd;
-      return (uint8_t)(bucket == 0 && sd + 1 < F::LAST ? (sd + 1) | ENDED : sd + 1);
+      return (uint8_t)(bucket == 0 && !sg.plain && sd + 1 < F::LAST ? (sd + 1) | ENDED : sd + 1);
     };
     uint32_t pb = 0, pf = 0;  // entries of the lower slots
 #pragma unroll
@@ -1215,14 +1221,16 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
       const uint32_t st = sg.start + bv[i];
       if ((NB[i] >> l) & 1) {
         const uint32_t at = base_b + pb + bits_below_lane(NB[i]);
-        const Seg e = last ? Seg{st, cv[i], (uint16_t)(sg.r + 1), 0, nbuf, 1, 0, sg.coll}
-                           : Seg{st, cv[i], sg.r, next_digit((uint32_t)i * 64 + l), nbuf, 0, 0, sg.coll};
+        // (the one segment that an ended digit leaves: whether one in eight has ended)
+        const uint8_t plain = ended ? (uint8_t)(8ull * cv[i] > 7ull * sg.len) : sg.plain;
+        const Seg e = last ? Seg{st, cv[i], (uint16_t)(sg.r + 1), 0, nbuf, 1, 0, plain, sg.coll}
+                           : Seg{st, cv[i], sg.r, next_digit((uint32_t)i * 64 + l), nbuf, 0, 0, plain, sg.coll};
         if (at < L.cap_big) L.big_next[at] = e;
         else overflow = true;
       }
       if ((FIN[i] >> l) & 1) {
         const uint32_t at = base_f + pf + bits_below_lane(FIN[i]);
-        if (at < L.cap_finals) L.finals[at] = Seg{st, cv[i], sg.r, (uint8_t)(sg.d + 1), nbuf, 0, 0, sg.coll};
+        if (at < L.cap_finals) L.finals[at] = Seg{st, cv[i], sg.r, (uint8_t)(sg.d + 1), nbuf, 0, 0, 0, sg.coll};
         else overflow = true;
       }
       pb += (uint32_t)__popcll(NB[i]);
