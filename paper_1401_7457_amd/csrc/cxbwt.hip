@@ -1439,6 +1439,11 @@ int finish_device_levels(const Build &b, const uint32_t (&hc0)[C_COUNT], PhaseTi
 #ifndef CXBWT_INDUCE_MIN_BASES
 #define CXBWT_INDUCE_MIN_BASES 16500000ull
 #endif
+// Time that the runs beyond the regions may take besides a hundredth of the
+// nanoseconds of the bases (run_induced).
+#ifndef CXBWT_INDUCE_TAIL_NS
+#define CXBWT_INDUCE_TAIL_NS 50000ull
+#endif
 // Not for reads this short: their suffixes end inside the first window, so
 // the sort has no windows to save (47 Mbases of 30-base reads: 4.0 ms by the
 // sort, 2.4 here), and their groups of identical suffixes are what final_big
@@ -1568,7 +1573,7 @@ int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
   // runs beyond the regions are followed a base at a time by one workgroup
   // (about 5 us a base, 1 ns a suffix): left to the sort where they could
   // cost half of what this saves (20 ns per 1000 bases) and more
-  if (tail_steps * 5000 + tail > nb / 100 + 50000) return CXBWT_OK;
+  if (tail_steps * 5000 + tail > nb / 100 + CXBWT_INDUCE_TAIL_NS) return CXBWT_OK;
 
   // the samples' sort buffers, the sorted samples and the rows, in the space
   // of the general sort buffers
