@@ -204,9 +204,10 @@ struct RecordTypes {
   uint32_t sample;
   uint32_t eq, eq2;  // the next base is the same and in the same read; of the 16 positions after these
   uint32_t cut;      // the read ends one or two positions on
-  bool slow;         // a run reaches past the 32 positions: the masks do not hold
+  bool slow;         // a run reaches past the 32 positions: s and sample hold only with after_s
 };
-__host__ __device__ __forceinline__ RecordTypes record_types(const TextRec &t) {
+// after_s: of a slow record, whether the position after its 16 is S.
+__host__ __device__ __forceinline__ RecordTypes record_types(const TextRec &t, bool after_s = false) {
   RecordTypes r;
   const uint32_t a = (uint32_t)(t.hi >> 32), b = (uint32_t)t.hi, c = (uint32_t)(t.lo >> 32);
   const uint32_t an = (a << 2) | (b >> 30), bn = (b << 2) | (c >> 30);
@@ -220,7 +221,7 @@ __host__ __device__ __forceinline__ RecordTypes record_types(const TextRec &t) {
   r.cut = (ea << 2) | (eb >> 30) | (ea << 4) | (eb >> 28);
   // S of position 16: of the last position of its run
   const uint32_t last = ~r.eq2 & LANES;
-  const uint32_t s16 = last ? (below(b, bn) & ~eb) >> (31 - (uint32_t)__builtin_clz(last)) & 1u : 0u;
+  const uint32_t s16 = last ? (below(b, bn) & ~eb) >> (31 - (uint32_t)__builtin_clz(last)) & 1u : (uint32_t)after_s;
   // S: below the next, or equal to it and the next one S (runs of up to 16
   // here, by doubling)
   uint32_t g = (below(a, an) & ~ea) | (r.eq & s16), p = r.eq;
@@ -244,17 +245,20 @@ __host__ __device__ __forceinline__ uint32_t lanes_within(uint64_t w, uint64_t a
   if (p + 16 > e && p < e) m &= ~(~0u >> (2 * (uint32_t)(e - p)));
   return m;
 }
-// the same, one position at a time
+// A slow record's types, from one walk along the run that the 16 positions
+// after it belong to; the run of the first of them.  (A walk for each of the
+// record's positions, each with its own counter updates: 1.0 ms for 20 Mbases
+// with runs of 90 bases in a tenth of the reads, and 0.55 so.)
+__host__ __device__ __forceinline__ RecordTypes slow_types(const TextRec *__restrict__ text, const TextRec &t, uint64_t w,
+                                                           uint32_t &after_run) {
+  const SuffixType ty = suffix_type(text, text[w + 1], 16 * w + 16);
+  after_run = ty.run;
+  return record_types(t, ty.s);
+}
 __host__ __device__ __forceinline__ uint32_t slow_samples(const TextRec *__restrict__ text, const TextRec &t, uint64_t w,
                                                           uint32_t valid) {
-  uint32_t m = 0;
-  for (uint32_t o = 0; o < 16; ++o) {
-    const uint32_t bit = 1u << (30 - 2 * o);
-    if (!(valid & bit)) continue;
-    const SuffixType ty = suffix_type(text, t, 16 * w + o);
-    if (ty.s && !((t.lo >> o) & 1u) && base_before(t, o) > ty.base) m |= bit;
-  }
-  return m;
+  uint32_t run;
+  return slow_types(text, t, w, run).sample & valid;
 }
 
 // Counts of every collection and first-digit counts of every tile's samples.
@@ -330,14 +334,28 @@ __global__ __launch_bounds__(BLOCK) void k_sample_hist(const Seg *__restrict__ s
       const uint32_t valid = lanes_within(w, start, end);
       if (!valid) continue;
       const TextRec t = text[w];
-      const RecordTypes ty = record_types(t);
-      uint32_t sample = ty.sample & valid;
-      if (!ty.slow) {
+      RecordTypes ty = record_types(t);
+      uint32_t counted = valid;
+      if (ty.slow) {
+        // the positions of the run that goes on past the record: one class
+        uint32_t run;
+        ty = slow_types(text, t, w, run);
+        const uint32_t other = ~ty.eq & LANES;
+        const uint32_t chain = (other ? (other & (0u - other)) - 1u : ~0u) & valid;
+        if (chain) {
+          const uint32_t j = ((ty.s & 1u) << 2) | (ty.bases & 3u);
+          atomicAdd(&cls[j * 16 + RUN_REGIONS], (uint32_t)__popc(chain));
+          atomicMax(&cls[TC_MAXRUN + j], run + 16u - ((uint32_t)__builtin_clz(chain) >> 1));
+        }
+        counted &= ~chain;
+      }
+      const uint32_t sample = ty.sample & valid;
+      {
         const uint32_t bh = ty.bases >> 1, bl = ty.bases;
         uint32_t m[8];
 #pragma unroll
         for (int j = 0; j < 8; ++j)
-          m[j] = valid & ((j & 4) ? ty.s : ~ty.s) & ((j & 2) ? bh : ~bh) & ((j & 1) ? bl : ~bl);
+          m[j] = counted & ((j & 4) ? ty.s : ~ty.s) & ((j & 2) ? bh : ~bh) & ((j & 1) ? bl : ~bl);
         uint32_t e = ty.eq, f = ty.eq2, e1 = ty.eq;  // positions with runs of at least k; the rest shifted along
 #pragma unroll
         for (int j = 0; j < 8; ++j) acc[0][j] += (uint32_t)__popc(m[j]);
@@ -350,8 +368,8 @@ __global__ __launch_bounds__(BLOCK) void k_sample_hist(const Seg *__restrict__ s
           e &= e1;
         }
         // runs of KR and more, one by one: moved from "at least k - 1" to k
-        for (uint32_t k = KR; e & valid; ++k) {
-          for (uint32_t left = e & valid; left;) {
+        for (uint32_t k = KR; e & counted; ++k) {
+          for (uint32_t left = e & counted; left;) {
             const uint32_t bit = 31u - (uint32_t)__builtin_clz(left);
             left &= ~(1u << bit);
             const uint32_t j = (((ty.s >> bit) & 1u) << 2) | ((ty.bases >> bit) & 3u);
@@ -364,17 +382,6 @@ __global__ __launch_bounds__(BLOCK) void k_sample_hist(const Seg *__restrict__ s
           e1 = (e1 << 2) | (f >> 30);
           f <<= 2;
           e &= e1;
-        }
-      } else {
-        sample = 0;
-        for (uint32_t o = 0; o < 16; ++o) {
-          const uint32_t bit = 1u << (30 - 2 * o);
-          if (!(valid & bit)) continue;
-          const SuffixType ty1 = suffix_type(text, t, 16 * w + o);
-          const uint32_t j = (ty1.s ? 4u : 0u) + ty1.base;
-          atomicAdd(&cls[j * 16 + min(ty1.run, (uint32_t)RUN_REGIONS)], 1u);
-          if (ty1.run >= RUN_REGIONS) atomicMax(&cls[TC_MAXRUN + j], ty1.run);
-          if (ty1.s && !((t.lo >> o) & 1u) && base_before(t, o) > ty1.base) sample |= bit;
         }
       }
 #pragma unroll
