@@ -16,7 +16,7 @@ OUT = os.path.join(HERE, "libcxbwt.so")
 CEILINGS_SOURCES = [os.path.join(HERE, "csrc", "ceilings.hip")]
 CEILINGS_OUT = os.path.join(HERE, "libcxbwt_ceilings.so")
 SMALL_OUT = os.path.join(HERE, "libcxbwt_small.so")
-SMALL_FLAGS = ["-DCXBWT_INDUCE_MIN_BASES=60000ull", "-DCXBWT_INDUCE_TAIL_NS=1000000ull"]
+SMALL_FLAGS = ["-DCXBWT_INDUCE_MIN_BASES=60000ull", "-DCXBWT_INDUCE_TAIL_NS=1000000ull", "-DCXBWT_INDUCE_COLL_CHUNKS=20ull"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

@@ -1306,12 +1306,16 @@ struct Level1Vectors {
   }
 };
 
+// Adds the level 1 of b's collections.
 void level1_stats(const Build &b) {
-  g_stats.chunk_suffixes = b.nb;
+  for (const Seg &g : b.small) g_stats.chunk_suffixes += g.len;
   if (!b.big.empty()) {
-    g_stats.levels = 1;
-    g_stats.big_segments = b.big.size();
-    for (const Seg &g : b.big) g_stats.level_suffixes += g.len;
+    g_stats.levels++;
+    g_stats.big_segments += b.big.size();
+    for (const Seg &g : b.big) {
+      g_stats.chunk_suffixes += g.len;
+      g_stats.level_suffixes += g.len;
+    }
   }
 }
 
@@ -1498,6 +1502,35 @@ StepPlan plan_step(StepBlob &blob, const std::vector<std::vector<IndSeg>> &src) 
   return p;
 }
 
+// The collections of b to be built by induced order (`large`) and those to be
+// sorted in any case (`rest`); false when too few bases are in large ones.
+// A collection of up to about 256 chunks is sorted by one level: cheaper than
+// its samples and their steps, whose host plan and descriptors cost half a
+// microsecond a collection besides (by the sort and by samples, 200 Mbases in
+// collections of 30, 65, 100, 130 and 200 kbases: 3.5 and 6.6, 3.8 and 4.7, 3.9
+// and 4.3, 6.7 and 4.1, 9.7 and 5.3 ms; the level's buckets are uneven, so some
+// are above a chunk from 200 chunks on).  A few small ones are carried along:
+// a sort of their own is a dozen launches and two waits.
+#ifndef CXBWT_INDUCE_COLL_CHUNKS
+#define CXBWT_INDUCE_COLL_CHUNKS 215ull
+#endif
+constexpr size_t INDUCE_CARRIED = 400;
+bool pick_induced(const Build &b, std::vector<Seg> &large, std::vector<Seg> &rest) {
+  const uint64_t least = CXBWT_INDUCE_COLL_CHUNKS * b.tu.chunk();
+  uint64_t bases = 0;
+  for (const Seg &g : b.big) {
+    const bool is = b.ncoll == 1 || g.len >= least;
+    (is ? large : rest).push_back(g);
+    if (is) bases += g.len;
+  }
+  if (bases < CXBWT_INDUCE_MIN_BASES) return false;
+  if (rest.size() <= INDUCE_CARRIED) {
+    large = b.big;
+    rest.clear();
+  }
+  return true;
+}
+
 // Plans and runs the build by induced order of b's collections above one
 // chunk (the others have been built).  *taken stays false, and nothing has
 // been written, where it does not apply.
@@ -1670,9 +1703,8 @@ int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
   s.Ls.pack = b.maxlen >= PAIR_MIN_READ ? PAIR_PACK : SAMPLE_CHUNK;
   s.Ls.tile_len = s.tile_len;
   std::vector<Seg> seg(nc);
-  g_stats.chunk_suffixes = M;
-  for (const Seg &g : b.small) g_stats.chunk_suffixes += g.len;
-  g_stats.levels = 1;
+  g_stats.chunk_suffixes += M;
+  g_stats.levels++;
   g_stats.big_segments += nc;
   g_stats.level_suffixes += M;
   for (uint32_t c = 0; c < nc; ++c) {
@@ -1790,24 +1822,29 @@ int run_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n, uint6
   if (ahead && ncoll == 1) plan_single(b);
   else if ((rc = plan_level1(b, T, st))) return rc;
   uint32_t hc[C_COUNT];
+  Build apart;           // collections sorted beside a build by induced order
+  Level1Vectors v, va;   // sources of copies: kept until the last wait
   if (!msd) {
     if ((rc = run_stringword(b, T, st))) return rc;
   } else {
     bool done = false;
-    Level1Vectors v;
-    v.make(b);
-    if (induce && !b.big.empty()) {
-      if (!b.small.empty()) {
-        // the collections of one chunk, by themselves
-        Level1Src small = v.src;
-        small.big = SegSrc{};
-        if ((rc = enqueue_body(b, small, 0, T, st))) return rc;
-        v.src.small = SegSrc{};
+    std::vector<Seg> large, rest;
+    if (induce && pick_induced(b, large, rest)) {
+      if (!rest.empty() || !b.small.empty()) {
+        apart = b;
+        apart.big.swap(rest);
+        va.make(apart);
+        level1_stats(apart);
+        if ((rc = enqueue_body(apart, va.src, 0, T, st))) return rc;
+        if ((rc = fill_u32(b.B.counters + C_NFINAL, 3, 0, st))) return rc;  // the lists, as level 1 finds them
       }
+      b.big.swap(large);
+      b.small.clear();
       if ((rc = run_induced(b, &done, T, st))) return rc;
       b.planned = false;  // its tiles have taken the plan's place
     }
     if (!done) {
+      v.make(b);
       level1_stats(b);
       const bool listed = ahead && !b.big.empty();
       if ((rc = enqueue_body(b, v.src, listed ? levels_ahead(b) : 0, T, st))) return rc;

@@ -144,6 +144,28 @@ def test_declined_builds_are_sorted():
     _check(col, b, t, "long runs")
 
 
+@pytest.mark.parametrize("large", ["none", "induced", "declined"])
+def test_many_small_collections_are_sorted(large):
+    """More than 400 collections that one level sorts, alone, beside large ones
+    and beside one whose induction is declined: they are sorted whole."""
+    rng = np.random.default_rng(11)
+    cols = [datagen.sample_reads(rng, datagen.random_genome(rng, 300), n, 50, 0.01)
+            for n in rng.choice([2, 5, 20, 60, 120], size=800)]
+    small = sum(c.n_bases for c in cols)
+    if large != "none":
+        for k, at in enumerate((0, 300, 802)):
+            c = datagen.sample_reads(rng, datagen.random_genome(rng, 20_000), 1500 + 100 * k, 100, 0.005)
+            cols.insert(at, _with_runs(c, rng, [60, 90], 40) if large == "declined" and k == 1 else c)
+    total = sum(c.n_bases for c in cols)
+    _say(f"{large}: {len(cols)} collections, {total} bases")
+    outs = cxbwt.build_batch_host(cols)
+    st = cxbwt.last_stats()
+    final = {"none": total, "induced": small + (total - small) // 2, "declined": total}[large]
+    assert st["chunk_suffixes"] <= final and st["chunk_suffixes"] >= (small if large == "induced" else 0.9 * total)
+    for i, (c, (b, t)) in enumerate(zip(cols, outs)):
+        _check(c, b, t, f"collection {i}")
+
+
 def test_two_induced_builds_in_flight():
     """Started on two streams, each waiting for its own levels: four rounds, so
     that the host blocks and events go round."""
