@@ -348,8 +348,8 @@ def _plain_line(args, workload: str, col=None, label: str | None = None) -> dict
                  "equals_eager_build": same}
         g.close()
 
-    tuning_str = "%dx%d" % cxbwt.get_tuning()
-    model = algorithmic_bytes(stats, n, nb, tile_len=256 * cxbwt.get_tuning()[0])
+    tuning_str = "%dx%d" % cxbwt.build_tuning(nb)
+    model = algorithmic_bytes(stats, n, nb, tile_len=256 * cxbwt.build_tuning(nb)[0])
     dom = max(per_ms, key=per_ms.get)
     dom_ms = per_ms[dom]
     launches = max(1, per_launch[dom])
@@ -483,7 +483,7 @@ def _ranges_mode(args) -> dict:
     return {
         "metric": "BWT build Gbases/s at 1 GPU in key ranges", "value": lines[-1]["gbases_per_s"], "unit": "Gbases/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "higher_is_better": True, "data": "synthetic",
-        "config": {"workload": label, "reads": n, "bases": nb, "tuning": "x".join(map(str, cxbwt.get_tuning()))},
+        "config": {"workload": label, "reads": n, "bases": nb, "tuning": "x".join(map(str, cxbwt.build_tuning(nb // 8 + 1)))},
         "lines": lines,
     }
 

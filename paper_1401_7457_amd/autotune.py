@@ -83,6 +83,19 @@ def _save_file(key: tuple, choice: tuple) -> None:
         pass  # the in-memory cache still holds the choice
 
 
+def fastest(times: dict) -> tuple:
+    """The choice to take of {choice: ms}.
+
+    A shape class spans sizes on both sides of those from which the library
+    takes other sizes unasked, or sorts samples with sizes of their own, where
+    all choices take the same time (within 1%): of equal choices the default,
+    whose size rule is applied to each build.
+    """
+    best = min(times, key=times.get)
+    own = (*cxbwt.TUNING_CHOICES[0], cxbwt.SCHEDULE_MSD)
+    return own if times.get(own, math.inf) <= 1.02 * times[best] else best
+
+
 def tune_build(packed, offsets, n_reads: int, n_bases: int, max_read_len: int, coll_reads=None,
                repeats: int = 3, choices=None, workspace=None, out=None, persist: bool = True) -> dict:
     """Time every choice on this input and select the fastest.
@@ -133,14 +146,7 @@ def tune_build(packed, offsets, n_reads: int, n_bases: int, max_read_len: int, c
     except Exception:
         apply(before)
         raise
-    best = min(times, key=times.get)
-    # A shape class spans builds that sort every suffix and larger ones that
-    # sort samples with sizes of their own, where all choices take the same time
-    # (within 1%): of equal choices the one the library takes unasked.
-    own = (16, 8) if n_bases >= 12_000_000 else (8, 6)
-    own = (*own, cxbwt.SCHEDULE_MSD)
-    if own in times and times[own] <= 1.02 * times[best]:
-        best = own
+    best = fastest(times)
     apply(best)
     key = shape_key(n_reads, n_bases, max_read_len, n_coll)
     _cache[key] = best

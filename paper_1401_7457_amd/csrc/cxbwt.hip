@@ -71,17 +71,26 @@ struct Tuning {
   uint32_t tile_items;   // 6, 8 or 16 suffixes per 256 threads' thread in a level tile (16: 8 waves x 8)
   uint32_t chunk_items;  // 3, 6 or 8 suffixes per lane in a chunk
   uint32_t schedule = CXBWT_SCHEDULE_MSD;  // sort schedule of single-collection builds
-  bool chosen = false;   // by the caller (cxbwt_set_tuning, cxbwt_opts)
   uint32_t tile_len() const { return BLOCK * tile_items; }
   uint32_t chunk() const { return LOCAL_WG * chunk_items; }
 };
-thread_local Tuning g_tuning{8, 6};
 
-// Suffixes sorted at once from which a build whose instantiation nobody chose
-// takes 16 x 8 instead of 8 x 6 (8 x 6 and 16 x 8: 8 Mbases of 100-base reads
+// What a build that sorts n_sort suffixes at once takes.  The default pair
+// leaves it to the library (so that the pair is all there is to a choice, and
+// cxbwt_set_tuning with what cxbwt_get_tuning gave restores a thread): from
+// LARGE_SORT suffixes on 16 x 8 (8 x 6 and 16 x 8: 8 Mbases of 100-base reads
 // 0.576 and 0.550 ms, 8.75 of 100 to 250 bases 0.622 and 0.644, 16 Mbases 1.18
 // and 0.93, 200 Mbases in four ranges 13.9 and 13.0).
 constexpr uint64_t LARGE_SORT = 12000000;
+constexpr uint32_t DEFAULT_TILE = 8, DEFAULT_CHUNK = 6;
+thread_local Tuning g_tuning{DEFAULT_TILE, DEFAULT_CHUNK};
+Tuning tuning_for(Tuning t, uint64_t n_sort) {
+  if (t.tile_items == DEFAULT_TILE && t.chunk_items == DEFAULT_CHUNK && n_sort >= LARGE_SORT) {
+    t.tile_items = 16;
+    t.chunk_items = 8;
+  }
+  return t;
+}
 
 // tile_items 16 is the wide tile: 8 waves x 8 items (4096 suffixes); the
 // histogram kernels take it as two sub-tiles of BLOCK * MAX_TILE_ITEMS
@@ -802,12 +811,7 @@ void build_init(Build &b, const uint64_t *packed, const uint64_t *offsets, uint6
   b.term_pos = term_pos;
   b.Lo = make_layout(n, nb, ncoll, m_sort, wide);
   b.B = buffers_of(ws, b.Lo);
-  b.tu = g_tuning;
-  // nobody chose: large sorts take the wide tile and the long chunk
-  if (!b.tu.chosen && b.Lo.sort_cap >= LARGE_SORT) {
-    b.tu.tile_items = 16;
-    b.tu.chunk_items = 8;
-  }
+  b.tu = tuning_for(g_tuning, b.Lo.sort_cap);
   b.rmax = maxlen / W + 1;
   b.tile_len = b.tu.tile_len();
   uint32_t *c = b.B.counters;
@@ -2298,7 +2302,6 @@ bool job_choices(const cxbwt_opts *opts, Tuning &tu, int &timing) {
   tu.tile_items = opts->tile_items;
   tu.chunk_items = opts->chunk_items;
   tu.schedule = opts->schedule;
-  tu.chosen = true;
   timing = opts->timing ? 1 : 0;
   return true;
 }
@@ -2580,7 +2583,6 @@ int cxbwt_set_tuning(uint32_t tile_items, uint32_t chunk_items) {
   if (!tuning_ok(tile_items, chunk_items)) return CXBWT_EINVAL;
   g_tuning.tile_items = tile_items;
   g_tuning.chunk_items = chunk_items;
-  g_tuning.chosen = true;
   return CXBWT_OK;
 }
 
@@ -2600,6 +2602,14 @@ int cxbwt_get_tuning(uint32_t *tile_items, uint32_t *chunk_items) {
   if (!tile_items || !chunk_items) return CXBWT_EINVAL;
   *tile_items = g_tuning.tile_items;
   *chunk_items = g_tuning.chunk_items;
+  return CXBWT_OK;
+}
+
+int cxbwt_build_tuning(uint64_t n_sort, uint32_t *tile_items, uint32_t *chunk_items) {
+  if (!tile_items || !chunk_items) return CXBWT_EINVAL;
+  const Tuning t = tuning_for(g_tuning, n_sort);
+  *tile_items = t.tile_items;
+  *chunk_items = t.chunk_items;
   return CXBWT_OK;
 }
 

@@ -27,11 +27,12 @@ NOALLOC_WORKSPACE_BYTES = 256 << 20
 ABI_FUNCTIONS = ("cxbwt_packed_words", "cxbwt_pack", "cxbwt_workspace_bytes", "cxbwt_build", "cxbwt_build_noalloc",
                  "cxbwt_range_workspace_bytes", "cxbwt_build_ranges", "cxbwt_batch_workspace_bytes", "cxbwt_build_batch",
                  "cxbwt_build_start", "cxbwt_build_batch_start", "cxbwt_job_done", "cxbwt_job_wait", "cxbwt_last_stats", "cxbwt_set_timing",
-                 "cxbwt_set_tuning", "cxbwt_get_tuning", "cxbwt_set_schedule", "cxbwt_get_schedule", "cxbwt_graph_create", "cxbwt_graph_launch",
+                 "cxbwt_set_tuning", "cxbwt_get_tuning", "cxbwt_build_tuning", "cxbwt_set_schedule", "cxbwt_get_schedule", "cxbwt_graph_create", "cxbwt_graph_launch",
                  "cxbwt_graph_finish", "cxbwt_graph_destroy", "cxbwt_status_str", "cxbwt_last_error")
 
 # kernel instantiations the library holds: (suffixes per thread in a level
-# tile, suffixes per lane in a chunk); the first is the default
+# tile, suffixes per lane in a chunk); the first is the default, which leaves
+# the choice to the library
 TUNING_CHOICES = ((8, 6), (8, 8), (8, 3), (6, 6), (6, 8), (6, 3), (16, 6), (16, 8), (16, 3))
 
 # sort schedules (cxbwt_set_schedule): MSD with tie refinement (default), and
@@ -119,6 +120,8 @@ def lib():
             L.cxbwt_set_tuning.restype = ctypes.c_int
             L.cxbwt_get_tuning.argtypes = [ctypes.POINTER(u32), ctypes.POINTER(u32)]
             L.cxbwt_get_tuning.restype = ctypes.c_int
+            L.cxbwt_build_tuning.argtypes = [u64, ctypes.POINTER(u32), ctypes.POINTER(u32)]
+            L.cxbwt_build_tuning.restype = ctypes.c_int
             L.cxbwt_set_schedule.argtypes = [u32]
             L.cxbwt_set_schedule.restype = ctypes.c_int
             L.cxbwt_get_schedule.argtypes = [ctypes.POINTER(u32)]
@@ -554,6 +557,15 @@ def get_tuning() -> tuple:
     st = lib().cxbwt_get_tuning(ctypes.byref(t), ctypes.byref(c))
     if st != 0:
         raise CxbwtError(st, "cxbwt_get_tuning")
+    return int(t.value), int(c.value)
+
+
+def build_tuning(n_sort: int) -> tuple:
+    """The instantiation a build on this thread that sorts n_sort suffixes at once would take."""
+    t, c = ctypes.c_uint32(), ctypes.c_uint32()
+    st = lib().cxbwt_build_tuning(int(n_sort), ctypes.byref(t), ctypes.byref(c))
+    if st != 0:
+        raise CxbwtError(st, "cxbwt_build_tuning")
     return int(t.value), int(c.value)
 
 
