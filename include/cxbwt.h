@@ -395,17 +395,18 @@ typedef struct cxbwt_stats {
  *                the largest run of small buckets finished in LDS is 64 x this
  * The output is the same for every choice; only speed differs.  (8, 6), the
  * default, leaves the choice to the library: (8, 6) for a build that sorts
- * few suffixes at once, (16, 8) from 12 million on.  CXBWT_EINVAL for other
+ * few suffixes at once, from 12 million on (16, 8), or (8, 8) where the mean
+ * collection of a batch is 2048 bases and less.  CXBWT_EINVAL for other
  * values.  cxbwt_get_tuning reads the current choice, and setting it again
- * restores the thread; cxbwt_build_tuning reads what a build that sorts n_sort
- * suffixes at once (its bases, or the most in one of its ranges) would take
- * (both CXBWT_EINVAL on NULL).  The workspace size does not depend on the
+ * restores the thread; cxbwt_build_tuning reads what a build of n_coll
+ * collections that sorts n_sort suffixes at once (its bases, or the most in
+ * one of its ranges) would take (both CXBWT_EINVAL on NULL, and on n_coll 0).  The workspace size does not depend on the
  * choice.  The autotuner in the Python package times the choices on a sample
  * of a workload and sets the fastest.
  */
 int cxbwt_set_tuning(uint32_t tile_items, uint32_t chunk_items);
 int cxbwt_get_tuning(uint32_t *tile_items, uint32_t *chunk_items);
-int cxbwt_build_tuning(uint64_t n_sort, uint32_t *tile_items, uint32_t *chunk_items);
+int cxbwt_build_tuning(uint64_t n_sort, uint32_t n_coll, uint32_t *tile_items, uint32_t *chunk_items);
 
 /*
  * cxbwt_set_schedule -- the sort schedule of later single-collection builds

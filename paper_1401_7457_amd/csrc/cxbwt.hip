@@ -75,18 +75,23 @@ struct Tuning {
   uint32_t chunk() const { return LOCAL_WG * chunk_items; }
 };
 
-// What a build that sorts n_sort suffixes at once takes.  The default pair
+// What a build of n_coll collections that sorts n_sort suffixes at once takes.  The default pair
 // leaves it to the library (so that the pair is all there is to a choice, and
 // cxbwt_set_tuning with what cxbwt_get_tuning gave restores a thread): from
 // LARGE_SORT suffixes on 16 x 8 (8 x 6 and 16 x 8: 8 Mbases of 100-base reads
 // 0.576 and 0.550 ms, 8.75 of 100 to 250 bases 0.622 and 0.644, 16 Mbases 1.18
-// and 0.93, 200 Mbases in four ranges 13.9 and 13.0).
+// and 0.93, 200 Mbases in four ranges 13.9 and 13.0).  Collections that do not
+// fill the narrow tile (2048 suffixes) keep it, and take the long chunk only:
+// each has a tile of its own (30 Mbases in collections of 1 kbase, 8 x 6, 8 x 8
+// and 16 x 8: 1.10, 1.11 and 1.21 ms, of 2 kbases 0.86, 0.84 and 0.88, of 3
+// kbases 0.82, 0.82 and 0.80; of 500 bases, which fit the long chunk, 1.69, 1.00
+// and 1.00).
 constexpr uint64_t LARGE_SORT = 12000000;
 constexpr uint32_t DEFAULT_TILE = 8, DEFAULT_CHUNK = 6;
 thread_local Tuning g_tuning{DEFAULT_TILE, DEFAULT_CHUNK};
-Tuning tuning_for(Tuning t, uint64_t n_sort) {
+Tuning tuning_for(Tuning t, uint64_t n_sort, uint64_t n_coll) {
   if (t.tile_items == DEFAULT_TILE && t.chunk_items == DEFAULT_CHUNK && n_sort >= LARGE_SORT) {
-    t.tile_items = 16;
+    t.tile_items = n_sort / n_coll > BLOCK * MAX_TILE_ITEMS ? 16 : 8;
     t.chunk_items = 8;
   }
   return t;
@@ -811,7 +816,7 @@ void build_init(Build &b, const uint64_t *packed, const uint64_t *offsets, uint6
   b.term_pos = term_pos;
   b.Lo = make_layout(n, nb, ncoll, m_sort, wide);
   b.B = buffers_of(ws, b.Lo);
-  b.tu = tuning_for(g_tuning, b.Lo.sort_cap);
+  b.tu = tuning_for(g_tuning, b.Lo.sort_cap, ncoll);
   b.rmax = maxlen / W + 1;
   b.tile_len = b.tu.tile_len();
   uint32_t *c = b.B.counters;
@@ -2605,9 +2610,9 @@ int cxbwt_get_tuning(uint32_t *tile_items, uint32_t *chunk_items) {
   return CXBWT_OK;
 }
 
-int cxbwt_build_tuning(uint64_t n_sort, uint32_t *tile_items, uint32_t *chunk_items) {
-  if (!tile_items || !chunk_items) return CXBWT_EINVAL;
-  const Tuning t = tuning_for(g_tuning, n_sort);
+int cxbwt_build_tuning(uint64_t n_sort, uint32_t n_coll, uint32_t *tile_items, uint32_t *chunk_items) {
+  if (!n_coll || !tile_items || !chunk_items) return CXBWT_EINVAL;
+  const Tuning t = tuning_for(g_tuning, n_sort, n_coll);
   *tile_items = t.tile_items;
   *chunk_items = t.chunk_items;
   return CXBWT_OK;

@@ -120,7 +120,7 @@ def lib():
             L.cxbwt_set_tuning.restype = ctypes.c_int
             L.cxbwt_get_tuning.argtypes = [ctypes.POINTER(u32), ctypes.POINTER(u32)]
             L.cxbwt_get_tuning.restype = ctypes.c_int
-            L.cxbwt_build_tuning.argtypes = [u64, ctypes.POINTER(u32), ctypes.POINTER(u32)]
+            L.cxbwt_build_tuning.argtypes = [u64, u32, ctypes.POINTER(u32), ctypes.POINTER(u32)]
             L.cxbwt_build_tuning.restype = ctypes.c_int
             L.cxbwt_set_schedule.argtypes = [u32]
             L.cxbwt_set_schedule.restype = ctypes.c_int
@@ -560,10 +560,10 @@ def get_tuning() -> tuple:
     return int(t.value), int(c.value)
 
 
-def build_tuning(n_sort: int) -> tuple:
-    """The instantiation a build on this thread that sorts n_sort suffixes at once would take."""
+def build_tuning(n_sort: int, n_coll: int = 1) -> tuple:
+    """The instantiation a build on this thread of n_coll collections that sorts n_sort suffixes at once would take."""
     t, c = ctypes.c_uint32(), ctypes.c_uint32()
-    st = lib().cxbwt_build_tuning(int(n_sort), ctypes.byref(t), ctypes.byref(c))
+    st = lib().cxbwt_build_tuning(int(n_sort), int(n_coll), ctypes.byref(t), ctypes.byref(c))
     if st != 0:
         raise CxbwtError(st, "cxbwt_build_tuning")
     return int(t.value), int(c.value)

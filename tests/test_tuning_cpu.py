@@ -30,8 +30,16 @@ def test_saved_and_set_again_is_what_it_was():
 def test_null_pointers_are_refused():
     v = ctypes.c_uint32()
     L = cxbwt.lib()
-    assert L.cxbwt_build_tuning(10, None, ctypes.byref(v)) == cxbwt.EINVAL
-    assert L.cxbwt_build_tuning(10, ctypes.byref(v), None) == cxbwt.EINVAL
+    assert L.cxbwt_build_tuning(10, 1, None, ctypes.byref(v)) == cxbwt.EINVAL
+    assert L.cxbwt_build_tuning(10, 1, ctypes.byref(v), None) == cxbwt.EINVAL
+    assert L.cxbwt_build_tuning(10, 0, ctypes.byref(v), ctypes.byref(v)) == cxbwt.EINVAL
+
+
+@pytest.mark.parametrize("mean,tile", [(500, 8), (2048, 8), (2049, 16), (100_000, 16)])
+def test_collections_below_a_tile_keep_the_narrow_one(mean, tile):
+    for count in (10_000, 100_000):
+        got = cxbwt.build_tuning(mean * count, count)
+        assert got == ((tile, 8) if mean * count >= 12_000_000 else cxbwt.TUNING_CHOICES[0])
 
 
 @pytest.mark.parametrize("ms,best", [({(8, 6): 1.01, (16, 8): 1.0, (8, 3): 1.4}, (8, 6)),
