@@ -1526,17 +1526,15 @@ StepPlan plan_step(StepBlob &blob, const std::vector<std::vector<IndSeg>> &src) 
 constexpr size_t INDUCE_CARRIED = 400;
 bool pick_induced(const Build &b, std::vector<Seg> &large, std::vector<Seg> &rest) {
   const uint64_t least = CXBWT_INDUCE_COLL_CHUNKS * b.tu.chunk();
+  auto is_large = [&](const Seg &g) { return b.ncoll == 1 || g.len >= least; };
   uint64_t bases = 0;
+  size_t small = 0;
   for (const Seg &g : b.big) {
-    const bool is = b.ncoll == 1 || g.len >= least;
-    (is ? large : rest).push_back(g);
-    if (is) bases += g.len;
+    if (is_large(g)) bases += g.len;
+    else ++small;
   }
   if (bases < CXBWT_INDUCE_MIN_BASES) return false;
-  if (rest.size() <= INDUCE_CARRIED) {
-    large = b.big;
-    rest.clear();
-  }
+  for (const Seg &g : b.big) (small <= INDUCE_CARRIED || is_large(g) ? large : rest).push_back(g);
   return true;
 }
 
