@@ -312,11 +312,13 @@ int cxbwt_job_done(const cxbwt_job *job);
  * cxbwt_graph_create -- capture a build.  Arguments as cxbwt_build_batch
  *   (coll_reads may be NULL with n_coll == 1 for a single collection), plus
  *   levels        sort levels scheduled inside the graph, level 1 included;
- *                 0 = as many as the build at creation took and two more
- *                 (small builds: three; at most 8 per 27-base window, plus
- *                 2).  Each scheduled level that finds no work costs a few
- *                 empty launches; levels that a replay needs beyond them run
- *                 in cxbwt_graph_finish.
+ *                 0 = enough for any input of max_read_len (at most 8 per
+ *                 27-base window, plus half of the levels that the build at
+ *                 creation took).  Each scheduled level that finds no work
+ *                 costs a few empty launches (about 10 us): a caller whose
+ *                 contents are alike passes the levels that an eager build of
+ *                 them took (cxbwt_last_stats); levels that a replay needs
+ *                 beyond them run in cxbwt_graph_finish.
  *   stream        the caller's stream: creation first runs one eager build
  *                 on it (it writes bwt and term_pos) and waits; the counts
  *                 each of its levels saw size the captured launches (larger
@@ -330,6 +332,8 @@ int cxbwt_job_done(const cxbwt_job *job);
  * (invalid offsets found by the eager pass) or CXBWT_EDEVICE.
  *
  * cxbwt_graph_launch -- enqueue one replay on `stream` and return at once.
+ *   Its outputs are complete in stream order, except in the two cases that
+ *   cxbwt_graph_finish completes (below).
  *
  * cxbwt_graph_finish -- wait for the replay on `stream`, check it and read
  *   its statistics (cxbwt_last_stats).  If the input needed more levels than

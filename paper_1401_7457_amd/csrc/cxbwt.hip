@@ -822,7 +822,7 @@ void build_init(Build &b, const uint64_t *packed, const uint64_t *offsets, uint6
   uint32_t *c = b.B.counters;
   b.Ls = Lists{b.B.big_next, c + C_NBIG, (uint32_t)b.Lo.cap_big, b.B.chunks, (unsigned long long *)(c + C_NCHUNK),
                (uint32_t)b.Lo.cap_chunks, b.B.finals, c + C_NFINAL, (uint32_t)b.Lo.cap_finals, c + C_STATUS, b.rmax,
-               b.B.stats, b.tu.chunk(), b.tu.chunk(), b.tile_len};
+               b.B.stats, b.tu.chunk(), b.tu.chunk(), b.tile_len, 1};
   b.coll_reads.assign(coll_reads, coll_reads + ncoll + 1);
   b.planned = ncoll == 1;
 }
@@ -1026,7 +1026,7 @@ int finish_rest(const Build &b, LevelRest &rest, PhaseTimer &T, hipStream_t st) 
 // two: 20 Mbases at 2000x, 17 levels, 5.65 -> 5.07 ms; 200 Mbases in four
 // ranges 13.0 -> 12.6; 400 Mbases, 5 levels, 11.6 -> 11.4).  Two levels then share the lists: with chunks of 512 a
 // level makes at most nb / 128 chunks and nb / 513 groups (four lists' worth of
-// S / C as in lists_hold_all, and the samples, packed by 256, are at most half
+// S / C as for LISTED_LEVELS, and the samples, packed by 256, are at most half
 // of nb), and half of the lists holds nb / 96 and nb / 386.  Smaller chunks are
 // finished at once.
 int run_levels(const Build &b, LevelOut acc, bool first, PhaseTimer &T, hipStream_t st) {
@@ -1115,15 +1115,25 @@ int run_levels(const Build &b, LevelOut acc, bool first, PhaseTimer &T, hipStrea
   return finish_rest(b, rest, T, st);
 }
 
-// Whether the chunks and final groups of `levels` levels fit their lists
-// together.  A level makes at most 2 S / C chunks of the S suffixes that leave
-// it in chunks of up to C, plus one for every segment it splits and every
-// large bucket (each of more than C suffixes) it makes: over three levels at
-// most 7 nb / C, which for C = 384 is less than the 4 nb / 192 that the list
-// holds for one level of the smallest chunks.  Final groups are disjoint.
-bool lists_hold_all(const Build &b, uint32_t levels) {
-  return b.tu.chunk_items >= 6 && levels <= 3 && b.Lo.seg_slots <= NEXT_SEGS &&
-         b.Lo.cap_finals + 1 <= 256 * b.Lo.max_groups;  // their tile prefixes
+// Levels whose chunks and final groups stay in their lists together: those of
+// any three in a row fit.  A level makes at most 2 S / C chunks of the S
+// suffixes that leave it in chunks of up to C, plus one for every segment it
+// splits and every large bucket (each of more than C suffixes) it makes: over
+// three levels at most 7 nb / C, which for C = 384 is less than the 4 nb / 192
+// that the list holds for one level of the smallest chunks.  Final groups are
+// disjoint.
+constexpr uint32_t LISTED_LEVELS = 3;
+// Most levels of a build that splits by the windows' own digits alone: eight a
+// window, and in the last one, of which reads hold rem bases, those of its
+// bases, one that finds the digits after them constant, and the length.
+uint32_t most_levels(uint32_t maxlen) {
+  const uint32_t d = (maxlen % W + 3) / 4;
+  return 8 * (maxlen / W) + d + (d < 7 ? 1 : 0) + 1;
+}
+// Whether a build's levels can be listed.
+bool levels_listed(const Build &b) {
+  return b.tu.chunk_items >= 6 && b.Lo.seg_slots <= NEXT_SEGS &&
+         b.Lo.cap_finals + 1 <= 256 * b.Lo.max_groups;  // the groups' tile prefixes
 }
 
 // Levels scheduled at once for a build that the host will only look at when
@@ -1133,50 +1143,73 @@ uint32_t levels_ahead(const Build &b) {
   return b.nb <= 16ull * b.tu.chunk() ? 1u : b.nb <= 256ull * b.tu.chunk() ? 2u : 3u;
 }
 
+// The lists of a level whose number is `level` among `ended`: the segments it
+// makes are those of level + 1.
+Lists lists_for(const Build &b, uint32_t level, uint32_t ended) {
+  Lists Ls = b.Ls;
+  Ls.ended = level < ended;
+  return Ls;
+}
+
 // After level 1's scan and scatter: the rest of `levels` levels sized on the
-// device, then all their chunks and final groups.  Five launches a level.
-// Grids cover the counts seen (or the most that level 2 can have; later
-// levels of a small build hold little); every kernel loops.
-int enqueue_listed_levels(const Build &b, uint32_t levels, PhaseTimer &T, hipStream_t st,
+// device, five launches each, and every LISTED_LEVELS of them the chunks and
+// final groups they listed.  Grids cover the counts seen (or the most that
+// level 2 can have; later levels of a small build hold little, and those past
+// LISTED_LEVELS that nothing was seen of are there for the rare input: two
+// workgroups a CU); every kernel loops.
+int enqueue_listed_levels(const Build &b, uint32_t levels, uint32_t ended, PhaseTimer &T, hipStream_t st,
                           const std::vector<LevelShape> *shapes) {
+  constexpr uint32_t RARE = 512;
   const Buffers &B = b.B;
   const Layout &Lo = b.Lo;
   const uint64_t nb = b.nb, chunk = b.tu.chunk();
+  auto seen = [&](uint32_t lv) { return shapes && lv < shapes->size(); };
   int rc;
   uint32_t seen_chunks = 0;
   for (uint32_t lv = 0;; ++lv) {
-    if (shapes && lv < shapes->size()) seen_chunks += (*shapes)[lv].nchunks;
-    const int last = lv + 1 == levels;
+    if (seen(lv)) seen_chunks += (*shapes)[lv].nchunks;
+    const int last = lv + 1 == levels, flush = last || (lv + 1) % LISTED_LEVELS == 0;
     k_next_level<<<1, NEXT_WG, 0, st>>>(B.counters, B.stats, B.big_next, B.segs, B.tile_prefix, B.group_prefix, B.seg_or,
                                         B.seg_and, b.tile_len, Lo.seg_slots, Lo.max_tiles, Lo.max_groups, B.finals,
-                                        (uint32_t)Lo.cap_finals, B.gsum, last);
+                                        (uint32_t)Lo.cap_finals, B.gsum, (uint32_t)Lo.cap_chunks, flush, last);
     CX_LAUNCHED();
+    if (flush) {
+      const bool rare = lv >= LISTED_LEVELS && !seen_chunks;
+      T.begin();
+      // chunks hold two thirds of a chunk's suffixes and more on average; a small
+      // build takes the looping kernel alone
+      const uint64_t expect = rare ? RARE : std::max<uint64_t>(seen_chunks, 3 * nb / (2 * chunk) + 1);
+      if ((rc = launch_local(B, b.tu, nb, b.rmax, b.bwt, (uint32_t)Lo.cap_chunks, B.counters + C_LCHUNK, st,
+                             rare || nb <= 1u << 20 ? 0u : grid_from((uint32_t)expect, 0), (unsigned)expect)))
+        return rc;
+      T.end(PH_LOCAL);
+      T.begin();
+      const uint64_t groups = rare ? 64 : std::min<uint64_t>(PG_EMIT, nb / (2 * chunk) + 16);
+      k_emit_final<true><<<(unsigned)groups, BLOCK, 0, st>>>(B.finals, B.gsum, 0, B.counters + C_LFINAL, b.tile_len,
+                                                            B.keys0, B.keys1, B.hdl0, B.hdl1, B.pos64, B.text, B.srank,
+                                                            B.cmap, b.bwt, B.start_row);
+      CX_LAUNCHED();
+      T.end(PH_FINAL);
+      seen_chunks = 0;
+    }
     if (last) break;
     LevelShape sh;
-    if (shapes && lv + 1 < shapes->size()) {
+    if (seen(lv + 1)) {
       sh = (*shapes)[lv + 1];
     } else {
       const uint64_t segs = std::min<uint64_t>(256ull * b.big.size(), nb / (chunk + 1) + 1);
       sh.nsegs = (uint32_t)(lv == 0 ? segs : segs / 8 + 1);
       sh.ntiles = (uint32_t)((lv == 0 ? nb : nb / 8) / b.tile_len + sh.nsegs);
       sh.ngroups = (uint32_t)(sh.ntiles / GROUP_TILES + sh.nsegs);
+      if (lv + 1 >= LISTED_LEVELS) {
+        sh.nsegs = std::min(sh.nsegs, RARE);
+        sh.ntiles = std::min(sh.ntiles, RARE);
+        sh.ngroups = std::min(sh.ngroups, RARE);
+      }
     }
-    if ((rc = launch_level_kernels(B, b.tu, b.Ls, nb, 0, 0, 0, B.counters + C_NCUR, T, st, &sh))) return rc;
+    if ((rc = launch_level_kernels(B, b.tu, lists_for(b, lv + 2, ended), nb, 0, 0, 0, B.counters + C_NCUR, T, st, &sh)))
+      return rc;
   }
-  T.begin();
-  // chunks hold two thirds of a chunk's suffixes and more on average; a small
-  // build takes the looping kernel alone
-  const uint64_t expect = std::max<uint64_t>(seen_chunks, 3 * nb / (2 * chunk) + 1);
-  if ((rc = launch_local(B, b.tu, nb, b.rmax, b.bwt, (uint32_t)Lo.cap_chunks, B.counters + C_NCHUNK, st,
-                         nb <= 1u << 20 ? 0u : grid_from((uint32_t)expect, 0), (unsigned)expect)))
-    return rc;
-  T.end(PH_LOCAL);
-  T.begin();
-  k_emit_final<true><<<(unsigned)std::min<uint64_t>(PG_EMIT, nb / (2 * chunk) + 16), BLOCK, 0, st>>>(
-      B.finals, B.gsum, 0, B.counters + C_NFINAL, b.tile_len, B.keys0, B.keys1, B.hdl0, B.hdl1, B.pos64, B.text, B.srank,
-      B.cmap, b.bwt, B.start_row);
-  CX_LAUNCHED();
-  T.end(PH_FINAL);
   return CXBWT_OK;
 }
 
@@ -1185,9 +1218,10 @@ int enqueue_listed_levels(const Build &b, uint32_t levels, PhaseTimer &T, hipStr
 // with a counter readback per level, or the next device_levels levels are
 // enqueued with their sizes read on the device (no host wait: the whole
 // sequence can be captured), followed by a last step that flags segments
-// left over.  Ends with term_pos.
+// left over.  The first `ended` levels split off ended suffixes first.  Ends
+// with term_pos.
 int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, PhaseTimer &T, hipStream_t st,
-                 const std::vector<LevelShape> *shapes = nullptr) {
+                 const std::vector<LevelShape> *shapes = nullptr, uint32_t ended = ~0u) {
   const Buffers &B = b.B;
   const Layout &Lo = b.Lo;
   uint32_t *counters = B.counters;
@@ -1228,7 +1262,7 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
     T.begin();
     k_group_scan<false><<<ngroups, BLOCK, 0, st>>>(B.tile_prefix, B.group_prefix, ns, nullptr, B.tile_hist, B.gsum);
     CX_LAUNCHED();
-    launch_level_scan(B, ns, ngroups, b.Ls, 1, st);
+    launch_level_scan(B, ns, ngroups, lists_for(b, 1, ended), 1, st);
     CX_LAUNCHED();
     T.end(PH_SCAN);
     T.begin();
@@ -1246,8 +1280,8 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
       if ((rc = read_level(B, o, T, st))) return rc;
       record_shape(0, LevelShape{ns, ntiles, ngroups, o.n_chunks, o.n_finals, (uint32_t)o.final_tiles});
       if ((rc = run_levels(b, o, true, T, st))) return rc;
-    } else if (lists_hold_all(b, device_levels)) {
-      if ((rc = enqueue_listed_levels(b, device_levels, T, st, shapes))) return rc;
+    } else if (levels_listed(b)) {
+      if ((rc = enqueue_listed_levels(b, device_levels, ended, T, st, shapes))) return rc;
     } else {
       const uint32_t *ncur = counters + C_NCUR;
       const LevelShape none;
@@ -1276,7 +1310,8 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
           return rc;
         k_fill_seg<<<PG_FILL, 256, 0, st>>>(B.seg_or, B.seg_and, ncur);
         CX_LAUNCHED();
-        if ((rc = launch_level_kernels(B, b.tu, b.Ls, nb, 0, 0, 0, ncur, T, st, &seen(lv + 1)))) return rc;
+        if ((rc = launch_level_kernels(B, b.tu, lists_for(b, lv + 2, ended), nb, 0, 0, 0, ncur, T, st, &seen(lv + 1))))
+          return rc;
       }
     }
   }
@@ -1822,7 +1857,7 @@ int run_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n, uint6
   // small builds run their levels without a look from the host in between;
   // for one collection it need not look at the offsets' verdict either
   // (kernels stay in bounds on invalid offsets, as in a replayed graph)
-  const bool ahead = msd && !induce && lists_hold_all(b, levels_ahead(b));
+  const bool ahead = msd && !induce && levels_listed(b);
   int rc;
   if ((rc = enqueue_prep(b, b.coll_reads.data(), nullptr, T, st))) return rc;
   if ((rc = enqueue_records(b, T, st))) return rc;
@@ -2203,18 +2238,22 @@ int graph_capture(GraphPlan &P, hipStream_t st) {
   src.small = SegSrc{(const Seg *)(h + o_ss), (const uint32_t *)(h + o_stp), (const uint32_t *)(h + o_sgp),
                      (uint32_t)nsm, v.stp.back(), v.sgp.back()};
   src.nsmall = (const uint32_t *)(h + o_ns);
-  // levels by default: as many as this build took and two more (a replay that
-  // needs more is completed by graph_finish); three when all can be listed,
-  // which is then their cheapest form
-  if (!P.levels) {
-    const uint32_t took = (uint32_t)P.shapes.size();
-    P.levels = took <= 3 && lists_hold_all(b, 3) ? 3 : std::min(took + 2, 8 * b.rmax + 2);
+  // levels by default: enough for any input, and those that are spent on ended
+  // suffixes, every other one at most of the first ones.  These are as many as
+  // this build took (three where that is the form anyway): past them ended
+  // suffixes are not split off.  (1 Mbase of 100-base reads, which takes 3: 32
+  // scheduled, 500 us a replay, where 3 take 225.)
+  uint32_t ended = ~0u;
+  const uint32_t full = most_levels(b.maxlen);
+  if (!P.levels || P.levels >= full) {
+    ended = std::min(std::max((uint32_t)P.shapes.size(), LISTED_LEVELS), full);
+    P.levels = std::max(P.levels, full + ended / 2);
   }
   // capture: every size below is fixed now or read on the device
   CX_CHECK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
   rc = enqueue_prep(b, (const uint64_t *)(h + o_cr), (const uint64_t *)(h + o_cb), T, st);
   if (!rc) rc = enqueue_records(b, T, st);
-  if (!rc) rc = enqueue_body(b, src, P.levels ? P.levels : 1, T, st, &P.shapes);
+  if (!rc) rc = enqueue_body(b, src, P.levels, T, st, &P.shapes, ended);
   hipGraph_t g = nullptr;
   const hipError_t ec = hipStreamEndCapture(st, &g);
   if (rc) {

@@ -40,8 +40,10 @@ constexpr uint32_t ST_PLAN_MISMATCH = 32u;  // inputs no longer match a captured
 // block are folded into the 64-bit words from C_FOLD on; a build whose
 // levels are scheduled on the device keeps its running totals (G_*) from
 // C_CUM on.
-enum { C_STATUS = 0, C_NFINAL = 1, C_NCHUNK = 2, C_NBIG = 3, C_NCUR = 4, C_FLAGS = 5, C_FOLD = 16, C_CUM = 32,
-       C_TOTALS = 52, C_COUNT = 64 };  // C_TOTALS: window fetches, scattered suffixes (k_term)
+// C_LCHUNK, C_LFINAL: the entries of the chunk and group lists to be finished
+// (k_next_level).  C_TOTALS: window fetches, scattered suffixes (k_term).
+enum { C_STATUS = 0, C_NFINAL = 1, C_NCHUNK = 2, C_NBIG = 3, C_NCUR = 4, C_FLAGS = 5, C_LCHUNK = 6, C_LFINAL = 7,
+       C_FOLD = 16, C_CUM = 32, C_TOTALS = 52, C_COUNT = 64 };
 enum { G_LEVELS, G_BIGSEG, G_LEVSUF, G_REGATH, G_MAXWIN, G_CHUNKS, G_FINALS, G_FINLEN, G_BATCHES, G_COUNT };
 constexpr uint32_t FL_STALLED = 1u;     // a level did not fit the scratch: the host finishes the build
 constexpr uint32_t FL_INCOMPLETE = 2u;  // segments remain after the last scheduled level
@@ -115,6 +117,7 @@ struct Lists {
   uint32_t chunk;  // largest run finished by one wave (the selected chunk size)
   uint32_t pack;   // several buckets make one chunk up to this size
   uint32_t tile_len;  // suffixes per level tile
+  uint32_t ended;     // whether ended suffixes are split off before a digit (see ENDED)
 };
 
 // Key formats of the level kernels: which bits order, how they fall into
@@ -1213,7 +1216,7 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
     // split off; before digit d + 1 of bucket 0 they are split off first
     const auto next_digit = [&](uint32_t bucket) {
       if (ended) return sd;
-      return (uint8_t)(bucket == 0 && !sg.plain && sd + 1 < F::LAST ? (sd + 1) | ENDED : sd + 1);
+      return (uint8_t)(L.ended && bucket == 0 && !sg.plain && sd + 1 < F::LAST ? (sd + 1) | ENDED : sd + 1);
     };
     uint32_t pb = 0, pf = 0;  // entries of the lower slots
 #pragma unroll
@@ -1322,10 +1325,11 @@ __global__ void k_level_step(uint32_t *__restrict__ c, uint64_t seg_slots, uint6
 // The same step, with k_level_fold's work before it and k_seg_count's,
 // k_seg_scan's and k_fill_seg's after it, in one workgroup: for builds whose
 // per-segment scratch holds few segments, where a launch costs more than the
-// list.  The chunks and final groups of all levels stay in their lists, for
-// one launch each after the last level, before which it writes the groups'
-// tile prefixes to `fprefix`, the scan groups' totals area, which is free
-// then.  (The groups' rows are given out by the tile.  With a workgroup a
+// list.  The chunks and final groups of the levels stay in their lists until
+// `flush`, for one launch each: their counts go to C_LCHUNK and C_LFINAL, the
+// lists begin again, and the groups' tile prefixes are written to `fprefix`,
+// the scan groups' totals area, which is free until the next level.  (The
+// groups' rows are given out by the tile.  With a workgroup a
 // group, a build of 15 M reads of one base, four groups, took 16.2 ms, and 1.44
 // so; 640000 copies of a read of 25 bases 3.14 and 0.47; 1 Mbase of 100-base
 // reads the same.)
@@ -1339,14 +1343,17 @@ __global__ __launch_bounds__(NEXT_WG) void k_next_level(uint32_t *__restrict__ c
                                                         unsigned long long *__restrict__ seg_and, uint32_t tile_len,
                                                         uint64_t seg_slots, uint64_t max_tiles, uint64_t max_groups,
                                                         const Seg *__restrict__ finals, uint32_t cap_finals,
-                                                        uint32_t *__restrict__ fprefix, int last) {
+                                                        uint32_t *__restrict__ fprefix, uint32_t cap_chunks, int flush,
+                                                        int last) {
   constexpr int NW = NEXT_WG / 64;
   __shared__ unsigned long long f[K_LEVEL_KINDS];
   __shared__ uint32_t tmp[NW];
   __shared__ uint32_t cur;
   const uint32_t w = threadIdx.x >> 6, l = lane_id();
-  if (last) {
-    const uint32_t n = min(c[C_NFINAL], cap_finals);
+  unsigned long long *const g = reinterpret_cast<unsigned long long *>(c + C_CUM);
+  const uint32_t flags = c[C_FLAGS];
+  if (flush) {
+    const uint32_t nc = min(c[C_NCHUNK], cap_chunks), n = min(c[C_NFINAL], cap_finals);
     uint32_t tiles = 0;
     for (uint32_t i0 = 0; i0 < n; i0 += NEXT_WG) {
       const uint32_t i = i0 + threadIdx.x;
@@ -1355,9 +1362,18 @@ __global__ __launch_bounds__(NEXT_WG) void k_next_level(uint32_t *__restrict__ c
       if (i < n) fprefix[i] = tiles + e;
       tiles += total;
     }
-    if (threadIdx.x == 0) fprefix[n] = tiles;
+    __syncthreads();  // every wave has read the counts
+    if (threadIdx.x == 0) {
+      fprefix[n] = tiles;
+      c[C_LCHUNK] = nc;
+      c[C_LFINAL] = n;
+      c[C_NCHUNK] = 0;
+      c[C_NFINAL] = 0;
+      g[G_CHUNKS] += nc;
+      g[G_FINALS] += n;
+    }
   }
-  if (c[C_FLAGS] & (FL_STALLED | FL_INCOMPLETE)) return;  // keep what the host resumes from
+  if (flags & (FL_STALLED | FL_INCOMPLETE)) return;  // keep what the host resumes from
   if (w < (uint32_t)K_LEVEL_KINDS) {
     unsigned long long *slot = stats + (K_LEVEL_FIRST + w) * STAT_KIND + (uint64_t)l * STAT_STRIDE;
     unsigned long long v = *slot;
@@ -1374,9 +1390,6 @@ __global__ __launch_bounds__(NEXT_WG) void k_next_level(uint32_t *__restrict__ c
   if (threadIdx.x == 0) {
     unsigned long long *const out = reinterpret_cast<unsigned long long *>(c + C_FOLD);
     for (int k = 0; k < K_LEVEL_KINDS; ++k) out[k] = f[k];
-    unsigned long long *g = reinterpret_cast<unsigned long long *>(c + C_CUM);
-    g[G_CHUNKS] = c[C_NCHUNK];
-    g[G_FINALS] = c[C_NFINAL];
     g[G_FINLEN] += f[K_FINAL_LEN - K_LEVEL_FIRST];
     const uint32_t nbig = c[C_NBIG];
     cur = 0;

@@ -422,7 +422,14 @@ class BuildGraph:
     sizes, same bases per collection) and call run() (or launch() then
     finish()) for each build; the result lands in `bwt` / `term`.
     coll_reads: host read boundaries of the collections, or None for one.
-    levels: sort levels scheduled inside the graph (0: enough for any input).
+    levels: sort levels scheduled inside the graph (0: enough for any input;
+    each costs about 10 us where it finds no work, so a caller whose contents
+    are alike passes the `levels` that last_stats() gave for an eager build).
+
+    After launch() the outputs are complete in stream order, but where the
+    scheduled levels were not enough, or a level had more segments than the
+    scratch holds in one batch: finish() waits, completes those and raises on
+    invalid contents, so outputs are to be used after it.
     """
 
     def __init__(self, packed, offsets, n_reads: int, n_bases: int, max_read_len: int, coll_reads=None,
