@@ -238,6 +238,19 @@ int fail_status(uint32_t status) {
   return CXBWT_EDEVICE;
 }
 
+// A C entry's work: no C++ exception (host memory that has run out) leaves it,
+// and the device is through with the caller's buffers when it returns.
+template <class Work>
+int guarded(hipStream_t st, Work work) {
+  try {
+    return work();
+  } catch (...) {
+    (void)hipStreamSynchronize(st);
+    snprintf(g_last_error, sizeof(g_last_error), "out of host memory");
+    return CXBWT_EDEVICE;
+  }
+}
+
 #define CX_CHECK(x)                                                        \
   do {                                                                     \
     const hipError_t cx_e_ = (x);                                          \
@@ -563,6 +576,10 @@ struct LevelShape {
   uint32_t nsegs = 0, ntiles = 0, ngroups = 0, nchunks = 0, nfinals = 0, ftiles = 0;
 };
 thread_local std::vector<LevelShape> *g_shapes = nullptr;  // recorder of an eager build, when set
+struct ShapeScope {
+  explicit ShapeScope(std::vector<LevelShape> *to) { g_shapes = to; }
+  ~ShapeScope() { g_shapes = nullptr; }
+};
 
 void record_shape(uint32_t level, const LevelShape &x) {
   if (!g_shapes) return;
@@ -2199,9 +2216,10 @@ int graph_capture(GraphPlan &P, hipStream_t st) {
   level1_stats(b);
   P.base = g_stats;
   P.shapes.clear();
-  g_shapes = &P.shapes;
-  rc = enqueue_body(b, v.src, 0, T, st);
-  g_shapes = nullptr;
+  {
+    ShapeScope record(&P.shapes);
+    rc = enqueue_body(b, v.src, 0, T, st);
+  }
   uint32_t hc[C_COUNT];
   if (!rc) rc = read_totals(b, T, st, hc);
   if (rc) return rc;
@@ -2455,8 +2473,10 @@ int cxbwt_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n_read
   if (!job_choices(opts, tu, timing)) return CXBWT_EINVAL;
   ChoiceScope scope(tu, timing);
   const uint64_t one[2] = {0, n_reads};
-  return run_build(packed, offsets, n_reads, n_bases, max_read_len, one, 1, bwt, term_pos, (unsigned char *)workspace,
-                   (hipStream_t)stream);
+  return guarded((hipStream_t)stream, [&] {
+    return run_build(packed, offsets, n_reads, n_bases, max_read_len, one, 1, bwt, term_pos, (unsigned char *)workspace,
+                     (hipStream_t)stream);
+  });
 }
 
 int cxbwt_build_noalloc(const uint64_t *packed, const uint64_t *offsets, uint64_t n_reads, uint64_t n_bases,
@@ -2469,8 +2489,10 @@ int cxbwt_build_noalloc(const uint64_t *packed, const uint64_t *offsets, uint64_
   if (rc) return rc;
   const uint64_t one[2] = {0, n_reads};
   // no kernel timing here: it would create HIP events
-  return run_build(packed, offsets, n_reads, n_bases, max_read_len, one, 1, bwt, term_pos, ws, (hipStream_t)stream,
-                   false);
+  return guarded((hipStream_t)stream, [&] {
+    return run_build(packed, offsets, n_reads, n_bases, max_read_len, one, 1, bwt, term_pos, ws, (hipStream_t)stream,
+                     false);
+  });
 }
 
 size_t cxbwt_range_workspace_bytes(uint64_t n_reads, uint64_t n_bases, uint32_t max_read_len,
@@ -2489,8 +2511,10 @@ int cxbwt_build_ranges(const uint64_t *packed, const uint64_t *offsets, uint64_t
   if (workspace_bytes < cxbwt_range_workspace_bytes(n_reads, n_bases, max_read_len, max_range_suffixes, flags))
     return CXBWT_ENOMEM;
   if (((uintptr_t)workspace & 255u) != 0) return CXBWT_EINVAL;
-  return run_range_build(packed, offsets, n_reads, n_bases, max_read_len, max_range_suffixes,
-                         range_wide(n_bases, flags), bwt, term_pos, (unsigned char *)workspace, (hipStream_t)stream);
+  return guarded((hipStream_t)stream, [&] {
+    return run_range_build(packed, offsets, n_reads, n_bases, max_read_len, max_range_suffixes,
+                           range_wide(n_bases, flags), bwt, term_pos, (unsigned char *)workspace, (hipStream_t)stream);
+  });
 }
 
 int cxbwt_build_start(const uint64_t *packed, const uint64_t *offsets, uint64_t n_reads, uint64_t n_bases,
@@ -2523,11 +2547,13 @@ int cxbwt_build_batch_start(const uint64_t *packed, const uint64_t *offsets, uin
     if (coll_reads[c + 1] <= coll_reads[c]) return CXBWT_EINVAL;
   if (workspace_bytes < cxbwt_batch_workspace_bytes(n_reads, n_bases, max_read_len, n_coll)) return CXBWT_ENOMEM;
   if (((uintptr_t)workspace & 255u) != 0) return CXBWT_EINVAL;
-  JobArgs a{packed, offsets, n_reads, n_bases, max_read_len,
-            std::vector<uint64_t>(coll_reads, coll_reads + n_coll + 1), bwt, term_pos,
-            (unsigned char *)workspace, (hipStream_t)stream, 0, Tuning{8, 6}, 0};
-  if (!job_choices(opts, a.tu, a.timing)) return CXBWT_EINVAL;
-  return start_job(std::move(a), job);
+  return guarded((hipStream_t)stream, [&] {
+    JobArgs a{packed, offsets, n_reads, n_bases, max_read_len,
+              std::vector<uint64_t>(coll_reads, coll_reads + n_coll + 1), bwt, term_pos,
+              (unsigned char *)workspace, (hipStream_t)stream, 0, Tuning{8, 6}, 0};
+    if (!job_choices(opts, a.tu, a.timing)) return (int)CXBWT_EINVAL;
+    return start_job(std::move(a), job);
+  });
 }
 
 int cxbwt_job_done(const cxbwt_job *job) { return job && job->done.load(std::memory_order_acquire) ? 1 : 0; }
@@ -2560,8 +2586,10 @@ int cxbwt_build_batch(const uint64_t *packed, const uint64_t *offsets, uint64_t 
   int timing = 0;
   if (!job_choices(opts, tu, timing)) return CXBWT_EINVAL;
   ChoiceScope scope(tu, timing);
-  return run_build(packed, offsets, n_reads, n_bases, max_read_len, coll_reads, n_coll, bwt, term_pos,
-                   (unsigned char *)workspace, (hipStream_t)stream);
+  return guarded((hipStream_t)stream, [&] {
+    return run_build(packed, offsets, n_reads, n_bases, max_read_len, coll_reads, n_coll, bwt, term_pos,
+                     (unsigned char *)workspace, (hipStream_t)stream);
+  });
 }
 
 int cxbwt_graph_create(const uint64_t *packed, const uint64_t *offsets, uint64_t n_reads, uint64_t n_bases,
@@ -2584,8 +2612,6 @@ int cxbwt_graph_create(const uint64_t *packed, const uint64_t *offsets, uint64_t
   if (((uintptr_t)workspace & 255u) != 0) return CXBWT_EINVAL;
   cxbwt_graph *g = new (std::nothrow) cxbwt_graph;
   if (!g) return CXBWT_ENOMEM;
-  build_init(g->p.b, packed, offsets, n_reads, n_bases, max_read_len, coll_reads, n_coll, bwt, term_pos,
-             (unsigned char *)workspace);
   g->p.levels = levels;
   // the eager pass runs on the caller's stream; the capture on a stream of
   // its own (a capture needs a non-default stream)
@@ -2593,7 +2619,12 @@ int cxbwt_graph_create(const uint64_t *packed, const uint64_t *offsets, uint64_t
   int rc = CXBWT_OK;
   if (hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess) rc = CXBWT_EDEVICE;
   if (!rc && hipStreamSynchronize((hipStream_t)stream) != hipSuccess) rc = CXBWT_EDEVICE;
-  if (!rc) rc = graph_capture(g->p, cs);
+  if (!rc)
+    rc = guarded(cs, [&] {
+      build_init(g->p.b, packed, offsets, n_reads, n_bases, max_read_len, coll_reads, n_coll, bwt, term_pos,
+                 (unsigned char *)workspace);
+      return graph_capture(g->p, cs);
+    });
   if (cs) (void)hipStreamDestroy(cs);
   if (rc) {
     delete g;
@@ -2610,7 +2641,7 @@ int cxbwt_graph_launch(cxbwt_graph *g, void *stream) {
 
 int cxbwt_graph_finish(cxbwt_graph *g, void *stream) {
   if (!g || !g->p.exec) return CXBWT_EINVAL;
-  return graph_finish(g->p, (hipStream_t)stream);
+  return guarded((hipStream_t)stream, [&] { return graph_finish(g->p, (hipStream_t)stream); });
 }
 
 void cxbwt_graph_destroy(cxbwt_graph *g) { delete g; }
