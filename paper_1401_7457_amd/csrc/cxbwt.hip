@@ -1593,7 +1593,9 @@ bool pick_induced(const Build &b, std::vector<Seg> &large, std::vector<Seg> &res
 // Plans and runs the build by induced order of b's collections above one
 // chunk (the others have been built).  *taken stays false, and nothing has
 // been written, where it does not apply.
-int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
+// blob: the host image of the steps, which the caller keeps until it has waited
+// for the stream.
+int run_induced(const Build &b, StepBlob &blob, bool *taken, PhaseTimer &T, hipStream_t st) {
   *taken = false;
   const Layout &Lo = b.Lo;
   const uint64_t nb = b.nb;
@@ -1690,7 +1692,6 @@ int run_induced(const Build &b, bool *taken, PhaseTimer &T, hipStream_t st) {
   if (off > room) return CXBWT_OK;
 
   // the steps: terminators; L of A, C, G; S of T, G, C; the rows of A
-  StepBlob blob;
   std::vector<CollMap> cm(nc);
   std::vector<uint32_t> cur((size_t)nc * 128, 0);
   std::vector<IndTail> tails[2][4];
@@ -1882,7 +1883,8 @@ int run_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n, uint6
   else if ((rc = plan_level1(b, T, st))) return rc;
   uint32_t hc[C_COUNT];
   Build apart;           // collections sorted beside a build by induced order
-  Level1Vectors v, va;   // sources of copies: kept until the last wait
+  Level1Vectors v, va;   // sources of copies, kept until the last wait
+  StepBlob blob;         // the same
   if (!msd) {
     if ((rc = run_stringword(b, T, st))) return rc;
   } else {
@@ -1899,7 +1901,7 @@ int run_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n, uint6
       }
       b.big.swap(large);
       b.small.clear();
-      if ((rc = run_induced(b, &done, T, st))) return rc;
+      if ((rc = run_induced(b, blob, &done, T, st))) return rc;
       b.planned = false;  // its tiles have taken the plan's place
     }
     if (!done) {
