@@ -494,11 +494,23 @@ int read_level(const Buffers &B, LevelOut &o, PhaseTimer &T, hipStream_t st) {
   return o.status ? CXBWT_EDEVICE : CXBWT_OK;
 }
 
+// While it lives, calls of this thread that allocate or free do not disturb a
+// capture on another one: nothing here is part of it.
+struct BesideCaptures {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool on = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  ~BesideCaptures() {
+    if (on) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  }
+};
+
 // Counters blocks in host memory that the device writes: one a build while
-// its levels run, kept for the builds that follow (at most 16 of them).
+// its levels run, kept for the builds that follow (at most MOST of them).
 struct HostBlocks {
+  static constexpr size_t MOST = 16;
   std::mutex m;
   std::vector<uint32_t *> idle;
+  HostBlocks() { idle.reserve(MOST); }  // (a block is given back by a destructor, which must not throw)
   uint32_t *take() {
     {
       std::lock_guard<std::mutex> g(m);
@@ -508,25 +520,23 @@ struct HostBlocks {
         return p;
       }
     }
-    // (a capture on another thread is not disturbed: nothing here is part of it)
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    BesideCaptures beside;
     uint32_t *p = nullptr;
     if (hipHostMalloc((void **)&p, 4 * C_COUNT, hipHostMallocPortable) != hipSuccess) {
       (void)hipGetLastError();
       p = nullptr;
     }
-    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
     return p;
   }
   void give(uint32_t *p) {
     {
       std::lock_guard<std::mutex> g(m);
-      if (idle.size() < 16) {
+      if (idle.size() < MOST) {
         idle.push_back(p);
         return;
       }
     }
+    BesideCaptures beside;
     (void)hipHostFree(p);
   }
 };
