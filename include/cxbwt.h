@@ -374,8 +374,8 @@ typedef struct cxbwt_stats {
    * A large build sorts the samples of its suffixes only (three tenths of
    * them) and derives the order of the rest: chunks to window_fetches then
    * count samples, whose windows hold 22 bases, later ones in a wave 25;
-   * with reads above 160 bases window_fetches counts loads of two windows
-   * each, of 25 and 18 bases.                                                 */
+   * with a mean read length of 150 bases and more window_fetches counts loads
+   * of two windows each, of 25 and 18 bases.                                  */
   /* With timing on (cxbwt_set_timing): summed kernel time in ms and launch
    * count per kernel class: 0 prep, 1 key generation, 2 level histogram,
    * 3 level scan, 4 level scatter, 5 in-wave finish, 6 final emit, 7 the

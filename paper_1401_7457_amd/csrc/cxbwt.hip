@@ -362,7 +362,7 @@ struct Buffers {
   uint8_t *seg_split;
   // a build by induced order: the sort buffers above hold its samples, in
   // SampleKey's format, and finished ones go to smp
-  bool sample = false;
+  bool sample = false, pair = false;  // pair: two windows a load (k_sample_chunk)
   SampleOut smp{};
 };
 
@@ -665,7 +665,7 @@ int finish_level(const Buffers &B, const Layout &Lo, const Tuning &tu, uint64_t 
 #define CX_CHUNK(LI, OCC, PAIR, ABOVE)                                                                             \
   k_sample_chunk<LI, OCC, PAIR><<<n_chunks, LOCAL_WG, 0, st>>>(B.chunks, B.keys0, B.keys1, B.hdl0, B.hdl1, B.text, \
                                                                maxlen, ABOVE, B.smp, B.counters + C_STATUS, B.stats)
-      if (maxlen >= PAIR_MIN_READ) {
+      if (B.pair) {
         CX_CHUNK(4, 6, true, 0);
         CX_LAUNCHED();
         CX_CHUNK(8, 4, true, PAIR_PACK);
@@ -1519,10 +1519,11 @@ int finish_device_levels(const Build &b, const uint32_t (&hc0)[C_COUNT], PhaseTi
 #ifndef CXBWT_INDUCE_TAIL_NS
 #define CXBWT_INDUCE_TAIL_NS 50000ull
 #endif
-// Not for reads this short: their suffixes end inside the first window, so
-// the sort has no windows to save (47 Mbases of 30-base reads: 4.0 ms by the
-// sort, 2.4 here), and their groups of identical suffixes are what final_big
-// reports.
+// Not where all reads are shorter.  They would be faster this way too (47 Mbases
+// of 30-base reads 3.5 ms by the sort, 1.7 by samples; 20 Mbases the same), but
+// nearly all of their suffixes are in large groups of identical ones, which
+// cxbwt_stats.final_big counts for the callers of such builds, and of which the
+// samples are a third.
 constexpr uint32_t INDUCE_MIN_READ = 33;
 
 // One collection's plan: the buckets' parts from the counted types.
@@ -1683,6 +1684,7 @@ int run_induced(const Build &b, StepBlob &blob, bool *taken, PhaseTimer &T, hipS
   // of the general sort buffers
   Build s = b;
   s.B.sample = true;
+  s.B.pair = nb >= PAIR_MEAN_READ * b.n;
   unsigned char *const arena = (unsigned char *)b.B.keys0;
   const uint64_t room = (uint64_t)((unsigned char *)(b.B.hdl1 + nb) - arena);
   uint64_t off = 0;
@@ -1770,7 +1772,7 @@ int run_induced(const Build &b, StepBlob &blob, bool *taken, PhaseTimer &T, hipS
   s.rmax = b.maxlen / SampleKey::FULL + 1;
   s.Ls.rmax = s.rmax;
   s.Ls.chunk = SAMPLE_CHUNK;
-  s.Ls.pack = b.maxlen >= PAIR_MIN_READ ? PAIR_PACK : SAMPLE_CHUNK;
+  s.Ls.pack = s.B.pair ? PAIR_PACK : SAMPLE_CHUNK;
   s.Ls.tile_len = s.tile_len;
   std::vector<Seg> seg(nc);
   g_stats.chunk_suffixes += M;

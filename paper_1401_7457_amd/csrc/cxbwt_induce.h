@@ -583,15 +583,18 @@ __global__ __launch_bounds__(BLOCK) void k_sample_final(const Seg *__restrict__ 
 // waves a CU, and only one above that takes a chunk of up to 512 (15 waves)
 // before it is worth a level.
 //
-// PAIR is for reads above 160 bases, whose ties pass more windows: 200 Mbases
-// of 400 bases 8.8 -> 8.1 ms a build, 1.2 Gbases of 250 bases 41.8 -> 37.3.
-// Reads of 75 to 150 bases lose 1%; of 100 bases, 400 Mbases gain 1.6% and 2
-// Gbases with repeats lose 3%.  (Text lines of 64 bytes, three windows each:
-// equal at 200 Mbases, 3% slower at 2 G.  Chunks of 256 alone, without those
-// of 512: 2 Gbases 54 -> 66 ms.)
+// PAIR is for a mean read length of 150 bases and more, whose ties pass more
+// windows (the mean, which the sizes give, and not the caller's bound: a bound of
+// 250 on reads of 100 says nothing of them).  Single records and pairs, 250
+// Mbases at 20x: reads of 100 bases 7.15 and 7.15 ms, 125 7.53 and 7.47, 150 7.90
+// and 7.63, 200 8.59 and 8.03, 400 10.5 and 9.38; 1 Gbase 25.7 and 25.7, 26.7 and
+// 26.0, 28.7 and 27.0, 31.5 and 28.0, 39.5 and 34.0; 2 Gbases of 100 bases with
+// repeats are 3% slower by pairs, and 60 Mbases 4% (100 bases) to 1% (400).
+// (Text lines of 64 bytes, three windows each: equal at 200 Mbases, 3% slower at
+// 2 G.  Chunks of 256 alone, without those of 512: 2 Gbases 54 -> 66 ms.)
 // ---------------------------------------------------------------------------
 constexpr uint32_t SAMPLE_CHUNK = 512, PAIR_PACK = 256;
-constexpr uint32_t PAIR_MIN_READ = 161;
+constexpr uint64_t PAIR_MEAN_READ = 150;
 constexpr uint64_t PLACE = 511ull;
 constexpr uint32_t WINDOW_0 = 25, WINDOW_1 = 18;  // of a pair of records: 59 bases and 58 starts, less an offset
 

@@ -135,6 +135,18 @@ def test_batches_against_the_oracle(seed):
         _check(c, b, t, f"collection {i}")
 
 
+def test_the_bound_on_read_lengths_chooses_nothing():
+    # the bound may be any number above the lengths: the same kernels, the same loads
+    col = _deep(np.random.default_rng(6), 200_000)
+    loads = []
+    for bound in (100, 161, 400, 65_535):
+        _say(f"bound {bound}")
+        b, t = cxbwt.build_host(col.text, col.offsets, max_read_len=bound)
+        loads.append(cxbwt.last_stats()["window_fetches"])
+        _check(col, b, t, f"bound {bound}")
+    assert len(set(loads)) == 1, loads
+
+
 def test_declined_builds_are_sorted():
     col = _with_runs(datagen.sample_reads(np.random.default_rng(3), datagen.random_genome(np.random.default_rng(4), 20_000),
                                           2000, 100, 0.005), np.random.default_rng(5), [70, 90], 100)
