@@ -59,7 +59,7 @@ struct Seg {
   uint8_t buf : 1;
   uint8_t regather : 1;  // keys must be re-fetched for window r before use
   uint8_t unsplit : 1;   // chunk only: suffixes are not yet in the order of digit d
-  uint8_t plain : 1;     // levels only: few suffixes end here, ended ones are not split off first
+  uint8_t plain : 1;     // levels only: of a run of zero digits where few suffixes end (see ENDED)
   uint32_t coll;         // collection the suffixes belong to
 };
 static_assert(sizeof(Seg) == 16, "segment records are 16 bytes");
@@ -134,9 +134,9 @@ struct Lists {
 // of a 1 Mbase build 5 -> 3, 690 -> 500 us; of 400 Mbases 7 -> 4, 12.5 -> 11.6
 // ms; where nothing ends there the pass is wasted: 20 Mbases at 2000x, 5.85 ->
 // 6.05 ms).  Where fewer than one in eight end (runs of A inside the reads,
-// whose every digit is zero), what is left and all that comes of it is Seg::plain
-// and split by its own digits only: in random reads about half of bucket 0 end
-// there; with runs of 90 A in a tenth of the reads of 20 Mbases a pass before
+// whose every digit is zero), what is left is Seg::plain and split by its own
+// digits only as long as they are zero: in random reads about half of bucket 0
+// end there; with runs of 90 A in a tenth of the reads of 20 Mbases a pass before
 // every digit made 28 levels 49, and 4.9 ms 7.2.
 constexpr int ENDED = 16;
 constexpr uint32_t ENDED_NOT = 31;
@@ -1218,16 +1218,19 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
       if (ended) return sd;
       return (uint8_t)(L.ended && bucket == 0 && !sg.plain && sd + 1 < F::LAST ? (sd + 1) | ENDED : sd + 1);
     };
+    // of the one segment that an ended digit leaves, whether one in eight has
+    // ended; kept along zero digits
+    const uint8_t few = ended ? (uint32_t)__builtin_amdgcn_readlane((int)cv[0], ENDED_NOT) > sg.len - sg.len / 8 : sg.plain;
     uint32_t pb = 0, pf = 0;  // entries of the lower slots
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint32_t st = sg.start + bv[i];
       if ((NB[i] >> l) & 1) {
         const uint32_t at = base_b + pb + bits_below_lane(NB[i]);
-        // (the one segment that an ended digit leaves: whether one in eight has ended)
-        const uint8_t plain = ended ? (uint8_t)(8ull * cv[i] > 7ull * sg.len) : sg.plain;
+        const uint32_t bucket = (uint32_t)i * 64 + l;
+        const uint8_t plain = ended || last || bucket == 0 ? few : 0;
         const Seg e = last ? Seg{st, cv[i], (uint16_t)(sg.r + 1), 0, nbuf, 1, 0, plain, sg.coll}
-                           : Seg{st, cv[i], sg.r, next_digit((uint32_t)i * 64 + l), nbuf, 0, 0, plain, sg.coll};
+                           : Seg{st, cv[i], sg.r, next_digit(bucket), nbuf, 0, 0, plain, sg.coll};
         if (at < L.cap_big) L.big_next[at] = e;
         else overflow = true;
       }
