@@ -132,12 +132,15 @@ struct Lists {
 // bases and an end, identical suffixes of a quarter, a sixteenth .. of the
 // reads, are then final at once instead of passing every later level (levels
 // of a 1 Mbase build 5 -> 3, 690 -> 500 us; of 400 Mbases 7 -> 4, 12.5 -> 11.6
-// ms; where nothing ends there the pass is wasted: 20 Mbases at 2000x, 5.85 ->
-// 6.05 ms).  Where fewer than one in eight end (runs of A inside the reads,
-// whose every digit is zero), what is left is Seg::plain and split by its own
-// digits only as long as they are zero: in random reads about half of bucket 0
-// end there; with runs of 90 A in a tenth of the reads of 20 Mbases a pass before
-// every digit made 28 levels 49, and 4.9 ms 7.2.
+// ms).  The pass is wasted where few suffixes end: in runs of A inside the reads,
+// whose digits are all zero, and at great depth, where a segment is one place of
+// the genome.  It is left out where bucket 0 is 7/8 of its segment and more (of the
+// suffixes of a segment one in 25 ends within four bases in reads of 100; a
+// segment of one place that goes on with AAAA keeps 24 of 25), and, once it has
+// found fewer than one in eight ending, for the zero digits that follow
+// (Seg::plain).  A pass before every zero digit: 20 Mbases with runs of 90 A in a
+// tenth of the reads 28 levels -> 49 and 4.9 ms -> 7.2, so 29 and 4.8; 8 Mbases of
+// 250-base reads at 1500x 43 -> 45 and 22.8 -> 23.3, so 43 and 22.9.
 constexpr int ENDED = 16;
 constexpr uint32_t ENDED_NOT = 31;
 struct GeneralKey {
@@ -1213,10 +1216,12 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
     }
     const bool last = sg.d == F::LAST;
     // the next digit of a large bucket: the same once the ended suffixes are
-    // split off; before digit d + 1 of bucket 0 they are split off first
-    const auto next_digit = [&](uint32_t bucket) {
+    // split off; before digit d + 1 of a bucket 0 where many may have ended they
+    // are split off first
+    const auto next_digit = [&](uint32_t bucket, uint32_t len) {
       if (ended) return sd;
-      return (uint8_t)(L.ended && bucket == 0 && !sg.plain && sd + 1 < F::LAST ? (sd + 1) | ENDED : sd + 1);
+      const bool first = L.ended && !sg.plain && bucket == 0 && len < sg.len - sg.len / 8 && sd + 1 < F::LAST;
+      return (uint8_t)(first ? (sd + 1) | ENDED : sd + 1);
     };
     // of the one segment that an ended digit leaves, whether one in eight has
     // ended; kept along zero digits
@@ -1230,7 +1235,7 @@ __global__ __launch_bounds__(BLOCK) void k_level_scan(const Seg *__restrict__ se
         const uint32_t bucket = (uint32_t)i * 64 + l;
         const uint8_t plain = ended || last || bucket == 0 ? few : 0;
         const Seg e = last ? Seg{st, cv[i], (uint16_t)(sg.r + 1), 0, nbuf, 1, 0, plain, sg.coll}
-                           : Seg{st, cv[i], sg.r, next_digit(bucket), nbuf, 0, 0, plain, sg.coll};
+                           : Seg{st, cv[i], sg.r, next_digit(bucket, cv[i]), nbuf, 0, 0, plain, sg.coll};
         if (at < L.cap_big) L.big_next[at] = e;
         else overflow = true;
       }
