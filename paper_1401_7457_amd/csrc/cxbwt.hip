@@ -153,8 +153,11 @@ Layout make_layout(uint64_t n_reads, uint64_t nb_text, uint32_t n_coll, uint64_t
   // segments split in one batch of a level: the per-segment and per-tile
   // scratch is sized for segments of more than SEG_BATCH_MIN suffixes; a
   // level with more segments runs in several batches.  Level 1 (one segment
-  // per collection) always fits one batch.
-  L.seg_slots = std::max<uint64_t>(nb / (SEG_BATCH_MIN + 1) + 2, (uint64_t)n_coll + 1);
+  // per collection) always fits one batch, and so do the 256 segments that level
+  // 1 of one collection can leave (of 100 to 525 kbases: fewer than 2048 suffixes
+  // each, so that builds of these sizes, whose levels are listed, were finished
+  // by the host: 400 kbases 0.63 ms, and 0.25 so; 0.5 MB of scratch).
+  L.seg_slots = std::max<uint64_t>({nb / (SEG_BATCH_MIN + 1) + 2, (uint64_t)n_coll + 1, 256 + 2});
   L.max_tiles = ceil_div(nb, MIN_TILE) + L.seg_slots + 1;
   L.max_groups = ceil_div(nb, (uint64_t)MIN_TILE * GROUP_TILES) + L.seg_slots + 1;
   L.n_rec = nb_text / 16 + 2;
@@ -1163,6 +1166,15 @@ bool levels_listed(const Build &b) {
          b.Lo.cap_finals + 1 <= 256 * b.Lo.max_groups;  // the groups' tile prefixes
 }
 
+// Whether the segments that level 1 leaves of several collections fit the
+// scratch of one batch: up to 256 of each that does not fall into chunks.  (Else
+// level 2 stalls and the host finishes the build: not worth listing.)
+bool level2_fits(const Build &b) {
+  uint64_t segs = 0;
+  for (const Seg &g : b.big) segs += g.len > 230ull * b.tu.chunk() ? 256 : 0;
+  return b.ncoll == 1 || segs <= b.Lo.seg_slots;
+}
+
 // Levels scheduled at once for a build that the host will only look at when
 // they are through (it finishes the build if that is not all): one level of
 // 256 buckets, two of 65536, and the split of their ended suffixes.
@@ -1919,7 +1931,7 @@ int run_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n, uint6
     if (!done) {
       v.make(b);
       level1_stats(b);
-      const bool listed = ahead && !b.big.empty();
+      const bool listed = ahead && !b.big.empty() && level2_fits(b);
       if ((rc = enqueue_body(b, v.src, listed ? levels_ahead(b) : 0, T, st))) return rc;
       if (listed) {
         if ((rc = read_totals(b, T, st, hc))) return rc;
