@@ -315,10 +315,11 @@ int cxbwt_job_done(const cxbwt_job *job);
  *                 0 = enough for any input of max_read_len (at most 8 per
  *                 27-base window, plus half of the levels that the build at
  *                 creation took).  Each scheduled level that finds no work
- *                 costs a few empty launches (about 10 us): a caller whose
- *                 contents are alike passes the levels that an eager build of
- *                 them took (cxbwt_last_stats); levels that a replay needs
- *                 beyond them run in cxbwt_graph_finish.
+ *                 costs a few empty launches (of a build of up to 16 Mbases
+ *                 one, about 2 us): a caller whose contents are alike can pass
+ *                 the levels that an eager build of them took
+ *                 (cxbwt_last_stats); levels that a replay needs beyond them
+ *                 run in cxbwt_graph_finish.
  *   stream        the caller's stream: creation first runs one eager build
  *                 on it (it writes bwt and term_pos) and waits; the counts
  *                 each of its levels saw size the captured launches (larger

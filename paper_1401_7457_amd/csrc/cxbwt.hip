@@ -1163,7 +1163,8 @@ uint32_t most_levels(uint32_t maxlen) {
 // Whether a build's levels can be listed.
 bool levels_listed(const Build &b) {
   return b.tu.chunk_items >= 6 && b.Lo.seg_slots <= NEXT_SEGS &&
-         b.Lo.cap_finals + 1 <= 256 * b.Lo.max_groups;  // the groups' tile prefixes
+         b.Lo.cap_finals + 1 <= 256 * b.Lo.max_groups &&      // the groups' tile prefixes
+         sizeof(Seg) * b.Lo.cap_big <= b.Lo.tile_hist_bytes;  // k_rest_level's second list
 }
 
 // Whether the segments that level 1 leaves of several collections fit the
@@ -1193,12 +1194,10 @@ Lists lists_for(const Build &b, uint32_t level, uint32_t ended) {
 // After level 1's scan and scatter: the rest of `levels` levels sized on the
 // device, five launches each, and every LISTED_LEVELS of them the chunks and
 // final groups they listed.  Grids cover the counts seen (or the most that
-// level 2 can have; later levels of a small build hold little, and those past
-// LISTED_LEVELS that nothing was seen of are there for the rare input: two
-// workgroups a CU); every kernel loops.
-int enqueue_listed_levels(const Build &b, uint32_t levels, uint32_t ended, PhaseTimer &T, hipStream_t st,
+// level 2 can have; later levels of a small build hold little); every kernel
+// loops.  Then `rest` levels of a launch each, for inputs that need them.
+int enqueue_listed_levels(const Build &b, uint32_t levels, uint32_t rest, uint32_t ended, PhaseTimer &T, hipStream_t st,
                           const std::vector<LevelShape> *shapes) {
-  constexpr uint32_t RARE = 512;
   const Buffers &B = b.B;
   const Layout &Lo = b.Lo;
   const uint64_t nb = b.nb, chunk = b.tu.chunk();
@@ -1210,20 +1209,20 @@ int enqueue_listed_levels(const Build &b, uint32_t levels, uint32_t ended, Phase
     const int last = lv + 1 == levels, flush = last || (lv + 1) % LISTED_LEVELS == 0;
     k_next_level<<<1, NEXT_WG, 0, st>>>(B.counters, B.stats, B.big_next, B.segs, B.tile_prefix, B.group_prefix, B.seg_or,
                                         B.seg_and, b.tile_len, Lo.seg_slots, Lo.max_tiles, Lo.max_groups, B.finals,
-                                        (uint32_t)Lo.cap_finals, B.gsum, (uint32_t)Lo.cap_chunks, flush, last);
+                                        (uint32_t)Lo.cap_finals, B.gsum, (uint32_t)Lo.cap_chunks, flush,
+                                        !last ? NEXT_NOT_LAST : rest ? NEXT_REST : NEXT_LAST);
     CX_LAUNCHED();
     if (flush) {
-      const bool rare = lv >= LISTED_LEVELS && !seen_chunks;
       T.begin();
       // chunks hold two thirds of a chunk's suffixes and more on average; a small
       // build takes the looping kernel alone
-      const uint64_t expect = rare ? RARE : std::max<uint64_t>(seen_chunks, 3 * nb / (2 * chunk) + 1);
+      const uint64_t expect = std::max<uint64_t>(seen_chunks, 3 * nb / (2 * chunk) + 1);
       if ((rc = launch_local(B, b.tu, nb, b.rmax, b.bwt, (uint32_t)Lo.cap_chunks, B.counters + C_LCHUNK, st,
-                             rare || nb <= 1u << 20 ? 0u : grid_from((uint32_t)expect, 0), (unsigned)expect)))
+                             nb <= 1u << 20 ? 0u : grid_from((uint32_t)expect, 0), (unsigned)expect)))
         return rc;
       T.end(PH_LOCAL);
       T.begin();
-      const uint64_t groups = rare ? 64 : std::min<uint64_t>(PG_EMIT, nb / (2 * chunk) + 16);
+      const uint64_t groups = std::min<uint64_t>(PG_EMIT, nb / (2 * chunk) + 16);
       k_emit_final<true><<<(unsigned)groups, BLOCK, 0, st>>>(B.finals, B.gsum, 0, B.counters + C_LFINAL, b.tile_len,
                                                             B.keys0, B.keys1, B.hdl0, B.hdl1, B.pos64, B.text, B.srank,
                                                             B.cmap, b.bwt, B.start_row);
@@ -1240,14 +1239,24 @@ int enqueue_listed_levels(const Build &b, uint32_t levels, uint32_t ended, Phase
       sh.nsegs = (uint32_t)(lv == 0 ? segs : segs / 8 + 1);
       sh.ntiles = (uint32_t)((lv == 0 ? nb : nb / 8) / b.tile_len + sh.nsegs);
       sh.ngroups = (uint32_t)(sh.ntiles / GROUP_TILES + sh.nsegs);
-      if (lv + 1 >= LISTED_LEVELS) {
-        sh.nsegs = std::min(sh.nsegs, RARE);
-        sh.ntiles = std::min(sh.ntiles, RARE);
-        sh.ngroups = std::min(sh.ngroups, RARE);
-      }
     }
     if ((rc = launch_level_kernels(B, b.tu, lists_for(b, lv + 2, ended), nb, 0, 0, 0, B.counters + C_NCUR, T, st, &sh)))
       return rc;
+  }
+  // the two lists in turn: the level's own, and the histograms' area
+  constexpr unsigned REST_GRID = 256;
+  Seg *const lists[2] = {B.big_next, (Seg *)B.tile_hist};
+  for (uint32_t k = 0; k < rest; ++k) {
+    uint32_t *const c = B.counters, *const nchunk = c + C_RCHUNK + k / LISTED_LEVELS % 2;
+    const bool last = k + 1 == rest, opens = k % LISTED_LEVELS == 0;
+    k_rest_level<<<REST_GRID, 64 * REST_NW, 0, st>>>(
+        lists[k % 2], k ? c + C_REST + (k - 1) % 3 : c + C_NBIG, lists[1 - k % 2], last ? nullptr : c + C_REST + k % 3,
+        (uint32_t)Lo.cap_big, c + C_REST + (k + 1) % 3, B.chunks, nchunk, (uint32_t)Lo.cap_chunks,
+        opens ? c + C_RCHUNK + (k / LISTED_LEVELS + 1) % 2 : nullptr, (uint32_t)chunk, b.rmax, B.keys0, B.keys1, B.hdl0,
+        B.hdl1, B.text, nb, B.srank, B.cmap, b.bwt, B.start_row, c, B.stats);
+    CX_LAUNCHED();
+    if (last || (k + 1) % LISTED_LEVELS == 0)
+      if ((rc = launch_local(B, b.tu, nb, b.rmax, b.bwt, (uint32_t)Lo.cap_chunks, nchunk, st, 0, 2 * REST_GRID))) return rc;
   }
   return CXBWT_OK;
 }
@@ -1257,8 +1266,8 @@ int enqueue_listed_levels(const Build &b, uint32_t levels, uint32_t ended, Phase
 // with a counter readback per level, or the next device_levels levels are
 // enqueued with their sizes read on the device (no host wait: the whole
 // sequence can be captured), followed by a last step that flags segments
-// left over.  The first `ended` levels split off ended suffixes first.  Ends
-// with term_pos.
+// left over.  The first `ended` levels split off ended suffixes first; the listed
+// form takes a launch each for those after them.  Ends with term_pos.
 int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, PhaseTimer &T, hipStream_t st,
                  const std::vector<LevelShape> *shapes = nullptr, uint32_t ended = ~0u) {
   const Buffers &B = b.B;
@@ -1320,7 +1329,8 @@ int enqueue_body(const Build &b, const Level1Src &src, uint32_t device_levels, P
       record_shape(0, LevelShape{ns, ntiles, ngroups, o.n_chunks, o.n_finals, (uint32_t)o.final_tiles});
       if ((rc = run_levels(b, o, true, T, st))) return rc;
     } else if (levels_listed(b)) {
-      if ((rc = enqueue_listed_levels(b, device_levels, ended, T, st, shapes))) return rc;
+      const uint32_t levels = std::min(device_levels, ended);
+      if ((rc = enqueue_listed_levels(b, levels, device_levels - levels, ended, T, st, shapes))) return rc;
     } else {
       const uint32_t *ncur = counters + C_NCUR;
       const LevelShape none;
@@ -2286,7 +2296,7 @@ int graph_capture(GraphPlan &P, hipStream_t st) {
   // suffixes, every other one at most of the first ones.  These are as many as
   // this build took (three where that is the form anyway): past them ended
   // suffixes are not split off.  (1 Mbase of 100-base reads, which takes 3: 32
-  // scheduled, 500 us a replay, where 3 take 225.)
+  // scheduled, 301 us a replay, where 3 take 227.)
   uint32_t ended = ~0u;
   const uint32_t full = most_levels(b.maxlen);
   if (!P.levels || P.levels >= full) {

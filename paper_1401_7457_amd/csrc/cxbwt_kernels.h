@@ -41,9 +41,10 @@ constexpr uint32_t ST_PLAN_MISMATCH = 32u;  // inputs no longer match a captured
 // levels are scheduled on the device keeps its running totals (G_*) from
 // C_CUM on.
 // C_LCHUNK, C_LFINAL: the entries of the chunk and group lists to be finished
-// (k_next_level).  C_TOTALS: window fetches, scattered suffixes (k_term).
+// (k_next_level).  C_REST, C_RCHUNK: the counts of k_rest_level, three and two.
+// C_TOTALS: window fetches, scattered suffixes (k_term).
 enum { C_STATUS = 0, C_NFINAL = 1, C_NCHUNK = 2, C_NBIG = 3, C_NCUR = 4, C_FLAGS = 5, C_LCHUNK = 6, C_LFINAL = 7,
-       C_FOLD = 16, C_CUM = 32, C_TOTALS = 52, C_COUNT = 64 };
+       C_REST = 8, C_RCHUNK = 11, C_FOLD = 16, C_CUM = 32, C_TOTALS = 52, C_COUNT = 64 };
 enum { G_LEVELS, G_BIGSEG, G_LEVSUF, G_REGATH, G_MAXWIN, G_CHUNKS, G_FINALS, G_FINLEN, G_BATCHES, G_COUNT };
 constexpr uint32_t FL_STALLED = 1u;     // a level did not fit the scratch: the host finishes the build
 constexpr uint32_t FL_INCOMPLETE = 2u;  // segments remain after the last scheduled level
@@ -1342,6 +1343,7 @@ __global__ void k_level_step(uint32_t *__restrict__ c, uint64_t seg_slots, uint6
 // so; 640000 copies of a read of 25 bases 3.14 and 0.47; 1 Mbase of 100-base
 // reads the same.)
 constexpr int NEXT_WG = 1024;
+enum { NEXT_NOT_LAST = 0, NEXT_LAST = 1, NEXT_REST = 2 };  // `last`: k_rest_level takes what is left
 constexpr uint64_t NEXT_SEGS = 8192;  // most segments it takes: about 1 us per thousand
 __global__ __launch_bounds__(NEXT_WG) void k_next_level(uint32_t *__restrict__ c, unsigned long long *__restrict__ stats,
                                                         const Seg *__restrict__ list, Seg *__restrict__ segs,
@@ -1402,7 +1404,7 @@ __global__ __launch_bounds__(NEXT_WG) void k_next_level(uint32_t *__restrict__ c
     const uint32_t nbig = c[C_NBIG];
     cur = 0;
     if (nbig && last) {
-      c[C_FLAGS] |= FL_INCOMPLETE;
+      if (last == NEXT_LAST) c[C_FLAGS] |= FL_INCOMPLETE;
     } else if (nbig && (nbig > seg_slots || f[K_NEXT_TILES - K_LEVEL_FIRST] > max_tiles ||
                         f[K_NEXT_GROUPS - K_LEVEL_FIRST] > max_groups)) {
       c[C_FLAGS] |= FL_STALLED;
@@ -1623,6 +1625,248 @@ __global__ __launch_bounds__(64 * NW) void k_level_scatter(const Seg *__restrict
         (uint64_t)gsum[(uint64_t)g * 256 + threadIdx.x] + tile_hist[(uint64_t)tile * 256 + threadIdx.x];
   tile_scatter<F>(S, kr, hr, dig, m, d, Ko, Ho);
   if (!PERSIST) break;
+  }
+}
+
+// A level by one workgroup a segment, all of it in one launch: for the levels that
+// a replay's schedule holds for contents unlike those at capture.  Where there
+// are none, a scheduled level costs a launch instead of five (1 Mbase of
+// 100-base reads, 28 such levels: 500 us a replay by the level kernels, 301 so),
+// and segments of thousands of suffixes fill the device (1 Mbase at 2000x, 23 of
+// its 26 levels here: 2.8 ms and 2.1).  What it is slow at is one segment of very
+// many: 0.7 ms a level for a million (1 Mbase of one base, captured on other
+// contents: 0.74 ms and 4.4).
+//
+// Segments come from `in` (*n_in of them) and go to `out`; n_zero is cleared for
+// the level after, n_chunks0 (when given) for the chunks that follow this launch's
+// next finish.  Rows of identical suffixes are written at once.  Segments have
+// digits of their own only (no ended ones).
+constexpr int REST_NW = 8, REST_TI = 8;
+__global__ __launch_bounds__(64 * REST_NW) void k_rest_level(
+    const Seg *__restrict__ in, const uint32_t *__restrict__ n_in, Seg *__restrict__ out, uint32_t *__restrict__ n_out,
+    uint32_t cap_out, uint32_t *__restrict__ n_zero, Seg *__restrict__ chunks, uint32_t *__restrict__ n_chunks,
+    uint32_t cap_chunks, uint32_t *__restrict__ n_chunks0, uint32_t chunk, uint32_t rmax, uint64_t *keys0,
+    uint64_t *keys1, uint32_t *hdl0, uint32_t *hdl1, const TextRec *__restrict__ text, uint64_t nb,
+    const uint32_t *__restrict__ srank, const CollMap *__restrict__ cmap, uint8_t *__restrict__ bwt,
+    uint64_t *__restrict__ start_row, uint32_t *c, unsigned long long *stats) {
+  constexpr uint32_t WG = 64 * REST_NW, TL = WG * REST_TI;
+  __shared__ ScatterSmem<REST_TI, REST_NW> S;
+  __shared__ uint32_t hist[256], start[256];
+  __shared__ uint32_t final_of[8];  // bit per bucket: rows to be written
+  __shared__ uint8_t held[256];     // the buckets that hold any
+  __shared__ unsigned long long or_of, and_of;
+  __shared__ int mode;  // 0: nothing more to do, 1: every row to be written in place, 2: scatter
+  if (c[C_FLAGS] & FL_STALLED) return;  // the host resumes from the list
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    *n_zero = 0;
+    if (n_chunks0) *n_chunks0 = 0;
+  }
+  const uint32_t n = min(*n_in, cap_out);
+  unsigned long long *const g = reinterpret_cast<unsigned long long *>(c + C_CUM);
+  if (n && blockIdx.x == 0 && threadIdx.x == 0) {
+    atomicAdd(&g[G_LEVELS], 1ull);
+    atomicAdd(&g[G_BIGSEG], (unsigned long long)n);
+    atomicAdd(&g[G_BATCHES], 1ull);
+  }
+  for (uint32_t s = blockIdx.x; s < n; s += gridDim.x) {
+    const Seg sg = in[s];
+    const int d = sg.d;
+    uint64_t *const Ki = sg.buf ? keys1 : keys0, *const Ko = sg.buf ? keys0 : keys1;
+    uint32_t *const Hi = sg.buf ? hdl1 : hdl0, *const Ho = sg.buf ? hdl0 : hdl1;
+    const uint64_t first = sg.start, end = first + sg.len;
+    __syncthreads();  // the previous segment's LDS is read
+    if (threadIdx.x < 256) hist[threadIdx.x] = 0;
+    if (threadIdx.x < 8) final_of[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+      or_of = 0;
+      and_of = ~0ull;
+    }
+    __syncthreads();
+    uint64_t o = 0, a = ~0ull;
+    for (uint64_t t0 = first; t0 < end; t0 += TL) {  // loads of a tile before their use
+      uint64_t kr[REST_TI];
+      bool in_seg[REST_TI];
+#pragma unroll
+      for (int i = 0; i < REST_TI; ++i) {
+        const uint64_t j = t0 + (uint64_t)i * WG + threadIdx.x;
+        in_seg[i] = j < end;
+        kr[i] = Ki[in_seg[i] ? j : first];
+      }
+      if (sg.regather) {
+        uint32_t hr[REST_TI];
+#pragma unroll
+        for (int i = 0; i < REST_TI; ++i) hr[i] = Hi[in_seg[i] ? t0 + (uint64_t)i * WG + threadIdx.x : first];
+        TextRec tr[REST_TI];
+#pragma unroll
+        for (int i = 0; i < REST_TI; ++i) tr[i] = window_load(text, nb, hr[i], sg.r);
+#pragma unroll
+        for (int i = 0; i < REST_TI; ++i)
+          if (in_seg[i]) {
+            kr[i] = window_combine(tr[i], nb, hr[i], sg.r, (uint32_t)kr[i] & 7u);
+            Ki[t0 + (uint64_t)i * WG + threadIdx.x] = kr[i];
+          }
+      }
+#pragma unroll
+      for (int i = 0; i < REST_TI; ++i) {
+        const uint64_t live = __ballot(in_seg[i]);
+        if (!live) continue;
+        // a large segment is often one bucket: one update a wave then
+        const uint32_t dg = digit_of(kr[i], d);
+        const uint32_t any = (uint32_t)__builtin_amdgcn_readlane((int)dg, (int)__builtin_ctzll(live));
+        if (__ballot(in_seg[i] && dg != any) == 0) {
+          if (lane_id() == 0) atomicAdd(&hist[any], (uint32_t)__popcll(live));
+        } else if (in_seg[i]) {
+          atomicAdd(&hist[dg], 1u);
+        }
+        if (in_seg[i]) {
+          o |= kr[i];
+          a &= kr[i];
+        }
+      }
+    }
+    o = wave_or(o);
+    a = wave_and(a);
+    if (lane_id() == 0) {
+      atomicOr(&or_of, (unsigned long long)o);
+      atomicAnd(&and_of, (unsigned long long)a);
+    }
+    __syncthreads();
+    uint32_t nheld;
+    {
+      const uint32_t len = threadIdx.x < 256 ? hist[threadIdx.x] : 0u;
+      const uint32_t at = block_excl_sum<REST_NW>(len, S.tmp, nullptr);
+      const uint32_t k = block_excl_sum<REST_NW>(len ? 1u : 0u, S.tmp, &nheld);
+      if (threadIdx.x < 256) {
+        start[threadIdx.x] = at;
+        S.goff[threadIdx.x] = first + at;
+        if (len) held[k] = (uint8_t)threadIdx.x;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const uint64_t diff = order_bits(or_of ^ and_of);
+      const bool one = nheld == 1;
+      uint32_t next_len = 0, nf = 0, fin_len = 0, nc = 0;
+      bool over = false;
+      auto push = [&](const Seg &e) {
+        if (!n_out || e.r > rmax) {  // no input has these
+          atomicOr(c + C_STATUS, ST_WINDOW_BOUND);
+          return;
+        }
+        const uint32_t at = atomicAdd(n_out, 1u);
+        if (at < cap_out) out[at] = e;
+        else over = true;
+        next_len += e.len;
+      };
+      if (one && diff == 0 && clamp_of(and_of) < (uint32_t)W) {
+        mode = 1;
+        nf = 1;
+        fin_len = sg.len;
+      } else if (one) {
+        mode = 0;
+        Seg e = sg;
+        e.regather = 0;
+        if (diff == 0) {
+          e.r = (uint16_t)(sg.r + 1);
+          e.d = 0;
+          e.regather = 1;
+        } else {
+          e.d = (uint8_t)GeneralKey::digit_of_bit(63 - __builtin_clzll(diff));
+        }
+        push(e);
+      } else {
+        mode = 2;
+        const uint8_t nbuf = (uint8_t)(sg.buf ^ 1);
+        uint32_t cstart = 0, clen = 0;  // the chunk being filled: neighbouring small buckets
+        auto close = [&]() {
+          if (!clen) return;
+          const uint32_t k = atomicAdd(n_chunks, 1u);
+          if (k < cap_chunks) chunks[k] = Seg{sg.start + cstart, clen, sg.r, sg.d, nbuf, 0, 0, 0, sg.coll};
+          else over = true;
+          ++nc;
+          clen = 0;
+        };
+        for (uint32_t x = 0; x < nheld; ++x) {
+          const uint32_t b = held[x], len = hist[b], at = start[b];
+          if (len > chunk) {
+            close();
+            if (d == 7 && b < (uint32_t)W) {
+              final_of[b >> 5] |= 1u << (b & 31u);
+              ++nf;
+              fin_len += len;
+            } else if (d == 7) {
+              push(Seg{sg.start + at, len, (uint16_t)(sg.r + 1), 0, nbuf, 1, 0, 0, sg.coll});
+            } else {
+              push(Seg{sg.start + at, len, sg.r, (uint8_t)(d + 1), nbuf, 0, 0, 0, sg.coll});
+            }
+          } else {
+            if (clen + len > chunk) close();
+            if (!clen) cstart = at;
+            clen += len;
+          }
+        }
+        close();
+        atomicAdd(stat_slot(stats + K_SCATTERED * STAT_KIND), (unsigned long long)sg.len);
+      }
+      if (over) atomicOr(c + C_STATUS, ST_LIST_OVERFLOW);
+      atomicAdd(&g[G_LEVSUF], (unsigned long long)sg.len);
+      if (nc) atomicAdd(&g[G_CHUNKS], (unsigned long long)nc);
+      if (nf) {
+        atomicAdd(&g[G_FINALS], (unsigned long long)nf);
+        atomicAdd(&g[G_FINLEN], (unsigned long long)fin_len);
+      }
+      if (next_len && (mode == 2 ? d == 7 : diff == 0)) {
+        atomicAdd(&g[G_REGATH], (unsigned long long)next_len);
+        atomicMax(&g[G_MAXWIN], (unsigned long long)(sg.r + 1));
+      }
+    }
+    __syncthreads();
+    const CollMap cm = cmap[sg.coll];
+    if (mode == 1)
+      for (uint64_t j = first + threadIdx.x; j < end; j += WG)
+        emit_row(j, cm, Ki[j], Hi[j], nullptr, text, srank, bwt, start_row);
+    if (mode != 2) continue;
+    for (uint64_t t0 = first; t0 < end; t0 += TL) {
+      const uint32_t m = (uint32_t)min((uint64_t)TL, end - t0);
+      uint64_t kr[REST_TI];
+      uint32_t hr[REST_TI], dig[REST_TI], pos[REST_TI];
+#pragma unroll
+      for (int i = 0; i < REST_TI; ++i) {
+        const uint32_t li = item_index<REST_TI>(i);
+        const uint64_t at = t0 + (li < m ? li : m - 1);
+        kr[i] = Ki[at];
+        hr[i] = Hi[at];
+      }
+#pragma unroll
+      for (int i = 0; i < REST_TI; ++i) dig[i] = item_index<REST_TI>(i) < m ? digit_of(kr[i], d) : NODIGIT;
+      block_multisplit<REST_TI, REST_NW>(dig, pos, S.wcount, S.dstart, S.tmp);
+      __syncthreads();  // every wave has read its counters before the stage is written
+#pragma unroll
+      for (int i = 0; i < REST_TI; ++i) {
+        if (dig[i] != NODIGIT) {
+          S.sk[pos[i]] = kr[i];
+          S.sh[pos[i]] = hr[i];
+        }
+      }
+      __syncthreads();
+      for (uint32_t q = threadIdx.x; q < m; q += WG) {
+        const uint64_t k = S.sk[q];
+        const uint32_t h = S.sh[q], dd = digit_of(k, d);
+        const uint64_t at = S.goff[dd] + (q - S.dstart[dd]);
+        if ((final_of[dd >> 5] >> (dd & 31u)) & 1u) {
+          emit_row(at, cm, k, h, nullptr, text, srank, bwt, start_row);
+        } else {
+          Ko[at] = k;
+          Ho[at] = h;
+        }
+      }
+      __syncthreads();
+      if (threadIdx.x < 256) {
+        const uint32_t after = threadIdx.x < 255 ? S.dstart[threadIdx.x + 1] : m;
+        S.goff[threadIdx.x] += after - S.dstart[threadIdx.x];
+      }
+      __syncthreads();
+    }
   }
 }
 

@@ -423,8 +423,9 @@ class BuildGraph:
     finish()) for each build; the result lands in `bwt` / `term`.
     coll_reads: host read boundaries of the collections, or None for one.
     levels: sort levels scheduled inside the graph (0: enough for any input;
-    each costs about 10 us where it finds no work, so a caller whose contents
-    are alike passes the `levels` that last_stats() gave for an eager build).
+    each costs an empty launch or, in large builds, a dozen where it finds no
+    work, so a caller whose contents are alike can pass the `levels` that
+    last_stats() gave for an eager build).
 
     After launch() the outputs are complete in stream order, but where the
     scheduled levels were not enough, or a level had more segments than the
