@@ -142,8 +142,8 @@ size_t cxbwt_workspace_bytes(uint64_t n_reads, uint64_t n_bases, uint32_t max_re
  *   sort levels, so it returns only after the device work is complete.
  *   Returns CXBWT_EINVAL (null pointer, n_reads == 0), CXBWT_ERANGE (sizes
  *   above the limits), CXBWT_ENOMEM (workspace too small), CXBWT_EDATA
- *   (offsets invalid or a read longer than max_read_len, found on the device
- *   before any sorting; outputs are then unspecified), CXBWT_EDEVICE.
+ *   (offsets invalid or a read longer than max_read_len, found on the device;
+ *   outputs are then unspecified), CXBWT_EDEVICE.
  */
 int cxbwt_build(const uint64_t *packed, const uint64_t *offsets, uint64_t n_reads, uint64_t n_bases,
                 uint32_t max_read_len, uint8_t *bwt, uint64_t *term_pos, void *workspace,

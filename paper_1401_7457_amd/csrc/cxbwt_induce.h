@@ -1275,8 +1275,8 @@ __device__ __forceinline__ uint32_t ind_place(bool ok, uint32_t d, uint32_t (&nx
 // kept in LDS, and their further copies written k by k, so that full waves
 // write them.  (Listed per tile by place and loaded again they cost a second
 // read of a quarter of the rows: 2.46 instead of 1.90 GB counted in the
-// right-to-left steps of 400 Mbases.)  Bound by its traffic: 10.3 GB read and
-// written in both directions in 2.41 ms (1.35 right to left), 4.3 TB/s where a
+// right-to-left steps of 400 Mbases.)  Bound by its traffic: 10.1 GB read and
+// written in both directions in 2.42 ms (1.35 right to left), 4.2 TB/s where a
 // copy reaches 4.5.
 template <bool LTR>
 __global__ __launch_bounds__(BLOCK) void k_ind_scatter(IndStep P, IndData D) {
