@@ -1531,7 +1531,7 @@ int finish_device_levels(const Build &b, const uint32_t (&hc0)[C_COUNT], PhaseTi
 // own, and up to 16.7 Mbases the sort lists its levels: 16 Mbases of 100-base
 // reads at 20x take 0.97 ms here and 0.95 by the sort, 17 Mbases 0.99 and 1.08,
 // 18 of 250 bases 1.21 and 1.41 (deeper reads gain from less on: at 2000x, 10
-// Mbases take 3.8 ms here and 9.7 by the sort, but the depth is not known
+// Mbases take 3.8 ms here and 9.2 by the sort, but the depth is not known
 // before).
 #ifndef CXBWT_INDUCE_MIN_BASES
 #define CXBWT_INDUCE_MIN_BASES 16500000ull
